@@ -60,41 +60,106 @@ __device__ __forceinline__ uint32_t y_count(K key) {
   return (uint32_t)popc_k((key >> 1) & ~key & even_bits<K>());
 }
 
-// Image of a key under a compiled Clifford chain (tables staged in LDS by the caller): the
-// product of the images of its bytes. Entry b of byte k holds the image key and, in tn, its
-// sign (bit 0) and its number of Y digits mod 4 (bits 1-2). With x = lo ^ hi and z = hi the
-// planes of a digit key and P = i^(x.z) X^x Z^z, an ordered product of images P_j is
-// i^e P(xor of the keys) with e = sum_j y_j + 2 sum_{i<j} z_i.x_j - y(product) (mod 4); the
-// images commute, so e is 0 or 2. The cross term only matters mod 2: the z plane of the
-// product so far ANDed with each image's x plane, accumulated by XOR, counted once.
+// LDS a chain table takes: entries (of sizeof(K) bytes each) and sign bytes.
 template <typename K>
-__device__ __forceinline__ K apply_table(K key, const K* __restrict__ tk, const uint8_t* __restrict__ tn,
-                                         uint32_t& neg) {
-  K acc = 0, cross = 0;
-  uint32_t e = 0;
+constexpr int table_entries() { return sizeof(K) > 8 ? kPartGroups * 16 : (int)sizeof(K) * 256; }
+template <typename K>
+constexpr int table_sign_bytes() { return sizeof(K) > 8 ? kPartGroups * 4 : (int)sizeof(K) * 256; }
+
+// Bit b of v (b < 32) at bit 2b.
+__device__ __forceinline__ uint64_t spread_bits(uint32_t v) {
+  uint32_t h[2] = {v & 0xFFFFu, v >> 16};
 #pragma unroll
-  for (int k = 0; k < (int)sizeof(K); ++k) {
-    const uint32_t b = (uint32_t)(key >> (8 * k)) & 0xFFu;
-    if (b == 0) continue;  // four identities map to identity
-    const K img = tk[k * 256 + b];
-    const uint32_t t = tn[k * 256 + b];
-    neg ^= t & 1u;
-    e += t >> 1;
-    cross ^= (acc >> 1) & (img ^ (img >> 1));
-    acc ^= img;
+  for (int k = 0; k < 2; ++k) {
+    h[k] = (h[k] | (h[k] << 8)) & 0x00FF00FFu;
+    h[k] = (h[k] | (h[k] << 4)) & 0x0F0F0F0Fu;
+    h[k] = (h[k] | (h[k] << 2)) & 0x33333333u;
+    h[k] = (h[k] | (h[k] << 1)) & 0x55555555u;
   }
-  e += 2u * ((uint32_t)popc_k(cross & even_bits<K>()) & 1u) - y_count(acc);
-  neg ^= (e >> 1) & 1u;
-  return acc;
+  return ((uint64_t)h[1] << 32) | h[0];
 }
 
-// Stage a chain table into LDS (all threads of the block take part).
+// The digit key of a string given by its planes (digit = 2 z + (x ^ z)).
+template <typename K>
+__device__ __forceinline__ K key_of_planes(uint64_t x, uint64_t z) {
+  const uint64_t lo = x ^ z;
+  const uint64_t k0 = (spread_bits((uint32_t)z) << 1) | spread_bits((uint32_t)lo);
+  if constexpr (sizeof(K) > 8)
+    return ((K)((spread_bits((uint32_t)(z >> 32)) << 1) | spread_bits((uint32_t)(lo >> 32))) << 64) | (K)k0;
+  else
+    return (K)k0;
+}
+
+// Image of a key under a compiled Clifford chain (tables staged in LDS by the caller): the
+// product of the images of its parts. With P = i^(x.z) X^x Z^z, an ordered product of images
+// P_j is i^e P(xor of the planes) with e = sum_j y_j + 2 sum_{i<j} z_i.x_j - y(product) (mod 4),
+// y the number of Y digits; the images commute, so e is 0 or 2. The cross term only matters
+// mod 2: the z plane of the product so far ANDed with each image's x plane, accumulated by
+// XOR, counted once.
+// Keys of 4 and 8 bytes: parts are bytes; entry b of byte k holds the image key and, in tn, its
+// sign (bit 0) and its number of Y digits mod 4 (bits 1-2).
+// 16-byte keys: parts are groups of four bits whose entries are planes, so that an entry costs
+// six XORs and ANDs of words instead of the sixteen that shifted digit keys would; the image
+// key is interleaved once at the end. The group's phase word is the same for every lane.
+template <typename K>
+__device__ __forceinline__ K apply_table(K key, const K* __restrict__ tk, const uint8_t* __restrict__ tn,
+                                         uint32_t groups, uint32_t& neg) {
+  if constexpr (sizeof(K) > 8) {
+    const ulonglong2* __restrict__ e = (const ulonglong2*)tk;
+    const uint32_t* __restrict__ ph = (const uint32_t*)tn;
+    uint64_t x = 0, z = 0, cross = 0;
+    uint32_t p = 0;
+    const uint32_t kw[4] = {(uint32_t)key, (uint32_t)(key >> 32), (uint32_t)(key >> 64), (uint32_t)(key >> 96)};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      if ((uint32_t)(8 * w) >= groups) break;  // the words past the key's qubits are zero
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const uint32_t v = (kw[w] >> (4 * j)) & 15u;
+        const ulonglong2 img = e[(8 * w + j) * 16 + v];
+        p += ph[8 * w + j] >> (2 * v);  // (only its two low bits count)
+        cross ^= z & img.x;
+        x ^= img.x;
+        z ^= img.y;
+      }
+    }
+    p += 2u * ((uint32_t)__popcll(cross) & 1u) - (uint32_t)__popcll(x & z);
+    neg ^= (p >> 1) & 1u;
+    return key_of_planes<K>(x, z);
+  } else {
+    K acc = 0, cross = 0;
+    uint32_t e = 0;
+#pragma unroll
+    for (int k = 0; k < (int)sizeof(K); ++k) {
+      const uint32_t b = (uint32_t)(key >> (8 * k)) & 0xFFu;
+      if (b == 0) continue;  // four identities map to identity
+      const K img = tk[k * 256 + b];
+      const uint32_t t = tn[k * 256 + b];
+      neg ^= t & 1u;
+      e += t >> 1;
+      cross ^= (acc >> 1) & (img ^ (img >> 1));
+      acc ^= img;
+    }
+    e += 2u * ((uint32_t)popc_k(cross & even_bits<K>()) & 1u) - y_count(acc);
+    neg ^= (e >> 1) & 1u;
+    return acc;
+  }
+}
+
+// Stage a chain table into LDS (all threads of the block take part). 16-byte keys: whole words
+// of eight groups (the entries past the key's qubits are identities).
 template <typename K>
 __device__ __forceinline__ void stage_table(const ChainTable& t, K* sk, uint8_t* sn) {
   const K* gk = (const K*)t.tab_key;
-  for (int i = threadIdx.x; i < (int)sizeof(K) * 256; i += blockDim.x) {
-    sk[i] = gk[i];
-    sn[i] = t.tab_neg[i];
+  if constexpr (sizeof(K) > 8) {
+    const uint32_t g8 = min((t.groups + 7u) & ~7u, (uint32_t)kPartGroups);
+    for (uint32_t i = threadIdx.x; i < g8 * 16; i += blockDim.x) ((uint4*)sk)[i] = ((const uint4*)gk)[i];
+    for (uint32_t i = threadIdx.x; i < g8; i += blockDim.x) ((uint32_t*)sn)[i] = ((const uint32_t*)t.tab_neg)[i];
+  } else {
+    for (int i = threadIdx.x; i < (int)sizeof(K) * 256; i += blockDim.x) {
+      sk[i] = gk[i];
+      sn[i] = t.tab_neg[i];
+    }
   }
 }
 
@@ -380,7 +445,7 @@ __device__ __forceinline__ uint64_t a_chain_and_fanout(K& key, uint32_t& neg, co
                                                         const uint8_t* tn, uint32_t* err,
                                                         const Exp1Desc* E1s = nullptr) {
   if (pa.drop) return 0;
-  if (pa.useA) key = apply_table(key, tk, tn, neg);
+  if (pa.useA) key = apply_table(key, tk, tn, pa.tA.groups, neg);
   else for (uint32_t a = 0; a < pa.nA; ++a) key = apply_perm(key, pa.A[a], neg);
   if (!E1s) E1s = pa.E1;
   uint64_t f = 1;
@@ -403,7 +468,7 @@ k_expand(const K* __restrict__ keys, const uint8_t* __restrict__ asign, const ty
   using W = typename WTraits<WP>::W;
   constexpr int kWaves = kExpandBlock / 64;
   constexpr int kWin = kExpandTile + 1;
-  constexpr int kTab = (int)sizeof(K) * 256;
+  constexpr int kTab = table_entries<K>(), kTabS = table_sign_bytes<K>();
   // dynamic LDS: offset window (relative to the tile's first image), image -> parent map,
   // the chain tables that this pass uses, then its expanding operators' descriptors
   extern __shared__ __align__(16) uint8_t lds[];
@@ -416,7 +481,7 @@ k_expand(const K* __restrict__ keys, const uint8_t* __restrict__ asign, const ty
   K* tbk = (K*)cur;
   cur += pa.useB ? kTab * sizeof(K) : 0;
   uint8_t* tbn = cur;
-  cur += pa.useB ? kTab : 0;
+  cur += pa.useB ? kTabS : 0;
   uint64_t* edesc = (uint64_t*)cur;
   __shared__ uint64_t bounds[2];
   // digit counts of the images for the sort passes hp_begin .. n_pass-1 (one copy per wave),
@@ -505,7 +570,7 @@ k_expand(const K* __restrict__ keys, const uint8_t* __restrict__ asign, const ty
       W wv = wp[it];
       uint32_t neg = sp[it];
       expand_ops<K, WP>(key, wv, rk[it], pa, E1s, E2s, err);
-      if (pa.useB) key = apply_table(key, tbk, tbn, neg);
+      if (pa.useB) key = apply_table(key, tbk, tbn, pa.tB.groups, neg);
       else for (uint32_t b = 0; b < pa.nB; ++b) key = apply_perm(key, pa.B[b], neg);
       if (neg) wv = -wv;
       keys_out[g] = key;
@@ -540,10 +605,10 @@ k_expand_small(const K* __restrict__ keys, const typename WTraits<WP>::W* __rest
                uint64_t* __restrict__ blk_begin, uint64_t* __restrict__ blk_end, uint32_t* __restrict__ blk_seg,
                uint32_t* __restrict__ seg_blk, uint32_t* err) {
   using W = typename WTraits<WP>::W;
-  constexpr int kTabN = sizeof(K) <= 8 ? (int)sizeof(K) * 256 : 1;  // no tables for 16-byte keys
+  constexpr int kTabN = table_entries<K>(), kTabS = table_sign_bytes<K>();
   constexpr uint32_t kPer = kChunkCap / kSmallBlock;                 // scan run per thread
-  __shared__ K tk[kTabN];
-  __shared__ uint8_t tn[kTabN];
+  __shared__ __align__(16) K tk[kTabN];
+  __shared__ __align__(4) uint8_t tn[kTabS];
   __shared__ K akey[kChunkCap];
   __shared__ uint32_t off[kChunkCap + 1];
   __shared__ uint8_t negs[kChunkCap];
@@ -620,7 +685,7 @@ k_expand_small(const K* __restrict__ keys, const typename WTraits<WP>::W* __rest
     W wv = w[a0 + j];
     uint32_t neg = negs[j];
     expand_ops<K, WP>(key, wv, g - off[j], pa, pa.E1, pa.E2, err);
-    if (pa.useB) key = apply_table(key, tk, tn, neg);
+    if (pa.useB) key = apply_table(key, tk, tn, pa.tB.groups, neg);
     else for (uint32_t b = 0; b < pa.nB; ++b) key = apply_perm(key, pa.B[b], neg);
     if (neg) wv = -wv;
     keys_out[c0 + g] = key;
@@ -960,9 +1025,9 @@ __global__ void __launch_bounds__(256) k_count_scan(const K* __restrict__ keys, 
                                                     K* __restrict__ akeys, uint8_t* __restrict__ asign,
                                                     uint64_t narrow_lim) {
   constexpr int kItems = kSortTile / 256;  // input tiles hold at most kSortTile terms
-  constexpr int kTabN = sizeof(K) <= 8 ? (int)sizeof(K) * 256 : 1;  // no tables for 16-byte keys
-  __shared__ K tk[kTabN];
-  __shared__ uint8_t tn[kTabN];
+  constexpr int kTabN = table_entries<K>(), kTabS = table_sign_bytes<K>();
+  __shared__ __align__(16) K tk[kTabN];
+  __shared__ __align__(4) uint8_t tn[kTabS];
   __shared__ uint32_t sf[kSortTile + kSortTile / kItems];  // fan-outs (< 2^32); one pad word per run of items
   __shared__ uint64_t scan_sh[4];
   __shared__ uint64_t base_sh;
@@ -1080,10 +1145,10 @@ k_count_expand(const K* __restrict__ keys, const typename WTraits<WP>::W* __rest
                typename WTraits<WP>::W* __restrict__ w_out, uint64_t out_cap, uint32_t* __restrict__ ghist,
                uint32_t n_pass, uint32_t hp_begin, uint32_t* err) {
   using W = typename WTraits<WP>::W;
-  constexpr int kTabN = sizeof(K) <= 8 ? (int)sizeof(K) * 256 : 1;  // no tables for 16-byte keys
+  constexpr int kTabN = table_entries<K>(), kTabS = table_sign_bytes<K>();
   constexpr int kWaves = kFuseBlock / 64;
-  __shared__ K tk[kTabN];
-  __shared__ uint8_t tn[kTabN];
+  __shared__ __align__(16) K tk[kTabN];
+  __shared__ __align__(4) uint8_t tn[kTabS];
   __shared__ K akey[kFuseTile];
   __shared__ uint8_t aneg[kFuseTile];
   __shared__ uint32_t loff[kFuseTile + 1];
@@ -1223,7 +1288,7 @@ k_count_expand(const K* __restrict__ keys, const typename WTraits<WP>::W* __rest
         uint32_t neg = aneg[j];
         if (e1lds) expand_ops<K, WP>(key, wv, g - loff[j], pa, (const Exp1Desc*)e1sh, pa.E2, err);
         else expand_ops<K, WP>(key, wv, g - loff[j], pa, pa.E1, pa.E2, err);
-        if (pa.useB) key = apply_table(key, tk, tn, neg);
+        if (pa.useB) key = apply_table(key, tk, tn, pa.tB.groups, neg);
         else for (uint32_t q = 0; q < pa.nB; ++q) key = apply_perm(key, pa.B[q], neg);
         if (neg) wv = -wv;
         keys_out[base + g] = key;
@@ -1914,10 +1979,10 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
     typename WTraits<WP>::W* __restrict__ wslot1, typename WTraits<WP>::W* __restrict__ wimg,
     uint32_t* __restrict__ cnt, int fp64_acc, uint32_t* err) {
   using W = typename WTraits<WP>::W;
-  constexpr int kTabN = (int)sizeof(K) * 256;
+  constexpr int kTabN = table_entries<K>(), kTabS = table_sign_bytes<K>();
   constexpr int kItems = kChunkCap / kGroupBlock, kWaves = kGroupBlock / 64;
-  __shared__ K tk[kTabN];
-  __shared__ uint8_t tn[kTabN];
+  __shared__ __align__(16) K tk[kTabN];
+  __shared__ __align__(4) uint8_t tn[kTabS];
   __shared__ K akey[kChunkCap];
   __shared__ uint8_t negs[kChunkCap];
   __shared__ uint32_t off[kChunkCap + 1];
@@ -2000,7 +2065,7 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
       W wv = win[j];
       uint32_t neg = negs[j];
       expand_ops<K, WP>(key, wv, g - off[j], pa, pa.E1, pa.E2, err);
-      if (pa.useB) key = apply_table(key, tk, tn, neg);
+      if (pa.useB) key = apply_table(key, tk, tn, pa.tB.groups, neg);
       else for (uint32_t q = 0; q < pa.nB; ++q) key = apply_perm(key, pa.B[q], neg);
       if (neg) wv = -wv;
       sk[g] = key;
@@ -2541,18 +2606,164 @@ k_merge(const K* __restrict__ keys, const W* __restrict__ w, Tiling tl, const Pa
   }
 }
 
-// One thread per (job, byte position, byte value): push that 4-qubit Pauli string through
-// the job's chain one op at a time.
+// ------------------------------------------------------------------------ chain tables
+// A chain's table follows from the images of the one-qubit strings X, Y, Z on every qubit (192
+// at most): every entry is a product of them. One block takes a run of the chain, its ops
+// staged in LDS, one thread per string; a long chain is cut into runs whose tables one block
+// then applies one after the other (k_chain_joins), so that its length is no longer a serial
+// chain: an op costs a thread about 300 cycles of dependent work whatever the split, so the
+// time is that of the longest run plus the joins. Measured: a graph state at n = 48 with 59300
+// ops 26.1 ms as ops applied per term, 0.144 ms here; the 120 chains of the n = 32 Clifford+Rz
+// circuit 0.12 ms with every op read from memory by 2048 strings, 0.041 ms here; n = 48
+// Clifford+Rz count and expansion 9.6 -> 0.74 ms per step from op lists to tables.
+// A string i^p X^x Z^z; the product of two.
+struct Str {
+  uint64_t x, z;
+  uint32_t p;
+};
+__device__ __forceinline__ Str str_mul(const Str& a, const Str& b) {
+  return Str{a.x ^ b.x, a.z ^ b.z, (a.p + b.p + 2u * (uint32_t)__popcll(a.z & b.x)) & 3u};
+}
+
+constexpr int kChainBlock = 256;
+constexpr int kChainStrings = 3 * 64;  // digit d (1..3) of qubit bit k: string 3k + d - 1
+static_assert(kChainStrings <= kChainBlock, "one thread per string");
+
+// The images of the one-qubit strings (in LDS) written as a part or as the table of K keys.
 template <typename K>
-__global__ void k_build_tables(const TableJob* __restrict__ jobs) {
-  const TableJob jb = jobs[blockIdx.y];
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= sizeof(K) * 256) return;
-  K key = (K)(i & 255u) << (8 * (i >> 8));
+__device__ __forceinline__ void write_table(const Str* img, ChainPart* part, void* tab_key, uint8_t* tab_neg,
+                                            uint32_t* phase_sh) {
+  auto single = [&](uint32_t bit, uint32_t d) -> Str { return d ? img[3 * bit + d - 1] : Str{0, 0, 0}; };
+  if (part || sizeof(K) > 8) {
+    for (uint32_t g = threadIdx.x; g < kPartGroups; g += kChainBlock) phase_sh[g] = 0u;
+    __syncthreads();
+    uint64_t* const xz = part ? &part->xz[0][0] : (uint64_t*)tab_key;
+    for (uint32_t i = threadIdx.x; i < kPartGroups * 16; i += kChainBlock) {
+      const uint32_t g = i >> 4, v = i & 15u;
+      const Str s = str_mul(single(2 * g, v & 3u), single(2 * g + 1, v >> 2));
+      xz[2 * i] = s.x;
+      xz[2 * i + 1] = s.z;
+      atomicOr(&phase_sh[g], s.p << (2 * v));
+    }
+    __syncthreads();
+    uint32_t* const ph = part ? part->phase : (uint32_t*)tab_neg;
+    for (uint32_t g = threadIdx.x; g < kPartGroups; g += kChainBlock) ph[g] = phase_sh[g];
+  } else {
+    for (uint32_t i = threadIdx.x; i < (uint32_t)table_entries<K>(); i += kChainBlock) {
+      const uint32_t k = i >> 8, b = i & 255u;
+      Str s{0, 0, 0};
+      for (uint32_t q = 0; q < 4; ++q) s = str_mul(s, single(4 * k + q, (b >> (2 * q)) & 3u));
+      const uint32_t y = (uint32_t)__popcll(s.x & s.z);
+      ((K*)tab_key)[i] = key_of_planes<K>(s.x, s.z);
+      tab_neg[i] = (uint8_t)((((s.p - y) >> 1) & 1u) | ((y & 3u) << 1));  // see apply_table
+    }
+  }
+}
+
+template <typename K>
+__global__ void __launch_bounds__(kChainBlock) k_chain_segs(const TableSeg* __restrict__ segs) {
+  __shared__ __align__(16) PermDesc ops[kChainSeg];
+  __shared__ Str img[kChainStrings];
+  __shared__ uint32_t phase_sh[kPartGroups];
+  const TableSeg sg = segs[blockIdx.x];
+  const uint32_t bit = threadIdx.x / 3, d = threadIdx.x % 3 + 1;
+  const bool live = threadIdx.x < kChainStrings && bit < 4 * sizeof(K);
+  uint64_t x = 0, z = 0;
   uint32_t neg = 0;
-  for (uint32_t o = 0; o < jb.n_ops; ++o) key = apply_perm(key, jb.ops[o], neg);
-  ((K*)jb.tab_key)[i] = key;
-  jb.tab_neg[i] = (uint8_t)(neg | ((y_count(key) & 3u) << 1));  // see apply_table
+  if (live) {
+    x = (uint64_t)(d <= 2) << bit;  // X, Y
+    z = (uint64_t)(d >= 2) << bit;  // Y, Z
+  }
+  for (uint32_t o0 = 0; o0 < sg.n_ops; o0 += kChainSeg) {
+    const uint32_t n = min(kChainSeg, sg.n_ops - o0);
+    constexpr uint32_t kWords = sizeof(PermDesc) / 8;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n * kWords; i += kChainBlock)
+      ((uint64_t*)ops)[i] = ((const uint64_t*)(sg.ops + o0))[i];
+    __syncthreads();
+    if (live) {
+      for (uint32_t o = 0; o < n; ++o) {
+        const PermDesc& p = ops[o];
+        const uint32_t a = p.pa >> 1, b = p.pb >> 1;
+        const bool two = p.arity == 2;
+        const uint32_t za = (uint32_t)(z >> a) & 1u, xa = (uint32_t)(x >> a) & 1u;
+        const uint32_t zb = (uint32_t)(z >> b) & 1u, xb = (uint32_t)(x >> b) & 1u;
+        uint32_t in = 2u * za + (xa ^ za);
+        if (two) in = 4u * in + 2u * zb + (xb ^ zb);
+        const uint32_t e = (uint32_t)((in < 8 ? p.lo : p.hi) >> (8u * (in & 7u))) & 0xFFu;
+        neg ^= e >> 4;
+        const uint32_t oa = two ? (e >> 2) & 3u : e & 3u;
+        const uint32_t ob = two ? e & 3u : 2u * zb + (xb ^ zb);  // (one wire: b is not written)
+        const uint64_t ma = 1ull << a, mb = two ? 1ull << b : 0ull;
+        x = (x & ~(ma | mb)) | ((uint64_t)((oa ^ (oa >> 1)) & 1u) << a) | (mb & ((uint64_t)((ob ^ (ob >> 1)) & 1u) << b));
+        z = (z & ~(ma | mb)) | ((uint64_t)(oa >> 1) << a) | (mb & ((uint64_t)(ob >> 1) << b));
+      }
+    }
+  }
+  if (threadIdx.x < kChainStrings) img[threadIdx.x] = Str{x, z, (2u * (neg & 1u) + (uint32_t)__popcll(x & z)) & 3u};
+  __syncthreads();
+  write_table<K>(img, sg.part, sg.tab_key, sg.tab_neg, phase_sh);
+}
+
+// The strings' images through n_in parts, one after the other; the next part is loaded to
+// registers while the current one, in LDS, is applied.
+template <typename K>
+__global__ void __launch_bounds__(kChainBlock) k_chain_joins(const TableJoin* __restrict__ joins) {
+  constexpr uint32_t kWords = sizeof(ChainPart) / 16, kPer = (kWords + kChainBlock - 1) / kChainBlock;
+  static_assert(sizeof(ChainPart) % 16 == 0, "parts move in 16-byte words");
+  __shared__ __align__(16) ChainPart cur;
+  __shared__ Str img[kChainStrings];
+  __shared__ uint32_t phase_sh[kPartGroups];
+  const TableJoin jn = joins[blockIdx.x];
+  const uint32_t bit = threadIdx.x / 3, d = threadIdx.x % 3 + 1;
+  const bool live = threadIdx.x < kChainStrings && bit < 4 * sizeof(K);
+  uint64_t x = 0, z = 0;
+  uint32_t neg = 0;
+  if (live) {
+    x = (uint64_t)(d <= 2) << bit;
+    z = (uint64_t)(d >= 2) << bit;
+  }
+  uint4 nx[kPer];
+  auto load = [&](uint32_t k) {
+#pragma unroll
+    for (uint32_t r = 0; r < kPer; ++r) nx[r] = ((const uint4*)(jn.in + k))[min(r * kChainBlock + threadIdx.x, kWords - 1)];
+  };
+  if (jn.n_in) load(0);
+  for (uint32_t k = 0; k < jn.n_in; ++k) {
+    __syncthreads();  // the previous part is no longer read
+#pragma unroll
+    for (uint32_t r = 0; r < kPer; ++r)
+      if (r * kChainBlock + threadIdx.x < kWords) ((uint4*)&cur)[r * kChainBlock + threadIdx.x] = nx[r];
+    __syncthreads();
+    if (k + 1 < jn.n_in) load(k + 1);
+    if (live) {
+      const unsigned __int128 key = key_of_planes<unsigned __int128>(x, z);
+      const unsigned __int128 im = apply_table<unsigned __int128>(key, (const unsigned __int128*)cur.xz,
+                                                                  (const uint8_t*)cur.phase, (uint32_t)sizeof(K) * 2u, neg);
+      // back to planes: z is the odd bits, x the even bits XOR the odd ones
+      uint64_t zz = 0, lo = 0;
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        uint64_t h = (uint64_t)(im >> (64 * w));
+        uint64_t e[2] = {h & 0x5555555555555555ull, (h >> 1) & 0x5555555555555555ull};
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          e[q] = (e[q] | (e[q] >> 1)) & 0x3333333333333333ull;
+          e[q] = (e[q] | (e[q] >> 2)) & 0x0F0F0F0F0F0F0F0Full;
+          e[q] = (e[q] | (e[q] >> 4)) & 0x00FF00FF00FF00FFull;
+          e[q] = (e[q] | (e[q] >> 8)) & 0x0000FFFF0000FFFFull;
+          e[q] = (e[q] | (e[q] >> 16)) & 0x00000000FFFFFFFFull;
+        }
+        lo |= e[0] << (32 * w);
+        zz |= e[1] << (32 * w);
+      }
+      z = zz;
+      x = lo ^ zz;
+    }
+  }
+  if (threadIdx.x < kChainStrings) img[threadIdx.x] = Str{x, z, (2u * (neg & 1u) + (uint32_t)__popcll(x & z)) & 3u};
+  __syncthreads();
+  write_table<K>(img, jn.part, jn.tab_key, jn.tab_neg, phase_sh);
 }
 
 // Z_j of freshly admitted circuits, written at the end of the term array: for entry c,
@@ -2673,7 +2884,7 @@ inline uint32_t grid_for(uint64_t n, uint32_t block) { return (uint32_t)((n + bl
 const char* kernel_kind_name(int k) {
   static const char* names[kKNum] = {"init", "count", "scan", "expand", "sort_hist", "sort_scatter",
                                      "merge_count", "merge_write", "compose_ptm", "chunk_sort", "count_expand",
-                                     "dense_merge", "chunk_finish", "small_passes"};
+                                     "dense_merge", "chunk_finish", "small_passes", "chain_tables"};
   return (k >= 0 && k < kKNum) ? names[k] : "?";
 }
 
@@ -2822,7 +3033,7 @@ hipError_t launch_expand(int KC, int WP, const void* keys, const uint8_t* asign,
   const size_t hist = ghist ? (size_t)(n_pass - hp_begin) * (kExpandBlock / 64) * kRadix * 4 : 0;
   hipEvent_t ev = prof_begin(prof, s, kKExpand);
   QIMAX_DISPATCH_K(KC, {
-    const size_t tab = sizeof(K) * 256 * (sizeof(K) + 1);  // a B-chain table (A chains: done by the count)
+    const size_t tab = sizeof(K) * table_entries<K>() + table_sign_bytes<K>();  // a B-chain table (A chains: done by the count)
     const size_t lds = kExpandLdsHead + (any_tables ? tab : 0) +
                        e_bytes + hist + 64;
     if (WP == 64)
@@ -3139,10 +3350,18 @@ hipError_t launch_pull(const void* src, void* dst, size_t bytes, hipStream_t s) 
   return hipGetLastError();
 }
 
-hipError_t launch_build_tables(int KC, const TableJob* jobs, uint32_t n_jobs, hipStream_t s, Prof* prof) {
-  (void)prof;
-  if (n_jobs == 0) return hipSuccess;
-  QIMAX_DISPATCH_K(KC, { k_build_tables<K><<<dim3((uint32_t)sizeof(K), n_jobs), 256, 0, s>>>(jobs); });
+hipError_t launch_build_tables(int KC, const TableLaunch& t, hipStream_t s, Prof* prof) {
+  if (t.n_segs == 0) return hipSuccess;
+  hipEvent_t ev = prof_begin(prof, s, kKTables);
+  QIMAX_DISPATCH_K(KC, {
+    k_chain_segs<K><<<t.n_segs, kChainBlock, 0, s>>>(t.segs);
+    const TableJoin* j = t.joins;
+    for (uint32_t n : t.levels) {
+      if (n) k_chain_joins<K><<<n, kChainBlock, 0, s>>>(j);
+      j += n;
+    }
+  });
+  prof_end(prof, s, ev, kKTables, 0.0);
   return hipGetLastError();
 }
 

@@ -79,6 +79,7 @@ struct HostOp {
   int q0 = 0, q1 = 0;
   int dim = 4;
   int64_t group = 0;  // operator group (U_k / V_k run); ids increase in circuit order
+  int64_t run = 0;    // its number within the call
   bool perm = false;
   bool conj = false;  // a signed permutation that is a conjugation by a unitary (multiplicative)
   uint64_t mask = 0;  // wires touched
@@ -285,6 +286,11 @@ struct qimax_ctx {
   DevBuf cnt, off, scan_tmp, hist, hist_off, blk_begin, blk_end, blk_seg, seg_blk, blk_cnt, blk_off, img_seg;
   DevBuf desc, desc2, err, f64tmp;
   DevBuf ptab;  // chain tables of a whole call, compiled in one launch
+  // Memory a context can do without: the scratch of long chains' joins (chain_parts) and the
+  // tables of 16-byte keys (wtab for a round's, ptab for a call's). Where it leaves too little
+  // for the rest, it is given back and the call runs again without it (lean from then on).
+  DevBuf chain_parts, wtab;
+  bool opt_busy = false, lean = false;
   DevBuf akeys, asign;  // input terms after their pass's A chain, and the signs (count -> expand)
   DevBuf chunk_off, chunk_cnt, chunk_start;  // chunk-local merge: offset, kept terms, deferred runs per chunk
   DevBuf grp_cnt;  // persistent small passes: counts per pass and segment
@@ -379,6 +385,19 @@ void dev_free(qimax_ctx* c, DevBuf& b) {
   b.bytes = 0;
 }
 
+// Gives back the memory the context can do without (see qimax_ctx::chain_parts); false if it
+// holds none or a call is using it.
+bool drop_optional(qimax_ctx* c) {
+  DevBuf* const opt[] = {&c->chain_parts, &c->wtab, c->kb > 8 ? &c->ptab : nullptr};
+  bool any = false;
+  for (DevBuf* b : opt) any |= b && b->p;
+  if (!any || c->opt_busy || c->rec) return false;
+  (void)hipStreamSynchronize(c->stream);
+  for (DevBuf* b : opt)
+    if (b) dev_free(c, *b);
+  return true;
+}
+
 // Grow-only device buffer with the context's memory cap.
 qimax_status ensure(qimax_ctx* c, DevBuf& b, size_t bytes, bool headroom = true) {
   if (bytes <= b.bytes && b.p) return QIMAX_OK;
@@ -391,8 +410,10 @@ qimax_status ensure(qimax_ctx* c, DevBuf& b, size_t bytes, bool headroom = true)
   if (c->cap && after > c->cap) {
     if (bytes > 0 && c->alloc_bytes - b.bytes + bytes <= c->cap)
       want = (bytes + 255) & ~(size_t)255;
-    if (c->alloc_bytes - b.bytes + want > c->cap)
+    if (c->alloc_bytes - b.bytes + want > c->cap) {
+      if (drop_optional(c)) return ensure(c, b, bytes, headroom);
       return fail(c, QIMAX_ENOMEM, "memory cap exceeded (requested " + std::to_string(bytes) + " bytes)");
+    }
   }
   if (b.p) {
     HIPCHK(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
@@ -402,6 +423,7 @@ qimax_status ensure(qimax_ctx* c, DevBuf& b, size_t bytes, bool headroom = true)
   hipError_t e = hipMalloc(&p, want);
   if (e != hipSuccess) {
     (void)hipGetLastError();
+    if (drop_optional(c)) return ensure(c, b, bytes, headroom);
     return fail(c, QIMAX_ENOMEM, "hipMalloc of " + std::to_string(want) + " bytes failed");
   }
   b.p = p;
@@ -420,12 +442,15 @@ qimax_status ensure_keep(qimax_ctx* c, DevBuf& b, size_t bytes, size_t keep) {
   size_t want = align256(bytes + bytes / 4 + 256);
   if (c->cap && c->alloc_bytes + want > c->cap) {
     want = align256(bytes);
-    if (c->alloc_bytes + want > c->cap)
+    if (c->alloc_bytes + want > c->cap) {
+      if (drop_optional(c)) return ensure_keep(c, b, bytes, keep);
       return fail(c, QIMAX_ENOMEM, "memory cap exceeded (requested " + std::to_string(bytes) + " bytes)");
+    }
   }
   hipError_t e = hipMalloc(&nb.p, want);
   if (e != hipSuccess) {
     (void)hipGetLastError();
+    if (drop_optional(c)) return ensure_keep(c, b, bytes, keep);
     return fail(c, QIMAX_ENOMEM, "hipMalloc of " + std::to_string(want) + " bytes failed");
   }
   nb.bytes = want;
@@ -446,6 +471,26 @@ qimax_status ensure_keep(qimax_ctx* c, DevBuf& b, size_t bytes, size_t keep) {
   }
   b = nb;
   return QIMAX_OK;
+}
+
+// Runs a call's work, and once more without the memory it can do without where that left too
+// little (a failing call leaves the state as it was).
+template <typename F>
+qimax_status with_optional(qimax_ctx* c, const F& body) {
+  const qimax_stats st0 = c->st;
+  const std::vector<uint64_t> upd0 = c->gen_updates;
+  const int64_t base0 = c->group_base;
+  c->opt_busy = true;
+  qimax_status s = body();
+  c->opt_busy = false;
+  if (s == QIMAX_ENOMEM && !c->lean && drop_optional(c)) {
+    c->lean = true;
+    c->st = st0;
+    c->gen_updates = upd0;
+    c->group_base = base0;
+    s = body();
+  }
+  return s;
 }
 
 #define QCHK(expr)                         \
@@ -758,14 +803,102 @@ inline uint64_t pass_updates(const Pass& p, uint64_t t_in, uint64_t t_img, uint6
   return p.ng_in * t_in + (p.E.empty() ? 0 : t_img) + p.ng_out * t_out;
 }
 
+// ------------------------------------------------------------------ chain tables
+// A chain of at least kChainTableMin conjugations becomes a table.
+bool tableable(const qimax_ctx* c, const std::vector<const HostOp*>& v) {
+  if ((int)v.size() < kChainTableMin || (c->kb > 8 && c->lean)) return false;
+  for (auto* op : v)
+    if (!op->conj) return false;
+  return true;
+}
+
+size_t table_key_bytes(const qimax_ctx* c) { return c->kb > 8 ? (size_t)kPartGroups * 16 * 16 : c->kb * 256 * c->kb; }
+size_t table_bytes(const qimax_ctx* c) {
+  return align256(table_key_bytes(c)) + align256(c->kb > 8 ? (size_t)kPartGroups * 4 : c->kb * 256);
+}
+ChainTable table_at(const qimax_ctx* c, uint8_t* dev, uint32_t n) {
+  return ChainTable{dev, dev + align256(table_key_bytes(c)), (n + 1) / 2, 0};
+}
+
+// The work that compiles chains of the given lengths: the runs and the joins of every level,
+// with the ChainParts between them. split = false: every chain in one run (no parts).
+struct TablePlan {
+  size_t n_segs = 0, n_joins = 0, n_parts = 0;
+  std::vector<uint32_t> levels;
+  bool split = true;
+};
+
+void plan_tables(const std::vector<uint32_t>& lens, bool split, TablePlan& tp) {
+  tp = TablePlan();
+  tp.split = split;
+  for (uint32_t len : lens) {
+    size_t k = split ? ((size_t)len + kChainSeg - 1) / kChainSeg : 1;
+    tp.n_segs += k;
+    for (size_t lv = 0; k > 1; ++lv) {
+      tp.n_parts += k;
+      k = (k + kChainJoin - 1) / kChainJoin;
+      if (tp.levels.size() <= lv) tp.levels.push_back(0);
+      tp.levels[lv] += (uint32_t)k;
+      tp.n_joins += k;
+    }
+  }
+}
+
+size_t plan_host_bytes(const TablePlan& tp) {
+  return align256(tp.n_segs * sizeof(TableSeg)) + align256(tp.n_joins * sizeof(TableJoin));
+}
+
+// Writes the work into host staging at `host` (its device copy at `dev`); chain i has
+// lens[i] ops at ops[i] and goes to tabs[i]; parts: device scratch of tp.n_parts ChainParts.
+void put_tables(const TablePlan& tp, const std::vector<uint32_t>& lens, const std::vector<const PermDesc*>& ops,
+                const std::vector<ChainTable>& tabs, ChainPart* parts, uint8_t* host, const uint8_t* dev,
+                TableLaunch& out) {
+  TableSeg* segs = (TableSeg*)host;
+  const size_t oj = align256(tp.n_segs * sizeof(TableSeg));
+  TableJoin* joins = (TableJoin*)(host + oj);
+  std::vector<size_t> at(tp.levels.size(), 0);  // next join of every level
+  for (size_t lv = 1; lv < at.size(); ++lv) at[lv] = at[lv - 1] + tp.levels[lv - 1];
+  size_t ns = 0, np = 0;
+  for (size_t i = 0; i < lens.size(); ++i) {
+    void* tk = const_cast<void*>(tabs[i].tab_key);
+    uint8_t* tn = const_cast<uint8_t*>(tabs[i].tab_neg);
+    size_t k = tp.split ? ((size_t)lens[i] + kChainSeg - 1) / kChainSeg : 1;
+    if (k <= 1) {
+      segs[ns++] = TableSeg{ops[i], lens[i], 0, tk, tn, nullptr};
+      continue;
+    }
+    ChainPart* in = parts + np;
+    np += k;
+    for (size_t r = 0; r < k; ++r) {
+      const uint32_t a = (uint32_t)r * kChainSeg;
+      segs[ns++] = TableSeg{ops[i] + a, std::min(kChainSeg, lens[i] - a), 0, nullptr, nullptr, in + r};
+    }
+    for (size_t lv = 0; k > 1; ++lv) {
+      const size_t k2 = (k + kChainJoin - 1) / kChainJoin;
+      ChainPart* next = k2 > 1 ? parts + np : nullptr;
+      if (k2 > 1) np += k2;
+      for (size_t r = 0; r < k2; ++r) {
+        const uint32_t n_in = (uint32_t)std::min<size_t>(kChainJoin, k - r * kChainJoin);
+        joins[at[lv]++] = TableJoin{in + r * kChainJoin, n_in, 0, next ? nullptr : tk, next ? nullptr : tn,
+                                    next ? next + r : nullptr};
+      }
+      in = next;
+      k = k2;
+    }
+  }
+  out.segs = (const TableSeg*)dev;
+  out.n_segs = (uint32_t)tp.n_segs;
+  out.joins = (const TableJoin*)(dev + oj);
+  out.levels = tp.levels;
+}
+
 // A round's descriptors staged for upload (in c->stage[0]; their device copy, c->desc, is
 // pulled by the round's first launch): the entries' permutations and expanding-operator
-// descriptors, one PassArgs per entry, the segments' entry numbers and the chain-table jobs.
+// descriptors, one PassArgs per entry, the segments' entry numbers and the chain-table work.
 struct RoundDesc {
   const PassArgs* pas = nullptr;   // device addresses
   const uint32_t* sent = nullptr;
-  const TableJob* jobs = nullptr;
-  size_t n_jobs = 0;
+  TableLaunch tables;
   size_t host_bytes = 0;
   size_t e_bytes = 0;              // largest expanding-operator descriptor set of an entry
   bool any_b_tables = false;
@@ -781,17 +914,12 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
   std::vector<Exp2Desc> e2;
   struct Lay { size_t a, b, x1, x2; uint32_t nA, nB, nE1, nE2; bool useA, useB; };
   std::vector<Lay> lay(E);
-  size_t n_jobs = 0;
   size_t e_bytes = 0;  // largest expanding-operator descriptor set of an entry (staged in LDS)
-  bool any_tables = false;
   bool any_b_tables = false;
   uint32_t max_n = 1;
-  auto tableable = [c](const std::vector<const HostOp*>& v) {
-    if (c->kb > 8 || (int)v.size() < kChainTableMin) return false;  // no tables for 16-byte keys
-    for (auto* op : v)
-      if (!op->conj) return false;
-    return true;
-  };
+  std::vector<uint32_t> lens;       // the chains compiled here, with their first op and qubits
+  std::vector<size_t> first;
+  std::vector<uint32_t> chain_n;
   for (size_t e = 0; e < E; ++e) {
     Lay& L = lay[e];
     L = Lay{perms.size(), 0, e1.size(), e2.size(), 0, 0, 0, 0, false, false};
@@ -808,24 +936,31 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
       else { e2.push_back(make_exp2(entries[e].n, *op)); ++L.nE2; }
     }
     e_bytes = std::max(e_bytes, L.nE1 * sizeof(Exp1Desc) + L.nE2 * sizeof(Exp2Desc));
-    L.useA = tableable(p->A);
-    L.useB = tableable(p->B);
-    n_jobs += (L.useA && !p->pre[0].tab_key) + (L.useB && !p->pre[1].tab_key);
-    any_tables |= L.useA || L.useB;
+    L.useA = tableable(c, p->A);
+    L.useB = tableable(c, p->B);
+    auto compile = [&](size_t a, uint32_t len) {
+      lens.push_back(len);
+      first.push_back(a);
+      chain_n.push_back(entries[e].n);
+    };
+    if (L.useA && !p->pre[0].tab_key) compile(L.a, L.nA);
+    if (L.useB && !p->pre[1].tab_key) compile(L.b, L.nB);
     any_b_tables |= L.useB;
   }
-  const size_t entries_tab = c->kb * 256;
-  const size_t tab_bytes = align256(entries_tab * c->kb) + align256(entries_tab);
   const size_t oP = 0;
   const size_t o1 = align256(oP + perms.size() * sizeof(PermDesc));
   const size_t o2 = align256(o1 + e1.size() * sizeof(Exp1Desc));
   const size_t oA = align256(o2 + e2.size() * sizeof(Exp2Desc));
   const size_t oS = align256(oA + E * sizeof(PassArgs));
   const size_t oJ = align256(oS + S * 4);
-  const size_t host_bytes = align256(oJ + n_jobs * sizeof(TableJob));
-  const size_t oTab = align256(host_bytes);
-  const size_t total = oTab + n_jobs * tab_bytes + 256;
-  QCHK(ensure(c, c->desc, total));
+  TablePlan tp;
+  plan_tables(lens, !c->lean, tp);
+  const size_t host_bytes = align256(oJ + plan_host_bytes(tp));
+  DevBuf& tab_buf = c->kb > 8 ? c->wtab : c->desc;
+  const size_t oTab = c->kb > 8 ? 0 : host_bytes, tab_total = lens.size() * table_bytes(c);
+  QCHK(ensure(c, c->desc, host_bytes + (c->kb > 8 ? 0 : tab_total) + 256));
+  if (c->kb > 8 && tab_total) QCHK(ensure(c, c->wtab, tab_total));
+  if (tp.n_parts) QCHK(ensure(c, c->chain_parts, tp.n_parts * sizeof(ChainPart)));
   QCHK(ensure_stage(c, 0, host_bytes));
   uint8_t* hs = (uint8_t*)c->stage[0];
   uint8_t* ds = (uint8_t*)c->desc.p;
@@ -834,7 +969,13 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
   if (!e1.empty()) std::memcpy(hs + o1, e1.data(), e1.size() * sizeof(Exp1Desc));
   if (!e2.empty()) std::memcpy(hs + o2, e2.data(), e2.size() * sizeof(Exp2Desc));
   PassArgs* pas_h = (PassArgs*)(hs + oA);
-  TableJob* jobs_h = (TableJob*)(hs + oJ);
+  std::vector<ChainTable> tabs(lens.size());
+  std::vector<const PermDesc*> chain_ops(lens.size());
+  for (size_t i = 0; i < lens.size(); ++i) {
+    tabs[i] = table_at(c, (uint8_t*)tab_buf.p + oTab + i * table_bytes(c), chain_n[i]);
+    chain_ops[i] = (const PermDesc*)(ds + oP) + first[i];
+  }
+  put_tables(tp, lens, chain_ops, tabs, (ChainPart*)c->chain_parts.p, hs + oJ, ds + oJ, rd.tables);
   size_t job = 0;
   for (size_t e = 0; e < E; ++e) {
     const Lay& L = lay[e];
@@ -846,29 +987,20 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
     pa.nA = L.nA; pa.nB = L.nB; pa.nE1 = L.nE1; pa.nE2 = L.nE2;
     pa.drop = entries[e].drop ? 1u : 0u;
     pa.thr = entries[e].thr;
-    auto table_for = [&](const PermDesc* ops, uint32_t nops, ChainTable& t) {
-      uint8_t* tk = ds + oTab + job * tab_bytes;
-      uint8_t* tn = tk + align256(entries_tab * c->kb);
-      jobs_h[job] = TableJob{ops, nops, 0, tk, tn};
-      t = ChainTable{tk, tn};
-      ++job;
-    };
     const Pass* pp = entries[e].pass;
     if (L.useA) {
       pa.useA = 1;
-      if (pp->pre[0].tab_key) pa.tA = pp->pre[0]; else table_for(pa.A, pa.nA, pa.tA);
+      pa.tA = pp->pre[0].tab_key ? pp->pre[0] : tabs[job++];
     }
     if (L.useB) {
       pa.useB = 1;
-      if (pp->pre[1].tab_key) pa.tB = pp->pre[1]; else table_for(pa.B, pa.nB, pa.tB);
+      pa.tB = pp->pre[1].tab_key ? pp->pre[1] : tabs[job++];
     }
     pas_h[e] = pa;
   }
   std::memcpy(hs + oS, seg_entry.data(), S * 4);
   rd.pas = (const PassArgs*)(ds + oA);
   rd.sent = (const uint32_t*)(ds + oS);
-  rd.jobs = (const TableJob*)(ds + oJ);
-  rd.n_jobs = n_jobs;
   rd.host_bytes = host_bytes;
   rd.e_bytes = e_bytes;
   rd.any_b_tables = any_b_tables;
@@ -892,7 +1024,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   uint8_t* ds = (uint8_t*)c->desc.p;
   const PassArgs* pas = rd.pas;
   const uint32_t* sent = rd.sent;
-  const size_t host_bytes = rd.host_bytes, n_jobs = rd.n_jobs, e_bytes = rd.e_bytes;
+  const size_t host_bytes = rd.host_bytes, e_bytes = rd.e_bytes;
   const bool any_b_tables = rd.any_b_tables;
   const uint32_t max_n = rd.max_n;
   const bool sweep = !c->classic_sort;
@@ -948,7 +1080,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
     HIPCHK(c, launch_round_start(blob, ds, host_bytes, (uint32_t*)c->err.p, ctr, 256,
                                  (uint32_t*)c->ghist.p, nh, seg_in, S, job, T_in, c->stream), "round start");
   }
-  HIPCHK(c, launch_build_tables(c->KC, rd.jobs, (uint32_t)n_jobs, c->stream, &c->prof), "chain tables");
+  HIPCHK(c, launch_build_tables(c->KC, rd.tables, c->stream, &c->prof), "chain tables");
   // ---- fan-out count fused with its scan -> image offsets of every input term
   // mstatus: one word per tile, shared by the count and merge sweeps (distinct epochs)
   auto status_words = [&](uint64_t tiles) -> qimax_status {
@@ -1430,52 +1562,46 @@ struct BusyTimer {
 // Compile every chain table of a call's passes in one launch ahead of the rounds (a chain
 // table depends on the operators only), so that rounds need no table launch of their own.
 qimax_status prebuild_tables(qimax_ctx* c, std::vector<Pass>& passes) {
-  if (c->kb > 8) return QIMAX_OK;  // no tables for 16-byte keys
-  auto tableable = [](const std::vector<const HostOp*>& v) {
-    if ((int)v.size() < kChainTableMin) return false;
-    for (auto* op : v)
-      if (!op->conj) return false;
-    return true;
-  };
   std::vector<std::pair<Pass*, int>> chains;
+  std::vector<uint32_t> lens;
   size_t n_perm = 0;
   for (auto& p : passes)
     for (int ab = 0; ab < 2; ++ab) {
       const auto& v = ab ? p.B : p.A;
-      if (tableable(v)) {
+      if (tableable(c, v)) {
         chains.push_back({&p, ab});
+        lens.push_back((uint32_t)v.size());
         n_perm += v.size();
       }
     }
   if (chains.empty()) return QIMAX_OK;
-  const size_t entries_tab = c->kb * 256;
-  const size_t tab_bytes = align256(entries_tab * c->kb) + align256(entries_tab);
-  const size_t oJ = 0, oP = align256(chains.size() * sizeof(TableJob));
-  const size_t host_bytes = oP + align256(n_perm * sizeof(PermDesc));
-  const size_t oT = align256(host_bytes);
-  QCHK(ensure(c, c->ptab, oT + chains.size() * tab_bytes + 256));
-  QCHK(ensure_stage(c, 1, host_bytes));
+  const size_t perm_bytes = align256(n_perm * sizeof(PermDesc));
+  TablePlan tp;
+  plan_tables(lens, !c->lean, tp);
+  const size_t oT = align256(perm_bytes + plan_host_bytes(tp));
+  QCHK(ensure(c, c->ptab, oT + chains.size() * table_bytes(c) + 256));
+  if (tp.n_parts) QCHK(ensure(c, c->chain_parts, tp.n_parts * sizeof(ChainPart)));
+  QCHK(ensure_stage(c, 1, oT));
   uint8_t* hs = (uint8_t*)c->stage[1];
   uint8_t* ds = (uint8_t*)c->ptab.p;
-  TableJob* jobs = (TableJob*)(hs + oJ);
-  PermDesc* perms = (PermDesc*)(hs + oP);
+  PermDesc* perms = (PermDesc*)hs;
+  std::vector<ChainTable> tabs(chains.size());
+  std::vector<const PermDesc*> ops(chains.size());
   size_t np = 0;
   for (size_t j = 0; j < chains.size(); ++j) {
     Pass& p = *chains[j].first;
     const int ab = chains[j].second;
-    const auto& v = ab ? p.B : p.A;
-    const size_t first = np;
-    for (auto* op : v) perms[np++] = make_perm(c->n, *op);
-    uint8_t* tk = ds + oT + j * tab_bytes;
-    uint8_t* tn = tk + align256(entries_tab * c->kb);
-    jobs[j] = TableJob{(const PermDesc*)(ds + oP) + first, (uint32_t)v.size(), 0, tk, tn};
-    p.pre[ab] = ChainTable{tk, tn};
+    ops[j] = (const PermDesc*)ds + np;
+    for (auto* op : ab ? p.B : p.A) perms[np++] = make_perm(c->n, *op);
+    tabs[j] = table_at(c, ds + oT + j * table_bytes(c), c->n);
+    p.pre[ab] = tabs[j];
   }
+  TableLaunch tables;
+  put_tables(tp, lens, ops, tabs, (ChainPart*)c->chain_parts.p, hs + perm_bytes, ds + perm_bytes, tables);
   const void* src = nullptr;  // (a recording reads its own copy: the staging area is rewritten later)
-  QCHK(rec_src(c, c->stage[1], c->stage_dev[1], host_bytes, &src));
-  HIPCHK(c, launch_pull(src, ds, host_bytes, c->stream), "upload chains");
-  HIPCHK(c, launch_build_tables(c->KC, (const TableJob*)(ds + oJ), (uint32_t)chains.size(), c->stream, &c->prof),
-         "chain tables");
+  QCHK(rec_src(c, c->stage[1], c->stage_dev[1], oT, &src));
+  HIPCHK(c, launch_pull(src, ds, oT, c->stream), "upload chains");
+  HIPCHK(c, launch_build_tables(c->KC, tables, c->stream, &c->prof), "chain tables");
   return QIMAX_OK;
 }
 
@@ -1538,7 +1664,7 @@ qimax_status run_small_group(qimax_ctx* c, std::vector<Pass>& passes, size_t i0,
     HIPCHK(c, launch_round_start(blob, c->desc.p, rd.host_bytes, (uint32_t*)c->err.p, (uint32_t*)c->tile_ctr.p, 256,
                                  (uint32_t*)c->ghist.p, 0, s_in, S, job, T_in, c->stream), "round start");
   }
-  HIPCHK(c, launch_build_tables(c->KC, rd.jobs, (uint32_t)rd.n_jobs, c->stream, &c->prof), "chain tables");
+  HIPCHK(c, launch_build_tables(c->KC, rd.tables, c->stream, &c->prof), "chain tables");
   const size_t eb = c->kb, wbt = c->wb;
   const uint64_t n_work = (uint64_t)S * kChunkCap;
   for (int i = 0; i < 2; ++i) {
@@ -1594,13 +1720,11 @@ qimax_status run_small_group(qimax_ctx* c, std::vector<Pass>& passes, size_t i0,
   return QIMAX_OK;
 }
 
-qimax_status apply_ops(qimax_ctx* c, std::vector<HostOp>& ops) {
-  if (c->broken) return fail(c, QIMAX_ESTATE, "context unusable after an earlier device error");
-  BusyTimer bt(c);
+qimax_status apply_ops_once(qimax_ctx* c, std::vector<HostOp>& ops) {
   // group ids continue from earlier calls, so that deferred operators precede this call's
   int64_t next_base = c->group_base;
   for (auto& op : ops) {
-    op.group += c->group_base;
+    op.group = op.run + c->group_base;
     next_base = std::max(next_base, op.group + 1);
   }
   c->group_base = next_base;
@@ -1673,8 +1797,14 @@ qimax_status apply_ops(qimax_ctx* c, std::vector<HostOp>& ops) {
   return QIMAX_OK;
 }
 
-qimax_status flush_pending(qimax_ctx* c) {
-  if (c->pending.empty()) return QIMAX_OK;
+qimax_status apply_ops(qimax_ctx* c, std::vector<HostOp>& ops) {
+  if (c->broken) return fail(c, QIMAX_ESTATE, "context unusable after an earlier device error");
+  BusyTimer bt(c);
+  for (auto& op : ops) op.run = op.group;
+  return with_optional(c, [&] { return apply_ops_once(c, ops); });
+}
+
+qimax_status flush_once(qimax_ctx* c) {
   // a pass with only Clifford operators: images are the permuted terms, then sorted
   Pass p;
   for (auto& op : c->pending) p.A.push_back(&op);
@@ -1697,6 +1827,11 @@ qimax_status flush_pending(qimax_ctx* c) {
   c->T = so_out[c->n];
   c->pending.clear();
   return QIMAX_OK;
+}
+
+qimax_status flush_pending(qimax_ctx* c) {
+  if (c->pending.empty()) return QIMAX_OK;
+  return with_optional(c, [&] { return flush_once(c); });
 }
 
 qimax_status check_op_input(qimax_ctx* c, const qimax_op& in, int64_t group, HostOp& op) {
@@ -2181,9 +2316,10 @@ qimax_status expect_device(qimax_ctx* c, const std::vector<std::vector<int>>& Ps
   if ((double)T * (double)D > kSvMaxWork) return fail(c, QIMAX_ETOOLARGE, "expect: too many terms for the projection");
   const size_t sv_bytes = (size_t)D * 16, t_bytes = (size_t)std::max<uint64_t>(T, 1) * 32;
   const size_t need = 2 * sv_bytes + t_bytes + 512;
+  if (c->cap && c->alloc_bytes + need > c->cap) (void)drop_optional(c);
   if (c->cap && c->alloc_bytes + need > c->cap) return fail(c, QIMAX_ENOMEM, "expect: memory cap exceeded");
   void* mem = nullptr;
-  if (hipMalloc(&mem, need) != hipSuccess) {
+  if (hipMalloc(&mem, need) != hipSuccess && !(drop_optional(c) && hipMalloc(&mem, need) == hipSuccess)) {
     (void)hipGetLastError();
     return fail(c, QIMAX_ENOMEM, "expect: hipMalloc of the statevector failed");
   }
@@ -2934,7 +3070,7 @@ void qimax_destroy(qimax_ctx* c) {
   DevBuf* bufs[] = {&c->keys, &c->w, &c->seg, &c->pk[0], &c->pk[1], &c->pw[0], &c->pw[1], &c->pseg[0],
                     &c->pseg[1], &c->ik[0], &c->ik[1], &c->iw[0], &c->iw[1], &c->cnt, &c->off, &c->scan_tmp,
                     &c->hist, &c->hist_off, &c->blk_begin, &c->blk_end, &c->blk_seg, &c->seg_blk, &c->blk_cnt,
-                    &c->blk_off, &c->img_seg, &c->desc, &c->desc2, &c->err, &c->f64tmp, &c->gr_in, &c->gr_out, &c->ghist, &c->sbase, &c->sstatus, &c->tile_ctr, &c->mstatus, &c->dtile[0], &c->dtile[1], &c->dtile[2], &c->ptab, &c->akeys, &c->asign, &c->img_cnt, &c->dense_acc, &c->chunk_cnt, &c->chunk_start, &c->grp_cnt,
+                    &c->blk_off, &c->img_seg, &c->desc, &c->desc2, &c->err, &c->f64tmp, &c->gr_in, &c->gr_out, &c->ghist, &c->sbase, &c->sstatus, &c->tile_ctr, &c->mstatus, &c->dtile[0], &c->dtile[1], &c->dtile[2], &c->ptab, &c->chain_parts, &c->wtab, &c->akeys, &c->asign, &c->img_cnt, &c->dense_acc, &c->chunk_cnt, &c->chunk_start, &c->grp_cnt,
                     &c->chunk_off};
   for (DevBuf* b : bufs) dev_free(c, *b);
   if (c->pinned) (void)hipHostFree(c->pinned);
@@ -3205,8 +3341,10 @@ qimax_status qimax_batch_step(qimax_batch* b, size_t* n_active) {
   QCHK(ensure(c, c->seg, b->so.size() * 8));
   HIPCHK(c, hipMemcpyAsync(c->seg.p, b->so.data(), b->so.size() * 8, hipMemcpyHostToDevice, c->stream), "offsets");
   std::vector<uint64_t> so_out, so_img, upd;
-  QCHK(run_round(c, entries, seg_entry, c->keys.p, c->w.p, (const uint64_t*)c->seg.p, b->so, 0, so_out, so_img,
-                 &upd));
+  QCHK(with_optional(c, [&] {
+    return run_round(c, entries, seg_entry, c->keys.p, c->w.p, (const uint64_t*)c->seg.p, b->so, 0, so_out, so_img,
+                     &upd);
+  }));
   std::swap(c->keys, c->pk[0]);
   std::swap(c->w, c->pw[0]);
   std::swap(c->seg, c->pseg[0]);

@@ -46,17 +46,32 @@ struct Exp2Desc {
   float valf[16][16];
 };
 
-// One pass: terms -> [A perms] -> [E expanding ops] -> [B perms] -> images.
-// A Clifford chain compiled into per-byte tables: byte k of a key holds the digits of four
-// qubits; tab_key[k*256 + b] is the image key of that 4-qubit Pauli string under the chain
-// and tab_neg[k*256 + b] its sign bit (bit 0) and number of Y digits mod 4 (bits 1-2).
-// Conjugation is multiplicative, so the image of a whole key is the product of its bytes'
-// images (they commute) with the product's phase.
+// A Clifford chain compiled into tables of the images of a key's parts. Conjugation is
+// multiplicative, so the image of a whole key is the product of its parts' images (they
+// commute) with the product's phase.
+// Keys of 4 and 8 bytes: byte k of a key holds the digits of four qubits; tab_key[k*256 + b] is
+// the image key of that 4-qubit Pauli string under the chain and tab_neg[k*256 + b] its sign
+// bit (bit 0) and number of Y digits mod 4 (bits 1-2).
+// 16-byte keys: a group is four key bits (two qubits); tab_key[g*16 + v] is the image of the
+// string v of group g as its x plane (low 64 bits) and z plane (high), bit k of a plane being
+// the qubit at key bits 2k, 2k+1; tab_neg holds one 32-bit word per group, bits 2v, 2v+1 of it
+// the phase p of that image written i^p X^x Z^z. (A byte table of a 16-byte key would take
+// 68 KB of LDS; this one takes 8.3 KB, and the 16 entries of a group lie in 64 different
+// banks.)
 struct ChainTable {
-  const void* tab_key;     // K[nbytes * 256]
-  const uint8_t* tab_neg;  // [nbytes * 256]
+  const void* tab_key;     // K[nbytes * 256], or [groups * 16] plane pairs
+  const uint8_t* tab_neg;  // [nbytes * 256], or `groups` 32-bit words
+  uint32_t groups;         // 16-byte keys: groups a key of n qubits has
+  uint32_t pad;
+};
+// The table of part of a chain (or of a whole one) in the 16-byte keys' form, whatever the key.
+constexpr int kPartGroups = 32;
+struct ChainPart {
+  uint64_t xz[kPartGroups * 16][2];
+  uint32_t phase[kPartGroups];
 };
 
+// One pass: terms -> [A perms] -> [E expanding ops] -> [B perms] -> images.
 struct PassArgs {
   const PermDesc* A;
   const Exp1Desc* E1;
@@ -70,16 +85,37 @@ struct PassArgs {
   double thr;              // merge keeps |w| > thr
 };
 
-// A chain of permutation ops to compile into a ChainTable.
-struct TableJob {
+// A run of permutation ops to compile: into a ChainTable (tab_key, tab_neg), or, as one of
+// several runs of a long chain, into a ChainPart (part set).
+struct TableSeg {
   const PermDesc* ops;
   uint32_t n_ops;
   uint32_t pad;
   void* tab_key;
   uint8_t* tab_neg;
+  ChainPart* part;
+};
+// Consecutive parts of a chain to join, the earlier run first: into a table or a larger part.
+struct TableJoin {
+  const ChainPart* in;
+  uint32_t n_in;
+  uint32_t pad;
+  void* tab_key;
+  uint8_t* tab_neg;
+  ChainPart* part;
+};
+// The launches that compile a set of chains: every run, then level after level of joins.
+struct TableLaunch {
+  const TableSeg* segs = nullptr;    // device memory
+  uint32_t n_segs = 0;
+  const TableJoin* joins = nullptr;  // device memory, the levels one after the other
+  std::vector<uint32_t> levels;      // joins of each level
 };
 
 constexpr int kChainTableMin = 12;  // chains at least this long are compiled into tables
+// A chain is compiled in runs of at most kChainSeg ops, one block each, and kChainJoin parts
+// are joined by one block: 59300 ops are 464 runs, 20 joins and one.
+constexpr uint32_t kChainSeg = 128, kChainJoin = 24;
 
 // Segment-aligned tiling of an array of segments (generators): block b covers
 // [blk_begin[b], blk_end[b]) inside segment blk_seg[b]; segment s owns blocks
@@ -137,7 +173,7 @@ enum : uint32_t {
 // algorithmic bytes each launch must move (what the roofline is measured against).
 enum KernelKind : int {
   kKInit, kKCount, kKScan, kKExpand, kKSortHist, kKSortScatter, kKMergeCount, kKMergeWrite, kKCompose, kKChunkSort,
-  kKCountExpand, kKDense, kKChunkFinish, kKSmallPasses, kKNum
+  kKCountExpand, kKDense, kKChunkFinish, kKSmallPasses, kKTables, kKNum
 };
 const char* kernel_kind_name(int k);
 
@@ -296,8 +332,8 @@ hipError_t launch_dense_merge(int KC, int WP, const void* keys_in, const void* w
                               uint64_t* seg_off_out, const MergeFin& fin, uint32_t* err, hipStream_t s,
                               Prof* prof = nullptr);
 
-// Compile chains of permutation ops into ChainTables, one job per chain (jobs in device memory).
-hipError_t launch_build_tables(int KC, const TableJob* jobs, uint32_t n_jobs, hipStream_t s, Prof* prof = nullptr);
+// Compile chains of permutation ops into ChainTables.
+hipError_t launch_build_tables(int KC, const TableLaunch& tables, hipStream_t s, Prof* prof = nullptr);
 
 // Z_j of n_circ new circuits: circuit c's nq[c] terms are written from position dst[c].
 hipError_t launch_init_many(int KC, int WP, void* keys, void* w, const uint32_t* nq, const uint64_t* dst,
