@@ -1365,6 +1365,16 @@ __global__ void k_merge_publish(Tiling tl, const uint64_t* __restrict__ blk_off,
 }
 
 
+__global__ void k_publish(uint32_t S, MergeFin fin, const uint32_t* __restrict__ err) {
+  for (uint32_t s = threadIdx.x; s <= S; s += blockDim.x) {
+    const uint64_t v = fin.img_seg[s];
+    fin.result[s] = v;
+    fin.result[S + 1 + s] = v;
+  }
+  if (threadIdx.x == 0) fin.result[2 * (uint64_t)S + 2] = *err;
+  publish_seq(fin, S);
+}
+
 // ----------------------------------------------------------------- chunk-local sort
 // After stable global passes over the top m digits, every segment is grouped into buckets of
 // equal top digits, in order. Chunk c starts at the first bucket boundary at or after the
@@ -1960,17 +1970,21 @@ __global__ void __launch_bounds__(256) k_chunk_compact(const K* __restrict__ key
 }
 
 // ------------------------------------------------------------ persistent small passes
-// Consecutive passes of one circuit whose segments stay small (at most kChunkCap terms and
-// images each, by the host's fan-out bound) in one launch: one block per segment keeps its
+// Consecutive passes of one circuit whose segments stay small (at most kCap terms and images
+// each, by the host's fan-out bound) in one launch: one block per segment keeps its
 // terms in a slot of kChunkCap in global memory (L2-resident at these sizes) and, pass after
 // pass, applies the A chain and counts the fan-outs, scans them in LDS, forms the images
 // (expansion and B chain: keys to LDS, weights to a scratch slot), sorts the keys stably in
 // LDS (LSD passes over the digits that vary), sums each run of equal keys in array order,
 // prunes, and writes the kept terms to the other slot. These are the images, the order and
 // the sums of the round-by-round small path, so the results agree bit for bit; only the
-// launches and the host's waits between the passes are gone. cnt[(p*S + s)*3 + {0,1,2}]
-// receives segment s's input terms, images and kept terms in pass p.
+// launches and the host's waits between the passes are gone. A pass marked unsorted (its
+// images all differ) writes its images to the other slot as they come. cnt[(p*S + s)*3 +
+// {0,1,2}] receives segment s's input terms, images and kept terms in pass p.
+// 16-byte keys: half the terms, so that keys, images and counters fit a block's LDS (108 KB).
 constexpr int kGroupBlock = 512;
+template <typename K>
+constexpr int group_cap() { return sizeof(K) > 8 ? kChunkCap / 2 : kChunkCap; }
 template <typename K, int WP>
 __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
     const K* __restrict__ keys_in, const typename WTraits<WP>::W* __restrict__ w_in,
@@ -1980,15 +1994,16 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
     uint32_t* __restrict__ cnt, int fp64_acc, uint32_t* err) {
   using W = typename WTraits<WP>::W;
   constexpr int kTabN = table_entries<K>(), kTabS = table_sign_bytes<K>();
-  constexpr int kItems = kChunkCap / kGroupBlock, kWaves = kGroupBlock / 64;
+  constexpr int kCap = group_cap<K>();
+  constexpr int kItems = kCap / kGroupBlock, kWaves = kGroupBlock / 64;
   __shared__ __align__(16) K tk[kTabN];
   __shared__ __align__(4) uint8_t tn[kTabS];
-  __shared__ K akey[kChunkCap];
-  __shared__ uint8_t negs[kChunkCap];
-  __shared__ uint32_t off[kChunkCap + 1];
-  __shared__ uint16_t pmap[kChunkCap];
-  __shared__ K sk[kChunkCap];
-  __shared__ uint16_t sidx[kChunkCap];
+  __shared__ K akey[kCap];
+  __shared__ uint8_t negs[kCap];
+  __shared__ uint32_t off[kCap + 1];
+  __shared__ uint16_t pmap[kCap];
+  __shared__ K sk[kCap];
+  __shared__ uint16_t sidx[kCap];
   __shared__ __align__(16) uint32_t wrun[kWaves][kRadix];
   __shared__ __align__(16) uint32_t dbase[kWaves][kRadix];
   __shared__ uint32_t wdummy[kWaves][64];
@@ -2007,7 +2022,7 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
     K* kout = ((p & 1u) ? kslot1 : kslot0) + slot0;
     W* wout = ((p & 1u) ? wslot1 : wslot0) + slot0;
     uint32_t* cp = cnt + ((uint64_t)p * S + s) * 3;
-    if (n64 > (uint64_t)kChunkCap || pa.drop) {  // the caller's bound did not hold
+    if (n64 > (uint64_t)kCap || pa.drop) {  // the caller's bound did not hold
       if (threadIdx.x == 0) {
         atomicOr(err, kErrIndex | kErrFanout);
         cp[0] = cp[1] = cp[2] = 0;
@@ -2027,7 +2042,7 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
       const uint64_t f = a_chain_and_fanout(key, neg, pa, tk, tn, err);
       akey[i] = key;
       negs[i] = (uint8_t)(neg & 1u);
-      off[i] = (uint32_t)min<uint64_t>(f, kChunkCap + 1);  // larger: flagged by the total below
+      off[i] = (uint32_t)min<uint64_t>(f, kCap + 1);  // larger: flagged by the total below
     }
     __syncthreads();
     {
@@ -2038,12 +2053,12 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
       uint64_t run = block_excl_scan<kGroupBlock>(sum, scan_sh, &tot);
       for (uint32_t i = r0; i < r1; ++i) {  // (each thread rewrites only its own run)
         const uint32_t f = off[i];
-        off[i] = (uint32_t)min<uint64_t>(run, kChunkCap);
+        off[i] = (uint32_t)min<uint64_t>(run, kCap);
         run += f;
       }
       if (threadIdx.x == 0) {
-        if (tot > (uint64_t)kChunkCap) atomicOr(err, kErrIndex | kErrFanout);
-        nimg_sh = tot > (uint64_t)kChunkCap ? 0u : (uint32_t)tot;
+        if (tot > (uint64_t)kCap) atomicOr(err, kErrIndex | kErrFanout);
+        nimg_sh = tot > (uint64_t)kCap ? 0u : (uint32_t)tot;
         off[n] = nimg_sh;
       }
     }
@@ -2057,6 +2072,28 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
     if (pa.useB) {
       stage_table(pa.tB, tk, tn);
       __syncthreads();
+    }
+    if (pa.unsorted) {  // the images as they come
+      for (uint32_t g = threadIdx.x; g < n_img; g += kGroupBlock) {
+        const uint32_t j = pmap[g];
+        K key = akey[j];
+        W wv = win[j];
+        uint32_t neg = negs[j];
+        expand_ops<K, WP>(key, wv, g - off[j], pa, pa.E1, pa.E2, err);
+        if (pa.useB) key = apply_table(key, tk, tn, pa.tB.groups, neg);
+        else for (uint32_t q = 0; q < pa.nB; ++q) key = apply_perm(key, pa.B[q], neg);
+        kout[g] = key;
+        wout[g] = neg ? -wv : wv;
+      }
+      if (threadIdx.x == 0) {
+        cp[0] = n;
+        cp[1] = cp[2] = n_img;
+      }
+      __syncthreads();  // the images (global, this block's) before the next pass reads them
+      kin = kout;
+      win = wout;
+      n64 = n_img;
+      continue;
     }
     // ---- the images (as the expansion): keys to LDS with their positions, weights to wimg
     for (uint32_t g = threadIdx.x; g < n_img; g += kGroupBlock) {
@@ -3051,13 +3088,21 @@ hipError_t launch_expand(int KC, int WP, const void* keys, const uint8_t* asign,
 }
 
 size_t fuse_tile() { return (size_t)kFuseTile; }
+uint32_t small_group_cap(int KC) {
+  return (uint32_t)(KC == 2 ? group_cap<unsigned __int128>() : KC == 1 ? group_cap<uint64_t>() : group_cap<uint32_t>());
+}
+
+hipError_t launch_publish(uint32_t S, const MergeFin& fin, const uint32_t* err, hipStream_t s) {
+  k_publish<<<1, 256, 0, s>>>(S, fin, err);
+  return hipGetLastError();
+}
 
 hipError_t launch_small_passes(int KC, int WP, int fp64_acc, const void* keys_in, const void* w_in,
                                const uint64_t* seg_in, uint32_t S, const PassArgs* pas, uint32_t n_grp,
                                void* const kslot[2], void* const wslot[2], void* wimg, uint32_t* cnt,
                                void* keys_out, void* w_out, uint64_t* seg_off_out, uint32_t* err, hipStream_t s,
                                Prof* prof) {
-  if (S == 0 || n_grp == 0 || KC > 1) return hipErrorInvalidValue;  // keys of 4 or 8 bytes
+  if (S == 0 || n_grp == 0) return hipErrorInvalidValue;
   hipEvent_t ev = prof_begin(prof, s, kKSmallPasses);
   const int last = (int)((n_grp - 1) & 1u);
   const uint32_t* cnt_last = cnt + (uint64_t)(n_grp - 1) * S * 3;
@@ -3075,7 +3120,8 @@ hipError_t launch_small_passes(int KC, int WP, int fp64_acc, const void* keys_in
     k_small_gather<K, float><<<S, 256, 0, s>>>((const K*)kslot[last], (const float*)wslot[last], cnt_last, S,      \
                                                (K*)keys_out, (float*)w_out, seg_off_out);                         \
   }
-  if (KC == 0) { QIMAX_SMALL_PASSES(uint32_t) } else { QIMAX_SMALL_PASSES(uint64_t) }
+  if (KC == 0) { QIMAX_SMALL_PASSES(uint32_t) } else if (KC == 1) { QIMAX_SMALL_PASSES(uint64_t) }
+  else { QIMAX_SMALL_PASSES(unsigned __int128) }
 #undef QIMAX_SMALL_PASSES
   prof_end(prof, s, ev, kKSmallPasses, 0.0);  // bytes: added by the caller once the counts are back
   return hipGetLastError();

@@ -81,7 +81,7 @@ struct PassArgs {
   ChainTable tA, tB;       // used instead of the op lists when useA / useB is set
   uint32_t useA, useB;
   uint32_t drop;           // the entry's terms leave the array (f = 0)
-  uint32_t pad;
+  uint32_t unsorted;       // the images all differ and are the pass's output as they come
   double thr;              // merge keeps |w| > thr
 };
 
@@ -368,11 +368,13 @@ constexpr int kFuseMaxFanout = 16;
 size_t fuse_tile();
 
 // Several consecutive passes of one circuit in one launch (k_small_passes), for passes whose
-// segments stay within kChunkCap terms and images (the caller's fan-out bound): pas holds
+// segments stay within small_group_cap terms and images (the caller's fan-out bound): pas holds
 // n_grp PassArgs (pass p of the group), kslot / wslot two slot buffers and wimg one scratch
 // of S * kChunkCap elements each; cnt (n_grp * S * 3 words) receives every pass's input,
 // image and kept counts per segment; the last pass's terms go to keys_out / w_out with the
-// segment offsets in seg_off_out (S + 1). Keys of 4 or 8 bytes.
+// segment offsets in seg_off_out (S + 1). A segment may hold small_group_cap(KC) terms and
+// images.
+uint32_t small_group_cap(int KC);
 hipError_t launch_small_passes(int KC, int WP, int fp64_acc, const void* keys_in, const void* w_in,
                                const uint64_t* seg_in, uint32_t S, const PassArgs* pas, uint32_t n_grp,
                                void* const kslot[2], void* const wslot[2], void* wimg, uint32_t* cnt,
@@ -408,6 +410,10 @@ hipError_t launch_round_start(const void* blob_host, void* blob_dev, size_t blob
 // Zero the error word, n_ctr tile counters and nh digit-histogram words (one launch).
 hipError_t launch_round_prep(uint32_t* err, uint32_t* ctr, uint32_t n_ctr, uint32_t* ghist, uint64_t nh,
                              hipStream_t s);
+
+// The end of a round whose images are its output: fin.img_seg (S + 1 offsets) as output and as
+// image offsets, the error word and the sequence word (see MergeFin).
+hipError_t launch_publish(uint32_t S, const MergeFin& fin, const uint32_t* err, hipStream_t s);
 
 // Plain copy of n words (calibration of hardware traffic counters).
 hipError_t launch_copy_u64(const uint64_t* in, uint64_t* out, uint64_t n, hipStream_t s);
