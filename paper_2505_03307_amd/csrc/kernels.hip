@@ -2817,13 +2817,6 @@ __global__ void k_init_many(K* keys, W* w, const uint32_t* __restrict__ nq, cons
   }
 }
 
-template <int WP>
-__global__ void k_weights_to_f64(const typename WTraits<WP>::W* __restrict__ w, double* __restrict__ out,
-                                 uint64_t T) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < T) out[i] = (double)w[i];
-}
-
 // -------------------------------------------------------------------- grouping pass
 // The 4x4 transfer matrix R[out][in] of one gate (Pauli order I, X, Y, Z): the closed
 // form of (1/2) Tr(P_out U P_in U^dagger), i.e. diag(1, M) with M the SO(3) rotation of
@@ -3411,34 +3404,66 @@ hipError_t launch_build_tables(int KC, const TableLaunch& t, hipStream_t s, Prof
   return hipGetLastError();
 }
 
-// Terms as the C-ABI hands them out: each key as n_words little-endian 64-bit words (the
-// second word of a key of at most 8 bytes is 0), each weight as FP64.
-template <typename K, typename W>
-__global__ void __launch_bounds__(256) k_export(const K* __restrict__ keys, const W* __restrict__ w, uint64_t T,
-                                                uint32_t n_words, uint64_t* __restrict__ words,
-                                                double* __restrict__ wd) {
-  const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= T) return;
-  const K k = keys[i];
-  if (n_words == 2) {
-    words[2 * i] = (uint64_t)k;
-    if constexpr (sizeof(K) > 8) words[2 * i + 1] = (uint64_t)(k >> 64);
-    else words[2 * i + 1] = 0;
-  } else {
-    words[i] = (uint64_t)k;
-  }
-  wd[i] = (double)w[i];
+// The even bits of v, packed.
+__device__ __forceinline__ uint32_t pack_bits(uint64_t v) {
+  v &= 0x5555555555555555ull;
+  v = (v | (v >> 1)) & 0x3333333333333333ull;
+  v = (v | (v >> 2)) & 0x0F0F0F0F0F0F0F0Full;
+  v = (v | (v >> 4)) & 0x00FF00FF00FF00FFull;
+  v = (v | (v >> 8)) & 0x0000FFFF0000FFFFull;
+  return (uint32_t)(v | (v >> 16));
 }
 
-hipError_t launch_export(int KC, int WP, const void* keys, const void* w, uint64_t T, uint32_t n_words,
-                         uint64_t* words, double* wd, hipStream_t s) {
+// Terms as the C-ABI hands them out, written to mapped host memory: each key as one or two
+// little-endian 64-bit words, or as its x and z words, each weight as FP64. Bound by the link.
+template <typename K, typename W, int kForm>
+__global__ void __launch_bounds__(256) k_export(const K* __restrict__ keys, const W* __restrict__ w, uint64_t T,
+                                                uint32_t n, uint64_t* __restrict__ words, uint64_t* __restrict__ zs,
+                                                double* __restrict__ wd) {
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < T; i += (uint64_t)gridDim.x * 256) {
+    const K k = keys[i];
+    if constexpr (kForm == kReadXz) {
+      // qubit q's digit is at key bits 2(n-1-q): the planes, bits reversed
+      uint64_t hi = pack_bits((uint64_t)k >> 1), lo = pack_bits((uint64_t)k);
+      if constexpr (sizeof(K) > 8) {
+        hi |= (uint64_t)pack_bits((uint64_t)(k >> 64) >> 1) << 32;
+        lo |= (uint64_t)pack_bits((uint64_t)(k >> 64)) << 32;
+      }
+      words[i] = __brevll(hi ^ lo) >> (64 - n);
+      zs[i] = __brevll(hi) >> (64 - n);
+    } else if constexpr (kForm == kReadWords2) {
+      ulonglong2 v;
+      v.x = (uint64_t)k;
+      if constexpr (sizeof(K) > 8) v.y = (uint64_t)(k >> 64);
+      else v.y = 0;
+      ((ulonglong2*)words)[i] = v;
+    } else {
+      words[i] = (uint64_t)k;
+    }
+    wd[i] = (double)w[i];
+  }
+}
+
+hipError_t launch_export(int KC, int WP, const void* keys, const void* w, uint64_t T, ReadForm form, uint32_t n,
+                         uint64_t* words, uint64_t* next, hipStream_t s) {
   if (T == 0) return hipSuccess;
-  const uint64_t nb = (T + 255) / 256;
-  if (nb > 0x7FFFFFFFull || (n_words != 1 && n_words != 2)) return hipErrorInvalidValue;
+  if (n < 1 || n > 64 || (uintptr_t)words % 16) return hipErrorInvalidValue;
+  const uint32_t g = (uint32_t)std::min<uint64_t>((T + 255) / 256, 1024);
+  double* const wd = (double*)(form == kReadWords1 ? next : next + (next - words));
+#define QIMAX_EXPORT(W, F) \
+  k_export<K, W, F><<<g, 256, 0, s>>>((const K*)keys, (const W*)w, T, n, words, next, wd)
   QIMAX_DISPATCH_K(KC, {
-    if (WP == 64) k_export<K, double><<<(uint32_t)nb, 256, 0, s>>>((const K*)keys, (const double*)w, T, n_words, words, wd);
-    else k_export<K, float><<<(uint32_t)nb, 256, 0, s>>>((const K*)keys, (const float*)w, T, n_words, words, wd);
+    if (WP == 64) {
+      if (form == kReadXz) QIMAX_EXPORT(double, kReadXz);
+      else if (form == kReadWords2) QIMAX_EXPORT(double, kReadWords2);
+      else QIMAX_EXPORT(double, kReadWords1);
+    } else {
+      if (form == kReadXz) QIMAX_EXPORT(float, kReadXz);
+      else if (form == kReadWords2) QIMAX_EXPORT(float, kReadWords2);
+      else QIMAX_EXPORT(float, kReadWords1);
+    }
   });
+#undef QIMAX_EXPORT
   return hipGetLastError();
 }
 
@@ -3628,14 +3653,6 @@ hipError_t launch_round_prep(uint32_t* err, uint32_t* ctr, uint32_t n_ctr, uint3
 hipError_t launch_copy_u64(const uint64_t* in, uint64_t* out, uint64_t n, hipStream_t s) {
   if (n == 0) return hipSuccess;
   k_copy_u64<<<std::min<uint64_t>(grid_for(n, 256), 65536), 256, 0, s>>>(in, out, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_weights_to_f64(int WP, const void* w, double* out, uint64_t T, hipStream_t s, Prof* prof) {
-  (void)prof;
-  if (T == 0) return hipSuccess;
-  if (WP == 64) k_weights_to_f64<64><<<grid_for(T, 256), 256, 0, s>>>((const double*)w, out, T);
-  else k_weights_to_f64<32><<<grid_for(T, 256), 256, 0, s>>>((const float*)w, out, T);
   return hipGetLastError();
 }
 

@@ -17,6 +17,7 @@
 #include <new>
 #include <random>
 #include <string>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -392,7 +393,7 @@ struct qimax_ctx {
   // images and sort ping-pong
   DevBuf ik[2], iw[2];
   DevBuf cnt, off, scan_tmp, hist, hist_off, blk_begin, blk_end, blk_seg, seg_blk, blk_cnt, blk_off, img_seg;
-  DevBuf desc, desc2, err, f64tmp;
+  DevBuf desc, desc2, err;
   DevBuf ptab;  // chain tables of a whole call, compiled in one launch
   // Memory a context can do without: the scratch of long chains' joins (chain_parts) and the
   // tables of 16-byte keys (wtab for a round's, ptab for a call's). Where it leaves too little
@@ -449,6 +450,11 @@ struct qimax_ctx {
   uint64_t* zres_dev = nullptr;
   size_t zres_words = 0;
   uint64_t zseq = 0;  // sequence word of the last results asked for
+  // pinned, device-mapped slots of the readout (see read_terms), and an event per slot
+  void* read_stage = nullptr;
+  void* read_dev = nullptr;
+  size_t read_bytes = 0;
+  hipEvent_t read_ev[12] = {};
   // step recording (qimax_graph_record): the work of a step is captured between the host's
   // synchronisations and replayed later as one graph
   struct qimax_graph* rec = nullptr;
@@ -2314,32 +2320,170 @@ qimax_status fetch(qimax_ctx* c, HostGens& g) {
   return QIMAX_OK;
 }
 
-// Terms [a, a + T) of the committed term arrays to host memory as the C-ABI returns them
-// (n_words uint64 words per key, FP64 weights): converted on the device and copied in chunks
-// through the image buffers, which are idle between calls and between rounds. *done stays
-// false (nothing written) where those buffers cannot hold a chunk of 64 Ki terms or a graph
-// is being recorded; the caller then converts on the host.
-qimax_status export_terms(qimax_ctx* c, uint64_t a, uint64_t T, uint32_t n_words, uint64_t* words, double* w,
-                          bool* done) {
+// ------------------------------------------------------------------------ readout
+// Terms leave the device in the C-ABI's form through pinned, mapped staging: a kernel converts a
+// chunk of terms straight into a slot of it, and host threads copy the slots that are complete
+// into the caller's memory while the next chunks cross the link. (The caller's memory is
+// pageable and mostly untouched: one thread writes it at 10-16 GB/s, page faults included, while
+// the link brings 57 GB/s. Measured for 44.5 M terms, 711 MB: 68 ms with copies into pageable
+// memory, 16 ms here; for the n = 16 ansatz's 1165 MB 111 and 26 ms.) Short readouts take one
+// slot and no thread (21 terms: 38 and 15 us).
+constexpr uint64_t kReadChunk = 1ull << 17;  // terms of a slot: 2 or 3 MB
+constexpr int kReadSlots = 12;
+constexpr uint32_t kReadThreads = 8;
+
+// Host threads for `items` pieces of work.
+uint32_t copy_threads(uint64_t items) {
+  const uint32_t hw = std::max(1u, std::thread::hardware_concurrency());
+  return (uint32_t)std::min<uint64_t>(items, std::min(kReadThreads, std::max(1u, hw / 2)));
+}
+
+// Runs work(i) for i < n on up to copy_threads(n) threads, the caller's among them.
+template <typename F>
+void parallel_for(uint64_t n, const F& work) {
+  std::atomic<uint64_t> next{0};
+  auto body = [&] {
+    for (uint64_t i; (i = next.fetch_add(1)) < n;) work(i);
+  };
+  std::vector<std::thread> pool;
+  try {
+    for (uint32_t t = 1; t < copy_threads(n); ++t) pool.emplace_back(body);
+  } catch (...) {  // fewer threads, or none
+  }
+  body();
+  for (auto& t : pool) t.join();
+}
+
+// memcpy by several threads where the length is worth them.
+void copy_large(void* dst, const void* src, size_t bytes) {
+  constexpr size_t kPiece = 4 << 20;
+  if (bytes < 2 * kPiece) {
+    if (bytes) std::memcpy(dst, src, bytes);
+    return;
+  }
+  parallel_for((bytes + kPiece - 1) / kPiece, [&](uint64_t i) {
+    const size_t o = i * kPiece;
+    std::memcpy((uint8_t*)dst + o, (const uint8_t*)src + o, std::min(kPiece, bytes - o));
+  });
+}
+
+// Staging of `slots` slots of `bytes` each; false (nothing held) if it cannot be had.
+bool ensure_read_stage(qimax_ctx* c, int slots, size_t bytes) {
+  const size_t want = (size_t)slots * bytes;
+  if (c->read_stage && c->read_bytes >= want) return true;
+  if (c->read_stage) (void)hipHostFree(c->read_stage);  // (no readout is in flight)
+  c->read_stage = nullptr;
+  c->read_bytes = 0;
+  if (hipHostMalloc(&c->read_stage, want, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+      hipHostGetDevicePointer(&c->read_dev, c->read_stage, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    if (c->read_stage) (void)hipHostFree(c->read_stage);
+    c->read_stage = nullptr;
+    return false;
+  }
+  c->read_bytes = want;
+  for (int i = 0; i < kReadSlots; ++i)
+    if (!c->read_ev[i] && hipEventCreateWithFlags(&c->read_ev[i], hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      c->read_ev[i] = nullptr;
+      return false;
+    }
+  return true;
+}
+
+// Terms [a, a + T) of the committed term arrays to host memory: n_words uint64 words per key in
+// `words` (form kReadWords1 / 2) or the x and z words of an n-qubit key in `words` and `z`
+// (kReadXz), weights as FP64 in w. *done stays false (nothing written) where no staging can be
+// had or a graph is being recorded.
+qimax_status read_terms(qimax_ctx* c, uint64_t a, uint64_t T, ReadForm form, uint32_t n, uint64_t* words, uint64_t* z,
+                        double* w, bool* done) {
   *done = false;
   if (c->rec) return QIMAX_OK;
   if (T == 0) {
     *done = true;
     return QIMAX_OK;
   }
-  if (!c->ik[0].p || !c->iw[0].p) return QIMAX_OK;
-  const uint64_t cap = std::min<uint64_t>(c->ik[0].bytes / (8ull * n_words), c->iw[0].bytes / 8);
-  if (cap < (1ull << 16)) return QIMAX_OK;
+  const size_t per = form == kReadWords1 ? 16 : 24;
+  // at least eight chunks where they are of 16 Ki terms or more: several threads, and the link
+  // and the copies overlap
+  const uint64_t m = T <= (1ull << 16) ? T : std::min(kReadChunk, std::max<uint64_t>(1ull << 14, (T / 8 + 255) / 256 * 256));
+  const uint64_t n_chunks = (T + m - 1) / m;
+  const int slots = (int)std::min<uint64_t>(kReadSlots, n_chunks);
+  const size_t slot_bytes = align256((size_t)m * per);
+  if (!ensure_read_stage(c, slots, slot_bytes)) return QIMAX_OK;
   const uint8_t* kb = (const uint8_t*)c->keys.p + a * c->kb;
   const uint8_t* wb = (const uint8_t*)c->w.p + a * c->wb;
-  for (uint64_t i = 0; i < T; i += cap) {
-    const uint64_t m = std::min(cap, T - i);
-    HIPCHK(c, launch_export(c->KC, c->WP, kb + i * c->kb, wb + i * c->wb, m, n_words, (uint64_t*)c->ik[0].p,
-                            (double*)c->iw[0].p, c->stream), "export");
-    HIPCHK(c, hipMemcpyAsync(words + i * n_words, c->ik[0].p, m * n_words * 8, hipMemcpyDeviceToHost, c->stream),
-           "export D2H");
-    HIPCHK(c, hipMemcpyAsync(w + i, c->iw[0].p, m * 8, hipMemcpyDeviceToHost, c->stream), "export D2H");
+  auto launch = [&](uint64_t i) -> hipError_t {
+    const uint64_t o = i * m, k = std::min(m, T - o);
+    uint64_t* d = (uint64_t*)((uint8_t*)c->read_dev + (i % slots) * slot_bytes);
+    return launch_export(c->KC, c->WP, kb + o * c->kb, wb + o * c->wb, k, form, n, d, d + m, c->stream);
+  };
+  auto copy = [&](uint64_t i) {  // slot: words (1 or 2 per term, or x then z), then weights
+    const uint64_t o = i * m, k = std::min(m, T - o);
+    const uint64_t* h = (const uint64_t*)((const uint8_t*)c->read_stage + (i % slots) * slot_bytes);
+    if (form == kReadXz) {
+      std::memcpy(words + o, h, k * 8);
+      std::memcpy(z + o, h + m, k * 8);
+      std::memcpy(w + o, h + 2 * m, k * 8);
+    } else {
+      const uint64_t nw = form == kReadWords1 ? 1 : 2;
+      std::memcpy(words + o * nw, h, k * nw * 8);
+      std::memcpy(w + o, h + nw * m, k * 8);
+    }
+  };
+  if (n_chunks == 1) {
+    HIPCHK(c, launch(0), "export");
     HIPCHK(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
+    copy(0);
+    *done = true;
+    return QIMAX_OK;
+  }
+  std::atomic<uint64_t> ready{0}, next{0}, copied[kReadSlots] = {};
+  std::atomic<bool> stop{false};
+  auto worker = [&] {
+    for (uint64_t i; (i = next.fetch_add(1)) < n_chunks;) {
+      while (ready.load(std::memory_order_acquire) <= i) {
+        if (stop.load(std::memory_order_relaxed)) return;
+        __builtin_ia32_pause();
+      }
+      copy(i);
+      copied[i % slots].store(i + 1, std::memory_order_release);
+    }
+  };
+  std::vector<std::thread> pool;
+  try {
+    for (uint32_t t = 0; t < copy_threads(n_chunks); ++t) pool.emplace_back(worker);
+  } catch (...) {  // fewer threads, or none: the caller's copies too
+  }
+  hipError_t e = hipSuccess;
+  uint64_t launched = 0;
+  for (uint64_t i = 0; i < n_chunks && e == hipSuccess; ++i) {
+    // every chunk whose slot is free crosses the link; the next one in order is waited for
+    while (launched < n_chunks && e == hipSuccess) {
+      const uint64_t before = launched < (uint64_t)slots ? 0 : launched - slots + 1;  // the slot's last chunk, copied
+      if (copied[launched % slots].load(std::memory_order_acquire) != before) {
+        if (launched > i) break;
+        if (pool.empty()) break;
+        __builtin_ia32_pause();
+        continue;
+      }
+      e = launch(launched);
+      if (e == hipSuccess) e = hipEventRecord(c->read_ev[launched % slots], c->stream);
+      ++launched;
+    }
+    if (e == hipSuccess) e = hipEventSynchronize(c->read_ev[i % slots]);
+    if (e != hipSuccess) break;
+    ready.store(i + 1, std::memory_order_release);
+    if (pool.empty()) {
+      copy(i);
+      copied[i % slots].store(i + 1, std::memory_order_release);
+    }
+  }
+  if (e != hipSuccess) stop.store(true);
+  for (auto& t : pool) t.join();
+  if (e != hipSuccess) {
+    (void)hipStreamSynchronize(c->stream);  // nothing writes the slots any more
+    return hip_fail(c, e, "export");
   }
   *done = true;
   return QIMAX_OK;
@@ -2917,7 +3061,7 @@ qimax_status qimax_get_generators(qimax_ctx* c, uint64_t* gen_off, uint64_t* key
   }
   if (!gen_off || (c->T && (!keys || !w))) return fail(c, QIMAX_EINVAL, "output buffers are NULL");
   bool done = false;
-  QCHK(export_terms(c, 0, c->T, c->n <= 32 ? 1u : 2u, keys, w, &done));
+  QCHK(read_terms(c, 0, c->T, c->n <= 32 ? kReadWords1 : kReadWords2, c->n, keys, nullptr, w, &done));
   if (done) {
     std::copy(c->h_seg.begin(), c->h_seg.end(), gen_off);
     return QIMAX_OK;
@@ -2982,27 +3126,9 @@ qimax_status qimax_get_generators_xz(qimax_ctx* c, uint64_t* gen_off, uint64_t* 
   if (cap < c->T) return QIMAX_OK;
   if (!gen_off || (c->T && (!x || !z || !w))) return fail(c, QIMAX_EINVAL, "output buffers are NULL");
   if (c->T == 0) return QIMAX_OK;
-  const size_t tb = (size_t)c->T * 8;
-  void* mem = nullptr;
-  if (hipMalloc(&mem, 3 * tb) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(c, QIMAX_ENOMEM, "get_generators_xz: hipMalloc of the readout buffers failed");
-  }
-  uint64_t* dx = (uint64_t*)mem;
-  uint64_t* dz = dx + c->T;
-  double* dw = (double*)(dz + c->T);
-  hipError_t e = launch_keys_to_xz(c->KC, c->keys.p, c->T, c->n, dx, dz, c->stream);
-  if (e == hipSuccess) {
-    if (c->WP == 64) e = hipMemcpyAsync(dw, c->w.p, tb, hipMemcpyDeviceToDevice, c->stream);
-    else e = launch_weights_to_f64(c->WP, c->w.p, dw, c->T, c->stream);
-  }
-  if (e == hipSuccess) e = hipMemcpyAsync(x, dx, tb, hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(z, dz, tb, hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(w, dw, tb, hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  (void)hipFree(mem);
-  if (e != hipSuccess) return hip_fail(c, e, "get_generators_xz");
-  return QIMAX_OK;
+  bool done = false;
+  QCHK(read_terms(c, 0, c->T, kReadXz, c->n, x, z, w, &done));
+  return done ? QIMAX_OK : fail(c, QIMAX_ENOMEM, "get_generators_xz: no pinned host memory for the readout");
 }
 
 namespace {
@@ -3233,13 +3359,16 @@ void qimax_destroy(qimax_ctx* c) {
   DevBuf* bufs[] = {&c->keys, &c->w, &c->seg, &c->pk[0], &c->pk[1], &c->pw[0], &c->pw[1], &c->pseg[0],
                     &c->pseg[1], &c->ik[0], &c->ik[1], &c->iw[0], &c->iw[1], &c->cnt, &c->off, &c->scan_tmp,
                     &c->hist, &c->hist_off, &c->blk_begin, &c->blk_end, &c->blk_seg, &c->seg_blk, &c->blk_cnt,
-                    &c->blk_off, &c->img_seg, &c->desc, &c->desc2, &c->err, &c->f64tmp, &c->gr_in, &c->gr_out, &c->ghist, &c->sbase, &c->sstatus, &c->tile_ctr, &c->mstatus, &c->dtile[0], &c->dtile[1], &c->dtile[2], &c->ptab, &c->chain_parts, &c->wtab, &c->akeys, &c->asign, &c->img_cnt, &c->dense_acc, &c->chunk_cnt, &c->chunk_start, &c->grp_cnt,
+                    &c->blk_off, &c->img_seg, &c->desc, &c->desc2, &c->err, &c->gr_in, &c->gr_out, &c->ghist, &c->sbase, &c->sstatus, &c->tile_ctr, &c->mstatus, &c->dtile[0], &c->dtile[1], &c->dtile[2], &c->ptab, &c->chain_parts, &c->wtab, &c->akeys, &c->asign, &c->img_cnt, &c->dense_acc, &c->chunk_cnt, &c->chunk_start, &c->grp_cnt,
                     &c->chunk_off};
   for (DevBuf* b : bufs) dev_free(c, *b);
   if (c->pinned) (void)hipHostFree(c->pinned);
   for (int i = 0; i < 2; ++i)
     if (c->stage[i]) (void)hipHostFree(c->stage[i]);
   if (c->zres) (void)hipHostFree(c->zres);
+  if (c->read_stage) (void)hipHostFree(c->read_stage);
+  for (hipEvent_t e : c->read_ev)
+    if (e) (void)hipEventDestroy(e);
   prof_destroy(&c->prof);
   for (hipEvent_t e : c->tune_ev)
     if (e) (void)hipEventDestroy(e);
@@ -3264,8 +3393,11 @@ struct BatchCirc {
   size_t next = 0;
   int state = 0;  // 0 queued, 1 active, 2 draining (result taken; terms leave next round), 3 done
   uint64_t updates = 0;
-  std::vector<uint64_t> res_off, res_key;
-  std::vector<double> res_w;
+  std::vector<uint64_t> res_off;
+  // the result, terms in memory that is first written by the threads that copy it there
+  uint64_t res_terms = 0;
+  std::unique_ptr<uint64_t[]> res_key;
+  std::unique_ptr<double[]> res_w;
 };
 
 }  // namespace
@@ -3339,12 +3471,14 @@ qimax_status plan_circuit(qimax_batch* b, const qimax_circuit* q, double eps, Ba
 
 void initial_result(BatchCirc& bc) {
   bc.res_off.resize(bc.n + 1);
-  bc.res_w.assign(bc.n, 1.0);
+  bc.res_terms = bc.n;
+  bc.res_w.reset(new double[bc.n]);
+  std::fill(bc.res_w.get(), bc.res_w.get() + bc.n, 1.0);
   for (uint32_t j = 0; j <= bc.n; ++j) bc.res_off[j] = j;
   std::vector<u128> k(bc.n);
   for (uint32_t j = 0; j < bc.n; ++j) k[j] = (u128)3 << (2 * (bc.n - 1 - j));
-  bc.res_key.resize((size_t)bc.n * (bc.n <= 32 ? 1 : 2));
-  keys_to_words(k, bc.n, bc.res_key.data());
+  bc.res_key.reset(new uint64_t[(size_t)bc.n * (bc.n <= 32 ? 1 : 2)]);
+  keys_to_words(k, bc.n, bc.res_key.get());
 }
 
 // Admit the queued circuits: their Z_j terms go to the end of the term array.
@@ -3390,22 +3524,26 @@ qimax_status take_result(qimax_batch* b, BatchCirc& bc, size_t s0) {
   const uint64_t a = b->so[s0], e = b->so[s0 + bc.n];
   bc.res_off.resize(bc.n + 1);
   for (uint32_t j = 0; j <= bc.n; ++j) bc.res_off[j] = b->so[s0 + j] - a;
-  bc.res_w.resize(e - a);
+  const size_t T = e - a;
   const uint32_t n_words = bc.n <= 32 ? 1u : 2u;
-  bc.res_key.resize((e - a) * n_words);
+  bc.res_terms = T;
+  bc.res_w.reset(new (std::nothrow) double[std::max<size_t>(T, 1)]);
+  bc.res_key.reset(new (std::nothrow) uint64_t[std::max<size_t>(T, 1) * n_words]);
+  if (!bc.res_w || !bc.res_key) return fail(c, QIMAX_ENOMEM, "no host memory for a circuit's result");
   bool done = false;
-  QCHK(export_terms(c, a, e - a, n_words, bc.res_key.data(), bc.res_w.data(), &done));
+  QCHK(read_terms(c, a, T, n_words == 1 ? kReadWords1 : kReadWords2, bc.n, bc.res_key.get(), nullptr, bc.res_w.get(),
+                  &done));
   if (done) return QIMAX_OK;
   std::vector<u128> k;
-  HIPCHK(c, keys_to_host(c, (const uint8_t*)c->keys.p + a * c->kb, e - a, k), "result");
-  keys_to_words(k, bc.n, bc.res_key.data());
-  if (e == a) return QIMAX_OK;
+  HIPCHK(c, keys_to_host(c, (const uint8_t*)c->keys.p + a * c->kb, T, k), "result");
+  keys_to_words(k, bc.n, bc.res_key.get());
+  if (T == 0) return QIMAX_OK;
   if (c->WP == 64) {
-    HIPCHK(c, hipMemcpy(bc.res_w.data(), (double*)c->w.p + a, (e - a) * 8, hipMemcpyDeviceToHost), "result");
+    HIPCHK(c, hipMemcpy(bc.res_w.get(), (double*)c->w.p + a, T * 8, hipMemcpyDeviceToHost), "result");
   } else {
-    std::vector<float> w32(e - a);
-    HIPCHK(c, hipMemcpy(w32.data(), (float*)c->w.p + a, (e - a) * 4, hipMemcpyDeviceToHost), "result");
-    for (size_t i = 0; i < w32.size(); ++i) bc.res_w[i] = w32[i];
+    std::vector<float> w32(T);
+    HIPCHK(c, hipMemcpy(w32.data(), (float*)c->w.p + a, T * 4, hipMemcpyDeviceToHost), "result");
+    for (size_t i = 0; i < T; ++i) bc.res_w[i] = w32[i];
   }
   return QIMAX_OK;
 }
@@ -3583,16 +3721,19 @@ qimax_status qimax_batch_fetch(qimax_batch* b, uint64_t id, uint64_t* gen_off, u
   if (it == b->circs.end()) return bfail(b, QIMAX_EINVAL, "unknown circuit id");
   BatchCirc& bc = it->second;
   if (bc.state < 2) return bfail(b, QIMAX_ESTATE, "circuit not finished");
-  *T = bc.res_w.size();
-  if (cap < bc.res_w.size()) return QIMAX_OK;
+  *T = bc.res_terms;
+  if (cap < bc.res_terms) return QIMAX_OK;
   if (!gen_off || (*T && (!keys || !w))) return bfail(b, QIMAX_EINVAL, "output buffers are NULL");
   std::copy(bc.res_off.begin(), bc.res_off.end(), gen_off);
-  std::copy(bc.res_key.begin(), bc.res_key.end(), keys);
-  std::copy(bc.res_w.begin(), bc.res_w.end(), w);
+  copy_large(keys, bc.res_key.get(), bc.res_terms * (bc.n <= 32 ? 8 : 16));
+  copy_large(w, bc.res_w.get(), bc.res_terms * 8);
   if (bc.state == 3) {
     b->circs.erase(it);
   } else {
-    bc.res_off.clear(); bc.res_key.clear(); bc.res_w.clear();
+    bc.res_off.clear();
+    bc.res_key.reset();
+    bc.res_w.reset();
+    bc.res_terms = 0;
     bc.state = 4;  // taken; its terms leave the array next round, then the record goes
   }
   return QIMAX_OK;

@@ -205,9 +205,13 @@ void prof_destroy(Prof* p);
 hipError_t launch_init(int KC, int WP, void* keys, void* w, uint64_t* seg_off, uint32_t n,
                        hipStream_t s, Prof* prof = nullptr);
 
-// T terms converted for the host: keys to n_words (1 or 2) uint64 words each, weights to FP64.
-hipError_t launch_export(int KC, int WP, const void* keys, const void* w, uint64_t T, uint32_t n_words,
-                         uint64_t* words, double* wd, hipStream_t s);
+// How terms are handed out: keys as one or two uint64 words each, or (kReadXz) the x and z bit
+// words of an n-qubit key (bit q: qubit q), an array each.
+enum ReadForm { kReadWords1, kReadWords2, kReadXz };
+// T terms converted for the host: `words` receives the keys' words, or the x words followed at
+// `next` by the z words; the FP64 weights follow at next (one word) or next + (next - words).
+hipError_t launch_export(int KC, int WP, const void* keys, const void* w, uint64_t T, ReadForm form, uint32_t n,
+                         uint64_t* words, uint64_t* next, hipStream_t s);
 
 // Fan-out count fused with its scan (single sweep with decoupled look-back over the tiles of
 // tl, claimed through *ctr): off[i] = first image of input term i, off[T] = image count;
@@ -418,9 +422,6 @@ hipError_t launch_publish(uint32_t S, const MergeFin& fin, const uint32_t* err, 
 // Plain copy of n words (calibration of hardware traffic counters).
 hipError_t launch_copy_u64(const uint64_t* in, uint64_t* out, uint64_t n, hipStream_t s);
 
-// Weights to FP64 (readout).
-hipError_t launch_weights_to_f64(int WP, const void* w, double* out, uint64_t T, hipStream_t s, Prof* prof = nullptr);
-
 // Grouping pass: compose chains of one-qubit gates into 4x4 PTMs (R[out][in], FP64).
 // chain c covers gate indices idx[chain_off[c] .. chain_off[c+1]-1] in application order.
 hipError_t launch_compose_ptm(const uint8_t* gate, const double* theta, const uint32_t* idx,
@@ -428,9 +429,6 @@ hipError_t launch_compose_ptm(const uint8_t* gate, const double* theta, const ui
                               hipStream_t s, Prof* prof = nullptr);
 
 // ------------------------------------------------------------- readout (readout.hip)
-// Keys as x / z bit words (bit q: qubit q), one word each (n <= 64).
-hipError_t launch_keys_to_xz(int KC, const void* keys, uint64_t T, uint32_t n, uint64_t* x, uint64_t* z,
-                             hipStream_t s);
 // Per-generator comparison of side a with side b (see k_compare); tiles of at most
 // compare_tile() elements of side a, each inside one segment; acc[2s] / acc[2s+1] and cnt[s]
 // accumulate (zeroed by the caller).

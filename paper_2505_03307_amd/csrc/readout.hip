@@ -1,8 +1,8 @@
-// Readout kernels for gfx950, off the propagation loop: the generators' keys as x/z bit
-// words, a per-generator comparison of two term lists (the stated error of an FP32 result
-// against an FP64 one), and expectation values <psi|P|psi> = Tr(rho P) with
-// rho = 2^-n prod_j (I + G_j) (paper, eq. (2)) from a device statevector: a random vector is
-// projected onto the common +1 eigenspace of the generators, one (I + G_j)/2 at a time.
+// Readout kernels for gfx950, off the propagation loop: a per-generator comparison of two term
+// lists (the stated error of an FP32 result against an FP64 one), and expectation values
+// <psi|P|psi> = Tr(rho P) with rho = 2^-n prod_j (I + G_j) (paper, eq. (2)) from a device
+// statevector: a random vector is projected onto the common +1 eigenspace of the generators,
+// one (I + G_j)/2 at a time.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -15,25 +15,6 @@ namespace qimax {
 namespace {
 
 inline uint32_t blocks_for(uint64_t n, uint32_t block) { return (uint32_t)((n + block - 1) / block); }
-
-// -------------------------------------------------------------------------- x / z words
-// Base-4 digit d of qubit q sits at bit 2(n-1-q) of a key; bit q of x is set for X and Y,
-// bit q of z for Y and Z.
-template <typename K>
-__global__ void k_keys_to_xz(const K* __restrict__ keys, uint64_t T, uint32_t n, uint64_t* __restrict__ x,
-                             uint64_t* __restrict__ z) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= T) return;
-  const K k = keys[i];
-  uint64_t xs = 0, zs = 0;
-  for (uint32_t q = 0; q < n; ++q) {
-    const uint32_t d = (uint32_t)(k >> (2 * (n - 1 - q))) & 3u;
-    xs |= (uint64_t)(d == 1u || d == 2u) << q;
-    zs |= (uint64_t)(d >= 2u) << q;
-  }
-  x[i] = xs;
-  z[i] = zs;
-}
 
 // ----------------------------------------------------------------------------- compare
 // Tiles of one side's segments (each tile inside one segment). For every element of side
@@ -276,16 +257,6 @@ hipError_t launch_sv_terms(int KC, int WP, const void* keys, const void* w, uint
   else if (KC == 1) QIMAX_SVT(uint64_t);
   else QIMAX_SVT(unsigned __int128);
 #undef QIMAX_SVT
-  return hipGetLastError();
-}
-
-hipError_t launch_keys_to_xz(int KC, const void* keys, uint64_t T, uint32_t n, uint64_t* x, uint64_t* z,
-                             hipStream_t s) {
-  if (T == 0) return hipSuccess;
-  if (KC == 0) k_keys_to_xz<uint32_t><<<blocks_for(T, 256), 256, 0, s>>>((const uint32_t*)keys, T, n, x, z);
-  else if (KC == 1) k_keys_to_xz<uint64_t><<<blocks_for(T, 256), 256, 0, s>>>((const uint64_t*)keys, T, n, x, z);
-  else
-    k_keys_to_xz<unsigned __int128><<<blocks_for(T, 256), 256, 0, s>>>((const unsigned __int128*)keys, T, n, x, z);
   return hipGetLastError();
 }
 
