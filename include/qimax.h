@@ -174,8 +174,9 @@ qimax_status qimax_get_generators_xz(qimax_ctx* ctx, uint64_t* gen_off, uint64_t
  * fails as soon as two generators share a string). Two methods, both exact up to rounding:
  *  - every generator a single term of weight +-1 (a stabilizer state): GF(2) elimination of
  *    the generators' x/z vectors on the host, O(n^3);
- *  - otherwise, for n <= 30: a statevector on the device (2^n complex doubles, twice, plus
- *    the terms; allocated for the call and freed): a seeded random vector is projected by
+ *  - otherwise, for n <= 30: a statevector on the device (2^n complex doubles, at least twice;
+ *    kept for the next call up to 64 MiB in all, else freed, and given back when other memory
+ *    is short): a seeded random vector is projected by
  *    (I + G_j)/2 for every j, normalised, and <v|P|v> is reduced on the device. Cost: the
  *    sum of all generators' term counts times 2^n. QIMAX_ETOOLARGE for n > 30 or a cost
  *    above 4e13; QIMAX_ENOMEM when the statevector does not fit.

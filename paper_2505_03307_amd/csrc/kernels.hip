@@ -2778,22 +2778,9 @@ __global__ void __launch_bounds__(kChainBlock) k_chain_joins(const TableJoin* __
       const unsigned __int128 im = apply_table<unsigned __int128>(key, (const unsigned __int128*)cur.xz,
                                                                   (const uint8_t*)cur.phase, (uint32_t)sizeof(K) * 2u, neg);
       // back to planes: z is the odd bits, x the even bits XOR the odd ones
-      uint64_t zz = 0, lo = 0;
-#pragma unroll
-      for (int w = 0; w < 2; ++w) {
-        uint64_t h = (uint64_t)(im >> (64 * w));
-        uint64_t e[2] = {h & 0x5555555555555555ull, (h >> 1) & 0x5555555555555555ull};
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          e[q] = (e[q] | (e[q] >> 1)) & 0x3333333333333333ull;
-          e[q] = (e[q] | (e[q] >> 2)) & 0x0F0F0F0F0F0F0F0Full;
-          e[q] = (e[q] | (e[q] >> 4)) & 0x00FF00FF00FF00FFull;
-          e[q] = (e[q] | (e[q] >> 8)) & 0x0000FFFF0000FFFFull;
-          e[q] = (e[q] | (e[q] >> 16)) & 0x00000000FFFFFFFFull;
-        }
-        lo |= e[0] << (32 * w);
-        zz |= e[1] << (32 * w);
-      }
+      const uint64_t l = (uint64_t)im, h = (uint64_t)(im >> 64);
+      const uint64_t zz = ((uint64_t)pack_bits(h >> 1) << 32) | pack_bits(l >> 1);
+      const uint64_t lo = ((uint64_t)pack_bits(h) << 32) | pack_bits(l);
       z = zz;
       x = lo ^ zz;
     }
@@ -3402,16 +3389,6 @@ hipError_t launch_build_tables(int KC, const TableLaunch& t, hipStream_t s, Prof
   });
   prof_end(prof, s, ev, kKTables, 0.0);
   return hipGetLastError();
-}
-
-// The even bits of v, packed.
-__device__ __forceinline__ uint32_t pack_bits(uint64_t v) {
-  v &= 0x5555555555555555ull;
-  v = (v | (v >> 1)) & 0x3333333333333333ull;
-  v = (v | (v >> 2)) & 0x0F0F0F0F0F0F0F0Full;
-  v = (v | (v >> 4)) & 0x00FF00FF00FF00FFull;
-  v = (v | (v >> 8)) & 0x0000FFFF0000FFFFull;
-  return (uint32_t)(v | (v >> 16));
 }
 
 // Terms as the C-ABI hands them out, written to mapped host memory: each key as one or two

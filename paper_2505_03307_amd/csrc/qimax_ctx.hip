@@ -399,6 +399,8 @@ struct qimax_ctx {
   // tables of 16-byte keys (wtab for a round's, ptab for a call's). Where it leaves too little
   // for the rest, it is given back and the call runs again without it (lean from then on).
   DevBuf chain_parts, wtab;
+  void* sv_mem = nullptr;  // the statevector readout's memory (no part of a recorded step)
+  size_t sv_bytes = 0;
   bool opt_busy = false, lean = false;
   DevBuf akeys, asign;  // input terms after their pass's A chain, and the signs (count -> expand)
   DevBuf chunk_off, chunk_cnt, chunk_start;  // chunk-local merge: offset, kept terms, deferred runs per chunk
@@ -502,7 +504,20 @@ void dev_free(qimax_ctx* c, DevBuf& b) {
 
 // Gives back the memory the context can do without (see qimax_ctx::chain_parts); false if it
 // holds none or a call is using it.
+void drop_sv(qimax_ctx* c) {
+  if (!c->sv_mem) return;
+  (void)hipFree(c->sv_mem);
+  c->alloc_bytes -= c->sv_bytes;
+  c->sv_mem = nullptr;
+  c->sv_bytes = 0;
+}
+
 bool drop_optional(qimax_ctx* c) {
+  if (c->sv_mem && !c->rec) {  // (no propagation uses it)
+    (void)hipStreamSynchronize(c->stream);
+    drop_sv(c);
+    return true;
+  }
   DevBuf* const opt[] = {&c->chain_parts, &c->wtab, c->kb > 8 ? &c->ptab : nullptr};
   bool any = false;
   for (DevBuf* b : opt) any |= b && b->p;
@@ -588,6 +603,26 @@ qimax_status ensure_keep(qimax_ctx* c, DevBuf& b, size_t bytes, size_t keep) {
   return QIMAX_OK;
 }
 
+qimax_status ensure_sv(qimax_ctx* c, size_t bytes) {
+  if (c->sv_mem && c->sv_bytes >= bytes) return QIMAX_OK;
+  if (c->sv_mem) {
+    HIPCHK(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
+    drop_sv(c);
+  }
+  for (;;) {
+    if (!c->cap || c->alloc_bytes + bytes <= c->cap) {
+      if (hipMalloc(&c->sv_mem, bytes) == hipSuccess) break;
+      (void)hipGetLastError();
+      c->sv_mem = nullptr;
+    }
+    if (!drop_optional(c)) return fail(c, QIMAX_ENOMEM, "expect: no device memory for the statevector");
+  }
+  c->sv_bytes = bytes;
+  c->alloc_bytes += bytes;
+  c->peak_bytes = std::max(c->peak_bytes, c->alloc_bytes);
+  return QIMAX_OK;
+}
+
 // Runs a call's work, and once more without the memory it can do without where that left too
 // little (a failing call leaves the state as it was).
 template <typename F>
@@ -598,7 +633,10 @@ qimax_status with_optional(qimax_ctx* c, const F& body) {
   c->opt_busy = true;
   qimax_status s = body();
   c->opt_busy = false;
-  if (s == QIMAX_ENOMEM && !c->lean && drop_optional(c)) {
+  bool dropped = false;
+  if (s == QIMAX_ENOMEM && !c->lean)
+    while (drop_optional(c)) dropped = true;
+  if (dropped) {
     c->lean = true;
     c->st = st0;
     c->gen_updates = upd0;
@@ -2579,6 +2617,8 @@ struct CliffordReducer {
 
 constexpr uint32_t kSvMaxN = 30;     // device statevector readout: at most 2^30 amplitudes
 constexpr double kSvMaxWork = 4e13;  // sum over generators of terms x 2^n
+constexpr size_t kSvRows = 16384;    // strings of a launch
+constexpr size_t kSvKeep = 64u << 20;  // a statevector's memory up to this size is kept for the next call
 
 // Every generator a single term of weight +-1 (the state is a stabilizer state)?
 qimax_status clifford_reducer(qimax_ctx* c, bool* is_cliff, CliffordReducer& red) {
@@ -2615,71 +2655,65 @@ qimax_status expect_device(qimax_ctx* c, const std::vector<std::vector<int>>& Ps
   if (n > kSvMaxN) return fail(c, QIMAX_ETOOLARGE, "expect: a state with non-Clifford generators and n > 30");
   const uint64_t D = 1ull << n, T = c->T;
   if ((double)T * (double)D > kSvMaxWork) return fail(c, QIMAX_ETOOLARGE, "expect: too many terms for the projection");
-  const size_t sv_bytes = (size_t)D * 16, t_bytes = (size_t)std::max<uint64_t>(T, 1) * 32;
-  const size_t need = 2 * sv_bytes + t_bytes + 512;
-  if (c->cap && c->alloc_bytes + need > c->cap) (void)drop_optional(c);
-  if (c->cap && c->alloc_bytes + need > c->cap) return fail(c, QIMAX_ENOMEM, "expect: memory cap exceeded");
-  void* mem = nullptr;
-  if (hipMalloc(&mem, need) != hipSuccess && !(drop_optional(c) && hipMalloc(&mem, need) == hipSuccess)) {
-    (void)hipGetLastError();
-    return fail(c, QIMAX_ENOMEM, "expect: hipMalloc of the statevector failed");
-  }
-  c->peak_bytes = std::max(c->peak_bytes, (uint64_t)(c->alloc_bytes + need));
-  uint8_t* m = (uint8_t*)mem;
+  // device memory: v, the parts of G v (as many as the largest generator takes, at most v again
+  // or 32 bytes per term), the sums
+  const size_t sv_bytes = (size_t)D * 16, limit = std::max(sv_bytes, (size_t)T * 32);
+  uint32_t parts = 1;
+  for (uint32_t j = 0; j < n; ++j) parts = std::max(parts, sv_parts(c->h_seg[j + 1] - c->h_seg[j], D, limit));
+  size_t k = zall ? 11 : std::min<size_t>(Ps.size(), kSvRows);  // rows of sums
+  if (c->cap) k = std::min(k, std::max<size_t>(11, std::min(sv_bytes, (size_t)T * 32) / 24));
+  QCHK(ensure_sv(c, sv_bytes * (1 + (size_t)parts) + k * 3 * 8 + 256));
+  uint8_t* m = (uint8_t*)c->sv_mem;
   void* v = m;
-  void* tmp = m + sv_bytes;
-  uint64_t* xm = (uint64_t*)(m + 2 * sv_bytes);
-  uint64_t* zm = xm + std::max<uint64_t>(T, 1);
-  void* cf = zm + std::max<uint64_t>(T, 1);
-  double* acc = (double*)(m + 2 * sv_bytes + t_bytes);
-  auto done = [&](qimax_status st) {
-    (void)hipStreamSynchronize(c->stream);
-    (void)hipFree(mem);
-    return st;
-  };
-  hipError_t e = launch_sv_terms(c->KC, c->WP, c->keys.p, c->w.p, T, n, xm, zm, cf, c->stream);
-  if (e == hipSuccess) e = launch_sv_random(v, D, 0x5eed5eedull + n, c->stream);
+  void* part = m + sv_bytes;
+  double* acc = (double*)(m + sv_bytes * (1 + (size_t)parts));
+  std::vector<double> h(std::max<size_t>(33, 3 * k));
+  hipError_t e = launch_sv_random(v, D, 0x5eed5eedull + n, c->stream);
   for (uint32_t j = 0; j < n && e == hipSuccess; ++j) {
     const uint64_t a = c->h_seg[j], b = c->h_seg[j + 1];
-    e = launch_sv_project(v, tmp, D, xm + a, zm + a, (uint8_t*)cf + a * 16, b - a, c->stream);
+    e = launch_sv_project(c->KC, c->WP, (const uint8_t*)c->keys.p + a * c->kb, (const uint8_t*)c->w.p + a * c->wb, b - a,
+                          n, v, part, sv_parts(b - a, D, limit), c->stream);
   }
-  auto reduce = [&](uint64_t x, uint64_t z, double cre, double cim, int za, double* h) -> hipError_t {
-    hipError_t r = hipMemsetAsync(acc, 0, 64 * 8, c->stream);
-    if (r == hipSuccess) r = launch_sv_reduce(v, D, n, x, z, cre, cim, za, acc, c->stream);
-    if (r == hipSuccess) r = hipMemcpyAsync(h, acc, 64 * 8, hipMemcpyDeviceToHost, c->stream);
-    if (r == hipSuccess) r = hipStreamSynchronize(c->stream);
-    return r;
+  auto read = [&](size_t words) -> hipError_t {
+    hipError_t r = hipMemcpyAsync(h.data(), acc, words * 8, hipMemcpyDeviceToHost, c->stream);
+    return r == hipSuccess ? hipStreamSynchronize(c->stream) : r;
   };
-  double h[64];
+  qimax_status st = QIMAX_OK;
   if (e == hipSuccess && zall) {
-    e = reduce(0, 0, 0.0, 0.0, 1, h);
-    if (e == hipSuccess) {
-      if (!(h[0] > 1e-280)) return done(fail(c, QIMAX_EDEVICE, "expect: projection vanished"));
-      for (uint32_t q = 0; q < n; ++q) out[q] = h[1 + q] / h[0];
+    e = launch_sv_reduce(v, n, nullptr, 0, acc, c->stream);
+    if (e == hipSuccess) e = read(1 + n);
+    if (e == hipSuccess && !(h[0] > 1e-280)) st = fail(c, QIMAX_EDEVICE, "expect: projection vanished");
+    for (uint32_t q = 0; q < n && e == hipSuccess && st == QIMAX_OK; ++q) out[q] = h[1 + q] / h[0];
+  }
+  // the strings in one launch (kSvRows at a time), read from mapped staging
+  for (size_t i0 = 0; i0 < Ps.size() && e == hipSuccess && st == QIMAX_OK && !zall; i0 += k) {
+    const size_t rows = std::min(k, Ps.size() - i0);
+    st = ensure_stage(c, 0, rows * sizeof(SvString));
+    if (st != QIMAX_OK) break;
+    SvString* str = (SvString*)c->stage[0];
+    for (size_t i = 0; i < rows; ++i) {
+      uint64_t x = 0, z = 0;
+      int ny = 0;
+      for (uint32_t q = 0; q < n; ++q) {
+        const int d = Ps[i0 + i][q];
+        const uint64_t bit = 1ull << (n - 1 - q);
+        if (d == 1 || d == 2) x |= bit;
+        if (d == 2 || d == 3) z |= bit;
+        ny += d == 2;
+      }
+      static const double ph[4][2] = {{1, 0}, {0, 1}, {-1, 0}, {0, -1}};
+      str[i] = SvString{x, z, ph[ny & 3][0], ph[ny & 3][1]};
+    }
+    e = launch_sv_reduce(v, n, (const SvString*)c->stage_dev[0], (uint32_t)rows, acc, c->stream);
+    if (e == hipSuccess) e = read(3 * rows);
+    for (size_t i = 0; i < rows && e == hipSuccess && st == QIMAX_OK; ++i) {
+      if (!(h[3 * i] > 1e-280)) st = fail(c, QIMAX_EDEVICE, "expect: projection vanished");
+      else out[i0 + i] = h[3 * i + 1] / h[3 * i];
     }
   }
-  for (size_t i = 0; i < Ps.size() && e == hipSuccess && !zall; ++i) {
-    uint64_t x = 0, z = 0;
-    int ny = 0;
-    for (uint32_t q = 0; q < n; ++q) {
-      const int d = Ps[i][q];
-      const uint64_t bit = 1ull << (n - 1 - q);
-      if (d == 1 || d == 2) x |= bit;
-      if (d == 2 || d == 3) z |= bit;
-      ny += d == 2;
-    }
-    static const double ph[4][2] = {{1, 0}, {0, 1}, {-1, 0}, {0, -1}};
-    e = reduce(x, z, ph[ny & 3][0], ph[ny & 3][1], 0, h);
-    if (e == hipSuccess) {
-      if (!(h[0] > 1e-280)) return done(fail(c, QIMAX_EDEVICE, "expect: projection vanished"));
-      out[i] = h[1] / h[0];
-    }
-  }
-  if (e != hipSuccess) {
-    (void)hipFree(mem);
-    return hip_fail(c, e, "expect (device statevector)");
-  }
-  return done(QIMAX_OK);
+  (void)hipStreamSynchronize(c->stream);
+  if (c->sv_bytes > kSvKeep) drop_sv(c);
+  return e != hipSuccess ? hip_fail(c, e, "expect (device statevector)") : st;
 }
 
 // <P> for k strings: the GF(2) path for a stabilizer state, else the device statevector.
@@ -3362,6 +3396,7 @@ void qimax_destroy(qimax_ctx* c) {
                     &c->blk_off, &c->img_seg, &c->desc, &c->desc2, &c->err, &c->gr_in, &c->gr_out, &c->ghist, &c->sbase, &c->sstatus, &c->tile_ctr, &c->mstatus, &c->dtile[0], &c->dtile[1], &c->dtile[2], &c->ptab, &c->chain_parts, &c->wtab, &c->akeys, &c->asign, &c->img_cnt, &c->dense_acc, &c->chunk_cnt, &c->chunk_start, &c->grp_cnt,
                     &c->chunk_off};
   for (DevBuf* b : bufs) dev_free(c, *b);
+  drop_sv(c);
   if (c->pinned) (void)hipHostFree(c->pinned);
   for (int i = 0; i < 2; ++i)
     if (c->stage[i]) (void)hipHostFree(c->stage[i]);

@@ -156,6 +156,16 @@ constexpr int kScanBlock = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanBlock * kScanItems;
 
+// The even bits of v, packed.
+__device__ __forceinline__ uint32_t pack_bits(uint64_t v) {
+  v &= 0x5555555555555555ull;
+  v = (v | (v >> 1)) & 0x3333333333333333ull;
+  v = (v | (v >> 2)) & 0x0F0F0F0F0F0F0F0Full;
+  v = (v | (v >> 4)) & 0x00FF00FF00FF00FFull;
+  v = (v | (v >> 8)) & 0x0000FFFF0000FFFFull;
+  return (uint32_t)(v | (v >> 16));
+}
+
 // Error bits a kernel may raise in the context's device flag word.
 enum : uint32_t {
   kErrIndex = 1u,      // an index left its buffer (kernel refused to write)
@@ -440,16 +450,20 @@ hipError_t launch_compare(int KC, int WPa, int WPb, const void* ka, const void* 
                           const uint64_t* b_off, const uint64_t* t_begin, const uint64_t* t_end, const uint32_t* t_seg,
                           uint32_t n_tiles, int count_ref, double tau, double* acc, unsigned long long* cnt,
                           hipStream_t s);
-// Statevector readout: 2^n complex amplitudes (double2).
-hipError_t launch_sv_terms(int KC, int WP, const void* keys, const void* w, uint64_t T, uint32_t n, uint64_t* xm,
-                           uint64_t* zm, void* cf, hipStream_t s);
+// Statevector readout: 2^n complex amplitudes (double2), n <= 30.
 hipError_t launch_sv_random(void* v, uint64_t D, uint64_t seed, hipStream_t s);
-// v <- (v + G v) / 2 for the generator given by T terms (masks and coefficients); tmp: D amplitudes.
-hipError_t launch_sv_project(void* v, void* tmp, uint64_t D, const uint64_t* xm, const uint64_t* zm, const void* cf,
-                             uint64_t T, hipStream_t s);
-// acc[0] += |v|^2; zall = 0: acc[1] + i acc[2] += <v|c P|v> for the string (xm, zm, c);
-// zall = 1: acc[1 + q] += sum_i |v_i|^2 (1 - 2 bit_q(i)) for every qubit q < n (n <= 32).
-hipError_t launch_sv_reduce(const void* v, uint64_t D, uint32_t n, uint64_t xm, uint64_t zm, double c_re,
-                            double c_im, int zall, double* acc, hipStream_t s);
+// v <- (v + G v) / 2 for the generator given by T terms, G v summed in Y parts (part: Y * 2^n
+// amplitudes; sv_parts: the Y for T terms that takes at most `limit` bytes, at least 1).
+uint32_t sv_parts(uint64_t T, uint64_t D, size_t limit);
+hipError_t launch_sv_project(int KC, int WP, const void* keys, const void* w, uint64_t T, uint32_t n, void* v,
+                             void* part, uint32_t Y, hipStream_t s);
+// <v|v> and <v|c P|v> of k strings (in memory the device can read): acc[3i] = <v|v>, acc[3i + 1]
+// + i acc[3i + 2] = <v|c_i P_i|v>. str = null: acc[0] = <v|v> and acc[1 + q] = sum_i |v_i|^2
+// (1 - 2 bit_q(i)) for every qubit q < n (33 words).
+struct SvString {
+  uint64_t x, z;  // masks over the basis-index bits
+  double re, im;  // c
+};
+hipError_t launch_sv_reduce(const void* v, uint32_t n, const SvString* str, uint32_t k, double* acc, hipStream_t s);
 
 }  // namespace qimax

@@ -117,56 +117,136 @@ __global__ void k_sv_random(double2* __restrict__ v, uint64_t D, uint64_t seed) 
   v[i] = make_double2((double)(a >> 11) * 0x1.0p-53 - 0.5, (double)(b >> 11) * 0x1.0p-53 - 0.5);
 }
 
-// out[k] = sum over terms t of c_t (-1)^{popcount((k ^ x_t) & z_t)} v[k ^ x_t], the terms'
-// masks and complex coefficients (w_t i^{ny_t}) staged through LDS in chunks.
-constexpr int kSvBlock = 256, kSvChunk = 256;
-__global__ void __launch_bounds__(kSvBlock) k_sv_apply(const double2* __restrict__ v, double2* __restrict__ out,
-                                                      uint64_t D, const uint64_t* __restrict__ xm,
-                                                      const uint64_t* __restrict__ zm, const double2* __restrict__ cf,
-                                                      uint64_t T) {
-  __shared__ uint64_t sx[kSvChunk], sz[kSvChunk];
-  __shared__ double2 sc[kSvChunk];
-  const uint64_t k = (uint64_t)blockIdx.x * kSvBlock + threadIdx.x;
-  double re = 0.0, im = 0.0;
-  for (uint64_t t0 = 0; t0 < T; t0 += kSvChunk) {
-    const uint32_t nt = (uint32_t)min<uint64_t>(kSvChunk, T - t0);
+// A generator's terms [T y/Y, T (y+1)/Y) applied to v by the blocks (., y) of a grid of
+// ceil(D / kSvTile) x Y: part[y D + k] = sum over those terms t of c_t (-1)^{popcount(src & z_t)}
+// v[src], src = k ^ x_t. The terms are converted as they are staged to LDS; a coefficient
+// w i^ny is real or imaginary, so a term costs two multiply-adds per amplitude and its kind is
+// the same for the whole block. Small states have few amplitudes (n = 10: one tile), so the
+// terms are split too: a launch of D threads alone left 252 of 256 CUs idle (n = 10, 177216
+// terms: 15.3 ms per state, 0.35 ms here). v in LDS where it takes 32 KB at
+// most (n <= 11).
+// Bound by the LDS reads of v and the ten vector instructions per term and amplitude.
+constexpr int kSvBlock = 256, kSvItems = 4, kSvTile = kSvBlock * kSvItems, kSvChunk = 256;
+constexpr uint32_t kSvLdsQubits = 11;
+template <typename K, typename W, bool kLds>
+__global__ void __launch_bounds__(kSvBlock) k_sv_apply(const K* __restrict__ keys, const W* __restrict__ w, uint64_t T,
+                                                      uint32_t n, const double2* __restrict__ v, uint64_t D,
+                                                      double2* __restrict__ part) {
+  extern __shared__ __align__(16) uint8_t lds[];
+  __shared__ uint32_t sx[kSvChunk], sz[kSvChunk];  // planes (below 2^30); bit 31 of x: an odd number of Ys
+  __shared__ double sw[kSvChunk];
+  double2* const sv = (double2*)lds;
+  if constexpr (kLds)
+    for (uint32_t i = threadIdx.x; i < (uint32_t)D; i += kSvBlock) sv[i] = v[i];
+  const uint64_t k0 = (uint64_t)blockIdx.x * kSvTile + threadIdx.x;
+  const uint64_t t0 = T * blockIdx.y / gridDim.y, t1 = T * (blockIdx.y + 1) / gridDim.y;
+  double re[kSvItems] = {}, im[kSvItems] = {};
+  for (uint64_t c0 = t0; c0 < t1; c0 += kSvChunk) {
+    const uint32_t nt = (uint32_t)min<uint64_t>(kSvChunk, t1 - c0);
     __syncthreads();
     if (threadIdx.x < nt) {
-      sx[threadIdx.x] = xm[t0 + threadIdx.x];
-      sz[threadIdx.x] = zm[t0 + threadIdx.x];
-      sc[threadIdx.x] = cf[t0 + threadIdx.x];
+      const K key = keys[c0 + threadIdx.x];
+      const uint32_t z = pack_bits((uint64_t)key >> 1), x = pack_bits((uint64_t)key) ^ z;
+      const uint32_t ny = (uint32_t)__popc(x & z);
+      const double c = (double)w[c0 + threadIdx.x];
+      sx[threadIdx.x] = x | (ny << 31);
+      sz[threadIdx.x] = z;
+      sw[threadIdx.x] = (ny & 2u) ? -c : c;
     }
     __syncthreads();
-    if (k < D) {
-      for (uint32_t u = 0; u < nt; ++u) {
-        const uint64_t src = k ^ sx[u];
-        const double2 a = v[src];
-        const double2 c = sc[u];
-        const double sg = (__popcll(src & sz[u]) & 1) ? -1.0 : 1.0;
-        re += sg * (c.x * a.x - c.y * a.y);
-        im += sg * (c.x * a.y + c.y * a.x);
+    for (uint32_t u = 0; u < nt; ++u) {
+      const uint32_t xo = __builtin_amdgcn_readfirstlane(sx[u]), z = __builtin_amdgcn_readfirstlane(sz[u]);
+      const uint32_t x = xo & 0x7FFFFFFFu;
+      const double c = sw[u];
+      double2 a[kSvItems];
+      double ck[kSvItems];
+#pragma unroll
+      for (int i = 0; i < kSvItems; ++i) {
+        const uint32_t src = (uint32_t)(min(k0 + (uint64_t)i * kSvBlock, D - 1)) ^ x;  // x < D
+        a[i] = kLds ? sv[src] : v[src];
+        ck[i] = (__popc(src & z) & 1) ? -c : c;
+      }
+      if (xo >> 31) {
+#pragma unroll
+        for (int i = 0; i < kSvItems; ++i) {
+          re[i] -= ck[i] * a[i].y;
+          im[i] += ck[i] * a[i].x;
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < kSvItems; ++i) {
+          re[i] += ck[i] * a[i].x;
+          im[i] += ck[i] * a[i].y;
+        }
       }
     }
   }
-  if (k < D) out[k] = make_double2(re, im);
+#pragma unroll
+  for (int i = 0; i < kSvItems; ++i) {
+    const uint64_t k = k0 + (uint64_t)i * kSvBlock;
+    if (k < D) part[blockIdx.y * D + k] = make_double2(re[i], im[i]);
+  }
 }
 
-// v = (v + g) / 2, the projection (I + G) / 2 applied given g = G v.
-__global__ void k_sv_half_sum(double2* __restrict__ v, const double2* __restrict__ g, uint64_t D) {
+// v = (v + g) / 2, the projection (I + G) / 2 applied given g = G v in Y parts: sixteen threads
+// per amplitude each add every sixteenth part, then their sums in a fixed order.
+constexpr int kSvSumLanes = 16, kSvSumAmps = 256 / kSvSumLanes;
+__global__ void __launch_bounds__(256) k_sv_half_sum(double2* __restrict__ v, const double2* __restrict__ part,
+                                                    uint64_t D, uint32_t Y) {
+  __shared__ double2 sh[kSvSumLanes][kSvSumAmps];
+  const uint32_t ka = threadIdx.x % kSvSumAmps, l = threadIdx.x / kSvSumAmps;
+  const uint64_t k = (uint64_t)blockIdx.x * kSvSumAmps + ka;
+  double re = 0.0, im = 0.0;
+  if (k < D) {
+    uint32_t y = l;
+    for (; y + 3 * kSvSumLanes < Y; y += 4 * kSvSumLanes) {  // four loads in flight
+      double2 p[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) p[i] = part[(uint64_t)(y + i * kSvSumLanes) * D + k];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        re += p[i].x;
+        im += p[i].y;
+      }
+    }
+    for (; y < Y; y += kSvSumLanes) {
+      const double2 p = part[(uint64_t)y * D + k];
+      re += p.x;
+      im += p.y;
+    }
+  }
+  sh[l][ka] = make_double2(re, im);
+  __syncthreads();
+  if (l == 0 && k < D) {
+    for (int i = 1; i < kSvSumLanes; ++i) {
+      re += sh[i][ka].x;
+      im += sh[i][ka].y;
+    }
+    const double2 a = v[k];
+    v[k] = make_double2(0.5 * (a.x + re), 0.5 * (a.y + im));
+  }
+}
+
+// v = (v + g) / 2 with g in one part.
+__global__ void k_sv_half_sum1(double2* __restrict__ v, const double2* __restrict__ g, uint64_t D) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= D) return;
   const double2 a = v[i], b = g[i];
   v[i] = make_double2(0.5 * (a.x + b.x), 0.5 * (a.y + b.y));
 }
 
-// acc[0] += sum |v|^2, acc[1] += Re sum conj(v) (P v), acc[2] += Im of it (one string), or
-// with zall set acc[1 + q] += sum |v_i|^2 (1 - 2 bit_q(i)) for every qubit q (<Z_q>, unnormalised).
+// String y (of gridDim.y): acc[3y] += sum |v|^2, acc[3y + 1] += Re sum conj(v) (P v),
+// acc[3y + 2] += Im of it; or with zall set (one row) acc[0] and acc[1 + q] += sum |v_i|^2
+// (1 - 2 bit_q(i)) for every qubit q (<Z_q>, unnormalised). One block per row stores its sums,
+// several add theirs (acc is then cleared before).
 constexpr uint32_t kSvMaxQubits = 32;  // statevectors hold at most 2^kSvMaxQubits amplitudes
 __global__ void __launch_bounds__(kSvBlock) k_sv_reduce(const double2* __restrict__ v, uint64_t D, uint32_t n,
-                                                       uint64_t xm, uint64_t zm, double2 c, int zall,
+                                                       const SvString* __restrict__ str, int zall,
                                                        double* __restrict__ acc) {
   __shared__ double sh[kSvBlock / 64][1 + kSvMaxQubits];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  SvString p{0, 0, 0.0, 0.0};
+  if (!zall) p = str[blockIdx.y];
   double nv = 0.0, pr = 0.0, pi = 0.0;
   double zq[kSvMaxQubits];
   const uint32_t nz = zall ? min(n, kSvMaxQubits) : 0u;
@@ -181,10 +261,10 @@ __global__ void __launch_bounds__(kSvBlock) k_sv_reduce(const double2* __restric
       for (uint32_t q = 0; q < kSvMaxQubits; ++q)
         if (q < nz) zq[q] += ((i >> (n - 1 - q)) & 1u) ? -p2 : p2;
     } else {
-      const uint64_t src = i ^ xm;
+      const uint64_t src = i ^ p.x;
       const double2 b = v[src];
-      const double sg = (__popcll(src & zm) & 1) ? -1.0 : 1.0;
-      const double br = sg * (c.x * b.x - c.y * b.y), bi = sg * (c.x * b.y + c.y * b.x);  // (P v)[i]
+      const double sg = (__popcll(src & p.z) & 1) ? -1.0 : 1.0;
+      const double br = sg * (p.re * b.x - p.im * b.y), bi = sg * (p.re * b.y + p.im * b.x);  // (P v)[i]
       pr += a.x * br + a.y * bi;
       pi += a.x * bi - a.y * br;
     }
@@ -214,51 +294,12 @@ __global__ void __launch_bounds__(kSvBlock) k_sv_reduce(const double2* __restric
   if (threadIdx.x < nacc) {
     double s = 0.0;
     for (int w = 0; w < kSvBlock / 64; ++w) s += sh[w][threadIdx.x];
-    atomicAdd(&acc[threadIdx.x], s);
+    double* const o = acc + (uint64_t)blockIdx.y * 3 + threadIdx.x;
+    if (gridDim.x == 1) *o = s; else atomicAdd(o, s);
   }
-}
-
-// Terms of a generator as statevector operators: x / z masks over the basis-index bits and
-// the coefficient w * i^(number of Y letters).
-template <typename K, typename W>
-__global__ void k_sv_terms(const K* __restrict__ keys, const W* __restrict__ w, uint64_t T, uint32_t n,
-                           uint64_t* __restrict__ xm, uint64_t* __restrict__ zm, double2* __restrict__ cf) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= T) return;
-  const K k = keys[i];
-  uint64_t xs = 0, zs = 0;
-  uint32_t ny = 0;
-  for (uint32_t q = 0; q < n; ++q) {
-    const uint32_t d = (uint32_t)(k >> (2 * (n - 1 - q))) & 3u;
-    const uint64_t bit = 1ull << (n - 1 - q);
-    if (d == 1u || d == 2u) xs |= bit;
-    if (d >= 2u) zs |= bit;
-    ny += d == 2u;
-  }
-  const double v = (double)w[i];
-  const double2 ph[4] = {make_double2(v, 0.0), make_double2(0.0, v), make_double2(-v, 0.0), make_double2(0.0, -v)};
-  xm[i] = xs;
-  zm[i] = zs;
-  cf[i] = ph[ny & 3u];
 }
 
 }  // namespace
-
-hipError_t launch_sv_terms(int KC, int WP, const void* keys, const void* w, uint64_t T, uint32_t n, uint64_t* xm,
-                           uint64_t* zm, void* cf, hipStream_t s) {
-  if (T == 0) return hipSuccess;
-  const uint32_t g = blocks_for(T, 256);
-#define QIMAX_SVT(K)                                                                                              \
-  do {                                                                                                            \
-    if (WP == 64) k_sv_terms<K, double><<<g, 256, 0, s>>>((const K*)keys, (const double*)w, T, n, xm, zm, (double2*)cf); \
-    else k_sv_terms<K, float><<<g, 256, 0, s>>>((const K*)keys, (const float*)w, T, n, xm, zm, (double2*)cf);  \
-  } while (0)
-  if (KC == 0) QIMAX_SVT(uint32_t);
-  else if (KC == 1) QIMAX_SVT(uint64_t);
-  else QIMAX_SVT(unsigned __int128);
-#undef QIMAX_SVT
-  return hipGetLastError();
-}
 
 size_t compare_tile() { return (size_t)kCmpTile; }
 
@@ -318,18 +359,50 @@ hipError_t launch_sv_random(void* v, uint64_t D, uint64_t seed, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_sv_project(void* v, void* tmp, uint64_t D, const uint64_t* xm, const uint64_t* zm, const void* cf,
-                             uint64_t T, hipStream_t s) {
-  k_sv_apply<<<blocks_for(D, kSvBlock), kSvBlock, 0, s>>>((const double2*)v, (double2*)tmp, D, xm, zm,
-                                                          (const double2*)cf, T);
-  k_sv_half_sum<<<blocks_for(D, 256), 256, 0, s>>>((double2*)v, (const double2*)tmp, D);
+uint32_t sv_parts(uint64_t T, uint64_t D, size_t limit) {
+  // about 512 blocks, at least 64 terms each, and no more parts than `limit` bytes hold
+  const uint64_t tiles = (D + kSvTile - 1) / kSvTile;
+  const uint64_t y = std::min<uint64_t>({(T + 63) / 64, std::max<uint64_t>(512 / tiles, 1), limit / (D * 16)});
+  return (uint32_t)std::max<uint64_t>(y, 1);
+}
+
+hipError_t launch_sv_project(int KC, int WP, const void* keys, const void* w, uint64_t T, uint32_t n, void* v,
+                             void* part, uint32_t Y, hipStream_t s) {
+  const uint64_t D = 1ull << n;
+  if (n < 1 || n > 30 || KC > 1 || Y < 1 || Y > 65535) return hipErrorInvalidValue;
+  const dim3 grid((uint32_t)((D + kSvTile - 1) / kSvTile), Y);
+  const bool lds = n <= kSvLdsQubits;
+  const size_t bytes = lds ? (size_t)D * 16 : 0;
+#define QIMAX_SVA(K, W, L) \
+  k_sv_apply<K, W, L><<<grid, kSvBlock, bytes, s>>>((const K*)keys, (const W*)w, T, n, (const double2*)v, D, (double2*)part)
+#define QIMAX_SVA_L(K, W) do { if (lds) QIMAX_SVA(K, W, true); else QIMAX_SVA(K, W, false); } while (0)
+  if (KC == 0) {
+    if (WP == 64) QIMAX_SVA_L(uint32_t, double); else QIMAX_SVA_L(uint32_t, float);
+  } else {
+    if (WP == 64) QIMAX_SVA_L(uint64_t, double); else QIMAX_SVA_L(uint64_t, float);
+  }
+#undef QIMAX_SVA_L
+#undef QIMAX_SVA
+  if (Y == 1)
+    k_sv_half_sum1<<<blocks_for(D, 256), 256, 0, s>>>((double2*)v, (const double2*)part, D);
+  else
+    k_sv_half_sum<<<blocks_for(D, kSvSumAmps), 256, 0, s>>>((double2*)v, (const double2*)part, D, Y);
   return hipGetLastError();
 }
 
-hipError_t launch_sv_reduce(const void* v, uint64_t D, uint32_t n, uint64_t xm, uint64_t zm, double c_re,
-                            double c_im, int zall, double* acc, hipStream_t s) {
-  const uint32_t grid = (uint32_t)std::min<uint64_t>(blocks_for(D, kSvBlock), 4096);
-  k_sv_reduce<<<grid, kSvBlock, 0, s>>>((const double2*)v, D, n, xm, zm, make_double2(c_re, c_im), zall, acc);
+hipError_t launch_sv_reduce(const void* v, uint32_t n, const SvString* str, uint32_t k, double* acc, hipStream_t s) {
+  const uint64_t D = 1ull << n;
+  if (k > 65535) return hipErrorInvalidValue;
+  const bool zall = str == nullptr;
+  const uint32_t rows = zall ? 1 : k;
+  if (rows == 0) return hipSuccess;
+  // one block per row up to 2^14 amplitudes: 64 per thread, and no sums to combine
+  const uint32_t grid = D <= (1ull << 14) ? 1u : (uint32_t)std::min<uint64_t>(blocks_for(D, kSvBlock * 16), 1024);
+  if (grid > 1) {
+    const hipError_t e = launch_fill_u64((uint64_t*)acc, zall ? 1 + kSvMaxQubits : 3 * (uint64_t)rows, 0ull, s);
+    if (e != hipSuccess) return e;
+  }
+  k_sv_reduce<<<dim3(grid, rows), kSvBlock, 0, s>>>((const double2*)v, D, n, str, zall ? 1 : 0, acc);
   return hipGetLastError();
 }
 
