@@ -5,6 +5,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <stddef.h>
+
+#include <type_traits>
+
 #include "qimax_internal.h"
 
 namespace qimax {
@@ -1365,9 +1369,11 @@ __global__ void k_merge_publish(Tiling tl, const uint64_t* __restrict__ blk_off,
 }
 
 
-__global__ void k_publish(uint32_t S, MergeFin fin, const uint32_t* __restrict__ err) {
+__global__ void k_publish(uint32_t S, MergeFin fin, uint64_t* __restrict__ seg_off_out,
+                          const uint32_t* __restrict__ err) {
   for (uint32_t s = threadIdx.x; s <= S; s += blockDim.x) {
     const uint64_t v = fin.img_seg[s];
+    if (seg_off_out) seg_off_out[s] = v;
     fin.result[s] = v;
     fin.result[S + 1 + s] = v;
   }
@@ -2257,6 +2263,19 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
   }
 }
 
+// The counts of a group of small passes, the error word and the sequence word for the host (one
+// block, after k_small_passes).
+__global__ void __launch_bounds__(256) k_small_publish(const uint32_t* __restrict__ cnt, uint32_t n_words,
+                                                       uint64_t* result, uint64_t seq, const uint32_t* __restrict__ err) {
+  uint32_t* const out = (uint32_t*)result;
+  const uint32_t n64 = (n_words + 1) / 2;
+  for (uint32_t i = threadIdx.x; i < n_words; i += 256) out[i] = cnt[i];
+  if (threadIdx.x == 0) result[n64] = *err;
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) *(volatile uint64_t*)&result[n64 + 1] = seq;
+}
+
 // After k_small_passes: segment s's kept terms (its slot, cnt_last[s*3 + 2] of them) copied to
 // the pass output at the sum of the earlier segments' counts; seg_off receives the offsets.
 template <typename K, typename W>
@@ -2279,6 +2298,585 @@ __global__ void __launch_bounds__(256) k_small_gather(const K* __restrict__ kslo
   for (uint32_t i = threadIdx.x; i < m; i += 256) {
     keys_out[base + i] = kslot[src + i];
     w_out[base + i] = wslot[src + i];
+  }
+}
+
+// ---------------------------------------------------------------- gathered rounds
+// A round of large fan-out (every wire rotated, say) whose operators fall apart into full blocks
+// (see BlockDesc) merges before it expands. Parents whose A-chained keys agree outside the
+// operators' wires and by component on them (the same support, for rotations) have exactly the
+// same images, and no image belongs to two such groups. So the parents of a segment are grouped
+// (k_gather_plan: one block per segment orders them in LDS by component key, stably), and every
+// image of a group is formed once, its parents' products added in array order in registers
+// (k_gather): the products and the order of the sums are those of expanding, sorting and
+// merging, so results agree bit for bit. What goes away is the traffic of the images: only the
+// sums above the prune threshold are written, once, and sorted.
+// The parents' order within a group, the products (operators in order, operators of one output
+// digit being an exact factor of +-1 taken apart) and every threshold are the general path's.
+// Measured, per step: the n = 16 two-layer ansatz in FP32 (1.7e8 images, 7.3e7 kept) 7.7 -> 3.3 ms,
+// expansion, sorts and merge of the second layer 6.9 -> 3.1; ten layers at n = 6 (6e6 images a
+// layer for 24570 terms) 6.0 -> 2.2 ms, the merge of long runs 3.5 ms of it before; n = 13 0.77 ->
+// 0.57 ms. The plan takes 13 to 27 us (one block per generator).
+constexpr int kPlanBlock = 1024;
+template <typename K>
+constexpr int plan_cap() { return 65536 / (int)sizeof(K); }  // 64 KB of keys in LDS
+
+// One stable LSD radix pass after the other over the digits that vary, n keys in LDS with their
+// positions; elements in equal wave spans of whole 64-element rounds.
+template <typename K, int NT, int kItems>
+__device__ __forceinline__ void lds_sort(K* sk, uint16_t* sidx, uint32_t n, uint32_t (*wrun)[kRadix],
+                                         uint32_t (*dbase)[kRadix], uint32_t (*wdummy)[64], K* vary_sh) {
+  constexpr int kWaves = NT / 64;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
+  K vary = 0;
+  for (uint32_t j = threadIdx.x; j < n; j += NT) vary |= sk[j] ^ sk[0];
+  vary = block_or<NT>(vary, vary_sh);
+  const uint32_t span = (n + kWaves * 64 - 1) / (kWaves * 64) * 64, nr = span / 64;
+  static_assert(kItems % 2 == 0, "rounds in pairs");
+  auto rounds = [&](auto&& body) {  // a pair of rounds wholly past the span is skipped
+#pragma unroll
+    for (int r2 = 0; r2 < kItems; r2 += 2) {
+      if ((uint32_t)r2 < nr) {
+        body(r2);
+        body(r2 + 1);
+      }
+    }
+  };
+  for (uint32_t dp = 0; dp < (uint32_t)sizeof(K); ++dp) {
+    if (!((uint32_t)(vary >> (8u * dp)) & 255u)) continue;
+    for (int i = threadIdx.x; i < kWaves * kRadix; i += NT) (&wrun[0][0])[i] = 0;
+    __syncthreads();
+    K key[kItems];
+    uint16_t ix[kItems];
+    uint32_t rank[kItems], pk[kItems];
+    rounds([&](int r) {
+      const uint32_t li = min(wid * span + r * 64 + lane, n - 1);
+      key[r] = sk[li];
+      ix[r] = sidx[li];
+    });
+    rounds([&](int r) {
+      const uint32_t li = wid * span + r * 64 + lane;
+      const bool valid = (uint32_t)r < nr && li < n;
+      const uint32_t d = (uint32_t)(key[r] >> (8u * dp)) & (kRadix - 1);
+      const uint64_t vm = __builtin_amdgcn_ballot_w64(valid);
+      uint32_t dlo = ~(uint32_t)vm, dhi = ~(uint32_t)(vm >> 32);
+#pragma unroll
+      for (int bit = 0; bit < kRadixBits; ++bit) {
+        const int spread = __builtin_amdgcn_sbfe((int)d, bit, 1);
+        const uint64_t bb = __builtin_amdgcn_ballot_w64(spread != 0);
+        dlo |= (uint32_t)bb ^ (uint32_t)spread;
+        dhi |= (uint32_t)(bb >> 32) ^ (uint32_t)spread;
+      }
+      const uint64_t mk = ~(((uint64_t)dhi << 32) | dlo);
+      const int leader = __ffsll((long long)mk) - 1;
+      const bool lead_me = valid && lane == leader;
+      rank[r] = atomicAdd(lead_me ? &wrun[wid][d] : &wdummy[wid][lane], lead_me ? (uint32_t)__popcll(mk) : 0u);
+      pk[r] = d | ((uint32_t)(leader < 0 ? 0 : leader) << 8) | ((uint32_t)__popcll(mk & lt) << 16);
+    });
+    rounds([&](int r) { rank[r] = __shfl(rank[r], (pk[r] >> 8) & 63u, 64) + (pk[r] >> 16); });
+    __syncthreads();
+    {
+      uint32_t tot[4] = {0, 0, 0, 0}, pre[4] = {0, 0, 0, 0};
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const uint4 c = *(const uint4*)&wrun[w][4 * lane];
+        const uint32_t cw[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (w < wid) pre[j] += cw[j];
+          tot[j] += cw[j];
+        }
+      }
+      const uint32_t lane_sum = tot[0] + tot[1] + tot[2] + tot[3];
+      uint32_t run = (uint32_t)(wave_incl_scan((uint64_t)lane_sum) - lane_sum);
+      uint4 base;
+      base.x = run + pre[0]; run += tot[0];
+      base.y = run + pre[1]; run += tot[1];
+      base.z = run + pre[2]; run += tot[2];
+      base.w = run + pre[3];
+      *(uint4*)&dbase[wid][4 * lane] = base;
+    }
+    __syncthreads();  // every key read and every count scanned before keys move
+    rounds([&](int r) {
+      if ((uint32_t)r < nr && wid * span + r * 64 + lane < n) {
+        const uint32_t dst = dbase[wid][pk[r] & 255u] + rank[r];
+        sk[dst] = key[r];
+        sidx[dst] = ix[r];
+      }
+    });
+    __syncthreads();
+  }
+}
+
+template <typename K, int WP>
+__global__ void __launch_bounds__(kPlanBlock) k_gather_plan(
+    const K* __restrict__ keys, const typename WTraits<WP>::W* __restrict__ w, const uint64_t* __restrict__ seg_in,
+    const PassArgs* __restrict__ pas, const uint32_t* __restrict__ seg_entry, GatherPlan gp, uint32_t* err) {
+  using W = typename WTraits<WP>::W;
+  constexpr int kCap = plan_cap<K>(), kItems = kCap / kPlanBlock, kWaves = kPlanBlock / 64;
+  constexpr int kTabN = table_entries<K>(), kTabS = table_sign_bytes<K>();
+  __shared__ __align__(16) K tk[kTabN];
+  __shared__ __align__(4) uint8_t tn[kTabS];
+  __shared__ __align__(16) K sk[kCap];
+  __shared__ uint16_t sidx[kCap];
+  __shared__ __align__(16) uint32_t wrun[kWaves][kRadix];
+  __shared__ __align__(16) uint32_t dbase[kWaves][kRadix];
+  __shared__ uint32_t wdummy[kWaves][64];
+  __shared__ uint64_t scan_sh[kWaves];
+  __shared__ __align__(16) uint8_t vary_sh[kWaves * sizeof(K)];
+  // the operators' positions, components and output counts, read for every term, in LDS
+  __shared__ uint32_t gpos[kMaxE1], gcomp[kMaxE1], gsize[kMaxE1];
+  const uint32_t s = blockIdx.x;
+  const PassArgs pa = pas[seg_entry[s]];
+  const uint64_t a0 = seg_in[s], n64 = seg_in[s + 1] - a0;
+  uint64_t* const tot_out = gp.totals + 4 * (uint64_t)s;
+  if (n64 == 0 || pa.drop || n64 > (uint64_t)kCap) {
+    if (threadIdx.x == 0) {
+      if (n64 > (uint64_t)kCap && !pa.drop) atomicOr(err, kErrIndex | kErrFanout);  // the caller's bound did not hold
+      for (int k = 0; k < 4; ++k) tot_out[k] = 0;
+      gp.n_groups[s] = 0;
+    }
+    return;
+  }
+  const uint32_t n = (uint32_t)n64;
+  K* const ak = (K*)gp.akeys + a0;
+  if (pa.useA) stage_table(pa.tA, tk, tn);
+  if (threadIdx.x < pa.nE1) {
+    const BlockDesc& d = pa.G1[threadIdx.x];
+    gpos[threadIdx.x] = d.pos;
+    gcomp[threadIdx.x] = *(const uint32_t*)d.comp;
+    gsize[threadIdx.x] = *(const uint32_t*)d.osize;
+  }
+  __syncthreads();
+  auto comp = [&](K key, uint32_t e) -> uint32_t { return (gcomp[e] >> (8 * get_d(key, gpos[e]))) & 255u; };
+  auto size = [&](K key, uint32_t e) -> uint32_t { return (gsize[e] >> (8 * get_d(key, gpos[e]))) & 255u; };
+  // the A chain, and the component key: the operators' digits replaced by their components
+  for (uint32_t i = threadIdx.x; i < n; i += kPlanBlock) {
+    K key = keys[a0 + i];
+    uint32_t neg = 0;
+    if (pa.useA) key = apply_table(key, tk, tn, pa.tA.groups, neg);
+    else for (uint32_t a = 0; a < pa.nA; ++a) key = apply_perm(key, pa.A[a], neg);
+    ak[i] = key;
+    gp.asign[a0 + i] = (uint8_t)(neg & 1u);
+    for (uint32_t e = 0; e < pa.nE1; ++e) key = set_d(key, gpos[e], comp(key, e));
+    sk[i] = key;
+    sidx[i] = (uint16_t)i;
+  }
+  __syncthreads();
+  if (n > 1) lds_sort<K, kPlanBlock, kItems>(sk, sidx, n, wrun, dbase, wdummy, (K*)vary_sh);
+  // the parents in that order
+  for (uint32_t j = threadIdx.x; j < n; j += kPlanBlock) {
+    const uint32_t i = sidx[j];
+    const W wv = w[a0 + i];
+    ((K*)gp.keys)[a0 + j] = ak[i];
+    ((W*)gp.w)[a0 + j] = gp.asign[a0 + i] ? -wv : wv;
+  }
+  // the groups' first parents
+  uint32_t ng;
+  {
+    const uint32_t j0 = threadIdx.x * kItems;
+    uint32_t cnt = 0;
+#pragma unroll
+    for (int t = 0; t < kItems; ++t) {
+      const uint32_t j = j0 + t;
+      if (j < n && (j == 0 || sk[j] != sk[j - 1])) ++cnt;
+    }
+    uint64_t tot;
+    uint32_t g = (uint32_t)block_excl_scan<kPlanBlock>(cnt, scan_sh, &tot);
+    ng = (uint32_t)tot;
+#pragma unroll
+    for (int t = 0; t < kItems; ++t) {
+      const uint32_t j = j0 + t;
+      if (j < n && (j == 0 || sk[j] != sk[j - 1])) gp.gstart[a0 + g++] = j;
+    }
+  }
+  __syncthreads();
+  // outputs and units of every group, and their scans
+  uint64_t outs = 0, units[2] = {0, 0}, images = 0;
+  for (uint32_t g0 = 0; g0 < ng; g0 += kPlanBlock) {
+    const uint32_t g = g0 + threadIdx.x;
+    uint64_t o = 0, u[2] = {0, 0};
+    uint32_t par = 0;
+    if (g < ng) {
+      const uint32_t j = gp.gstart[a0 + g], j1 = g + 1 < ng ? gp.gstart[a0 + g + 1] : n;
+      par = j1 - j;
+      const K key = sk[j];
+      uint32_t act = 0;
+      for (uint32_t e = 0; e < pa.nE1; ++e) act += size(key, e) > 1;
+      o = u[0] = u[1] = 1;
+      uint32_t a = 0;
+      for (uint32_t e = 0; e < pa.nE1; ++e) {
+        const uint32_t sz = size(key, e);
+        if (sz <= 1) continue;
+        o *= sz;
+        if (a + 1 < act) u[0] *= sz;
+        if (a + 3 < act) u[1] *= sz;
+        ++a;
+      }
+    }
+    uint64_t to, tu0, tu1, ti;
+    (void)block_excl_scan<kPlanBlock>(o, scan_sh, &to);
+    const uint64_t p0 = block_excl_scan<kPlanBlock>(u[0], scan_sh, &tu0);
+    const uint64_t p1 = block_excl_scan<kPlanBlock>(u[1], scan_sh, &tu1);
+    (void)block_excl_scan<kPlanBlock>(o * par, scan_sh, &ti);
+    if (g < ng) {
+      gp.goff[0][a0 + g] = units[0] + p0;
+      gp.goff[1][a0 + g] = units[1] + p1;
+    }
+    outs += to;
+    units[0] += tu0;
+    units[1] += tu1;
+    images += ti;
+  }
+  if (threadIdx.x == 0) {
+    tot_out[0] = outs;
+    tot_out[1] = units[0];
+    tot_out[2] = units[1];
+    tot_out[3] = images;
+    gp.n_groups[s] = ng;
+  }
+}
+
+// The scanned totals for the host and the segments' first tiles (one block).
+__global__ void __launch_bounds__(256) k_gather_publish(uint32_t S, GatherPlan gp, uint64_t* result, uint64_t seq,
+                                                        const uint32_t* __restrict__ err) {
+  __shared__ uint64_t sh[4];
+  uint64_t run[6] = {};
+  for (uint32_t base = 0; base < S; base += 256) {
+    const uint32_t s = base + threadIdx.x;
+    uint64_t v[6] = {};
+    if (s < S) {
+      for (int k = 0; k < 4; ++k) v[k] = gp.totals[4 * (uint64_t)s + k];
+      for (int k = 0; k < 2; ++k) v[4 + k] = (v[1 + k] + gather_tile(k) - 1) / gather_tile(k);
+    }
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      uint64_t tot;
+      const uint64_t pre = block_excl_scan<256>(v[k], sh, &tot);
+      if (s < S) {
+        if (k < 4) result[(uint64_t)k * (S + 1) + s] = run[k] + pre;
+        else gp.tiles[k - 4][s] = (uint32_t)min<uint64_t>(run[k] + pre, 0xFFFFFFFFull);
+      }
+      run[k] += tot;
+    }
+  }
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) result[(uint64_t)k * (S + 1) + S] = run[k];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) gp.tiles[k][S] = (uint32_t)min<uint64_t>(run[4 + k], 0xFFFFFFFFull);
+    result[4 * (uint64_t)(S + 1)] = *err;
+  }
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) *(volatile uint64_t*)&result[4 * (uint64_t)(S + 1) + 1] = seq;
+}
+
+// Product of two commuting strings given as digit keys, their signs in neg.
+template <typename K>
+__device__ __forceinline__ K key_mul(K a, K b, uint32_t& neg) {
+  const K k = a ^ b;
+  const K cross = (a >> 1) & (b ^ (b >> 1)) & even_bits<K>();
+  const uint32_t e = y_count(a) + y_count(b) + 2u * ((uint32_t)popc_k(cross) & 1u) - y_count(k);
+  neg ^= (e >> 1) & 1u;
+  return k;
+}
+
+// A unit is a choice of output digits for a group's operators except the last SW that have a
+// choice; its thread forms the 3^SW outputs (at most) that those leave open: per parent one
+// product of the unit's operators, then 3 + 9 + .. products and the sums, in registers. SW = 3
+// where there are outputs enough to fill the chip (two multiplications per image), SW = 1 and
+// blocks of one wave for more threads on more CUs. The images of an output under the B chain's table are the products of the
+// unit's image and the open digits' images. Outputs above the threshold are compacted in the
+// wave (ballots) and the tile's place found by look-back.
+// Bound: arithmetic and LDS reads of the matrix entries (one parent: the stores).
+template <typename K, int WP, int SW, typename Acc>
+__global__ void __launch_bounds__(gather_tile(SW == 3)) k_gather(GatherPlan gp, const uint64_t* __restrict__ goff,
+                                                        const uint32_t* __restrict__ seg_tile,
+                                                        const uint64_t* __restrict__ seg_in, uint32_t S, uint32_t n_tiles,
+                                                        const PassArgs* __restrict__ pas,
+                                                        const uint32_t* __restrict__ seg_entry, uint64_t* status,
+                                                        uint32_t* ctr, uint64_t epoch, uint64_t* __restrict__ img_seg,
+                                                        K* __restrict__ keys_out,
+                                                        typename WTraits<WP>::W* __restrict__ w_out, uint64_t out_cap,
+                                                        uint32_t* err) {
+  // (a product is rounded before it is added, as when it goes through memory)
+#pragma clang fp contract(off)
+  using W = typename WTraits<WP>::W;
+  constexpr int kTabN = table_entries<K>(), kTabS = table_sign_bytes<K>();
+  constexpr uint32_t kTile = gather_tile(SW == 3);
+  constexpr int kOut = SW == 3 ? 27 : 3, kWaves = (int)kTile / 64;
+  constexpr int kDescWords = (int)(sizeof(BlockDesc) / 8);
+  __shared__ __align__(16) K tk[kTabN];
+  __shared__ __align__(4) uint8_t tn[kTabS];
+  __shared__ uint64_t gsh[kMaxE1 * kDescWords];
+  __shared__ uint64_t scan_sh[kWaves];
+  __shared__ uint64_t base_sh;
+  __shared__ uint32_t tile_sh, seg_sh, g_sh[2];
+  if (threadIdx.x == 0) {
+    const uint32_t b = atomicAdd(ctr, 1u);  // launched with exactly n_tiles blocks
+    uint32_t lo = 0, hi = S;                // last segment whose first tile is at most b: it has tiles
+    while (hi - lo > 1) {
+      const uint32_t mid = (lo + hi) >> 1;
+      if (seg_tile[mid] <= b) lo = mid; else hi = mid;
+    }
+    tile_sh = b;
+    seg_sh = lo;
+  }
+  __syncthreads();
+  const uint32_t b = tile_sh, seg = seg_sh;
+  const PassArgs pa = pas[seg_entry[seg]];
+  const uint64_t a0 = seg_in[seg];
+  const uint32_t ng = gp.n_groups[seg], n = (uint32_t)(seg_in[seg + 1] - a0);
+  const uint64_t U = gp.totals[4 * (uint64_t)seg + (SW == 3 ? 2 : 1)];
+  const uint64_t u0 = (uint64_t)(b - seg_tile[seg]) * kTile;
+  const uint32_t n_u = (uint32_t)min<uint64_t>(kTile, U - u0);
+  goff += a0;
+  for (uint32_t i = threadIdx.x; i < pa.nE1 * (uint32_t)kDescWords; i += kTile) gsh[i] = ((const uint64_t*)pa.G1)[i];
+  if (pa.useB) stage_table(pa.tB, tk, tn);
+  // groups of the tile's first and last unit (by two waves where there are two)
+  for (uint32_t k = threadIdx.x >> 6; k < 2; k += kWaves) {
+    const uint32_t g = (uint32_t)(wave_upper_bound(goff, 0, ng, k ? u0 + n_u - 1 : u0) - 1);
+    if ((threadIdx.x & 63) == 0) g_sh[k] = g;
+  }
+  __syncthreads();
+  const BlockDesc* const G = (const BlockDesc*)gsh;
+  const bool live = threadIdx.x < n_u;
+  const uint64_t u = u0 + min(threadIdx.x, n_u - 1);
+  const uint32_t g = (uint32_t)(upper_bound_u64(goff, g_sh[0], (uint64_t)g_sh[1] + 1, u) - 1);
+  const uint32_t p0 = gp.gstart[a0 + g], p1 = g + 1 < ng ? gp.gstart[a0 + g + 1] : n;
+  const K* const pk = (const K*)gp.keys + a0;
+  const W* const pw = (const W*)gp.w + a0;
+  // the unit's output digits, and the operators left open
+  K key = pk[p0];
+  uint64_t r = u - goff[g];
+  uint64_t prefix = 0;
+  uint32_t neg = 0, open[SW], n_open = 0;
+#pragma unroll
+  for (int m = 0; m < SW; ++m) open[m] = ~0u;
+  uint32_t oc[SW] = {};  // their components
+  {
+    uint32_t act = 0, a = 0;
+    for (uint32_t e = 0; e < pa.nE1; ++e) act += G[e].osize[G[e].comp[get_d(key, G[e].pos)]] > 1;
+    for (uint32_t e = 0; e < pa.nE1; ++e) {
+      const uint32_t c = G[e].comp[get_d(key, G[e].pos)], sz = G[e].osize[c];
+      uint32_t out = 0;
+      if (sz <= 1) {
+        out = G[e].odig[c][0];
+        neg ^= G[e].neg[c];
+      } else {
+        if (a + SW < act) {
+          const uint64_t q = sz == 2 ? r >> 1 : r / 3;  // components with a choice have 2 or 3 outputs
+          out = G[e].odig[c][(uint32_t)(r - q * sz)];
+          r = q;
+          prefix |= 1ull << e;
+        } else {
+#pragma unroll
+          for (int m = 0; m < SW; ++m)
+            if ((uint32_t)m == n_open) {
+              open[m] = e;
+              oc[m] = c;
+            }
+          ++n_open;
+        }
+        ++a;
+      }
+      key = set_d(key, G[e].pos, out);
+    }
+  }
+  // sums of the open outputs, parents in order; an operator that is not there has one output
+  uint32_t os[SW];
+#pragma unroll
+  for (int m = 0; m < SW; ++m) os[m] = open[m] == ~0u ? 1u : (uint32_t)G[open[m]].osize[oc[m]];
+  Acc acc[kOut];
+  // the matrix rows of the unit's first kPre operators and their digits' places, in registers (the
+  // row's place in LDS in 8-byte or 4-byte entries): the loop over the parents then reads one
+  // entry per operator and nothing else; further operators are looked up as they come
+  constexpr int kPre = SW == 1 ? 8 : 4;
+  constexpr uint32_t kStride = (uint32_t)(sizeof(BlockDesc) / sizeof(W));
+  const W* const ent = (const W*)gsh + (WP == 64 ? offsetof(BlockDesc, r) / 8 : offsetof(BlockDesc, rf) / 4);
+  uint32_t row[kPre], rpos[kPre];
+  uint64_t rest = prefix;
+#pragma unroll
+  for (int q = 0; q < kPre; ++q) {
+    row[q] = rpos[q] = ~0u;
+    if (rest) {
+      const uint32_t e = (uint32_t)__ffsll((long long)rest) - 1;
+      rest &= rest - 1;
+      rpos[q] = G[e].pos;
+      row[q] = e * kStride + 4 * get_d(key, rpos[q]);
+    }
+  }
+  uint32_t opos[SW], orow[SW][3];
+#pragma unroll
+  for (int m = 0; m < SW; ++m) {
+    const uint32_t e = open[m] == ~0u ? 0u : open[m];
+    opos[m] = open[m] == ~0u ? 0u : G[e].pos;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) orow[m][i] = e * kStride + 4 * G[e].odig[oc[m]][i];
+  }
+  // kU parents at a time: their loads and products are independent, only the sums are in order
+  auto parents = [&](uint32_t j, auto count) {
+#pragma clang fp contract(off)
+    constexpr int kU = decltype(count)::value;
+    K kj[kU];
+    W v[kU];
+#pragma unroll
+    for (int t = 0; t < kU; ++t) {
+      kj[t] = pk[j + t];
+      v[t] = pw[j + t];
+    }
+#pragma unroll
+    for (int q = 0; q < kPre; ++q) {
+      if (row[q] == ~0u) break;
+#pragma unroll
+      for (int t = 0; t < kU; ++t) v[t] *= ent[row[q] + get_d(kj[t], rpos[q])];
+    }
+    for (uint64_t m = rest; m; m &= m - 1) {
+      const uint32_t e = (uint32_t)__ffsll((long long)m) - 1, pos = G[e].pos, at = e * kStride + 4 * get_d(key, pos);
+#pragma unroll
+      for (int t = 0; t < kU; ++t) v[t] *= ent[at + get_d(kj[t], pos)];
+    }
+#pragma unroll
+    for (int t = 0; t < kU; ++t) {
+      W f[SW][3];
+#pragma unroll
+      for (int m = 0; m < SW; ++m) {
+        const uint32_t in = get_d(kj[t], opos[m]);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) f[m][i] = open[m] == ~0u ? (W)1 : ent[orow[m][i] + in];
+      }
+      if constexpr (SW == 1) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+          if ((uint32_t)i < os[0]) acc[i].add(v[t] * f[0][i]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          const W v1 = v[t] * f[0][i];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const W v2 = v1 * f[1][k];
+#pragma unroll
+            for (int l = 0; l < 3; ++l)
+              if ((uint32_t)i < os[0] && (uint32_t)k < os[1] && (uint32_t)l < os[2]) acc[9 * i + 3 * k + l].add(v2 * f[2][l]);
+          }
+        }
+      }
+    }
+  };
+  constexpr uint32_t kBatch = SW == 1 ? 8 : 2;
+  uint32_t j = p0;
+  for (; p1 - j >= kBatch; j += kBatch) parents(j, std::integral_constant<int, (int)kBatch>{});
+  for (; j < p1; ++j) parents(j, std::integral_constant<int, 1>{});
+  // kept outputs
+  uint32_t keep = 0;
+  W sum[kOut];
+#pragma unroll
+  for (int o = 0; o < kOut; ++o) {
+    sum[o] = acc[o].value();
+    bool in;
+    if constexpr (SW == 1) in = (uint32_t)o < os[0];
+    else in = (uint32_t)(o / 9) < os[0] && (uint32_t)(o / 3 % 3) < os[1] && (uint32_t)(o % 3) < os[2];
+    if (live && in && fabs((double)sum[o]) > pa.thr) keep |= 1u << o;
+  }
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  uint32_t wave_cnt = 0;
+#pragma unroll
+  for (int o = 0; o < kOut; ++o) wave_cnt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64((keep >> o) & 1u));
+  if (lane == 0) scan_sh[wid] = wave_cnt;
+  __syncthreads();
+  uint64_t tot = 0, wave_at = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    if (w < wid) wave_at += scan_sh[w];
+    tot += scan_sh[w];
+  }
+  if (threadIdx.x == 0) {
+    const uint64_t ep = epoch << 48;
+    st_store(status + b, ep | (b == 0 ? kStPre : kStAgg) | tot);
+    uint64_t excl = 0;
+    if (b > 0) {
+      uint32_t t = b - 1;
+      uint32_t spins = 0;
+      while (true) {
+        const uint64_t v = st_load(status + t);
+        const bool ready = (v >> 48) == epoch && (v & (kStAgg | kStPre));
+        if (!ready) {
+          if (++spins > kSpinLimit) { atomicOr(err, kErrSpin); break; }
+          continue;
+        }
+        excl += v & kStValMask;
+        if ((v & kStPre) || t == 0) break;
+        --t;
+      }
+      st_store(status + b, ep | kStPre | (excl + tot));
+    }
+    base_sh = excl;
+    // the segments this tile starts (with any before it that have no tiles), and after the last
+    // tile the trailing ones and the total
+    for (uint32_t q = seg + 1; q-- > 0 && seg_tile[q] == b;) img_seg[q] = excl;
+    if (b + 1 == n_tiles)
+      for (uint32_t q = S; q > seg && seg_tile[q] == n_tiles; --q) img_seg[q] = excl + tot;
+  }
+  // the unit's image under the B chain, and the open digits'
+  uint32_t bneg = neg;
+  if (pa.useB) key = apply_table(key, tk, tn, pa.tB.groups, bneg);
+  K ik[SW][3];
+  uint32_t ineg[SW] = {};
+#pragma unroll
+  for (int m = 0; m < SW; ++m)
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      K v = 0;
+      uint32_t sg = 0;
+      if (open[m] != ~0u) {
+        v = set_d((K)0, G[open[m]].pos, (uint32_t)G[open[m]].odig[oc[m]][i]);
+        if (pa.useB) v = apply_table(v, tk, tn, pa.tB.groups, sg);
+      }
+      ik[m][i] = v;
+      ineg[m] |= sg << i;
+    }
+  __syncthreads();
+  const uint64_t base = base_sh;
+  if (base + tot > out_cap) {
+    if (threadIdx.x == 0 && tot) atomicOr(err, kErrIndex | kErrExpand);
+    return;
+  }
+  const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
+  uint64_t at = base + wave_at;
+  auto emit = [&](int o, K k, uint32_t sg) {
+    const uint64_t bal = __builtin_amdgcn_ballot_w64((keep >> o) & 1u);
+    if ((keep >> o) & 1u) {
+      if (!pa.useB)
+        for (uint32_t q = 0; q < pa.nB; ++q) k = apply_perm(k, pa.B[q], sg);
+      const uint64_t dst = at + (uint32_t)__popcll(bal & lt);
+      keys_out[dst] = k;
+      w_out[dst] = (sg & 1u) ? -sum[o] : sum[o];
+    }
+    at += (uint32_t)__popcll(bal);
+  };
+  auto times = [&](K k, K v, uint32_t& sg) -> K { return pa.useB ? key_mul(k, v, sg) : (K)(k | v); };
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    uint32_t s1 = bneg ^ ((ineg[0] >> i) & 1u);
+    const K k1 = times(key, ik[0][i], s1);
+    if constexpr (SW == 1) {
+      emit(i, k1, s1);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        uint32_t s2 = s1 ^ ((ineg[1] >> k) & 1u);
+        const K k2 = times(k1, ik[1][k], s2);
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {
+          uint32_t s3 = s2 ^ ((ineg[2] >> l) & 1u);
+          const K k3 = times(k2, ik[2][l], s3);
+          emit(9 * i + 3 * k + l, k3, s3);
+        }
+      }
+    }
   }
 }
 
@@ -2901,7 +3499,7 @@ inline uint32_t grid_for(uint64_t n, uint32_t block) { return (uint32_t)((n + bl
 const char* kernel_kind_name(int k) {
   static const char* names[kKNum] = {"init", "count", "scan", "expand", "sort_hist", "sort_scatter",
                                      "merge_count", "merge_write", "compose_ptm", "chunk_sort", "count_expand",
-                                     "dense_merge", "chunk_finish", "small_passes", "chain_tables"};
+                                     "dense_merge", "chunk_finish", "small_passes", "chain_tables", "gather"};
   return (k >= 0 && k < kKNum) ? names[k] : "?";
 }
 
@@ -3072,16 +3670,16 @@ uint32_t small_group_cap(int KC) {
   return (uint32_t)(KC == 2 ? group_cap<unsigned __int128>() : KC == 1 ? group_cap<uint64_t>() : group_cap<uint32_t>());
 }
 
-hipError_t launch_publish(uint32_t S, const MergeFin& fin, const uint32_t* err, hipStream_t s) {
-  k_publish<<<1, 256, 0, s>>>(S, fin, err);
+hipError_t launch_publish(uint32_t S, const MergeFin& fin, uint64_t* seg_off_out, const uint32_t* err, hipStream_t s) {
+  k_publish<<<1, 256, 0, s>>>(S, fin, seg_off_out, err);
   return hipGetLastError();
 }
 
 hipError_t launch_small_passes(int KC, int WP, int fp64_acc, const void* keys_in, const void* w_in,
                                const uint64_t* seg_in, uint32_t S, const PassArgs* pas, uint32_t n_grp,
                                void* const kslot[2], void* const wslot[2], void* wimg, uint32_t* cnt,
-                               void* keys_out, void* w_out, uint64_t* seg_off_out, uint32_t* err, hipStream_t s,
-                               Prof* prof) {
+                               void* keys_out, void* w_out, uint64_t* seg_off_out, uint64_t* result, uint64_t seq,
+                               uint32_t* err, hipStream_t s, Prof* prof) {
   if (S == 0 || n_grp == 0) return hipErrorInvalidValue;
   hipEvent_t ev = prof_begin(prof, s, kKSmallPasses);
   const int last = (int)((n_grp - 1) & 1u);
@@ -3103,6 +3701,7 @@ hipError_t launch_small_passes(int KC, int WP, int fp64_acc, const void* keys_in
   if (KC == 0) { QIMAX_SMALL_PASSES(uint32_t) } else if (KC == 1) { QIMAX_SMALL_PASSES(uint64_t) }
   else { QIMAX_SMALL_PASSES(unsigned __int128) }
 #undef QIMAX_SMALL_PASSES
+  k_small_publish<<<1, 256, 0, s>>>(cnt, n_grp * S * 3, result, seq, err);
   prof_end(prof, s, ev, kKSmallPasses, 0.0);  // bytes: added by the caller once the counts are back
   return hipGetLastError();
 }
@@ -3128,6 +3727,53 @@ hipError_t launch_count_expand(int KC, int WP, const void* keys, const void* w, 
   // bytes: every input term read; the images' bytes are added by the caller once known
   const double per = (4 << KC) + (WP == 64 ? 8 : 4);
   prof_end(prof, s, ev, kKCountExpand, per * (double)T_in);
+  return hipGetLastError();
+}
+
+uint32_t gather_cap(int KC) {
+  return (uint32_t)(KC == 2 ? plan_cap<unsigned __int128>() : KC == 1 ? plan_cap<uint64_t>() : plan_cap<uint32_t>());
+}
+
+hipError_t launch_gather_plan(int KC, int WP, const void* keys, const void* w, const uint64_t* seg_in, uint32_t S,
+                              const PassArgs* pas, const uint32_t* seg_entry, const GatherPlan& gp, uint64_t* result,
+                              uint64_t seq, uint32_t* err, hipStream_t s, Prof* prof) {
+  if (S == 0) return hipErrorInvalidValue;
+  hipEvent_t ev = prof_begin(prof, s, kKGather);
+  QIMAX_DISPATCH_K(KC, {
+    if (WP == 64)
+      k_gather_plan<K, 64><<<S, kPlanBlock, 0, s>>>((const K*)keys, (const double*)w, seg_in, pas, seg_entry, gp, err);
+    else
+      k_gather_plan<K, 32><<<S, kPlanBlock, 0, s>>>((const K*)keys, (const float*)w, seg_in, pas, seg_entry, gp, err);
+  });
+  prof_end(prof, s, ev, kKGather, 0.0);
+  k_gather_publish<<<1, 256, 0, s>>>(S, gp, result, seq, err);
+  return hipGetLastError();
+}
+
+hipError_t launch_gather(int KC, int WP, int fp64_acc, int variant, const GatherPlan& gp, const uint64_t* seg_in,
+                         uint32_t S, uint32_t n_tiles, const PassArgs* pas, const uint32_t* seg_entry, uint64_t* status,
+                         uint32_t* ctr, uint64_t epoch, uint64_t* img_seg, void* keys_out, void* w_out,
+                         uint64_t out_cap, uint32_t* err, hipStream_t s, Prof* prof) {
+  if (n_tiles == 0) {  // no outputs at all
+    k_fill_u64<<<grid_for(S + 1, 256), 256, 0, s>>>(img_seg, S + 1, 0ull);
+    return hipGetLastError();
+  }
+  hipEvent_t ev = prof_begin(prof, s, kKGather);
+#define QIMAX_GATHER(WPV, SWV, ACC)                                                                             \
+  k_gather<K, WPV, SWV, ACC><<<n_tiles, gather_tile(SWV == 3), 0, s>>>(gp, gp.goff[variant], gp.tiles[variant], seg_in, S, n_tiles, \
+                                                             pas, seg_entry, status, ctr, epoch, img_seg, (K*)keys_out,   \
+                                                             (typename WTraits<WPV>::W*)w_out, out_cap, err)
+  QIMAX_DISPATCH_K(KC, {
+    if (WP == 64) {
+      if (variant) QIMAX_GATHER(64, 3, PlainSum<double>); else QIMAX_GATHER(64, 1, PlainSum<double>);
+    } else if (fp64_acc) {
+      if (variant) QIMAX_GATHER(32, 3, F64Sum); else QIMAX_GATHER(32, 1, F64Sum);
+    } else {
+      if (variant) QIMAX_GATHER(32, 3, RunSum<float>); else QIMAX_GATHER(32, 1, RunSum<float>);
+    }
+  });
+#undef QIMAX_GATHER
+  prof_end(prof, s, ev, kKGather, 0.0);  // the outputs' bytes are added by the caller once known
   return hipGetLastError();
 }
 
@@ -3181,7 +3827,7 @@ hipError_t launch_sort_pass(int KC, int WP, const void* keys_in, const void* w_i
 hipError_t launch_sort_sweep(int KC, int WP, void* const keys[2], void* const w[2], uint64_t T, uint32_t key_bits,
                              uint32_t p_begin, bool upsweep, const Tiling& tl, const uint64_t* seg_off,
                              uint32_t* ghist, uint64_t* status, uint32_t* tile_ctr, uint64_t* epoch, uint32_t* err,
-                             int* cur, hipStream_t s, Prof* prof) {
+                             int* cur, hipStream_t s, Prof* prof, void* last_k, void* last_w) {
   *cur = 0;
   if (T == 0 || tl.n_blocks == 0) return hipSuccess;
   const uint32_t n_pass = (key_bits + kRadixBits - 1) / kRadixBits;
@@ -3199,14 +3845,16 @@ hipError_t launch_sort_sweep(int KC, int WP, void* const keys[2], void* const w[
     for (uint32_t p = p_begin; p < n_pass; ++p) {
       *epoch += 1;  // the caller keeps *epoch + n_pass below 2^16 (clearing status on wrap)
       const int c = *cur;
+      void* const ko = p + 1 == n_pass && last_k ? last_k : keys[c ^ 1];
+      void* const wo = p + 1 == n_pass && last_k ? last_w : w[c ^ 1];
       if (WP == 64)
         k_sort_scatter<K, double, true><<<tl.n_blocks, kSortBlock, 0, s>>>(
-            (const K*)keys[c], (const double*)w[c], (K*)keys[c ^ 1], (double*)w[c ^ 1], T, 8u * p, tl, nullptr,
+            (const K*)keys[c], (const double*)w[c], (K*)ko, (double*)wo, T, 8u * p, tl, nullptr,
             ghist + (uint64_t)p * kRadix, n_pass * kRadix, seg_off, status, tile_ctr + (uint64_t)p * kXcds, *epoch,
             err);
       else
         k_sort_scatter<K, float, true><<<tl.n_blocks, kSortBlock, 0, s>>>(
-            (const K*)keys[c], (const float*)w[c], (K*)keys[c ^ 1], (float*)w[c ^ 1], T, 8u * p, tl, nullptr,
+            (const K*)keys[c], (const float*)w[c], (K*)ko, (float*)wo, T, 8u * p, tl, nullptr,
             ghist + (uint64_t)p * kRadix, n_pass * kRadix, seg_off, status, tile_ctr + (uint64_t)p * kXcds, *epoch,
             err);
       *cur ^= 1;

@@ -355,7 +355,6 @@ struct KeySpan {
   }
 };
 
-constexpr int kMaxE1 = 64;
 constexpr int kBoundPathMaxFanout = 16;  // rounds with a larger fan-out bound read back their image count
 // tile counters of a round (after the per-pass, per-XCD sort counters)
 constexpr int kCtrCount = 252, kCtrMerge = 253, kCtrChunk = 254;
@@ -404,6 +403,7 @@ struct qimax_ctx {
   bool opt_busy = false, lean = false;
   DevBuf akeys, asign;  // input terms after their pass's A chain, and the signs (count -> expand)
   DevBuf chunk_off, chunk_cnt, chunk_start;  // chunk-local merge: offset, kept terms, deferred runs per chunk
+  DevBuf gat;      // gathered rounds: parents by group, groups, totals (see GatherPlan)
   DevBuf grp_cnt;  // persistent small passes: counts per pass and segment
   DevBuf img_cnt;                            // small rounds: image count per segment
   DevBuf ghist, sbase, sstatus, tile_ctr;  // single-sweep sort state
@@ -421,6 +421,7 @@ struct qimax_ctx {
   uint32_t chunk_tile = 0;    // nominal chunk of a fused round (0: from the expected bucket size)
   bool wide_offsets = false;  // count and expansion take their paths for 2^32 / 2^31 images (tests)
   bool classic_passes = false;  // multi-launch global sort passes in every round (tests)
+  bool gather = true;        // rounds of large fan-out merge before they expand (see k_gather_plan)
   bool merge_free = true;    // passes whose images all differ leave them unsorted (see KeySpan)
   bool small_groups = true;  // consecutive small passes in one launch (k_small_passes)
   int dense_mode = 0;         // dense accumulation: 0 off, 1 wherever it applies, 2 a tuner candidate
@@ -687,6 +688,44 @@ Exp1Desc make_exp1(uint32_t n, const HostOp& op) {
     d.rcp[in] = count_reciprocal(k);
   }
   return d;
+}
+
+// The operator as blocks; false where it does not fall apart into full blocks (see BlockDesc).
+bool make_block(uint32_t n, const HostOp& op, BlockDesc& d) {
+  d = BlockDesc{};
+  if (op.arity != 1) return false;
+  d.pos = bitpos(n, op.q0);
+  uint32_t outs[4] = {};
+  for (int in = 0; in < 4; ++in)
+    for (int r = 0; r < 4; ++r) {
+      const double v = op.R[r * 4 + in];
+      d.r[4 * r + in] = v;
+      d.rf[4 * r + in] = (float)v;
+      if (v != 0.0) outs[in] |= 1u << r;
+    }
+  for (int in = 0; in < 4; ++in) {
+    int c = in, size = 0;
+    for (int o = 3; o >= 0; --o) {
+      if (outs[o] == outs[in]) {
+        c = o;
+        ++size;
+      } else if (outs[o] & outs[in]) {
+        return false;
+      }
+    }
+    d.comp[in] = (uint8_t)c;
+    int k = 0;
+    for (int r = 0; r < 4; ++r)
+      if ((outs[in] >> r) & 1u) d.odig[c][k++] = (uint8_t)r;
+    if (k != size || k > 3) return false;
+    d.osize[c] = (uint8_t)k;
+    if (k == 1) {
+      const double v = op.R[d.odig[c][0] * 4 + in];
+      if (v != 1.0 && v != -1.0) return false;
+      d.neg[c] = v < 0;
+    }
+  }
+  return true;
 }
 
 Exp2Desc make_exp2(uint32_t n, const HostOp& op) {
@@ -1055,6 +1094,7 @@ struct RoundDesc {
   TableLaunch tables;
   size_t host_bytes = 0;
   size_t e_bytes = 0;              // largest expanding-operator descriptor set of an entry
+  bool blocks = true;              // every expanding operator has a block descriptor
   bool any_b_tables = false;
   uint32_t max_n = 1;
 };
@@ -1066,6 +1106,14 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
   std::vector<PermDesc> perms;
   std::vector<Exp1Desc> e1;
   std::vector<Exp2Desc> e2;
+  std::vector<BlockDesc> g1;  // one per e1 entry, while every operator has one
+  bool blocks = c->gather;
+  for (const RoundEntry& en : entries)
+    if (en.pass && !en.drop) blocks = blocks && en.pass->fanout_bound >= 1.0;
+  double f_max = 0.0;
+  for (const RoundEntry& en : entries)
+    if (en.pass && !en.drop) f_max = std::max(f_max, en.pass->fanout_bound);
+  blocks = blocks && f_max > (double)kBoundPathMaxFanout;  // (only rounds of large fan-out are gathered)
   struct Lay { size_t a, b, x1, x2; uint32_t nA, nB, nE1, nE2; bool useA, useB; };
   std::vector<Lay> lay(E);
   size_t e_bytes = 0;  // largest expanding-operator descriptor set of an entry (staged in LDS)
@@ -1086,6 +1134,8 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
     for (auto* op : p->B) perms.push_back(make_perm(entries[e].n, *op));
     L.nB = (uint32_t)p->B.size();
     for (auto* op : p->E) {
+      BlockDesc g;
+      if (blocks && (blocks = make_block(entries[e].n, *op, g))) g1.push_back(g);
       if (op->arity == 1) { e1.push_back(make_exp1(entries[e].n, *op)); ++L.nE1; }
       else { e2.push_back(make_exp2(entries[e].n, *op)); ++L.nE2; }
     }
@@ -1104,7 +1154,9 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
   const size_t oP = 0;
   const size_t o1 = align256(oP + perms.size() * sizeof(PermDesc));
   const size_t o2 = align256(o1 + e1.size() * sizeof(Exp1Desc));
-  const size_t oA = align256(o2 + e2.size() * sizeof(Exp2Desc));
+  if (!blocks) g1.clear();
+  const size_t oG = align256(o2 + e2.size() * sizeof(Exp2Desc));
+  const size_t oA = align256(oG + g1.size() * sizeof(BlockDesc));
   const size_t oS = align256(oA + E * sizeof(PassArgs));
   const size_t oJ = align256(oS + S * 4);
   TablePlan tp;
@@ -1122,6 +1174,7 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
   if (!perms.empty()) std::memcpy(hs + oP, perms.data(), perms.size() * sizeof(PermDesc));
   if (!e1.empty()) std::memcpy(hs + o1, e1.data(), e1.size() * sizeof(Exp1Desc));
   if (!e2.empty()) std::memcpy(hs + o2, e2.data(), e2.size() * sizeof(Exp2Desc));
+  if (!g1.empty()) std::memcpy(hs + oG, g1.data(), g1.size() * sizeof(BlockDesc));
   PassArgs* pas_h = (PassArgs*)(hs + oA);
   std::vector<ChainTable> tabs(lens.size());
   std::vector<const PermDesc*> chain_ops(lens.size());
@@ -1142,6 +1195,7 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
     pa.drop = entries[e].drop ? 1u : 0u;
     pa.unsorted = entries[e].pass && entries[e].pass->unsorted ? 1u : 0u;
     pa.thr = entries[e].thr;
+    if (blocks) pa.G1 = (const BlockDesc*)(ds + oG) + L.x1;
     const Pass* pp = entries[e].pass;
     if (L.useA) {
       pa.useA = 1;
@@ -1158,6 +1212,7 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
   rd.sent = (const uint32_t*)(ds + oS);
   rd.host_bytes = host_bytes;
   rd.e_bytes = e_bytes;
+  rd.blocks = blocks;
   rd.any_b_tables = any_b_tables;
   rd.max_n = max_n;
   return QIMAX_OK;
@@ -1217,6 +1272,10 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   // tile's images in reach of one block); its input tiles are smaller.
   const bool fused = bound_path && !small && c->fused_expand && (double)f_round <= (double)kFuseMaxFanout;
   const uint64_t in_tile = fused ? (uint64_t)fuse_tile() : (uint64_t)kSortTile;
+  // Gathered round: a large fan-out whose operators fall apart into full blocks, every segment's
+  // terms few enough to be grouped by one block (see k_gather_plan).
+  bool gather = sweep && !c->host_tiling && !bound_path && rd.blocks && T_in > 0 && c->dense_mode != 1 && S <= kSmallMaxSegs;
+  for (uint32_t s = 0; s < S && gather; ++s) gather = so_in[s + 1] - so_in[s] <= gather_cap(c->KC);
   // every pass of the round leaves its images unsorted: they are the round's output
   bool plain = fused && !c->dense_mode;
   for (const RoundEntry& en : entries) plain = plain && (en.drop || (en.pass && en.pass->unsorted));
@@ -1246,7 +1305,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
     c->st.alg_bytes += alg * (double)(c->kb + c->wb);
     c->st.rounds += 1;
     c->st.images += so_img[S];
-    c->st.sort_elems += plain ? 0 : so_img[S] * n_pass;
+    c->st.sort_elems += plain ? 0 : (gather ? so_out[S] : so_img[S]) * n_pass;
     return QIMAX_OK;
   };
   Tiling tl_in{};
@@ -1280,7 +1339,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
     }
     return QIMAX_OK;
   };
-  if (!small && !fused) {
+  if (!small && !fused && !gather) {
     QCHK(ensure(c, c->off, (T_in + 1) * 8));
     QCHK(ensure(c, c->akeys, std::max<uint64_t>(T_in, 1) * c->kb));
     QCHK(ensure(c, c->asign, std::max<uint64_t>(T_in, 1)));
@@ -1306,7 +1365,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
                                   n_pass, (uint32_t*)c->err.p, c->stream, &c->prof), "count and expand");
     const MergeFin fin{off, c->zres_dev, ++c->zseq};
     c->zres[2 * (size_t)S + 3] = 0;
-    HIPCHK(c, launch_publish(S, fin, (const uint32_t*)c->err.p, c->stream), "publish");
+    HIPCHK(c, launch_publish(S, fin, nullptr, (const uint32_t*)c->err.p, c->stream), "publish");
     QCHK(wait_zres(c, 2 * (size_t)S + 4, &e));
     if (e) return round_failed(e, cap);
     so_img.assign(c->zres + S + 1, c->zres + 2 * (size_t)(S + 1));
@@ -1319,8 +1378,35 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   QCHK(ensure(c, c->img_seg, (S + 1) * 8));
   Tiling tl_exp{}, tl{};
   TileJob2 img_jobs[2];
-  if (bound_path) {
-    T_img = (uint64_t)f_round * T_in;  // capacity: an upper bound of the image count
+  GatherPlan gp{};
+  std::vector<uint64_t> g_units[2], g_images;
+  std::vector<uint64_t> so_cap;  // gathered: the segments' outputs before the prune
+  if (gather) {
+    QCHK(ensure(c, c->akeys, T_in * c->kb));
+    QCHK(ensure(c, c->asign, T_in));
+    const size_t o1 = align256(T_in * c->kb), o2 = o1 + align256(T_in * c->wb), o3 = o2 + align256(T_in * 4);
+    const size_t o4 = o3 + align256(T_in * 8), o5 = o4 + align256(T_in * 8), o6 = o5 + align256((size_t)S * 4);
+    const size_t o7 = o6 + align256((size_t)S * 32), o8 = o7 + align256((size_t)(S + 1) * 4);
+    QCHK(ensure(c, c->gat, o8 + align256((size_t)(S + 1) * 4)));
+    uint8_t* d = (uint8_t*)c->gat.p;
+    gp = GatherPlan{d, d + o1, c->akeys.p, (uint8_t*)c->asign.p, (uint32_t*)(d + o2),
+                    {(uint64_t*)(d + o3), (uint64_t*)(d + o4)}, (uint32_t*)(d + o5), (uint64_t*)(d + o6),
+                    {(uint32_t*)(d + o7), (uint32_t*)(d + o8)}};
+    const size_t words = 4 * (size_t)(S + 1) + 2;
+    QCHK(ensure_zres(c, std::max(words, 2 * (size_t)S + 4)));
+    c->zres[words - 1] = 0;
+    HIPCHK(c, launch_gather_plan(c->KC, c->WP, k_in, w_in, seg_in, S, pas, sent, gp, c->zres_dev, ++c->zseq,
+                                 (uint32_t*)c->err.p, c->stream, &c->prof), "gather plan");
+    QCHK(wait_zres(c, words, &e));
+    if (e) return fail(c, (e & kErrFanout) ? QIMAX_ETOOLARGE : QIMAX_EDEVICE, "gather plan:" + err_text(e));
+    const uint64_t* z = c->zres;
+    so_cap.assign(z, z + S + 1);
+    for (int v = 0; v < 2; ++v) g_units[v].assign(z + (size_t)(1 + v) * (S + 1), z + (size_t)(2 + v) * (S + 1));
+    g_images.assign(z + 3 * (size_t)(S + 1), z + 4 * (size_t)(S + 1));
+    T_img = so_cap[S];
+  }
+  if (bound_path || gather) {
+    if (!gather) T_img = (uint64_t)f_round * T_in;  // capacity: an upper bound of the image count
     const uint32_t caps[2] = {(uint32_t)((T_img + kExpandTile - 1) / kExpandTile + S),
                               (uint32_t)((T_img + kSortTile - 1) / kSortTile + S)};
     const uint64_t tiles[2] = {(uint64_t)kExpandTile, (uint64_t)kSortTile};
@@ -1337,7 +1423,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
       *tls[i] = Tiling{(const uint64_t*)(d + o1), (const uint64_t*)(d + o2), (const uint32_t*)(d + o3),
                        (const uint32_t*)(d + o4), caps[i], S, (const uint32_t*)(d + o5), (const uint32_t*)(d + o6)};
     }
-    if (!small && !fused)  // (a fused round builds them after its launch, from the image offsets it wrote)
+    if (!small && !fused && !gather)  // (a fused or gathered round builds them after its launch, from the image offsets it wrote)
       HIPCHK(c, launch_make_tiles2((const uint64_t*)c->off.p, seg_in, S, (uint64_t*)c->img_seg.p, jobs[0], jobs[1],
                                    T_img, (uint32_t*)c->err.p, c->stream), "tiles");
   } else {
@@ -1388,18 +1474,23 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   bool dense = dense_ok && c->dense_mode == 1;
   if (small) m_top = 0;  // whole segments sorted in LDS
   uint64_t seg_max = 0;     // the largest segment's image count (or its bound)
+  bool whole = false;       // gathered: chunks are whole segments
   if (sweep && !small) {
     if (c->local_sort && c->redo_cooldown == 0) {
       for (uint32_t s = 0; s < S; ++s)
         seg_max = std::max<uint64_t>(seg_max, bound_path ? (uint64_t)(f_round * (double)(so_in[s + 1] - so_in[s]))
+                                              : gather   ? so_cap[s + 1] - so_cap[s]
                                                          : so_img[s + 1] - so_img[s]);
       uint32_t mm = 0;
       for (double cap_b = 512.0; mm < n_pass && (double)seg_max > cap_b; cap_b *= 256.0) ++mm;
+      // gathered outputs are distinct and few: whole segments in LDS where they fit a chunk
+      whole = gather && c->local_sort_m < 0 && seg_max <= (uint64_t)kChunkCap;
+      if (whole) mm = 0;
       m_top = c->local_sort_m >= 0 ? std::min<uint32_t>((uint32_t)c->local_sort_m, n_pass) : mm;
-      if (c->autotune && c->local_sort_m < 0 && (m_top < n_pass || dense_ok)) {
+      if (c->autotune && c->local_sort_m < 0 && !whole && (m_top < n_pass || dense_ok)) {
         // size class: key class << 8 | FP64 weights << 6 | log2 of the image capacity (| 2^20 with dense)
         tune_key = ((uint32_t)c->KC << 8) + (c->WP == 64 ? 64u : 0u) + (uint32_t)std::min(63, ilog2_u64(T_img)) +
-                   (dense_ok ? (1u << 20) : 0u);
+                   (dense_ok ? (1u << 20) : 0u) + (gather ? (1u << 21) : 0u);
         TuneState& ts = c->tune[tune_key];
         // (a recording never explores: its rounds are not timed)
         // (each candidate is timed kTuneSamples times, in turns; its time is the least)
@@ -1417,7 +1508,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
     }
     if (c->redo_cooldown > 0) --c->redo_cooldown;
   }
-  const bool hist_in_expand = sweep && !dense && !classic_passes && m_top <= kExpandHistPasses;
+  const bool hist_in_expand = sweep && !dense && !classic_passes && !gather && m_top <= kExpandHistPasses;
   // ---- expand into images
   const size_t eb = c->kb, wbt = c->wb;
   // image buffers: the capacity, or for a small round S chunks of kChunkCap
@@ -1460,6 +1551,26 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
     }
     HIPCHK(c, launch_make_tiles2(nullptr, (const uint64_t*)c->img_seg.p, S, nullptr, img_jobs[0], img_jobs[1], T_img,
                                  (uint32_t*)c->err.p, c->stream), "tiles");
+  } else if (gather) {
+    // three operators in a unit where that leaves two waves per CU and more: the n = 12 ansatz
+    // (59 Ki such units) 0.12 ms against 0.23 with one, n = 10 (7 Ki) 0.10 against 0.07, the
+    // saturated n = 6 one (1 Ki) 0.42 against 0.13 per layer
+    const int variant = g_units[1][S] >= (1ull << 15) ? 1 : 0;
+    uint64_t n_tiles = 0;
+    for (uint32_t s = 0; s < S; ++s)
+      n_tiles += (g_units[variant][s + 1] - g_units[variant][s] + gather_tile(variant) - 1) / gather_tile(variant);
+    if (n_tiles > 0x7FFFFFFFull) return fail(c, QIMAX_ETOOLARGE, "gather: too many outputs");
+    QCHK(status_words(n_tiles));
+    c->mepoch += 1;
+    HIPCHK(c, launch_gather(c->KC, c->WP, c->fp64_acc, variant, gp, seg_in, S, (uint32_t)n_tiles, pas, sent,
+                            (uint64_t*)c->mstatus.p, ctr + kCtrCount, c->mepoch, (uint64_t*)c->img_seg.p, c->ik[0].p,
+                            c->iw[0].p, T_img, (uint32_t*)c->err.p, c->stream, &c->prof), "gather");
+    if (whole) img_jobs[0].tile = (uint64_t)kChunkCap;
+    if (T_img)
+      HIPCHK(c, launch_make_tiles2(nullptr, (const uint64_t*)c->img_seg.p, S, nullptr, img_jobs[0], img_jobs[1], T_img,
+                                   (uint32_t*)c->err.p, c->stream), "tiles");
+    else
+      tl.n_blocks = tl_exp.n_blocks = 0;
   } else
   HIPCHK(c, launch_expand(c->KC, c->WP, c->akeys.p, (const uint8_t*)c->asign.p, w_in, T_in,
                           (const uint64_t*)c->off.p, T_img, tl_exp, pas, sent, seg_in, any_b_tables, e_bytes,
@@ -1469,6 +1580,12 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   const uint64_t hsize = (uint64_t)kRadix * std::max<uint32_t>(tl.n_blocks, 1);
   int cur = 0;
   int pre_chunk = -1;       // slot holding the images before the chunk-local sort
+  // gathered and sorted by global passes only: the last pass writes the round's output
+  const bool sorted_out = gather && !dense && m_top == n_pass && T_img > 0;
+  if (sorted_out) {
+    QCHK(ensure(c, c->pk[slot], T_img * eb));
+    QCHK(ensure(c, c->pw[slot], T_img * wbt));
+  }
   if (small) {
     pre_chunk = 0;
   } else if (dense) {
@@ -1502,15 +1619,18 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
       QCHK(ensure(c, c->hist_off, (hsize + 1) * 8));
       cur = 0;
       for (uint32_t p = n_pass - m_top; p < n_pass; ++p) {
-        HIPCHK(c, launch_sort_pass(c->KC, c->WP, kk[cur], ww[cur], kk[cur ^ 1], ww[cur ^ 1], T_img, p * kRadixBits,
+        const bool out = sorted_out && p + 1 == n_pass;
+        HIPCHK(c, launch_sort_pass(c->KC, c->WP, kk[cur], ww[cur], out ? c->pk[slot].p : kk[cur ^ 1],
+                                   out ? c->pw[slot].p : ww[cur ^ 1], T_img, p * kRadixBits,
                                    tl, (uint64_t*)c->hist.p, (uint64_t*)c->hist_off.p, (uint64_t*)c->scan_tmp.p,
                                    (uint32_t*)c->err.p, c->stream, &c->prof), "sort");
         cur ^= 1;
       }
     } else {
-      HIPCHK(c, launch_sort_sweep(c->KC, c->WP, kk, ww, T_img, key_bits, n_pass - m_top, !hist_in_expand, tl,
+      HIPCHK(c, launch_sort_sweep(c->KC, c->WP, kk, ww, T_img, key_bits, n_pass - m_top, !hist_in_expand && m_top > 0, tl,
                                   (const uint64_t*)c->img_seg.p, (uint32_t*)c->ghist.p, (uint64_t*)c->sstatus.p, ctr,
-                                  &c->epoch, (uint32_t*)c->err.p, &cur, c->stream, &c->prof), "sort");
+                                  &c->epoch, (uint32_t*)c->err.p, &cur, c->stream, &c->prof,
+                                  sorted_out ? c->pk[slot].p : nullptr, sorted_out ? c->pw[slot].p : nullptr), "sort");
     }
     if (m_top < n_pass) pre_chunk = cur;  // the chunk-local sort runs with the merge
   }
@@ -1529,7 +1649,9 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
       fin.seq = ++c->zseq;
       c->zres[2 * (size_t)S + 3] = 0;
     }
-    if (dense) {
+    if (sorted_out) {
+      HIPCHK(c, launch_publish(S, fin, (uint64_t*)c->pseg[slot].p, (const uint32_t*)c->err.p, c->stream), "publish");
+    } else if (dense) {
       const uint64_t tps = (per_seg + dense_tile() - 1) / dense_tile();
       const uint64_t n_tiles = tps * S;
       QCHK(ensure(c, c->dense_acc, (size_t)(S * per_seg) * 8));
@@ -1619,6 +1741,20 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   const uint64_t* rb = sweep ? c->zres : c->pinned;  // where the round's results came back
   so_out.assign(rb, rb + S + 1);
   const uint64_t T_out = so_out[S];
+  if (gather) {
+    so_img = g_images;  // every image counts, merged before it was formed or not
+    if (c->prof.on) {   // the launches were recorded with the outputs before the prune
+      const double kept = (double)rb[2 * S + 1], d = (double)T_img - kept;
+      auto add = [&](int kind, double bytes) {
+        if ((c->prof.mask >> kind) & 1u) c->prof.bytes[kind] += bytes;
+      };
+      add(kKGather, (double)(eb + wbt) * ((double)T_in + kept));
+      if (m_top && !classic_passes) add(kKSortHist, -(double)eb * d * (sorted_again ? 2 : 1));
+      add(kKSortScatter, -2.0 * (double)(eb + wbt) * (sorted_again ? n_pass + m_top : m_top) * d);
+      if (m_top < n_pass) add(kKChunkSort, -(double)(eb + wbt) * d);
+      if (!chunk_path && !sorted_out) add(kKMergeWrite, -(double)(eb + wbt) * d);
+    }
+  }
   if (bound_path) {
     so_img.assign(rb + S + 1, rb + 2 * (S + 1));
     // the launches were recorded with the capacity; count the real images
@@ -1650,7 +1786,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
     const double kept = (double)T_out * (double)(eb + wbt);
     if (dense) {
       if ((c->prof.mask >> kKDense) & 1u) c->prof.bytes[kKDense] += kept;
-    } else if (!chunk_path && ((c->prof.mask >> kKMergeWrite) & 1u)) {
+    } else if (!chunk_path && !sorted_out && ((c->prof.mask >> kKMergeWrite) & 1u)) {
       c->prof.bytes[kKMergeWrite] += kept;
     }
     if (chunk_path && ((c->prof.mask >> kKChunkSort) & 1u)) c->prof.bytes[kKChunkSort] += kept;
@@ -1790,10 +1926,12 @@ qimax_status prebuild_tables(qimax_ctx* c, std::vector<Pass>& passes) {
 // every segment's terms, multiplied by each pass's fan-out bound in turn, stay within what a
 // block holds (so do its images). 0 or 1: run the passes as rounds.
 constexpr size_t kMaxGroupPasses = 64;
+bool small_group_ok(const qimax_ctx* c) {
+  return c->small_groups && c->small_rounds && !c->classic_sort && !c->host_tiling && c->n <= kSmallMaxSegs;
+}
 size_t small_group_len(const qimax_ctx* c, const std::vector<Pass>& passes, size_t i0,
                        const std::vector<uint64_t>& so_in) {
-  if (!c->small_groups || !c->small_rounds || c->classic_sort || c->host_tiling || c->n > kSmallMaxSegs)
-    return 0;
+  if (!small_group_ok(c)) return 0;
   const double cap = (double)small_group_cap(c->KC);
   std::vector<double> len(c->n);
   for (uint32_t s = 0; s < c->n; ++s) len[s] = (double)(so_in[s + 1] - so_in[s]);
@@ -1812,11 +1950,12 @@ size_t small_group_len(const qimax_ctx* c, const std::vector<Pass>& passes, size
 // Passes i0 .. i0+k-1 of the context's circuit in one launch of k_small_passes (one block per
 // generator, the terms in LDS-sized slots between the passes); so_ins / so_imgs / so_outs
 // receive each pass's segment offsets of its input terms, images and kept terms, and the
-// last pass's terms go to pass slot `slot`. Counters as for k rounds.
+// last pass's terms go to pass slot `slot`. Counters as for k rounds. overflow: set (and nothing
+// done) where the images do not fit after all, for passes taken without a bound.
 qimax_status run_small_group(qimax_ctx* c, std::vector<Pass>& passes, size_t i0, size_t k, const void* k_in,
                              const void* w_in, const uint64_t* s_in, const std::vector<uint64_t>& so_in, int slot,
                              std::vector<std::vector<uint64_t>>& so_ins, std::vector<std::vector<uint64_t>>& so_imgs,
-                             std::vector<std::vector<uint64_t>>& so_outs) {
+                             std::vector<std::vector<uint64_t>>& so_outs, bool* overflow = nullptr) {
   const uint32_t S = c->n;
   std::vector<RoundEntry> en(k);
   for (size_t p = 0; p < k; ++p) {
@@ -1858,16 +1997,22 @@ qimax_status run_small_group(qimax_ctx* c, std::vector<Pass>& passes, size_t i0,
   QCHK(ensure(c, c->pseg[slot], (S + 1) * 8));
   const size_t cnt_words = (k * S * 3 + 1) / 2;
   QCHK(ensure(c, c->grp_cnt, cnt_words * 8));
+  QCHK(ensure_zres(c, cnt_words + 2));
+  c->zres[cnt_words + 1] = 0;
   void* const ks[2] = {c->ik[0].p, c->ik[1].p};
   void* const ws[2] = {c->iw[0].p, c->iw[1].p};
   HIPCHK(c, launch_small_passes(c->KC, c->WP, c->fp64_acc, k_in, w_in, s_in, S, rd.pas, (uint32_t)k, ks, ws,
                                 c->pw[slot].p, (uint32_t*)c->grp_cnt.p, c->pk[slot].p, c->pw[slot].p,
-                                (uint64_t*)c->pseg[slot].p, (uint32_t*)c->err.p, c->stream, &c->prof),
-         "small passes");
+                                (uint64_t*)c->pseg[slot].p, c->zres_dev, ++c->zseq, (uint32_t*)c->err.p, c->stream,
+                                &c->prof), "small passes");
   uint32_t e = 0;
-  QCHK(readback(c, c->grp_cnt.p, cnt_words, &e));
+  QCHK(wait_zres(c, cnt_words + 2, &e));
+  if (overflow && (e & kErrFanout)) {  // more images than a block holds: nothing is changed
+    *overflow = true;
+    return QIMAX_OK;
+  }
   if (e) return fail(c, (e & kErrFanout) ? QIMAX_ETOOLARGE : QIMAX_EDEVICE, "small passes:" + err_text(e));
-  const uint32_t* h = (const uint32_t*)c->pinned;
+  const uint32_t* h = (const uint32_t*)c->zres;
   so_ins.assign(k, {});
   so_imgs.assign(k, {});
   so_outs.assign(k, {});
@@ -1948,11 +2093,22 @@ qimax_status apply_ops_once(qimax_ctx* c, std::vector<HostOp>& ops) {
   std::vector<uint32_t> seg_entry(c->n, 0);
   int slot = 0;
   for (size_t i = 0; i < passes.size(); ++i) {
-    const size_t kg = small_group_len(c, passes, i, so_in);
-    if (kg >= 2) {  // consecutive small passes: one launch
-      std::vector<std::vector<uint64_t>> gi, gg, go;
-      qimax_status s = run_small_group(c, passes, i, kg, k_in, w_in, s_in, so_in, slot, gi, gg, go);
+    size_t kg = small_group_len(c, passes, i, so_in);
+    // Every generator one string still (a first layer): a pass of large fan-out bound may yet
+    // have few images (a rotation of every wire has three per string of weight one), so one
+    // launch tries it: 55 us for ten such strings against 115 in a round of its own. Where the
+    // images do not fit, the round follows (the try costs about 15 us).
+    bool overflow = false;
+    const bool attempt = kg == 0 && small_group_ok(c) && c->T == c->n && so_in[c->n] == c->n && i == 0 &&
+                         passes[i].fanout_bound > (double)kBoundPathMaxFanout;
+    if (attempt) kg = 1;
+    std::vector<std::vector<uint64_t>> gi, gg, go;
+    if (kg >= 2 || attempt) {  // consecutive small passes: one launch
+      qimax_status s = run_small_group(c, passes, i, kg, k_in, w_in, s_in, so_in, slot, gi, gg, go,
+                                       attempt ? &overflow : nullptr);
       if (s != QIMAX_OK) return s;  // committed state untouched
+    }
+    if ((kg >= 2 || attempt) && !overflow) {
       if (c->gen_updates.size() != c->n) c->gen_updates.assign(c->n, 0);
       for (size_t p = 0; p < kg; ++p) {
         for (uint32_t j = 0; j < c->n; ++j)
@@ -2792,6 +2948,8 @@ qimax_status qimax_create(uint32_t n, const qimax_opts* opts, qimax_ctx** out) {
     if (env && env[0])
       c->chunk_tile = std::min<uint32_t>(std::max<uint32_t>((uint32_t)std::strtoul(env, nullptr, 10), kExpandTile),
                                          (uint32_t)kChunkCap);
+    env = std::getenv("QIMAX_GATHER");  // 0: rounds of large fan-out expand every image
+    c->gather = !(env && env[0] == '0');
     env = std::getenv("QIMAX_MERGE_FREE");  // 0: every pass sorted and merged
     c->merge_free = !(env && env[0] == '0');
     env = std::getenv("QIMAX_SMALL_GROUPS");  // 0: every small pass as a round of its own
@@ -3393,7 +3551,7 @@ void qimax_destroy(qimax_ctx* c) {
   DevBuf* bufs[] = {&c->keys, &c->w, &c->seg, &c->pk[0], &c->pk[1], &c->pw[0], &c->pw[1], &c->pseg[0],
                     &c->pseg[1], &c->ik[0], &c->ik[1], &c->iw[0], &c->iw[1], &c->cnt, &c->off, &c->scan_tmp,
                     &c->hist, &c->hist_off, &c->blk_begin, &c->blk_end, &c->blk_seg, &c->seg_blk, &c->blk_cnt,
-                    &c->blk_off, &c->img_seg, &c->desc, &c->desc2, &c->err, &c->gr_in, &c->gr_out, &c->ghist, &c->sbase, &c->sstatus, &c->tile_ctr, &c->mstatus, &c->dtile[0], &c->dtile[1], &c->dtile[2], &c->ptab, &c->chain_parts, &c->wtab, &c->akeys, &c->asign, &c->img_cnt, &c->dense_acc, &c->chunk_cnt, &c->chunk_start, &c->grp_cnt,
+                    &c->blk_off, &c->img_seg, &c->desc, &c->desc2, &c->err, &c->gr_in, &c->gr_out, &c->ghist, &c->sbase, &c->sstatus, &c->tile_ctr, &c->mstatus, &c->dtile[0], &c->dtile[1], &c->dtile[2], &c->ptab, &c->chain_parts, &c->wtab, &c->akeys, &c->asign, &c->img_cnt, &c->dense_acc, &c->chunk_cnt, &c->chunk_start, &c->grp_cnt, &c->gat,
                     &c->chunk_off};
   for (DevBuf* b : bufs) dev_free(c, *b);
   drop_sv(c);

@@ -46,6 +46,21 @@ struct Exp2Desc {
   float valf[16][16];
 };
 
+// An expanding one-qubit operator whose matrix falls apart into full blocks: the digits come in
+// components of at most three input digits that all map to the same output digits, as many of
+// them, every entry nonzero (a rotation: {I}, {X, Y, Z}, or about an axis {I}, {Z}, {X, Y}).
+// Parents whose digits agree by component have the same images.
+struct BlockDesc {
+  uint32_t pos;
+  uint8_t comp[4];     // component of an input digit: its smallest input digit
+  uint8_t osize[4];    // of a component: output digits,
+  uint8_t odig[4][4];  // these digits ascending,
+  uint8_t neg[4];      // and, of one output digit, whether its entry is -1 (else 1)
+  double r[16];        // entry (out, in) at 4 out + in
+  float rf[16];
+};
+constexpr int kMaxE1 = 64;  // one-qubit operators of a pass
+
 // A Clifford chain compiled into tables of the images of a key's parts. Conjugation is
 // multiplicative, so the image of a whole key is the product of its parts' images (they
 // commute) with the product's phase.
@@ -83,6 +98,7 @@ struct PassArgs {
   uint32_t drop;           // the entry's terms leave the array (f = 0)
   uint32_t unsorted;       // the images all differ and are the pass's output as they come
   double thr;              // merge keeps |w| > thr
+  const BlockDesc* G1;     // the E1 operators as blocks (gathered rounds)
 };
 
 // A run of permutation ops to compile: into a ChainTable (tab_key, tab_neg), or, as one of
@@ -183,7 +199,7 @@ enum : uint32_t {
 // algorithmic bytes each launch must move (what the roofline is measured against).
 enum KernelKind : int {
   kKInit, kKCount, kKScan, kKExpand, kKSortHist, kKSortScatter, kKMergeCount, kKMergeWrite, kKCompose, kKChunkSort,
-  kKCountExpand, kKDense, kKChunkFinish, kKSmallPasses, kKTables, kKNum
+  kKCountExpand, kKDense, kKChunkFinish, kKSmallPasses, kKTables, kKGather, kKNum
 };
 const char* kernel_kind_name(int k);
 
@@ -270,13 +286,16 @@ hipError_t launch_sort_pass(int KC, int WP, const void* keys_in, const void* w_i
 // ghist: n_segs*n_pass*256 u32, zero on entry; seg_off: the segment offsets (n_segs + 1);
 // status: n_blocks*256 u64 (zeroed when allocated); tile_ctr: n_pass*kXcds u32, zero on
 // entry; *epoch is advanced per digit pass.
+// last_k / last_w (unless null): where the last digit pass writes instead of the pair (*cur is
+// then of no meaning).
 // p_begin: first digit pass (the passes p_begin .. n_pass-1 run; p_begin > 0 groups the
 // segments by their top digits only); upsweep: compute ghist for those passes first (else
 // it is current).
 hipError_t launch_sort_sweep(int KC, int WP, void* const keys[2], void* const w[2], uint64_t T, uint32_t key_bits,
                              uint32_t p_begin, bool upsweep, const Tiling& tl, const uint64_t* seg_off,
                              uint32_t* ghist, uint64_t* status, uint32_t* tile_ctr, uint64_t* epoch, uint32_t* err,
-                             int* cur, hipStream_t s, Prof* prof = nullptr);
+                             int* cur, hipStream_t s, Prof* prof = nullptr, void* last_k = nullptr,
+                             void* last_w = nullptr);
 
 
 hipError_t launch_fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s);
@@ -387,13 +406,13 @@ size_t fuse_tile();
 // of S * kChunkCap elements each; cnt (n_grp * S * 3 words) receives every pass's input,
 // image and kept counts per segment; the last pass's terms go to keys_out / w_out with the
 // segment offsets in seg_off_out (S + 1). A segment may hold small_group_cap(KC) terms and
-// images.
+// images. result: the counts (as 32-bit words), then the error word and seq.
 uint32_t small_group_cap(int KC);
 hipError_t launch_small_passes(int KC, int WP, int fp64_acc, const void* keys_in, const void* w_in,
                                const uint64_t* seg_in, uint32_t S, const PassArgs* pas, uint32_t n_grp,
                                void* const kslot[2], void* const wslot[2], void* wimg, uint32_t* cnt,
-                               void* keys_out, void* w_out, uint64_t* seg_off_out, uint32_t* err, hipStream_t s,
-                               Prof* prof = nullptr);
+                               void* keys_out, void* w_out, uint64_t* seg_off_out, uint64_t* result, uint64_t seq,
+                               uint32_t* err, hipStream_t s, Prof* prof = nullptr);
 hipError_t launch_count_expand(int KC, int WP, const void* keys, const void* w, uint64_t T_in, const Tiling& tl,
                                const PassArgs* pas, const uint32_t* seg_entry, uint64_t* status, uint32_t* ctr,
                                uint64_t epoch, uint64_t* img_seg, void* keys_out, void* w_out, uint64_t out_cap,
@@ -409,6 +428,35 @@ hipError_t launch_expand_small(int KC, int WP, const void* keys, const void* w, 
                                uint64_t T_in, const PassArgs* pas, const uint32_t* seg_entry, void* keys_out,
                                void* w_out, uint32_t* img_cnt, const TileJob2& tiles, uint32_t* err, hipStream_t s,
                                Prof* prof = nullptr);
+// A gathered round (see k_gather_plan): the terms of every segment (at most gather_cap(KC)),
+// under the A chain, ordered by component key and cut into groups of parents with the same
+// images.
+struct GatherPlan {
+  void* keys;          // T_in: the parents' keys under the A chain, group after group
+  void* w;             // and their weights, the A chain's sign applied
+  void* akeys;         // T_in each: scratch
+  uint8_t* asign;
+  uint32_t* gstart;    // of a segment's groups, from its first term's place on: first parent
+  uint64_t* goff[2];   // and first unit with 1 and with 3 operators in a unit
+  uint32_t* n_groups;  // per segment
+  uint64_t* totals;    // per segment: outputs, units (1), units (3), images
+  uint32_t* tiles[2];  // S + 1: first tile (of gather_tile units) of every segment
+};
+// units of a tile, one thread each: variant 0 in blocks of one wave (few units: on more CUs)
+constexpr uint32_t gather_tile(int variant) { return variant ? 256u : 64u; }
+uint32_t gather_cap(int KC);
+// result: the scanned totals, four arrays of S + 1 words, then the error word and seq.
+hipError_t launch_gather_plan(int KC, int WP, const void* keys, const void* w, const uint64_t* seg_in, uint32_t S,
+                              const PassArgs* pas, const uint32_t* seg_entry, const GatherPlan& gp, uint64_t* result,
+                              uint64_t seq, uint32_t* err, hipStream_t s, Prof* prof = nullptr);
+// The outputs of n_tiles tiles (variant 0: one operator in a unit, 1: three), pruned, to keys_out
+// / w_out (out_cap elements; segments at img_seg, S + 1 words), in an order of their own; tiles
+// claimed through *ctr (zero at launch) with look-back on status (tagged epoch).
+hipError_t launch_gather(int KC, int WP, int fp64_acc, int variant, const GatherPlan& gp, const uint64_t* seg_in,
+                         uint32_t S, uint32_t n_tiles, const PassArgs* pas, const uint32_t* seg_entry, uint64_t* status,
+                         uint32_t* ctr, uint64_t epoch, uint64_t* img_seg, void* keys_out, void* w_out,
+                         uint64_t out_cap, uint32_t* err, hipStream_t s, Prof* prof = nullptr);
+
 // The first launch of a round: clears *err, ctr[0..n_ctr) and ghist[0..nh), copies blob_bytes
 // (a multiple of 16, both addresses 16-byte aligned) from blob_host (mapped host memory, its
 // device address) to blob_dev, and builds one tiling of the terms themselves (segments at
@@ -426,8 +474,9 @@ hipError_t launch_round_prep(uint32_t* err, uint32_t* ctr, uint32_t n_ctr, uint3
                              hipStream_t s);
 
 // The end of a round whose images are its output: fin.img_seg (S + 1 offsets) as output and as
-// image offsets, the error word and the sequence word (see MergeFin).
-hipError_t launch_publish(uint32_t S, const MergeFin& fin, const uint32_t* err, hipStream_t s);
+// image offsets, the error word and the sequence word (see MergeFin); seg_off_out (unless null)
+// receives the offsets too.
+hipError_t launch_publish(uint32_t S, const MergeFin& fin, uint64_t* seg_off_out, const uint32_t* err, hipStream_t s);
 
 // Plain copy of n words (calibration of hardware traffic counters).
 hipError_t launch_copy_u64(const uint64_t* in, uint64_t* out, uint64_t n, hipStream_t s);
