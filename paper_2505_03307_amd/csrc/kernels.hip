@@ -2016,6 +2016,10 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
   __shared__ uint64_t scan_sh[kWaves];
   __shared__ uint32_t nimg_sh;
   __shared__ __align__(16) uint8_t vary_sh[kWaves * sizeof(K)];
+  // the pass's one-qubit operators, read for every term and image, in LDS (more than kE1Lds of
+  // them are read from global memory): ten rotations of one string 25 -> 14 us
+  constexpr uint32_t kE1Lds = 16, kE1Words = (uint32_t)(sizeof(Exp1Desc) / 8);
+  __shared__ uint64_t e1sh[kE1Lds * kE1Words];
   const uint32_t s = blockIdx.x;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const uint64_t slot0 = (uint64_t)s * kChunkCap;
@@ -2041,11 +2045,15 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
     const uint32_t n = (uint32_t)n64;
     // ---- A chain and fan-out of every term, their scan (as the round's count)
     if (pa.useA) stage_table(pa.tA, tk, tn);
+    const bool e1lds = pa.nE1 <= kE1Lds;
+    if (e1lds)
+      for (uint32_t i = threadIdx.x; i < pa.nE1 * kE1Words; i += kGroupBlock) e1sh[i] = ((const uint64_t*)pa.E1)[i];
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < n; i += kGroupBlock) {
       K key = kin[i];
       uint32_t neg = 0;
-      const uint64_t f = a_chain_and_fanout(key, neg, pa, tk, tn, err);
+      const uint64_t f = e1lds ? a_chain_and_fanout(key, neg, pa, tk, tn, err, (const Exp1Desc*)e1sh)
+                               : a_chain_and_fanout(key, neg, pa, tk, tn, err);
       akey[i] = key;
       negs[i] = (uint8_t)(neg & 1u);
       off[i] = (uint32_t)min<uint64_t>(f, kCap + 1);  // larger: flagged by the total below
@@ -2085,7 +2093,8 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
         K key = akey[j];
         W wv = win[j];
         uint32_t neg = negs[j];
-        expand_ops<K, WP>(key, wv, g - off[j], pa, pa.E1, pa.E2, err);
+        if (e1lds) expand_ops<K, WP>(key, wv, g - off[j], pa, (const Exp1Desc*)e1sh, pa.E2, err);
+        else expand_ops<K, WP>(key, wv, g - off[j], pa, pa.E1, pa.E2, err);
         if (pa.useB) key = apply_table(key, tk, tn, pa.tB.groups, neg);
         else for (uint32_t q = 0; q < pa.nB; ++q) key = apply_perm(key, pa.B[q], neg);
         kout[g] = key;
@@ -2107,7 +2116,8 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
       K key = akey[j];
       W wv = win[j];
       uint32_t neg = negs[j];
-      expand_ops<K, WP>(key, wv, g - off[j], pa, pa.E1, pa.E2, err);
+      if (e1lds) expand_ops<K, WP>(key, wv, g - off[j], pa, (const Exp1Desc*)e1sh, pa.E2, err);
+      else expand_ops<K, WP>(key, wv, g - off[j], pa, pa.E1, pa.E2, err);
       if (pa.useB) key = apply_table(key, tk, tn, pa.tB.groups, neg);
       else for (uint32_t q = 0; q < pa.nB; ++q) key = apply_perm(key, pa.B[q], neg);
       if (neg) wv = -wv;
@@ -2263,34 +2273,37 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
   }
 }
 
-// The counts of a group of small passes, the error word and the sequence word for the host (one
-// block, after k_small_passes).
-__global__ void __launch_bounds__(256) k_small_publish(const uint32_t* __restrict__ cnt, uint32_t n_words,
-                                                       uint64_t* result, uint64_t seq, const uint32_t* __restrict__ err) {
-  uint32_t* const out = (uint32_t*)result;
-  const uint32_t n64 = (n_words + 1) / 2;
-  for (uint32_t i = threadIdx.x; i < n_words; i += 256) out[i] = cnt[i];
-  if (threadIdx.x == 0) result[n64] = *err;
-  __threadfence_system();
-  __syncthreads();
-  if (threadIdx.x == 0) *(volatile uint64_t*)&result[n64 + 1] = seq;
-}
-
 // After k_small_passes: segment s's kept terms (its slot, cnt_last[s*3 + 2] of them) copied to
-// the pass output at the sum of the earlier segments' counts; seg_off receives the offsets.
+// the pass output at the sum of the earlier segments' counts; seg_off receives the offsets. One
+// more block hands every count of the group, the error word and the sequence word to the host.
 template <typename K, typename W>
 __global__ void __launch_bounds__(256) k_small_gather(const K* __restrict__ kslot, const W* __restrict__ wslot,
                                                       const uint32_t* __restrict__ cnt_last, uint32_t S,
                                                       K* __restrict__ keys_out, W* __restrict__ w_out,
-                                                      uint64_t* __restrict__ seg_off) {
+                                                      uint64_t* __restrict__ seg_off, const uint32_t* __restrict__ cnt,
+                                                      uint32_t n_words, uint64_t* result, uint64_t seq,
+                                                      const uint32_t* __restrict__ err) {
   __shared__ uint64_t base_sh;
   const uint32_t s = blockIdx.x;
-  if (threadIdx.x == 0) {
+  if (s == S) {
+    uint32_t* const out = (uint32_t*)result;
+    const uint32_t n64 = (n_words + 1) / 2;
+    for (uint32_t i = threadIdx.x; i < n_words; i += 256) out[i] = cnt[i];
+    if (threadIdx.x == 0) result[n64] = *err;
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) *(volatile uint64_t*)&result[n64 + 1] = seq;
+    return;
+  }
+  if (threadIdx.x < 64) {  // the first wave adds the earlier segments' counts
     uint64_t b = 0;
-    for (uint32_t q = 0; q < s; ++q) b += cnt_last[q * 3 + 2];
-    base_sh = b;
-    seg_off[s] = b;
-    if (s + 1 == S) seg_off[S] = b + cnt_last[s * 3 + 2];
+    for (uint32_t q = threadIdx.x; q < s; q += 64) b += cnt_last[q * 3 + 2];
+    for (int o = 32; o > 0; o >>= 1) b += __shfl_xor(b, o, 64);
+    if (threadIdx.x == 0) {
+      base_sh = b;
+      seg_off[s] = b;
+      if (s + 1 == S) seg_off[S] = b + cnt_last[s * 3 + 2];
+    }
   }
   __syncthreads();
   const uint64_t base = base_sh, src = (uint64_t)s * kChunkCap;
@@ -3403,91 +3416,111 @@ __global__ void k_init_many(K* keys, W* w, const uint32_t* __restrict__ nq, cons
 }
 
 // -------------------------------------------------------------------- grouping pass
-// The 4x4 transfer matrix R[out][in] of one gate (Pauli order I, X, Y, Z): the closed
-// form of (1/2) Tr(P_out U P_in U^dagger), i.e. diag(1, M) with M the SO(3) rotation of
-// the Bloch vector that U performs (Sec. II-C; Alg. 1 composes these per qubit).
-__device__ void gate_ptm(uint32_t code, double th, double R[4][4]) {
-  for (int a = 0; a < 4; ++a)
-    for (int b = 0; b < 4; ++b) R[a][b] = (a == b) ? 1.0 : 0.0;
-  // rotation about axis ax in {1,2,3} by angle t: the two other axes (u, v) in cyclic
-  // order turn as u -> cos t u + sin t v, v -> cos t v - sin t u
-  auto rot = [&](int ax, double t) {
-    double sn, cs;
-    sincos(t, &sn, &cs);
-    const int u = ax % 3 + 1, v = u % 3 + 1;
-    R[u][u] = cs; R[v][v] = cs; R[v][u] = sn; R[u][v] = -sn;
-  };
-  switch (code) {
-    case 0:  // H: X <-> Z, Y -> -Y
-      R[1][1] = 0; R[3][3] = 0; R[3][1] = 1; R[1][3] = 1; R[2][2] = -1; break;
-    case 1:  // S: X -> Y, Y -> -X
-      R[1][1] = 0; R[2][2] = 0; R[2][1] = 1; R[1][2] = -1; break;
-    case 2:  // S^dagger: X -> -Y, Y -> X
-      R[1][1] = 0; R[2][2] = 0; R[2][1] = -1; R[1][2] = 1; break;
-    case 3: rot(3, M_PI / 4); break;   // T
-    case 4: rot(3, -M_PI / 4); break;  // T^dagger
-    case 5:  // SX: Y -> Z, Z -> -Y
-      R[2][2] = 0; R[3][3] = 0; R[3][2] = 1; R[2][3] = -1; break;
-    case 6: R[2][2] = -1; R[3][3] = -1; break;  // X
-    case 7: R[1][1] = -1; R[3][3] = -1; break;  // Y
-    case 8: R[1][1] = -1; R[2][2] = -1; break;  // Z
-    case 9: rot(1, th); break;   // RX
-    case 10: rot(2, th); break;  // RY
-    case 11: rot(3, th); break;  // RZ
-    default: break;
+// The transfer matrix of a one-qubit gate is diag(1, M) with M the SO(3) rotation of the Bloch
+// vector that it performs (Sec. II-C; Alg. 1 composes these per qubit). M is held by rows X, Y, Z.
+// A later gate acts on the images of the earlier ones: m <- G m. Every gate but H turns two rows
+// about the third axis, u -> cos u - sin v, v -> sin u + cos v with (u, v) the other axes in
+// cyclic order (S, SX, X, .. with cosines and sines of 0 and +-1, exact); the sums are taken in
+// row order, as a full product takes them.
+struct Bloch {
+  double m[3][3];
+};
+__device__ __forceinline__ void turn(double (&a)[3], double (&b)[3], double caa, double cab, double cba, double cbb) {
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {  // rows a above b
+    const double x = a[j], y = b[j];
+    a[j] = fma(cab, y, caa * x);
+    b[j] = fma(cbb, y, cba * x);
   }
 }
+__device__ __forceinline__ void apply_gate(Bloch& r, uint32_t code, double th) {
+  double c = 1.0, s = 0.0;
+  uint32_t axis = 3;
+  switch (code) {
+    case 0:  // H: X <-> Z, Y -> -Y
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const double x = r.m[0][j];
+        r.m[0][j] = r.m[2][j];
+        r.m[2][j] = x;
+        r.m[1][j] = -r.m[1][j];
+      }
+      return;
+    case 1: c = 0.0; s = 1.0; break;                // S
+    case 2: c = 0.0; s = -1.0; break;               // S^dagger
+    case 3: sincos(M_PI / 4, &s, &c); break;        // T
+    case 4: sincos(-M_PI / 4, &s, &c); break;       // T^dagger
+    case 5: c = 0.0; s = 1.0; axis = 1; break;      // SX
+    case 6: c = -1.0; axis = 1; break;              // X
+    case 7: c = -1.0; axis = 2; break;              // Y
+    case 8: c = -1.0; break;                        // Z
+    case 9: sincos(th, &s, &c); axis = 1; break;    // RX
+    case 10: sincos(th, &s, &c); axis = 2; break;   // RY
+    case 11: sincos(th, &s, &c); break;             // RZ
+    default: return;
+  }
+  if (axis == 1) turn(r.m[1], r.m[2], c, -s, s, c);       // Y -> cos Y - sin Z
+  else if (axis == 2) turn(r.m[0], r.m[2], c, s, -s, c);  // Z -> cos Z - sin X
+  else turn(r.m[0], r.m[1], c, -s, s, c);                 // X -> cos X - sin Y
+}
 
-// One wave per chain (Alg. 1 composes the gates of one wire of a U_k, in gate order): lane l
-// multiplies the gates of its contiguous slice of the chain in order, then the 64 partial
-// products are combined by a tree in LDS, the later slice always on the left (matrix products
-// are associative; only the rounding order differs from a serial product). A chain of
-// #Repeats x 3 rotations (the |XYZ + chain> workload at 10^5 repeats) thus takes about
-// len / 64 serial steps instead of len.
+// One wave per chain (the gates of one wire of a U_k, in gate order): lane l multiplies the gates
+// of its contiguous slice of the chain, then the 64 partial products are combined by a tree in
+// LDS, the later slice always on the left (matrix products are associative; only the rounding
+// order differs from a serial product). Levels at which no two slices with gates meet copy.
+// The matrices go to mapped host memory, each followed by the chain's flag word, so that the
+// host waits for them alone and not for the stream. Few gates are read from mapped host memory
+// too, which saves a launch.
+// Bound by latency: a short chain is a few loads across the link and two or three products
+// (9.7 us with full 4 x 4 products, indices in scratch memory and a pull before it; see DESIGN).
 constexpr int kComposeWaves = 4;
 __global__ void __launch_bounds__(64 * kComposeWaves)
-k_compose_ptm(const uint8_t* __restrict__ gate, const double* __restrict__ theta, const uint32_t* __restrict__ idx,
-              const uint32_t* __restrict__ chain_off, uint32_t n_chains, double* __restrict__ out) {
-  __shared__ double part[kComposeWaves][64][16];
+k_compose_ptm(const uint8_t* __restrict__ gate, const double* __restrict__ theta, const uint32_t* __restrict__ chain_off,
+              uint32_t n_chains, double* __restrict__ out, uint64_t* __restrict__ flag, uint64_t seq) {
+  __shared__ Bloch part[kComposeWaves][64];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const uint32_t c = blockIdx.x * kComposeWaves + wid;
-  const bool valid = c < n_chains;  // a wave past the last chain still takes part in the barriers
-  const uint32_t a = valid ? chain_off[c] : 0u, len = valid ? chain_off[c + 1] - a : 0u;
+  if (c >= n_chains) return;  // (waves do not wait for each other)
+  const uint32_t a = chain_off[c], len = chain_off[c + 1] - a;
   const uint32_t k0 = a + (uint32_t)(((uint64_t)len * lane) / 64), k1 = a + (uint32_t)(((uint64_t)len * (lane + 1)) / 64);
-  double R[4][4], G[4][4], P[4][4];
-  for (int i = 0; i < 4; ++i)
-    for (int j = 0; j < 4; ++j) R[i][j] = (i == j) ? 1.0 : 0.0;
-  for (uint32_t k = k0; k < k1; ++k) {
-    const uint32_t gi = idx[k];
-    gate_ptm(gate[gi], theta[gi], G);
-    // a later gate acts on the images of the earlier ones: R <- G R
-    for (int i = 0; i < 4; ++i)
-      for (int j = 0; j < 4; ++j) {
-        double sum = 0.0;
-        for (int t = 0; t < 4; ++t) sum += G[i][t] * R[t][j];
-        P[i][j] = sum;
-      }
-    for (int i = 0; i < 4; ++i)
-      for (int j = 0; j < 4; ++j) R[i][j] = P[i][j];
-  }
-  for (int i = 0; i < 16; ++i) part[wid][lane][i] = R[i >> 2][i & 3];
+  Bloch r;
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) r.m[i][j] = (i == j) ? 1.0 : 0.0;
+  for (uint32_t k = k0; k < k1; ++k) apply_gate(r, gate[k], theta[k]);
+  uint64_t has = __builtin_amdgcn_ballot_w64(k1 > k0);  // lanes whose product is no identity
+  part[wid][lane] = r;
   for (int step = 1; step < 64; step <<= 1) {
-    __syncthreads();
-    if ((lane & (2 * step - 1)) == 0) {
-      const double* L = part[wid][lane + step];  // the later slice
-      const double* Rr = part[wid][lane];
-      double Q[16];
-      for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 4; ++j) {
-          double sum = 0.0;
-          for (int t = 0; t < 4; ++t) sum += L[i * 4 + t] * Rr[t * 4 + j];
-          Q[i * 4 + j] = sum;
-        }
-      for (int i = 0; i < 16; ++i) part[wid][lane][i] = Q[i];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if ((lane & (2 * step - 1)) == 0 && ((has >> (lane + step)) & 1u)) {
+      const Bloch l = part[wid][lane + step];  // the later slice
+      if ((has >> lane) & 1u) {
+        Bloch q;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+          for (int j = 0; j < 3; ++j)
+            q.m[i][j] = fma(l.m[i][2], r.m[2][j], fma(l.m[i][1], r.m[1][j], l.m[i][0] * r.m[0][j]));
+        r = q;
+      } else {
+        r = l;
+      }
+      part[wid][lane] = r;
     }
+    has |= has >> step;  // (only the lanes that hold a block's product are looked at)
   }
-  __syncthreads();
-  if (valid && lane < 16) out[(uint64_t)c * 16 + lane] = part[wid][0][lane];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  if (lane < 16) {
+    const int i = lane >> 2, j = lane & 3;
+    out[(uint64_t)c * 16 + lane] = (i == 0 || j == 0) ? (i == j ? 1.0 : 0.0) : part[wid][0].m[i - 1][j - 1];
+  }
+  __threadfence_system();
+  if (lane == 0) *(volatile uint64_t*)&flag[c] = seq;
 }
 
 inline uint32_t grid_for(uint64_t n, uint32_t block) { return (uint32_t)((n + block - 1) / block); }
@@ -3689,19 +3722,20 @@ hipError_t launch_small_passes(int KC, int WP, int fp64_acc, const void* keys_in
     k_small_passes<K, 64><<<S, kGroupBlock, 0, s>>>((const K*)keys_in, (const double*)w_in, seg_in, S, pas, n_grp, \
                                                     (K*)kslot[0], (double*)wslot[0], (K*)kslot[1], (double*)wslot[1], \
                                                     (double*)wimg, cnt, fp64_acc, err);                           \
-    k_small_gather<K, double><<<S, 256, 0, s>>>((const K*)kslot[last], (const double*)wslot[last], cnt_last, S,    \
-                                                (K*)keys_out, (double*)w_out, seg_off_out);                       \
+    k_small_gather<K, double><<<S + 1, 256, 0, s>>>((const K*)kslot[last], (const double*)wslot[last], cnt_last, S,    \
+                                                (K*)keys_out, (double*)w_out, seg_off_out, cnt, n_grp * S * 3,    \
+                                                result, seq, err);                                                \
   } else {                                                                                                        \
     k_small_passes<K, 32><<<S, kGroupBlock, 0, s>>>((const K*)keys_in, (const float*)w_in, seg_in, S, pas, n_grp,  \
                                                     (K*)kslot[0], (float*)wslot[0], (K*)kslot[1], (float*)wslot[1], \
                                                     (float*)wimg, cnt, fp64_acc, err);                            \
-    k_small_gather<K, float><<<S, 256, 0, s>>>((const K*)kslot[last], (const float*)wslot[last], cnt_last, S,      \
-                                               (K*)keys_out, (float*)w_out, seg_off_out);                         \
+    k_small_gather<K, float><<<S + 1, 256, 0, s>>>((const K*)kslot[last], (const float*)wslot[last], cnt_last, S,      \
+                                               (K*)keys_out, (float*)w_out, seg_off_out, cnt, n_grp * S * 3,      \
+                                               result, seq, err);                                                 \
   }
   if (KC == 0) { QIMAX_SMALL_PASSES(uint32_t) } else if (KC == 1) { QIMAX_SMALL_PASSES(uint64_t) }
   else { QIMAX_SMALL_PASSES(unsigned __int128) }
 #undef QIMAX_SMALL_PASSES
-  k_small_publish<<<1, 256, 0, s>>>(cnt, n_grp * S * 3, result, seq, err);
   prof_end(prof, s, ev, kKSmallPasses, 0.0);  // bytes: added by the caller once the counts are back
   return hipGetLastError();
 }
@@ -4281,13 +4315,12 @@ hipError_t launch_copy_u64(const uint64_t* in, uint64_t* out, uint64_t n, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_compose_ptm(const uint8_t* gate, const double* theta, const uint32_t* idx,
-                              const uint32_t* chain_off, uint32_t n_chains, double* ptm_out, hipStream_t s,
-                              Prof* prof) {
+hipError_t launch_compose_ptm(const uint8_t* gate, const double* theta, const uint32_t* chain_off, uint32_t n_chains,
+                              double* ptm_out, uint64_t* flag, uint64_t seq, hipStream_t s, Prof* prof) {
   if (n_chains == 0) return hipSuccess;
   hipEvent_t ev = prof_begin(prof, s, kKCompose);
-  k_compose_ptm<<<grid_for(n_chains, kComposeWaves), 64 * kComposeWaves, 0, s>>>(gate, theta, idx, chain_off,
-                                                                                    n_chains, ptm_out);
+  k_compose_ptm<<<grid_for(n_chains, kComposeWaves), 64 * kComposeWaves, 0, s>>>(gate, theta, chain_off, n_chains,
+                                                                                 ptm_out, flag, seq);
   prof_end(prof, s, ev, kKCompose, 0.0);
   return hipGetLastError();
 }

@@ -1924,7 +1924,7 @@ qimax_status prebuild_tables(qimax_ctx* c, std::vector<Pass>& passes) {
 
 // How many passes from i0 on (at most kMaxGroupPasses) one launch of k_small_passes can run:
 // every segment's terms, multiplied by each pass's fan-out bound in turn, stay within what a
-// block holds (so do its images). 0 or 1: run the passes as rounds.
+// block holds (so do its images). 0: run the pass as a round.
 constexpr size_t kMaxGroupPasses = 64;
 bool small_group_ok(const qimax_ctx* c) {
   return c->small_groups && c->small_rounds && !c->classic_sort && !c->host_tiling && c->n <= kSmallMaxSegs;
@@ -2103,12 +2103,12 @@ qimax_status apply_ops_once(qimax_ctx* c, std::vector<HostOp>& ops) {
                          passes[i].fanout_bound > (double)kBoundPathMaxFanout;
     if (attempt) kg = 1;
     std::vector<std::vector<uint64_t>> gi, gg, go;
-    if (kg >= 2 || attempt) {  // consecutive small passes: one launch
+    if (kg) {  // small passes, one or consecutive: one launch
       qimax_status s = run_small_group(c, passes, i, kg, k_in, w_in, s_in, so_in, slot, gi, gg, go,
                                        attempt ? &overflow : nullptr);
       if (s != QIMAX_OK) return s;  // committed state untouched
     }
-    if ((kg >= 2 || attempt) && !overflow) {
+    if (kg && !overflow) {
       if (c->gen_updates.size() != c->n) c->gen_updates.assign(c->n, 0);
       for (size_t p = 0; p < kg; ++p) {
         for (uint32_t j = 0; j < c->n; ++j)
@@ -2282,6 +2282,29 @@ int signed_perm_code4(const double* R) {
 }
 constexpr int kIdentityCode4 = 0 | (1 << 3) | (2 << 6) | (3 << 9);
 
+// The one-qubit Clifford gates (codes H, S, S^dagger, T, T^dagger, SX, X, Y, Z) in that form, from
+// the images of X, Y, Z as digit and sign; -1: no signed permutation.
+constexpr int clifford_code(int x, int nx, int y, int ny, int z, int nz) {
+  return ((x | (nx << 2)) << 3) | ((y | (ny << 2)) << 6) | ((z | (nz << 2)) << 9);
+}
+constexpr int kCliffordCode[9] = {
+    clifford_code(3, 0, 2, 1, 1, 0), clifford_code(2, 0, 1, 1, 3, 0), clifford_code(2, 1, 1, 0, 3, 0), -1, -1,
+    clifford_code(1, 0, 3, 0, 2, 1), clifford_code(1, 0, 2, 1, 3, 1), clifford_code(1, 1, 2, 0, 3, 1),
+    clifford_code(1, 1, 2, 1, 3, 0)};
+// gate after chain: each column's row goes on through the gate's column of that row
+inline int compose_code4(int gate, int chain) {
+  int out = 0;
+  for (int col = 0; col < 4; ++col) {
+    const int e = (chain >> (3 * col)) & 7;
+    out |= (((gate >> (3 * (e & 3))) & 7) ^ (e & 4)) << (3 * col);
+  }
+  return out;
+}
+
+// Bytes of gates that the composing kernel reads across the link itself: one launch where a pull
+// and it took two (three rotations on ten wires: 12 us against 17).
+constexpr size_t kComposeDirect = 16384;
+
 // The paper's grouping (Sec. III-A, Alg. 2): maximal runs of one-qubit gates (U_k) and
 // of two-qubit gates (V_k) in instruction order; inside U_k the gates of each wire form
 // U_{k,j}, composed into one transfer matrix on the device (Alg. 1).
@@ -2305,9 +2328,13 @@ qimax_status group_circuit(qimax_ctx* c, uint32_t n, const uint8_t* gate, const 
     i = j;
   }
   size_t nu = 0, nv = 0;
-  // one-qubit chains: per U run, per wire in increasing order
-  std::vector<uint32_t> idx, chain_off{0};
-  struct ChainRef { int run; int wire; };
+  // one-qubit chains: per U run, per wire in increasing order. A chain of Clifford gates is a
+  // signed permutation, known here by its code; the others are composed on the device, and where
+  // there are none nothing is launched.
+  struct ChainRef { int run; int wire; int code; uint32_t at; };  // code < 0: the device's chain `at`
+  std::vector<uint8_t> c_gate;
+  std::vector<double> c_theta;
+  std::vector<uint32_t> chain_off{0};
   std::vector<ChainRef> chains;
   std::vector<std::vector<uint32_t>> per_wire(n);
   for (size_t r = 0; r < runs.size(); ++r) {
@@ -2317,39 +2344,78 @@ qimax_status group_circuit(qimax_ctx* c, uint32_t n, const uint8_t* gate, const 
     for (size_t i = runs[r].a; i < runs[r].b; ++i) per_wire[q0[i]].push_back((uint32_t)i);
     for (uint32_t j = 0; j < n; ++j) {
       if (per_wire[j].empty()) continue;
-      for (uint32_t gi : per_wire[j]) idx.push_back(gi);
-      chain_off.push_back((uint32_t)idx.size());
-      chains.push_back({(int)r, (int)j});
+      int code = kIdentityCode4;
+      for (uint32_t gi : per_wire[j]) {
+        const int g = gate[gi] < 9 ? kCliffordCode[gate[gi]] : -1;
+        code = g < 0 ? -1 : compose_code4(g, code);
+        if (code < 0) break;
+      }
+      if (code < 0) {
+        for (uint32_t gi : per_wire[j]) {
+          c_gate.push_back(gate[gi]);
+          c_theta.push_back(theta ? theta[gi] : 0.0);
+        }
+        chain_off.push_back((uint32_t)c_gate.size());
+      }
+      chains.push_back({(int)r, (int)j, code, (uint32_t)chain_off.size() - 2});
     }
   }
+  const size_t n_dev = chain_off.size() - 1;
   const double* ptm = nullptr;
-  if (!chains.empty()) {
-    // inputs through mapped staging, pulled to the device by a kernel; the composed PTMs
-    // written by the kernel straight into mapped staging. (No launch still reads or writes
-    // the staging areas here: a round's first launch reads them, and every round's results
-    // have been waited for; a call's grouping result has been read.)
-    const size_t oG = 0, oT = align256(m), oI = oT + align256(m * 8), oO = oI + align256(idx.size() * 4);
-    const size_t up = oO + align256(chain_off.size() * 4), down = chains.size() * 16 * 8;
-    QCHK(ensure(c, c->gr_in, up));
+  if (n_dev) {
+    // inputs through mapped staging, read from there where they are few, else pulled to the
+    // device by a kernel; the composed PTMs written by the kernel straight into mapped memory,
+    // each with a flag that the host polls. (No launch still reads or writes the staging areas
+    // here: a round's first launch reads them, and every round's results have been waited for;
+    // a recording's launches have memory of their own.)
+    const size_t k = c_gate.size();
+    const size_t oT = 0, oO = align256(k * 8), oG = oO + align256(chain_off.size() * 4);
+    const size_t up = oG + align256(k), oF = align256(n_dev * 128), down = oF + n_dev * 8;
     QCHK(ensure_stage(c, 0, up));
     QCHK(ensure_stage(c, 1, down));
     uint8_t* hs = (uint8_t*)c->stage[0];
-    std::memcpy(hs + oG, gate, m);
-    if (theta) std::memcpy(hs + oT, theta, m * 8);
-    else std::memset(hs + oT, 0, m * 8);
-    std::memcpy(hs + oI, idx.data(), idx.size() * 4);
+    std::memcpy(hs + oT, c_theta.data(), k * 8);
     std::memcpy(hs + oO, chain_off.data(), chain_off.size() * 4);
-    const uint8_t* dg = (const uint8_t*)c->gr_in.p;
-    const void* gsrc = nullptr;
-    QCHK(rec_src(c, c->stage[0], c->stage_dev[0], up, &gsrc));
-    HIPCHK(c, launch_pull(gsrc, c->gr_in.p, up, c->stream), "group upload");
-    HIPCHK(c, launch_compose_ptm(dg + oG, (const double*)(dg + oT), (const uint32_t*)(dg + oI),
-                                 (const uint32_t*)(dg + oO), (uint32_t)chains.size(), (double*)c->stage_dev[1],
-                                 c->stream, &c->prof), "compose_ptm");
+    std::memcpy(hs + oG, c_gate.data(), k);
+    void* res = c->stage[1];
+    void* res_dev = c->stage_dev[1];
+    if (c->rec) {
+      HIPCHK(c, hipHostMalloc(&res, down, hipHostMallocMapped | hipHostMallocCoherent), "hipHostMalloc (recording)");
+      c->rec->snaps.push_back(res);
+      HIPCHK(c, hipHostGetDevicePointer(&res_dev, res, 0), "hipHostGetDevicePointer");
+    }
+    volatile uint64_t* flag = (volatile uint64_t*)((uint8_t*)res + oF);
+    const uint64_t seq = ++c->zseq;
+    for (size_t i = 0; i < n_dev; ++i) flag[i] = 0;
+    const void* src = nullptr;
+    QCHK(rec_src(c, c->stage[0], c->stage_dev[0], up, &src));
+    const uint8_t* d = (const uint8_t*)src;
+    if (up > kComposeDirect) {
+      QCHK(ensure(c, c->gr_in, up));
+      HIPCHK(c, launch_pull(src, c->gr_in.p, up, c->stream), "group upload");
+      d = (const uint8_t*)c->gr_in.p;
+    }
+    HIPCHK(c, launch_compose_ptm(d + oG, (const double*)(d + oT), (const uint32_t*)(d + oO), (uint32_t)n_dev,
+                                 (double*)res_dev, (uint64_t*)((uint8_t*)res_dev + oF), seq, c->stream, &c->prof),
+           "compose_ptm");
     QCHK(rec_cut(c));
-    HIPCHK(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
+    auto t_query = std::chrono::steady_clock::now();
+    for (size_t i = 0; i < n_dev; ++i)
+      for (uint32_t it = 1; flag[i] != seq; ++it) {
+        if ((it & 63u) == 0 && std::chrono::steady_clock::now() - t_query > std::chrono::milliseconds(1)) {
+          t_query = std::chrono::steady_clock::now();
+          const hipError_t q = hipStreamQuery(c->stream);
+          if (q == hipSuccess) {
+            if (flag[i] != seq) return fail(c, QIMAX_EDEVICE, "composed matrices missing after the stream finished");
+            break;
+          }
+          if (q != hipErrorNotReady) return hip_fail(c, q, "hipStreamQuery");
+        }
+        __builtin_ia32_pause();
+      }
+    std::atomic_thread_fence(std::memory_order_acquire);
     QCHK(rec_resume(c));
-    ptm = (const double*)c->stage[1];
+    ptm = (const double*)res;
   }
   // assemble the operator list in run order
   static const Ptm kCx = [] {
@@ -2430,11 +2496,11 @@ qimax_status group_circuit(qimax_ctx* c, uint32_t n, const uint8_t* gate, const 
       }
     } else {
       while (ci < chains.size() && chains[ci].run == (int)r) {
-        const double* R = ptm + ci * 16;
         HostOp op;
         op.arity = 1; op.dim = 4; op.q0 = op.q1 = chains[ci].wire; op.group = (int)r;
         op.mask = 1ull << op.q0;
-        const int code = signed_perm_code4(R);
+        const double* R = chains[ci].code < 0 ? ptm + (size_t)chains[ci].at * 16 : nullptr;
+        const int code = R ? signed_perm_code4(R) : chains[ci].code;
         if (code < 0) {  // not a signed permutation (a rotation chain)
           op.R.assign(R, R + 16);
           op.perm = op.conj = false;
@@ -2443,7 +2509,12 @@ qimax_status group_circuit(qimax_ctx* c, uint32_t n, const uint8_t* gate, const 
           auto it = perm_cache.find(code);
           if (it == perm_cache.end()) {
             Cls k;
-            k.R.assign(R, R + 16);
+            double P[16] = {};
+            for (int col = 0; col < 4; ++col) {
+              const int e = (code >> (3 * col)) & 7;
+              P[(e & 3) * 4 + col] = (e & 4) ? -1.0 : 1.0;
+            }
+            k.R.assign(P, P + 16);
             k.conj = is_conjugation(k.R, 4);
             it = perm_cache.emplace(code, std::move(k)).first;
           }

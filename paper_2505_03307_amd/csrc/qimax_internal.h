@@ -481,11 +481,11 @@ hipError_t launch_publish(uint32_t S, const MergeFin& fin, uint64_t* seg_off_out
 // Plain copy of n words (calibration of hardware traffic counters).
 hipError_t launch_copy_u64(const uint64_t* in, uint64_t* out, uint64_t n, hipStream_t s);
 
-// Grouping pass: compose chains of one-qubit gates into 4x4 PTMs (R[out][in], FP64).
-// chain c covers gate indices idx[chain_off[c] .. chain_off[c+1]-1] in application order.
-hipError_t launch_compose_ptm(const uint8_t* gate, const double* theta, const uint32_t* idx,
-                              const uint32_t* chain_off, uint32_t n_chains, double* ptm_out,
-                              hipStream_t s, Prof* prof = nullptr);
+// Grouping pass: compose chains of one-qubit gates into 4x4 PTMs (R[out][in], FP64). Chain c
+// holds the gates chain_off[c] .. chain_off[c+1]-1 in application order; its matrix goes to
+// ptm_out[16 c ..] (mapped host memory), and then seq to flag[c].
+hipError_t launch_compose_ptm(const uint8_t* gate, const double* theta, const uint32_t* chain_off, uint32_t n_chains,
+                              double* ptm_out, uint64_t* flag, uint64_t seq, hipStream_t s, Prof* prof);
 
 // ------------------------------------------------------------- readout (readout.hip)
 // Per-generator comparison of side a with side b (see k_compare); tiles of at most
