@@ -4073,56 +4073,44 @@ hipError_t launch_build_tables(int KC, const TableLaunch& t, hipStream_t s, Prof
   return hipGetLastError();
 }
 
-// Terms as the C-ABI hands them out, written to mapped host memory: each key as one or two
-// little-endian 64-bit words, or as its x and z words, each weight as FP64. Bound by the link.
-template <typename K, typename W, int kForm>
-__global__ void __launch_bounds__(256) k_export(const K* __restrict__ keys, const W* __restrict__ w, uint64_t T,
-                                                uint32_t n, uint64_t* __restrict__ words, uint64_t* __restrict__ zs,
-                                                double* __restrict__ wd) {
+// Terms written to mapped host memory, as they are or in the x/z form with FP64 weights. Bound by
+// the link.
+template <typename K, typename W, bool kXz>
+__global__ void __launch_bounds__(256) k_read(const K* __restrict__ keys, const W* __restrict__ w, uint64_t T, uint32_t n,
+                                              void* __restrict__ out, void* __restrict__ w_out) {
   for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < T; i += (uint64_t)gridDim.x * 256) {
     const K k = keys[i];
-    if constexpr (kForm == kReadXz) {
+    if constexpr (kXz) {
       // qubit q's digit is at key bits 2(n-1-q): the planes, bits reversed
       uint64_t hi = pack_bits((uint64_t)k >> 1), lo = pack_bits((uint64_t)k);
       if constexpr (sizeof(K) > 8) {
         hi |= (uint64_t)pack_bits((uint64_t)(k >> 64) >> 1) << 32;
         lo |= (uint64_t)pack_bits((uint64_t)(k >> 64)) << 32;
       }
-      words[i] = __brevll(hi ^ lo) >> (64 - n);
-      zs[i] = __brevll(hi) >> (64 - n);
-    } else if constexpr (kForm == kReadWords2) {
-      ulonglong2 v;
-      v.x = (uint64_t)k;
-      if constexpr (sizeof(K) > 8) v.y = (uint64_t)(k >> 64);
-      else v.y = 0;
-      ((ulonglong2*)words)[i] = v;
+      ((uint64_t*)out)[i] = __brevll(hi ^ lo) >> (64 - n);
+      ((uint64_t*)out)[T + i] = __brevll(hi) >> (64 - n);
+      ((double*)w_out)[i] = (double)w[i];
     } else {
-      words[i] = (uint64_t)k;
+      ((K*)out)[i] = k;
+      ((W*)w_out)[i] = w[i];
     }
-    wd[i] = (double)w[i];
   }
 }
 
-hipError_t launch_export(int KC, int WP, const void* keys, const void* w, uint64_t T, ReadForm form, uint32_t n,
-                         uint64_t* words, uint64_t* next, hipStream_t s) {
+hipError_t launch_read(int KC, int WP, bool xz, const void* keys, const void* w, uint64_t T, uint32_t n, void* out,
+                       void* w_out, hipStream_t s) {
   if (T == 0) return hipSuccess;
-  if (n < 1 || n > 64 || (uintptr_t)words % 16) return hipErrorInvalidValue;
+  if (n < 1 || n > 64 || ((uintptr_t)out | (uintptr_t)w_out) % 16) return hipErrorInvalidValue;
   const uint32_t g = (uint32_t)std::min<uint64_t>((T + 255) / 256, 1024);
-  double* const wd = (double*)(form == kReadWords1 ? next : next + (next - words));
-#define QIMAX_EXPORT(W, F) \
-  k_export<K, W, F><<<g, 256, 0, s>>>((const K*)keys, (const W*)w, T, n, words, next, wd)
+#define QIMAX_READ(W, X) k_read<K, W, X><<<g, 256, 0, s>>>((const K*)keys, (const W*)w, T, n, out, w_out)
   QIMAX_DISPATCH_K(KC, {
     if (WP == 64) {
-      if (form == kReadXz) QIMAX_EXPORT(double, kReadXz);
-      else if (form == kReadWords2) QIMAX_EXPORT(double, kReadWords2);
-      else QIMAX_EXPORT(double, kReadWords1);
+      if (xz) QIMAX_READ(double, true); else QIMAX_READ(double, false);
     } else {
-      if (form == kReadXz) QIMAX_EXPORT(float, kReadXz);
-      else if (form == kReadWords2) QIMAX_EXPORT(float, kReadWords2);
-      else QIMAX_EXPORT(float, kReadWords1);
+      if (xz) QIMAX_READ(float, true); else QIMAX_READ(float, false);
     }
   });
-#undef QIMAX_EXPORT
+#undef QIMAX_READ
   return hipGetLastError();
 }
 

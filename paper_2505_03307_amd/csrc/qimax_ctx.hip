@@ -457,7 +457,7 @@ struct qimax_ctx {
   void* read_stage = nullptr;
   void* read_dev = nullptr;
   size_t read_bytes = 0;
-  hipEvent_t read_ev[12] = {};
+  hipEvent_t read_ev[16] = {};
   // step recording (qimax_graph_record): the work of a step is captured between the host's
   // synchronisations and replayed later as one graph
   struct qimax_graph* rec = nullptr;
@@ -2586,15 +2586,17 @@ qimax_status fetch(qimax_ctx* c, HostGens& g) {
 }
 
 // ------------------------------------------------------------------------ readout
-// Terms leave the device in the C-ABI's form through pinned, mapped staging: a kernel converts a
-// chunk of terms straight into a slot of it, and host threads copy the slots that are complete
-// into the caller's memory while the next chunks cross the link. (The caller's memory is
-// pageable and mostly untouched: one thread writes it at 10-16 GB/s, page faults included, while
-// the link brings 57 GB/s. Measured for 44.5 M terms, 711 MB: 68 ms with copies into pageable
-// memory, 16 ms here; for the n = 16 ansatz's 1165 MB 111 and 26 ms.) Short readouts take one
-// slot and no thread (21 terms: 38 and 15 us).
-constexpr uint64_t kReadChunk = 1ull << 17;  // terms of a slot: 2 or 3 MB
-constexpr int kReadSlots = 12;
+// Terms leave the device through pinned, mapped staging: a kernel writes a chunk's keys and
+// weights to a slot as they are (or its x and z words), and host threads turn the slots that are
+// complete into the C-ABI's form in the caller's memory while the next chunks cross the link. (The
+// caller's memory is pageable and mostly untouched: one thread writes it at 10-16 GB/s, page
+// faults included. A kernel brings 50 GB/s across the link whatever the chunk; the copy engine
+// brings 57 in one piece, but 34 in slots of 2 MB, for what a copy costs to start. Keys and weights
+// of four bytes cross as such.) Measured: 44.5 M terms, 711 MB, 68 ms with copies into pageable
+// memory, 16 ms here; the n = 16 ansatz in FP32, 583 MB for 1165, 111 and 19 ms. Readouts below
+// 4 MB take no further thread (177216 terms 0.37 -> 0.19 ms).
+constexpr size_t kReadSlotBytes = 2u << 20;
+constexpr int kReadSlots = 16;
 constexpr uint32_t kReadThreads = 8;
 
 // Host threads for `items` pieces of work.
@@ -2668,43 +2670,61 @@ qimax_status read_terms(qimax_ctx* c, uint64_t a, uint64_t T, ReadForm form, uin
     *done = true;
     return QIMAX_OK;
   }
-  const size_t per = form == kReadWords1 ? 16 : 24;
-  // at least eight chunks where they are of 16 Ki terms or more: several threads, and the link
-  // and the copies overlap
-  const uint64_t m = T <= (1ull << 16) ? T : std::min(kReadChunk, std::max<uint64_t>(1ull << 14, (T / 8 + 255) / 256 * 256));
+  const size_t per_k = form == kReadXz ? 16 : c->kb, per_w = form == kReadXz ? 8 : c->wb, per = per_k + per_w;
+  const size_t out_per = form == kReadWords1 ? 16 : 24;
+  // chunks of a slot, and four at least of larger readouts: the link and the copies overlap
+  const uint64_t m = std::min<uint64_t>(kReadSlotBytes / per / 64 * 64,
+                                        std::max<uint64_t>(1ull << 14, (T / 4 + 63) / 64 * 64));
   const uint64_t n_chunks = (T + m - 1) / m;
   const int slots = (int)std::min<uint64_t>(kReadSlots, n_chunks);
-  const size_t slot_bytes = align256((size_t)m * per);
+  const size_t slot_bytes = align256((size_t)std::min(m, T) * per + 256);
   if (!ensure_read_stage(c, slots, slot_bytes)) return QIMAX_OK;
   const uint8_t* kb = (const uint8_t*)c->keys.p + a * c->kb;
   const uint8_t* wb = (const uint8_t*)c->w.p + a * c->wb;
+  auto w_at = [&](uint64_t k) { return ((size_t)k * per_k + 15) / 16 * 16; };  // the weights' place in a slot
   auto launch = [&](uint64_t i) -> hipError_t {
     const uint64_t o = i * m, k = std::min(m, T - o);
-    uint64_t* d = (uint64_t*)((uint8_t*)c->read_dev + (i % slots) * slot_bytes);
-    return launch_export(c->KC, c->WP, kb + o * c->kb, wb + o * c->wb, k, form, n, d, d + m, c->stream);
+    const size_t at = (size_t)(i % slots) * slot_bytes;
+    uint8_t* d = (uint8_t*)c->read_dev + at;
+    return launch_read(c->KC, c->WP, form == kReadXz, kb + o * c->kb, wb + o * c->wb, k, n, d, d + w_at(k), c->stream);
   };
-  auto copy = [&](uint64_t i) {  // slot: words (1 or 2 per term, or x then z), then weights
+  auto copy = [&](uint64_t i) {
     const uint64_t o = i * m, k = std::min(m, T - o);
-    const uint64_t* h = (const uint64_t*)((const uint8_t*)c->read_stage + (i % slots) * slot_bytes);
+    const uint8_t* h = (const uint8_t*)c->read_stage + (size_t)(i % slots) * slot_bytes;
+    const uint64_t nw = form == kReadWords2 ? 2 : 1;
     if (form == kReadXz) {
       std::memcpy(words + o, h, k * 8);
-      std::memcpy(z + o, h + m, k * 8);
-      std::memcpy(w + o, h + 2 * m, k * 8);
+      std::memcpy(z + o, h + k * 8, k * 8);
+    } else if (c->kb == 8 * nw) {
+      std::memcpy(words + o * nw, h, k * 8 * nw);
+    } else if (c->kb == 4) {  // (one word, or with n above 32 never)
+      const uint32_t* q = (const uint32_t*)h;
+      uint64_t* d = words + o;
+      for (uint64_t t = 0; t < k; ++t) d[t] = q[t];
+    } else {  // longer keys of few qubits (a batch of a wide class): the low word
+      const uint64_t* q = (const uint64_t*)h;
+      uint64_t* d = words + o;
+      for (uint64_t t = 0; t < k; ++t) d[t] = q[2 * t];
+    }
+    h += w_at(k);
+    if (per_w == 8) {
+      std::memcpy(w + o, h, k * 8);
     } else {
-      const uint64_t nw = form == kReadWords1 ? 1 : 2;
-      std::memcpy(words + o * nw, h, k * nw * 8);
-      std::memcpy(w + o, h + nw * m, k * 8);
+      const float* q = (const float*)h;
+      double* d = w + o;
+      for (uint64_t t = 0; t < k; ++t) d[t] = q[t];
     }
   };
-  if (n_chunks == 1) {
-    HIPCHK(c, launch(0), "export");
-    HIPCHK(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
-    copy(0);
-    *done = true;
-    return QIMAX_OK;
-  }
   std::atomic<uint64_t> ready{0}, next{0}, copied[kReadSlots] = {};
   std::atomic<bool> stop{false};
+  hipError_t e = hipSuccess;
+  uint64_t launched = 0;
+  auto launch_next = [&] {
+    e = launch(launched);
+    if (e == hipSuccess) e = hipEventRecord(c->read_ev[launched % slots], c->stream);
+    ++launched;
+  };
+  while (launched < (uint64_t)slots && e == hipSuccess) launch_next();  // before any thread is made
   auto worker = [&] {
     for (uint64_t i; (i = next.fetch_add(1)) < n_chunks;) {
       while (ready.load(std::memory_order_acquire) <= i) {
@@ -2716,25 +2736,21 @@ qimax_status read_terms(qimax_ctx* c, uint64_t a, uint64_t T, ReadForm form, uin
     }
   };
   std::vector<std::thread> pool;
-  try {
-    for (uint32_t t = 0; t < copy_threads(n_chunks); ++t) pool.emplace_back(worker);
+  try {  // a thread for every 4 MB of results
+    const uint32_t nt = copy_threads(T * out_per >> 22);
+    for (uint32_t t = 0; t < nt && e == hipSuccess; ++t) pool.emplace_back(worker);
   } catch (...) {  // fewer threads, or none: the caller's copies too
   }
-  hipError_t e = hipSuccess;
-  uint64_t launched = 0;
   for (uint64_t i = 0; i < n_chunks && e == hipSuccess; ++i) {
     // every chunk whose slot is free crosses the link; the next one in order is waited for
     while (launched < n_chunks && e == hipSuccess) {
-      const uint64_t before = launched < (uint64_t)slots ? 0 : launched - slots + 1;  // the slot's last chunk, copied
+      const uint64_t before = launched - slots + 1;  // the slot's last chunk, copied
       if (copied[launched % slots].load(std::memory_order_acquire) != before) {
         if (launched > i) break;
-        if (pool.empty()) break;
         __builtin_ia32_pause();
         continue;
       }
-      e = launch(launched);
-      if (e == hipSuccess) e = hipEventRecord(c->read_ev[launched % slots], c->stream);
-      ++launched;
+      launch_next();
     }
     if (e == hipSuccess) e = hipEventSynchronize(c->read_ev[i % slots]);
     if (e != hipSuccess) break;
@@ -2748,7 +2764,7 @@ qimax_status read_terms(qimax_ctx* c, uint64_t a, uint64_t T, ReadForm form, uin
   for (auto& t : pool) t.join();
   if (e != hipSuccess) {
     (void)hipStreamSynchronize(c->stream);  // nothing writes the slots any more
-    return hip_fail(c, e, "export");
+    return hip_fail(c, e, "readout");
   }
   *done = true;
   return QIMAX_OK;

@@ -234,10 +234,10 @@ hipError_t launch_init(int KC, int WP, void* keys, void* w, uint64_t* seg_off, u
 // How terms are handed out: keys as one or two uint64 words each, or (kReadXz) the x and z bit
 // words of an n-qubit key (bit q: qubit q), an array each.
 enum ReadForm { kReadWords1, kReadWords2, kReadXz };
-// T terms converted for the host: `words` receives the keys' words, or the x words followed at
-// `next` by the z words; the FP64 weights follow at next (one word) or next + (next - words).
-hipError_t launch_export(int KC, int WP, const void* keys, const void* w, uint64_t T, ReadForm form, uint32_t n,
-                         uint64_t* words, uint64_t* next, hipStream_t s);
+// T terms for the host (mapped memory): keys and weights as they are, or (xz) the x words and
+// the z words in `out`, one array after the other, and the weights as FP64.
+hipError_t launch_read(int KC, int WP, bool xz, const void* keys, const void* w, uint64_t T, uint32_t n, void* out,
+                       void* w_out, hipStream_t s);
 
 // Fan-out count fused with its scan (single sweep with decoupled look-back over the tiles of
 // tl, claimed through *ctr): off[i] = first image of input term i, off[T] = image count;
