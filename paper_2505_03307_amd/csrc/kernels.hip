@@ -1986,7 +1986,9 @@ __global__ void __launch_bounds__(256) k_chunk_compact(const K* __restrict__ key
 // the sums of the round-by-round small path, so the results agree bit for bit; only the
 // launches and the host's waits between the passes are gone. A pass marked unsorted (its
 // images all differ) writes its images to the other slot as they come. cnt[(p*S + s)*3 +
-// {0,1,2}] receives segment s's input terms, images and kept terms in pass p.
+// {0,1,2}] receives segment s's input terms, images and kept terms in pass p. With seg_first /
+// seg_len set, segment s runs the seg_len[s] passes from pas[seg_first[s]] on (circuits of a batch;
+// at most n_grp) and counts nothing in the others; with none, its terms go.
 // 16-byte keys: half the terms, so that keys, images and counters fit a block's LDS (108 KB).
 constexpr int kGroupBlock = 512;
 template <typename K>
@@ -1995,7 +1997,8 @@ template <typename K, int WP>
 __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
     const K* __restrict__ keys_in, const typename WTraits<WP>::W* __restrict__ w_in,
     const uint64_t* __restrict__ seg_in, uint32_t S, const PassArgs* __restrict__ pas, uint32_t n_grp,
-    K* __restrict__ kslot0, typename WTraits<WP>::W* __restrict__ wslot0, K* __restrict__ kslot1,
+    const uint32_t* __restrict__ seg_first, const uint32_t* __restrict__ seg_len, K* __restrict__ kslot0,
+    typename WTraits<WP>::W* __restrict__ wslot0, K* __restrict__ kslot1,
     typename WTraits<WP>::W* __restrict__ wslot1, typename WTraits<WP>::W* __restrict__ wimg,
     uint32_t* __restrict__ cnt, int fp64_acc, uint32_t* err) {
   using W = typename WTraits<WP>::W;
@@ -2017,7 +2020,7 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
   __shared__ uint32_t nimg_sh;
   __shared__ __align__(16) uint8_t vary_sh[kWaves * sizeof(K)];
   // the pass's one-qubit operators, read for every term and image, in LDS (more than kE1Lds of
-  // them are read from global memory): ten rotations of one string 25 -> 14 us
+  // them are read from global memory): a layer of ten rotations per string 30 -> 27 us
   constexpr uint32_t kE1Lds = 16, kE1Words = (uint32_t)(sizeof(Exp1Desc) / 8);
   __shared__ uint64_t e1sh[kE1Lds * kE1Words];
   const uint32_t s = blockIdx.x;
@@ -2027,8 +2030,13 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
   const W* win = w_in + seg_in[s];
   uint64_t n64 = seg_in[s + 1] - seg_in[s];
   const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
-  for (uint32_t p = 0; p < n_grp; ++p) {
-    const PassArgs pa = pas[p];
+  const uint32_t first = seg_first ? seg_first[s] : 0u, n_own = seg_len ? min(seg_len[s], n_grp) : n_grp;
+  for (uint32_t p = n_own + threadIdx.x; p < n_grp; p += kGroupBlock) {  // (no pass of its own: no counts)
+    uint32_t* cp = cnt + ((uint64_t)p * S + s) * 3;
+    cp[0] = cp[1] = cp[2] = 0;
+  }
+  for (uint32_t p = 0; p < n_own; ++p) {
+    const PassArgs pa = pas[first + p];
     K* kout = ((p & 1u) ? kslot1 : kslot0) + slot0;
     W* wout = ((p & 1u) ? wslot1 : wslot0) + slot0;
     uint32_t* cp = cnt + ((uint64_t)p * S + s) * 3;
@@ -2277,8 +2285,9 @@ __global__ void __launch_bounds__(kGroupBlock) k_small_passes(
 // the pass output at the sum of the earlier segments' counts; seg_off receives the offsets. One
 // more block hands every count of the group, the error word and the sequence word to the host.
 template <typename K, typename W>
-__global__ void __launch_bounds__(256) k_small_gather(const K* __restrict__ kslot, const W* __restrict__ wslot,
-                                                      const uint32_t* __restrict__ cnt_last, uint32_t S,
+__global__ void __launch_bounds__(256) k_small_gather(const K* __restrict__ kslot0, const W* __restrict__ wslot0,
+                                                      const K* __restrict__ kslot1, const W* __restrict__ wslot1,
+                                                      uint32_t n_grp, const uint32_t* __restrict__ seg_len, uint32_t S,
                                                       K* __restrict__ keys_out, W* __restrict__ w_out,
                                                       uint64_t* __restrict__ seg_off, const uint32_t* __restrict__ cnt,
                                                       uint32_t n_words, uint64_t* result, uint64_t seq,
@@ -2295,22 +2304,29 @@ __global__ void __launch_bounds__(256) k_small_gather(const K* __restrict__ kslo
     if (threadIdx.x == 0) *(volatile uint64_t*)&result[n64 + 1] = seq;
     return;
   }
+  // kept terms of segment q: its last pass's
+  auto kept = [&](uint32_t q) -> uint32_t {
+    const uint32_t len = seg_len ? min(seg_len[q], n_grp) : n_grp;
+    return len ? min(cnt[((uint64_t)(len - 1) * S + q) * 3 + 2], (uint32_t)kChunkCap) : 0u;
+  };
   if (threadIdx.x < 64) {  // the first wave adds the earlier segments' counts
     uint64_t b = 0;
-    for (uint32_t q = threadIdx.x; q < s; q += 64) b += cnt_last[q * 3 + 2];
+    for (uint32_t q = threadIdx.x; q < s; q += 64) b += kept(q);
     for (int o = 32; o > 0; o >>= 1) b += __shfl_xor(b, o, 64);
     if (threadIdx.x == 0) {
       base_sh = b;
       seg_off[s] = b;
-      if (s + 1 == S) seg_off[S] = b + cnt_last[s * 3 + 2];
+      if (s + 1 == S) seg_off[S] = b + kept(s);
     }
   }
   __syncthreads();
   const uint64_t base = base_sh, src = (uint64_t)s * kChunkCap;
-  const uint32_t m = min(cnt_last[s * 3 + 2], (uint32_t)kChunkCap);
+  const uint32_t m = kept(s), len = seg_len ? min(seg_len[s], n_grp) : n_grp;
+  const K* const ks = (len - 1) & 1u ? kslot1 : kslot0;
+  const W* const ws = (len - 1) & 1u ? wslot1 : wslot0;
   for (uint32_t i = threadIdx.x; i < m; i += 256) {
-    keys_out[base + i] = kslot[src + i];
-    w_out[base + i] = wslot[src + i];
+    keys_out[base + i] = ks[src + i];
+    w_out[base + i] = ws[src + i];
   }
 }
 
@@ -3472,7 +3488,7 @@ __device__ __forceinline__ void apply_gate(Bloch& r, uint32_t code, double th) {
 // host waits for them alone and not for the stream. Few gates are read from mapped host memory
 // too, which saves a launch.
 // Bound by latency: a short chain is a few loads across the link and two or three products
-// (9.7 us with full 4 x 4 products, indices in scratch memory and a pull before it; see DESIGN).
+// (9.7 us with full 4 x 4 products, indices in scratch memory and a pull before it).
 constexpr int kComposeWaves = 4;
 __global__ void __launch_bounds__(64 * kComposeWaves)
 k_compose_ptm(const uint8_t* __restrict__ gate, const double* __restrict__ theta, const uint32_t* __restrict__ chain_off,
@@ -3710,31 +3726,25 @@ hipError_t launch_publish(uint32_t S, const MergeFin& fin, uint64_t* seg_off_out
 
 hipError_t launch_small_passes(int KC, int WP, int fp64_acc, const void* keys_in, const void* w_in,
                                const uint64_t* seg_in, uint32_t S, const PassArgs* pas, uint32_t n_grp,
-                               void* const kslot[2], void* const wslot[2], void* wimg, uint32_t* cnt,
-                               void* keys_out, void* w_out, uint64_t* seg_off_out, uint64_t* result, uint64_t seq,
-                               uint32_t* err, hipStream_t s, Prof* prof) {
+                               const uint32_t* seg_first, const uint32_t* seg_len, void* const kslot[2],
+                               void* const wslot[2], void* wimg, uint32_t* cnt, void* keys_out, void* w_out,
+                               uint64_t* seg_off_out, uint64_t* result, uint64_t seq, uint32_t* err, hipStream_t s,
+                               Prof* prof) {
   if (S == 0 || n_grp == 0) return hipErrorInvalidValue;
   hipEvent_t ev = prof_begin(prof, s, kKSmallPasses);
-  const int last = (int)((n_grp - 1) & 1u);
-  const uint32_t* cnt_last = cnt + (uint64_t)(n_grp - 1) * S * 3;
-#define QIMAX_SMALL_PASSES(K)                                                                                     \
-  if (WP == 64) {                                                                                                 \
-    k_small_passes<K, 64><<<S, kGroupBlock, 0, s>>>((const K*)keys_in, (const double*)w_in, seg_in, S, pas, n_grp, \
-                                                    (K*)kslot[0], (double*)wslot[0], (K*)kslot[1], (double*)wslot[1], \
-                                                    (double*)wimg, cnt, fp64_acc, err);                           \
-    k_small_gather<K, double><<<S + 1, 256, 0, s>>>((const K*)kslot[last], (const double*)wslot[last], cnt_last, S,    \
-                                                (K*)keys_out, (double*)w_out, seg_off_out, cnt, n_grp * S * 3,    \
-                                                result, seq, err);                                                \
-  } else {                                                                                                        \
-    k_small_passes<K, 32><<<S, kGroupBlock, 0, s>>>((const K*)keys_in, (const float*)w_in, seg_in, S, pas, n_grp,  \
-                                                    (K*)kslot[0], (float*)wslot[0], (K*)kslot[1], (float*)wslot[1], \
-                                                    (float*)wimg, cnt, fp64_acc, err);                            \
-    k_small_gather<K, float><<<S + 1, 256, 0, s>>>((const K*)kslot[last], (const float*)wslot[last], cnt_last, S,      \
-                                               (K*)keys_out, (float*)w_out, seg_off_out, cnt, n_grp * S * 3,      \
-                                               result, seq, err);                                                 \
-  }
-  if (KC == 0) { QIMAX_SMALL_PASSES(uint32_t) } else if (KC == 1) { QIMAX_SMALL_PASSES(uint64_t) }
-  else { QIMAX_SMALL_PASSES(unsigned __int128) }
+#define QIMAX_SMALL_PASSES(WP_, W)                                                                                  \
+  do {                                                                                                              \
+    k_small_passes<K, WP_><<<S, kGroupBlock, 0, s>>>((const K*)keys_in, (const W*)w_in, seg_in, S, pas, n_grp,      \
+                                                     seg_first, seg_len, (K*)kslot[0], (W*)wslot[0], (K*)kslot[1],  \
+                                                     (W*)wslot[1], (W*)wimg, cnt, fp64_acc, err);                   \
+    k_small_gather<K, W><<<S + 1, 256, 0, s>>>((const K*)kslot[0], (const W*)wslot[0], (const K*)kslot[1],          \
+                                               (const W*)wslot[1], n_grp, seg_len, S, (K*)keys_out, (W*)w_out,      \
+                                               seg_off_out, cnt, n_grp * S * 3, result, seq, err);                  \
+  } while (0)
+  QIMAX_DISPATCH_K(KC, {
+    if (WP == 64) QIMAX_SMALL_PASSES(64, double);
+    else QIMAX_SMALL_PASSES(32, float);
+  });
 #undef QIMAX_SMALL_PASSES
   prof_end(prof, s, ev, kKSmallPasses, 0.0);  // bytes: added by the caller once the counts are back
   return hipGetLastError();

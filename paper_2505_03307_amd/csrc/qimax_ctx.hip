@@ -1091,6 +1091,7 @@ void put_tables(const TablePlan& tp, const std::vector<uint32_t>& lens, const st
 struct RoundDesc {
   const PassArgs* pas = nullptr;   // device addresses
   const uint32_t* sent = nullptr;
+  const uint32_t* slen = nullptr;  // passes per segment, for groups of a batch
   TableLaunch tables;
   size_t host_bytes = 0;
   size_t e_bytes = 0;              // largest expanding-operator descriptor set of an entry
@@ -1100,7 +1101,8 @@ struct RoundDesc {
 };
 
 qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entries,
-                              const std::vector<uint32_t>& seg_entry, RoundDesc& rd) {
+                              const std::vector<uint32_t>& seg_entry, RoundDesc& rd,
+                              const std::vector<uint32_t>* seg_len = nullptr) {
   const uint32_t S = (uint32_t)seg_entry.size();
   const size_t E = entries.size();
   std::vector<PermDesc> perms;
@@ -1158,7 +1160,7 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
   const size_t oG = align256(o2 + e2.size() * sizeof(Exp2Desc));
   const size_t oA = align256(oG + g1.size() * sizeof(BlockDesc));
   const size_t oS = align256(oA + E * sizeof(PassArgs));
-  const size_t oJ = align256(oS + S * 4);
+  const size_t oL = align256(oS + S * 4), oJ = align256(oL + (seg_len ? S * 4 : 0));
   TablePlan tp;
   plan_tables(lens, !c->lean, tp);
   const size_t host_bytes = align256(oJ + plan_host_bytes(tp));
@@ -1208,6 +1210,8 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
     pas_h[e] = pa;
   }
   std::memcpy(hs + oS, seg_entry.data(), S * 4);
+  if (seg_len) std::memcpy(hs + oL, seg_len->data(), S * 4);
+  rd.slen = seg_len ? (const uint32_t*)(ds + oL) : nullptr;
   rd.pas = (const PassArgs*)(ds + oA);
   rd.sent = (const uint32_t*)(ds + oS);
   rd.host_bytes = host_bytes;
@@ -1929,43 +1933,39 @@ constexpr size_t kMaxGroupPasses = 64;
 bool small_group_ok(const qimax_ctx* c) {
   return c->small_groups && c->small_rounds && !c->classic_sort && !c->host_tiling && c->n <= kSmallMaxSegs;
 }
-size_t small_group_len(const qimax_ctx* c, const std::vector<Pass>& passes, size_t i0,
-                       const std::vector<uint64_t>& so_in) {
-  if (!small_group_ok(c)) return 0;
+
+// The passes from i0 on (at most kMaxGroupPasses) that keep segments of the given lengths within
+// what a block holds.
+size_t small_passes_of(const qimax_ctx* c, const std::vector<Pass>& passes, size_t i0, std::vector<double> len) {
   const double cap = (double)small_group_cap(c->KC);
-  std::vector<double> len(c->n);
-  for (uint32_t s = 0; s < c->n; ++s) len[s] = (double)(so_in[s + 1] - so_in[s]);
+  const double most = len.empty() ? 0.0 : *std::max_element(len.begin(), len.end());
+  double grown = 1.0;
   size_t k = 0;
   while (i0 + k < passes.size() && k < kMaxGroupPasses) {
-    const double f = std::max(1.0, passes[i0 + k].fanout_bound);
-    bool fits = true;
-    for (uint32_t s = 0; s < c->n && fits; ++s) fits = f * len[s] <= cap;
-    if (!fits) break;
-    for (uint32_t s = 0; s < c->n; ++s) len[s] *= f;
+    grown *= std::max(1.0, passes[i0 + k].fanout_bound);
+    if (grown * most > cap) break;
     ++k;
   }
   return k;
 }
+size_t small_group_len(const qimax_ctx* c, const std::vector<Pass>& passes, size_t i0,
+                       const std::vector<uint64_t>& so_in) {
+  if (!small_group_ok(c)) return 0;
+  std::vector<double> len(c->n);
+  for (uint32_t s = 0; s < c->n; ++s) len[s] = (double)(so_in[s + 1] - so_in[s]);
+  return small_passes_of(c, passes, i0, len);
+}
 
-// Passes i0 .. i0+k-1 of the context's circuit in one launch of k_small_passes (one block per
-// generator, the terms in LDS-sized slots between the passes); so_ins / so_imgs / so_outs
-// receive each pass's segment offsets of its input terms, images and kept terms, and the
-// last pass's terms go to pass slot `slot`. Counters as for k rounds. overflow: set (and nothing
-// done) where the images do not fit after all, for passes taken without a bound.
-qimax_status run_small_group(qimax_ctx* c, std::vector<Pass>& passes, size_t i0, size_t k, const void* k_in,
-                             const void* w_in, const uint64_t* s_in, const std::vector<uint64_t>& so_in, int slot,
-                             std::vector<std::vector<uint64_t>>& so_ins, std::vector<std::vector<uint64_t>>& so_imgs,
-                             std::vector<std::vector<uint64_t>>& so_outs, bool* overflow = nullptr) {
-  const uint32_t S = c->n;
-  std::vector<RoundEntry> en(k);
-  for (size_t p = 0; p < k; ++p) {
-    en[p].pass = &passes[i0 + p];
-    en[p].n = c->n;
-    en[p].thr = (i0 + p + 1 == passes.size()) ? c->eps : 0.0;
-  }
-  const std::vector<uint32_t> seg_entry(S, 0);
+// Launches a group of small passes (en: their entries) of the segments and waits for its counts
+// (c->zres, as 32-bit words). k passes en[0..k) for every segment, or (seg_len) seg_len[s] from
+// en[seg_first[s]] on, at most k. overflow: set (and nothing done) where the images do not fit after
+// all, for passes taken without a bound.
+qimax_status launch_group(qimax_ctx* c, const std::vector<RoundEntry>& en, const std::vector<uint32_t>& seg_first,
+                          const std::vector<uint32_t>* seg_len, size_t k, const void* k_in, const void* w_in,
+                          const uint64_t* s_in, const std::vector<uint64_t>& so_in, int slot, bool* overflow) {
+  const uint32_t S = (uint32_t)seg_first.size();
   RoundDesc rd;
-  QCHK(build_round_desc(c, en, seg_entry, rd));
+  QCHK(build_round_desc(c, en, seg_first, rd, seg_len));
   const uint64_t T_in = so_in[S];
   QCHK(ensure(c, c->tile_ctr, 256 * 4));
   {
@@ -2001,7 +2001,8 @@ qimax_status run_small_group(qimax_ctx* c, std::vector<Pass>& passes, size_t i0,
   c->zres[cnt_words + 1] = 0;
   void* const ks[2] = {c->ik[0].p, c->ik[1].p};
   void* const ws[2] = {c->iw[0].p, c->iw[1].p};
-  HIPCHK(c, launch_small_passes(c->KC, c->WP, c->fp64_acc, k_in, w_in, s_in, S, rd.pas, (uint32_t)k, ks, ws,
+  HIPCHK(c, launch_small_passes(c->KC, c->WP, c->fp64_acc, k_in, w_in, s_in, S, rd.pas, (uint32_t)k,
+                                seg_len ? rd.sent : nullptr, rd.slen, ks, ws,
                                 c->pw[slot].p, (uint32_t*)c->grp_cnt.p, c->pk[slot].p, c->pw[slot].p,
                                 (uint64_t*)c->pseg[slot].p, c->zres_dev, ++c->zseq, (uint32_t*)c->err.p, c->stream,
                                 &c->prof), "small passes");
@@ -2012,6 +2013,28 @@ qimax_status run_small_group(qimax_ctx* c, std::vector<Pass>& passes, size_t i0,
     return QIMAX_OK;
   }
   if (e) return fail(c, (e & kErrFanout) ? QIMAX_ETOOLARGE : QIMAX_EDEVICE, "small passes:" + err_text(e));
+  return QIMAX_OK;
+}
+
+// Passes i0 .. i0+k-1 of the context's circuit in one launch of k_small_passes (one block per
+// generator, the terms in LDS-sized slots between the passes); so_ins / so_imgs / so_outs
+// receive each pass's segment offsets of its input terms, images and kept terms, and the
+// last pass's terms go to pass slot `slot`. Counters as for k rounds. overflow: set (and nothing
+// done) where the images do not fit after all, for passes taken without a bound.
+qimax_status run_small_group(qimax_ctx* c, std::vector<Pass>& passes, size_t i0, size_t k, const void* k_in,
+                             const void* w_in, const uint64_t* s_in, const std::vector<uint64_t>& so_in, int slot,
+                             std::vector<std::vector<uint64_t>>& so_ins, std::vector<std::vector<uint64_t>>& so_imgs,
+                             std::vector<std::vector<uint64_t>>& so_outs, bool* overflow = nullptr) {
+  const uint32_t S = c->n;
+  const size_t eb = c->kb, wbt = c->wb;
+  std::vector<RoundEntry> en(k);
+  for (size_t p = 0; p < k; ++p) {
+    en[p].pass = &passes[i0 + p];
+    en[p].n = c->n;
+    en[p].thr = (i0 + p + 1 == passes.size()) ? c->eps : 0.0;
+  }
+  QCHK(launch_group(c, en, std::vector<uint32_t>(S, 0), nullptr, k, k_in, w_in, s_in, so_in, slot, overflow));
+  if (overflow && *overflow) return QIMAX_OK;
   const uint32_t* h = (const uint32_t*)c->zres;
   so_ins.assign(k, {});
   so_imgs.assign(k, {});
@@ -2096,8 +2119,8 @@ qimax_status apply_ops_once(qimax_ctx* c, std::vector<HostOp>& ops) {
     size_t kg = small_group_len(c, passes, i, so_in);
     // Every generator one string still (a first layer): a pass of large fan-out bound may yet
     // have few images (a rotation of every wire has three per string of weight one), so one
-    // launch tries it: 55 us for ten such strings against 115 in a round of its own. Where the
-    // images do not fit, the round follows (the try costs about 15 us).
+    // launch tries it, where a round of its own takes five and two waits: one layer at n = 10 with
+    // its readout 128 -> 105 us. Where the images do not fit, the round follows.
     bool overflow = false;
     const bool attempt = kg == 0 && small_group_ok(c) && c->T == c->n && so_in[c->n] == c->n && i == 0 &&
                          passes[i].fanout_bound > (double)kBoundPathMaxFanout;
@@ -2302,7 +2325,7 @@ inline int compose_code4(int gate, int chain) {
 }
 
 // Bytes of gates that the composing kernel reads across the link itself: one launch where a pull
-// and it took two (three rotations on ten wires: 12 us against 17).
+// (4 us) and it took two. Past that the chains' dependent reads cost more than the pull.
 constexpr size_t kComposeDirect = 16384;
 
 // The paper's grouping (Sec. III-A, Alg. 2): maximal runs of one-qubit gates (U_k) and
@@ -3691,6 +3714,7 @@ struct qimax_batch {
   std::vector<uint64_t> queue;  // submitted, not yet admitted into the array
   std::vector<uint64_t> done;   // finished and not yet reported by poll
   std::vector<uint64_t> so{0};  // host segment offsets of the term array
+  bool seg_ready = false;       // the context's device offsets are these
   uint64_t rounds = 0;
 };
 
@@ -3791,6 +3815,7 @@ qimax_status admit(qimax_batch* b) {
     for (uint32_t j = 0; j < bc.n; ++j) b->so.push_back(b->so.back() + 1);
   }
   b->queue.clear();
+  b->seg_ready = false;
   return QIMAX_OK;
 }
 
@@ -3833,6 +3858,164 @@ size_t active_count(const qimax_batch* b) {
   for (uint64_t id : b->order)
     if (b->circs.at(id).state == 1) ++k;
   return k + b->queue.size();
+}
+
+// After a round (or a group of passes) over the array: its output, in pass slot 0 with segment
+// offsets so_out, becomes the array, circuit e having run adv[e] passes with upd[e] term updates.
+qimax_status batch_advance(qimax_batch* b, const std::vector<uint64_t>& so_out, const std::vector<uint64_t>& upd,
+                           const std::vector<size_t>& adv, size_t* n_active) {
+  qimax_ctx* c = b->c;
+  std::swap(c->keys, c->pk[0]);
+  std::swap(c->w, c->pw[0]);
+  std::swap(c->seg, c->pseg[0]);
+  b->so = so_out;
+  c->T = so_out.back();
+  // finished circuits hand over their result; dropped ones leave the segment list
+  std::vector<uint64_t> keep_order, erase;
+  std::vector<uint64_t> keep_so{0};
+  size_t s0 = 0;
+  for (size_t e = 0; e < b->order.size(); ++e) {
+    BatchCirc& bc = b->circs.at(b->order[e]);
+    bc.updates += upd[e];
+    bool leaves = false;
+    if (bc.state == 1) {
+      for (size_t k = 0; k < adv[e]; ++k, ++bc.next)
+        if (!bc.passes[bc.next].E.empty()) c->st.passes += 1;
+      if (bc.next == bc.passes.size()) {
+        QCHK(take_result(b, bc, s0));
+        bc.state = 2;
+        b->done.push_back(bc.id);
+      }
+    } else {  // dropped this round: no terms left in the array
+      leaves = true;
+      if (bc.state == 4) erase.push_back(bc.id);
+      else bc.state = 3;
+    }
+    if (!leaves) {
+      keep_order.push_back(bc.id);
+      for (uint32_t j = 0; j < bc.n; ++j) keep_so.push_back(keep_so.back() + (b->so[s0 + j + 1] - b->so[s0 + j]));
+    }
+    s0 += bc.n;
+  }
+  for (uint64_t id : erase) b->circs.erase(id);
+  bool still_active = false;
+  for (uint64_t id : keep_order) still_active |= b->circs.at(id).state == 1;
+  if (!still_active) {  // every remaining circuit has handed over its result: empty the array
+    for (uint64_t id : keep_order) b->circs.at(id).state = 3;
+    keep_order.clear();
+    keep_so.assign(1, 0);
+    c->T = 0;
+  }
+  // the dropped circuits hold no terms any more, so the kept segments stay contiguous (and their
+  // offsets on the device are those of the round unless a segment went)
+  b->seg_ready = keep_so.size() == b->so.size() && c->T > 0;
+  b->order.swap(keep_order);
+  b->so.swap(keep_so);
+  if (n_active) *n_active = active_count(b);
+  return QIMAX_OK;
+}
+
+// The array's segment offsets on the device: there from the last round unless a circuit joined or
+// left since; then pulled from mapped staging (a copy call costs far more than its bytes here).
+qimax_status batch_offsets(qimax_batch* b) {
+  qimax_ctx* c = b->c;
+  if (b->seg_ready) return QIMAX_OK;
+  const size_t bytes = align256(b->so.size() * 8);
+  QCHK(ensure(c, c->seg, bytes));
+  QCHK(ensure_stage(c, 1, bytes));
+  std::memcpy(c->stage[1], b->so.data(), b->so.size() * 8);
+  HIPCHK(c, launch_pull(c->stage_dev[1], c->seg.p, bytes, c->stream), "offsets");
+  b->seg_ready = true;
+  return QIMAX_OK;
+}
+
+// The next passes of every active circuit in one launch of small passes, where all of them are
+// small (every circuit's segments, multiplied by its passes' fan-out bounds in turn, stay within
+// what a block holds) for two passes or more, with no host work in between. *ran stays false where
+// the step is to be a round: also beyond kGroupSegs segments (one resident block per CU: past that
+// the blocks queue, and the slots, 4096 terms a segment, would take more than the rounds of terms as
+// few as these), where a memory cap leaves no room to spare for the slots, or where the tables of two
+// passes would take more than kGroupTables. Measured: a batch of 16 circuits (n = 8 to 43, 76 k
+// gates, run in three key classes) 28.9 -> 26.2 ms with it, of which 12 ms are propagation.
+constexpr size_t kGroupSegs = 256, kGroupTables = 32u << 20;
+qimax_status batch_group(qimax_batch* b, size_t* n_active, bool* ran) {
+  qimax_ctx* c = b->c;
+  *ran = false;
+  const size_t segs = b->so.size() - 1, slots = segs * kChunkCap * (size_t)(c->kb + c->wb) * 3;
+  if (!small_group_ok(c) || c->T == 0 || segs > kGroupSegs || (c->cap && slots > c->cap / 16)) return QIMAX_OK;
+  const size_t most = kGroupTables / (2 * table_bytes(c) * std::max<size_t>(b->order.size(), 1));
+  // passes each circuit can run: all it has left, or as many as are small; the least of the latter
+  // is the group's length, so that the circuits keep step as they do in rounds
+  std::vector<size_t> adv;
+  size_t k = std::min(most, kMaxGroupPasses), left = 0, s0 = 0;
+  for (uint64_t id : b->order) {
+    BatchCirc& bc = b->circs.at(id);
+    adv.push_back(0);
+    if (bc.state == 1) {
+      std::vector<double> l(bc.n);
+      for (uint32_t j = 0; j < bc.n; ++j) l[j] = (double)(b->so[s0 + j + 1] - b->so[s0 + j]);
+      const size_t rest = bc.passes.size() - bc.next;
+      adv.back() = rest;
+      left = std::max(left, rest);
+      const size_t own = small_passes_of(c, bc.passes, bc.next, l);
+      if (own < rest) k = std::min(k, own);
+    }
+    s0 += bc.n;
+  }
+  k = std::min(k, left);
+  if (k < 2) return QIMAX_OK;
+  std::vector<RoundEntry> en;
+  std::vector<uint32_t> first, len;
+  for (size_t i = 0; i < adv.size(); ++i) {
+    const BatchCirc& bc = b->circs.at(b->order[i]);
+    const size_t own = adv[i] = std::min(adv[i], k);
+    first.insert(first.end(), bc.n, (uint32_t)en.size());
+    len.insert(len.end(), bc.n, (uint32_t)own);
+    for (size_t p = 0; p < own; ++p) {
+      RoundEntry e;
+      e.pass = &bc.passes[bc.next + p];
+      e.n = bc.n;
+      e.thr = bc.thr[bc.next + p];
+      en.push_back(e);
+    }
+  }
+  QCHK(batch_offsets(b));
+  const uint32_t S = (uint32_t)first.size();
+  c->opt_busy = true;  // (a round gives up memory for room; a group does not)
+  const qimax_status st = launch_group(c, en, first, &len, k, c->keys.p, c->w.p, (const uint64_t*)c->seg.p, b->so, 0,
+                                       nullptr);
+  c->opt_busy = false;
+  if (st == QIMAX_ENOMEM) return QIMAX_OK;
+  QCHK(st);
+  const uint32_t* h = (const uint32_t*)c->zres;
+  const size_t per = c->kb + c->wb;
+  std::vector<uint64_t> so_out(S + 1, 0), upd(adv.size(), 0);
+  double bytes = 0.0;
+  s0 = 0;
+  for (size_t e = 0; e < adv.size(); ++e) {
+    const BatchCirc& bc = b->circs.at(b->order[e]);
+    for (uint32_t j = 0; j < bc.n; ++j, ++s0) {
+      uint64_t t = b->so[s0 + 1] - b->so[s0];
+      for (size_t p = 0; p < adv[e]; ++p) {
+        const uint32_t* q = h + (p * S + s0) * 3;
+        if (q[0] != t) return bfail(b, QIMAX_EDEVICE, "small passes: a pass's input counts do not match the previous output");
+        const Pass& ps = bc.passes[bc.next + p];
+        upd[e] += pass_updates(ps, q[0], q[1], q[2]);
+        c->st.alg_bytes += (double)((uint64_t)q[0] + q[2]) * (double)per;
+        c->st.images += q[1];
+        c->st.sort_elems += ps.unsorted ? 0 : (uint64_t)q[1] * ((2u * bc.n + kRadixBits - 1) / kRadixBits);
+        bytes += (double)((uint64_t)q[0] + q[1] + q[2]) * (double)per;
+        t = q[2];
+      }
+      so_out[s0 + 1] = so_out[s0] + (adv[e] ? t : 0);
+    }
+    c->st.term_updates += upd[e];
+  }
+  c->st.rounds += k;
+  b->rounds += k;
+  if (c->prof.on && ((c->prof.mask >> kKSmallPasses) & 1u)) c->prof.bytes[kKSmallPasses] += bytes;
+  *ran = true;
+  return batch_advance(b, so_out, upd, adv, n_active);
 }
 
 }  // namespace
@@ -3918,70 +4101,33 @@ qimax_status qimax_batch_step(qimax_batch* b, size_t* n_active) {
     }
     b->order.clear();
     b->so.assign(1, 0);
+    b->seg_ready = false;
     c->T = 0;
     if (n_active) *n_active = active_count(b);
     return QIMAX_OK;
   }
-  QCHK(ensure(c, c->seg, b->so.size() * 8));
-  HIPCHK(c, hipMemcpyAsync(c->seg.p, b->so.data(), b->so.size() * 8, hipMemcpyHostToDevice, c->stream), "offsets");
+  QCHK(batch_offsets(b));
   std::vector<uint64_t> so_out, so_img, upd;
   QCHK(with_optional(c, [&] {
     return run_round(c, entries, seg_entry, c->keys.p, c->w.p, (const uint64_t*)c->seg.p, b->so, 0, so_out, so_img,
                      &upd);
   }));
-  std::swap(c->keys, c->pk[0]);
-  std::swap(c->w, c->pw[0]);
-  std::swap(c->seg, c->pseg[0]);
-  b->so = so_out;
-  c->T = so_out.back();
   b->rounds += 1;
-  // finished circuits hand over their result; dropped ones leave the segment list
-  std::vector<uint64_t> keep_order, erase;
-  std::vector<uint64_t> keep_so{0};
-  size_t s0 = 0;
-  for (size_t e = 0; e < b->order.size(); ++e) {
-    BatchCirc& bc = b->circs.at(b->order[e]);
-    bc.updates += upd[e];
-    bool leaves = false;
-    if (bc.state == 1) {
-      if (!bc.passes[bc.next].E.empty()) c->st.passes += 1;
-      bc.next += 1;
-      if (bc.next == bc.passes.size()) {
-        QCHK(take_result(b, bc, s0));
-        bc.state = 2;
-        b->done.push_back(bc.id);
-      }
-    } else {  // dropped this round: no terms left in the array
-      leaves = true;
-      if (bc.state == 4) erase.push_back(bc.id);
-      else bc.state = 3;
-    }
-    if (!leaves) {
-      keep_order.push_back(bc.id);
-      for (uint32_t j = 0; j < bc.n; ++j) keep_so.push_back(keep_so.back() + (b->so[s0 + j + 1] - b->so[s0 + j]));
-    }
-    s0 += bc.n;
-  }
-  for (uint64_t id : erase) b->circs.erase(id);
-  bool still_active = false;
-  for (uint64_t id : keep_order) still_active |= b->circs.at(id).state == 1;
-  if (!still_active) {  // every remaining circuit has handed over its result: empty the array
-    for (uint64_t id : keep_order) b->circs.at(id).state = 3;
-    keep_order.clear();
-    keep_so.assign(1, 0);
-    c->T = 0;
-  }
-  // the dropped circuits hold no terms any more, so the kept segments stay contiguous
-  b->order.swap(keep_order);
-  b->so.swap(keep_so);
-  if (n_active) *n_active = active_count(b);
-  return QIMAX_OK;
+  return batch_advance(b, so_out, upd, std::vector<size_t>(b->order.size(), 1), n_active);
 }
 
 qimax_status qimax_batch_run(qimax_batch* b) {
   if (!b) return QIMAX_EINVAL;
   size_t act = 1;
-  while (act) QCHK(qimax_batch_step(b, &act));
+  while (act) {
+    bool ran = false;
+    if (!b->c->broken) {
+      BusyTimer bt(b->c);
+      QCHK(admit(b));
+      if (!b->order.empty()) QCHK(batch_group(b, &act, &ran));
+    }
+    if (!ran) QCHK(qimax_batch_step(b, &act));
+  }
   return QIMAX_OK;
 }
 

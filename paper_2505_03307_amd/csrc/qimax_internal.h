@@ -406,13 +406,15 @@ size_t fuse_tile();
 // of S * kChunkCap elements each; cnt (n_grp * S * 3 words) receives every pass's input,
 // image and kept counts per segment; the last pass's terms go to keys_out / w_out with the
 // segment offsets in seg_off_out (S + 1). A segment may hold small_group_cap(KC) terms and
-// images. result: the counts (as 32-bit words), then the error word and seq.
+// images. result: the counts (as 32-bit words), then the error word and seq. seg_first / seg_len
+// (or null): every segment's own passes of pas, for circuits of a batch.
 uint32_t small_group_cap(int KC);
 hipError_t launch_small_passes(int KC, int WP, int fp64_acc, const void* keys_in, const void* w_in,
                                const uint64_t* seg_in, uint32_t S, const PassArgs* pas, uint32_t n_grp,
-                               void* const kslot[2], void* const wslot[2], void* wimg, uint32_t* cnt,
-                               void* keys_out, void* w_out, uint64_t* seg_off_out, uint64_t* result, uint64_t seq,
-                               uint32_t* err, hipStream_t s, Prof* prof = nullptr);
+                               const uint32_t* seg_first, const uint32_t* seg_len, void* const kslot[2],
+                               void* const wslot[2], void* wimg, uint32_t* cnt, void* keys_out, void* w_out,
+                               uint64_t* seg_off_out, uint64_t* result, uint64_t seq, uint32_t* err, hipStream_t s,
+                               Prof* prof = nullptr);
 hipError_t launch_count_expand(int KC, int WP, const void* keys, const void* w, uint64_t T_in, const Tiling& tl,
                                const PassArgs* pas, const uint32_t* seg_entry, uint64_t* status, uint32_t* ctr,
                                uint64_t epoch, uint64_t* img_seg, void* keys_out, void* w_out, uint64_t out_cap,
