@@ -1478,15 +1478,30 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   bool dense = dense_ok && c->dense_mode == 1;
   if (small) m_top = 0;  // whole segments sorted in LDS
   uint64_t seg_max = 0;     // the largest segment's image count (or its bound)
+  // ... and the largest for every key width: a segment of n qubits has 2n key bits, so the top m
+  // digits (of the round's widest keys) split it by the bits it has among them only
+  uint64_t seg_max_n[65] = {};
+  auto bucket_avg = [&](uint32_t m) -> double {  // of the largest bucket on average, sorted by the top m digits
+    double most = 0.0;
+    for (uint32_t n = 1; n <= max_n; ++n) {
+      const int bits = (int)(2 * n) - (int)(kRadixBits * (n_pass - m));
+      most = std::max(most, std::ldexp((double)seg_max_n[n], -std::max(bits, 0)));
+    }
+    return most;
+  };
   bool whole = false;       // gathered: chunks are whole segments
   if (sweep && !small) {
     if (c->local_sort && c->redo_cooldown == 0) {
-      for (uint32_t s = 0; s < S; ++s)
-        seg_max = std::max<uint64_t>(seg_max, bound_path ? (uint64_t)(f_round * (double)(so_in[s + 1] - so_in[s]))
-                                              : gather   ? so_cap[s + 1] - so_cap[s]
-                                                         : so_img[s + 1] - so_img[s]);
+      for (uint32_t s = 0; s < S; ++s) {
+        const uint64_t len = bound_path ? (uint64_t)(f_round * (double)(so_in[s + 1] - so_in[s]))
+                             : gather   ? so_cap[s + 1] - so_cap[s]
+                                        : so_img[s + 1] - so_img[s];
+        seg_max = std::max(seg_max, len);
+        uint64_t& of_n = seg_max_n[entries[seg_entry[s]].n];
+        of_n = std::max(of_n, len);
+      }
       uint32_t mm = 0;
-      for (double cap_b = 512.0; mm < n_pass && (double)seg_max > cap_b; cap_b *= 256.0) ++mm;
+      while (mm < n_pass && bucket_avg(mm) > 512.0) ++mm;
       // gathered outputs are distinct and few: whole segments in LDS where they fit a chunk
       whole = gather && c->local_sort_m < 0 && seg_max <= (uint64_t)kChunkCap;
       if (whole) mm = 0;
@@ -1545,12 +1560,16 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
     // A fused round has no separate expansion: its first tiling only sets the chunk-local
     // sort's nominal chunks, as large as the buckets straddling their ends leave room for in
     // a chunk (kChunkCap): 4096 less four times the largest segment's average bucket, within
-    // [kExpandTile, kChunkTile] (the capacity was sized for kExpandTile).
+    // [kExpandTile, kChunkTile] (the capacity was sized for kExpandTile). Where the low digits
+    // have few values (dense segments: a bucket can be full next to empty ones), less the most a
+    // bucket holds: each of them from as many parents as an operator maps onto one.
     if (c->chunk_tile) {
       img_jobs[0].tile = c->chunk_tile;
     } else if (m_top < n_pass) {
-      const double bucket = (double)seg_max / std::ldexp(1.0, 8 * (int)m_top);
-      const double t = std::min((double)kChunkTile, std::max((double)kExpandTile, (double)kChunkCap - 4.0 * bucket));
+      double room = 4.0 * bucket_avg(m_top);
+      const double full = std::ldexp(std::max(1.0, f_round), (int)(kRadixBits * (n_pass - m_top)));
+      if (full <= kChunkCap / 2) room = full;
+      const double t = std::min((double)kChunkTile, std::max((double)kExpandTile, (double)kChunkCap - room));
       img_jobs[0].tile = (uint64_t)t / 256 * 256;
     }
     HIPCHK(c, launch_make_tiles2(nullptr, (const uint64_t*)c->img_seg.p, S, nullptr, img_jobs[0], img_jobs[1], T_img,
