@@ -119,72 +119,114 @@ __global__ void k_sv_random(double2* __restrict__ v, uint64_t D, uint64_t seed) 
 
 // A generator's terms [T y/Y, T (y+1)/Y) applied to v by the blocks (., y) of a grid of
 // ceil(D / kSvTile) x Y: part[y D + k] = sum over those terms t of c_t (-1)^{popcount(src & z_t)}
-// v[src], src = k ^ x_t. The terms are converted as they are staged to LDS; a coefficient
-// w i^ny is real or imaginary, so a term costs two multiply-adds per amplitude and its kind is
-// the same for the whole block. Small states have few amplitudes (n = 10: one tile), so the
-// terms are split too: a launch of D threads alone left 252 of 256 CUs idle (n = 10, 177216
-// terms: 15.3 ms per state, 0.35 ms here). v in LDS where it takes 32 KB at
-// most (n <= 11).
-// Bound by the LDS reads of v and the ten vector instructions per term and amplitude.
-constexpr int kSvBlock = 256, kSvItems = 4, kSvTile = kSvBlock * kSvItems, kSvChunk = 256;
+// v[src], src = k ^ x_t. Small states have few amplitudes (n = 10: one tile), so the terms are
+// split too, over the blocks and over the kSvGroups groups of a block, whose sums meet in LDS: a
+// launch of D threads alone left 252 of 256 CUs idle. A wave holds 64 terms, one per lane, and
+// reads them back as scalars; a coefficient w i^ny is real or imaginary, so a term costs two
+// multiply-adds per amplitude and its kind is the same for the whole wave. v in LDS where it takes
+// 32 KB at most (n <= 11).
+// Bound by the LDS reads of v (16 KB a term, 128 cycles of a CU at n = 10) and the thirty or so
+// vector instructions per term and thread; with one wave per SIMD the two did not overlap. One
+// state at n = 10 with 177216 terms in ten generators: 15.3 ms with D threads in all, 0.25 ms with
+// 346 blocks of four waves over terms staged in LDS, 0.14 ms here.
+constexpr int kSvThreads = 256, kSvItems = 4, kSvTile = kSvThreads * kSvItems, kSvGroups = 4, kSvUnroll = 4;
+// generators of fewer take blocks of one group: 5 to 7 us for them against 10 to 11, where four
+// groups save 11 to 23 us of 28 to 64 on generators of 20 to 80 thousand terms
+constexpr uint64_t kSvManyTerms = 1u << 14;
+
 constexpr uint32_t kSvLdsQubits = 11;
-template <typename K, typename W, bool kLds>
-__global__ void __launch_bounds__(kSvBlock) k_sv_apply(const K* __restrict__ keys, const W* __restrict__ w, uint64_t T,
-                                                      uint32_t n, const double2* __restrict__ v, uint64_t D,
-                                                      double2* __restrict__ part) {
+template <typename K, typename W, bool kLds, int kGroups>
+__global__ void __launch_bounds__(kSvThreads * kGroups)
+k_sv_apply(const K* __restrict__ keys, const W* __restrict__ w, uint64_t T, uint32_t n, const double2* __restrict__ v,
+           uint64_t D, double2* __restrict__ part) {
   extern __shared__ __align__(16) uint8_t lds[];
-  __shared__ uint32_t sx[kSvChunk], sz[kSvChunk];  // planes (below 2^30); bit 31 of x: an odd number of Ys
-  __shared__ double sw[kSvChunk];
+  __shared__ double2 sums[kGroups > 1 ? kGroups / 2 : 1][kSvTile];
   double2* const sv = (double2*)lds;
-  if constexpr (kLds)
-    for (uint32_t i = threadIdx.x; i < (uint32_t)D; i += kSvBlock) sv[i] = v[i];
-  const uint64_t k0 = (uint64_t)blockIdx.x * kSvTile + threadIdx.x;
-  const uint64_t t0 = T * blockIdx.y / gridDim.y, t1 = T * (blockIdx.y + 1) / gridDim.y;
+  if constexpr (kLds) {
+    for (uint32_t i = threadIdx.x; i < (uint32_t)D; i += kSvThreads * kGroups) sv[i] = v[i];
+    __syncthreads();
+  }
+  const uint32_t tid = threadIdx.x % kSvThreads, group = threadIdx.x / kSvThreads, lane = threadIdx.x & 63;
+  const uint64_t k0 = (uint64_t)blockIdx.x * kSvTile + tid;
+  const uint64_t p = (uint64_t)blockIdx.y * kGroups + group, np = (uint64_t)gridDim.y * kGroups;
+  const uint64_t t0 = T * p / np, t1 = T * (p + 1) / np;
+  // amplitude i of the thread is kb + 256 i, whose bits 8 and 9 are i's alone: the index of its
+  // source is one XOR away from amplitude 0's, and its sign a constant of the term away
+  static_assert(kSvThreads == 256 && kSvItems == 4, "an amplitude's bits 8 and 9");
+  const uint32_t kb = (uint32_t)k0, mask = (uint32_t)(D - 1);
   double re[kSvItems] = {}, im[kSvItems] = {};
-  for (uint64_t c0 = t0; c0 < t1; c0 += kSvChunk) {
-    const uint32_t nt = (uint32_t)min<uint64_t>(kSvChunk, t1 - c0);
-    __syncthreads();
-    if (threadIdx.x < nt) {
-      const K key = keys[c0 + threadIdx.x];
-      const uint32_t z = pack_bits((uint64_t)key >> 1), x = pack_bits((uint64_t)key) ^ z;
-      const uint32_t ny = (uint32_t)__popc(x & z);
-      const double c = (double)w[c0 + threadIdx.x];
-      sx[threadIdx.x] = x | (ny << 31);
-      sz[threadIdx.x] = z;
-      sw[threadIdx.x] = (ny & 2u) ? -c : c;
-    }
-    __syncthreads();
-    for (uint32_t u = 0; u < nt; ++u) {
-      const uint32_t xo = __builtin_amdgcn_readfirstlane(sx[u]), z = __builtin_amdgcn_readfirstlane(sz[u]);
-      const uint32_t x = xo & 0x7FFFFFFFu;
-      const double c = sw[u];
-      double2 a[kSvItems];
-      double ck[kSvItems];
+  for (uint64_t c0 = t0; c0 < t1; c0 += 64) {
+    const uint32_t nt = __builtin_amdgcn_readfirstlane((uint32_t)min<uint64_t>(64, t1 - c0));
+    const uint64_t t = min<uint64_t>(c0 + lane, t1 - 1);
+    const K key = keys[t];
+    const uint32_t lz = pack_bits((uint64_t)key >> 1), lx = pack_bits((uint64_t)key) ^ lz;  // below 2^30
+    const uint32_t ny = (uint32_t)__popc(lx & lz);
+    // bit 31 of x: an odd number of Ys; the weight's sign: two Ys more, and that of x & z
+    const uint32_t lxo = lx | (ny << 31);
+    const double wt = (double)w[t];
+    const uint32_t lhi = (uint32_t)__double2hiint(wt) ^ (((ny >> 1) ^ ny) << 31), llo = (uint32_t)__double2loint(wt);
+    for (uint32_t u0 = 0; u0 < nt; u0 += kSvUnroll) {
+      uint32_t xo[kSvUnroll];
+      double2 a[kSvUnroll][kSvItems];
 #pragma unroll
-      for (int i = 0; i < kSvItems; ++i) {
-        const uint32_t src = (uint32_t)(min(k0 + (uint64_t)i * kSvBlock, D - 1)) ^ x;  // x < D
-        a[i] = kLds ? sv[src] : v[src];
-        ck[i] = (__popc(src & z) & 1) ? -c : c;
-      }
-      if (xo >> 31) {
+      for (int j = 0; j < kSvUnroll; ++j) {
+        xo[j] = __builtin_amdgcn_readlane(lxo, min(u0 + j, nt - 1));
+        const uint32_t s0 = kb ^ (xo[j] & 0x7FFFFFFFu);
 #pragma unroll
         for (int i = 0; i < kSvItems; ++i) {
-          re[i] -= ck[i] * a[i].y;
-          im[i] += ck[i] * a[i].x;
+          const uint32_t src = (s0 ^ (uint32_t)(i * kSvThreads)) & mask;  // (k past D: read, not used)
+          a[j][i] = kLds ? sv[src] : v[src];
         }
-      } else {
+      }
 #pragma unroll
-        for (int i = 0; i < kSvItems; ++i) {
-          re[i] += ck[i] * a[i].x;
-          im[i] += ck[i] * a[i].y;
+      for (int j = 0; j < kSvUnroll; ++j) {
+        if (u0 + j >= nt) break;
+        const uint32_t z = __builtin_amdgcn_readlane(lz, u0 + j);
+        const uint32_t lo = __builtin_amdgcn_readlane(llo, u0 + j), hi0 = __builtin_amdgcn_readlane(lhi, u0 + j);
+        // (-1)^{popcount(src & z)}: of amplitude 0's k per thread, of i for the block (of x: above)
+        const uint32_t hi = hi0 ^ ((uint32_t)__popc(kb & z) << 31);
+        double ck[kSvItems];
+#pragma unroll
+        for (int i = 0; i < kSvItems; ++i)
+          ck[i] = __hiloint2double((int)(hi ^ ((uint32_t)__popc((uint32_t)(i * kSvThreads) & z) << 31)), (int)lo);
+        if (xo[j] >> 31) {
+#pragma unroll
+          for (int i = 0; i < kSvItems; ++i) {
+            re[i] -= ck[i] * a[j][i].y;
+            im[i] += ck[i] * a[j][i].x;
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < kSvItems; ++i) {
+            re[i] += ck[i] * a[j][i].x;
+            im[i] += ck[i] * a[j][i].y;
+          }
         }
       }
     }
   }
 #pragma unroll
-  for (int i = 0; i < kSvItems; ++i) {
-    const uint64_t k = k0 + (uint64_t)i * kSvBlock;
-    if (k < D) part[blockIdx.y * D + k] = make_double2(re[i], im[i]);
+  for (uint32_t half = kGroups / 2; half > 0; half /= 2) {
+    if (group >= half && group < 2 * half) {
+#pragma unroll
+      for (int i = 0; i < kSvItems; ++i) sums[group - half][tid + i * kSvThreads] = make_double2(re[i], im[i]);
+    }
+    __syncthreads();
+    if (group < half) {
+#pragma unroll
+      for (int i = 0; i < kSvItems; ++i) {
+        re[i] += sums[group][tid + i * kSvThreads].x;
+        im[i] += sums[group][tid + i * kSvThreads].y;
+      }
+    }
+    __syncthreads();
+  }
+  if (group == 0) {
+#pragma unroll
+    for (int i = 0; i < kSvItems; ++i) {
+      const uint64_t k = k0 + (uint64_t)i * kSvThreads;
+      if (k < D) part[blockIdx.y * D + k] = make_double2(re[i], im[i]);
+    }
   }
 }
 
@@ -240,6 +282,7 @@ __global__ void k_sv_half_sum1(double2* __restrict__ v, const double2* __restric
 // (1 - 2 bit_q(i)) for every qubit q (<Z_q>, unnormalised). One block per row stores its sums,
 // several add theirs (acc is then cleared before).
 constexpr uint32_t kSvMaxQubits = 32;  // statevectors hold at most 2^kSvMaxQubits amplitudes
+constexpr int kSvBlock = 256;
 __global__ void __launch_bounds__(kSvBlock) k_sv_reduce(const double2* __restrict__ v, uint64_t D, uint32_t n,
                                                        const SvString* __restrict__ str, int zall,
                                                        double* __restrict__ acc) {
@@ -360,9 +403,9 @@ hipError_t launch_sv_random(void* v, uint64_t D, uint64_t seed, hipStream_t s) {
 }
 
 uint32_t sv_parts(uint64_t T, uint64_t D, size_t limit) {
-  // about 512 blocks, at least 64 terms each, and no more parts than `limit` bytes hold
+  // about a block per CU, at least 16 terms for each, and no more parts than `limit` bytes hold
   const uint64_t tiles = (D + kSvTile - 1) / kSvTile;
-  const uint64_t y = std::min<uint64_t>({(T + 63) / 64, std::max<uint64_t>(512 / tiles, 1), limit / (D * 16)});
+  const uint64_t y = std::min<uint64_t>({(T + 15) / 16, std::max<uint64_t>(256 / tiles, 1), limit / (D * 16)});
   return (uint32_t)std::max<uint64_t>(y, 1);
 }
 
@@ -373,8 +416,9 @@ hipError_t launch_sv_project(int KC, int WP, const void* keys, const void* w, ui
   const dim3 grid((uint32_t)((D + kSvTile - 1) / kSvTile), Y);
   const bool lds = n <= kSvLdsQubits;
   const size_t bytes = lds ? (size_t)D * 16 : 0;
-#define QIMAX_SVA(K, W, L) \
-  k_sv_apply<K, W, L><<<grid, kSvBlock, bytes, s>>>((const K*)keys, (const W*)w, T, n, (const double2*)v, D, (double2*)part)
+#define QIMAX_SVA_G(K, W, L, G) \
+  k_sv_apply<K, W, L, G><<<grid, kSvThreads * G, bytes, s>>>((const K*)keys, (const W*)w, T, n, (const double2*)v, D, (double2*)part)
+#define QIMAX_SVA(K, W, L) do { if (T >= kSvManyTerms) QIMAX_SVA_G(K, W, L, kSvGroups); else QIMAX_SVA_G(K, W, L, 1); } while (0)
 #define QIMAX_SVA_L(K, W) do { if (lds) QIMAX_SVA(K, W, true); else QIMAX_SVA(K, W, false); } while (0)
   if (KC == 0) {
     if (WP == 64) QIMAX_SVA_L(uint32_t, double); else QIMAX_SVA_L(uint32_t, float);
@@ -383,6 +427,7 @@ hipError_t launch_sv_project(int KC, int WP, const void* keys, const void* w, ui
   }
 #undef QIMAX_SVA_L
 #undef QIMAX_SVA
+#undef QIMAX_SVA_G
   if (Y == 1)
     k_sv_half_sum1<<<blocks_for(D, 256), 256, 0, s>>>((double2*)v, (const double2*)part, D);
   else

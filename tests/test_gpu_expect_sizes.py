@@ -58,3 +58,19 @@ def test_many_strings_and_a_memory_cap():
     with Simulator(n, mem_cap_bytes=cap) as s:  # fewer strings at a time
         s.run(c)
         assert np.max(np.abs(s.expect_many(strings) - a)) <= 1e-13
+
+
+@pytest.mark.parametrize("n", [6, 8, 12])
+def test_generators_of_many_terms(n):
+    """Terms over one group of a block's waves and over four (16384 terms and more), amplitudes in
+    LDS and not: generators below, near and past the line in one state."""
+    c = W.random_circuit(3 * n, n, 330)
+    v = D.statevector(c)
+    rng = np.random.default_rng(n)
+    strings = ["".join(rng.choice(list("IXYZ"), n)) for _ in range(20)]
+    want = np.array([_pauli(v, s) for s in strings])
+    with Simulator(n) as s:
+        s.run(c)
+        print("[expect] terms per generator", np.diff(s.generators()[0]), flush=True)
+        got = s.expect_many(strings)
+    assert np.max(np.abs(got - want)) <= n * 1e-14
