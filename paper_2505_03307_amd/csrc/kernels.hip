@@ -764,12 +764,40 @@ __device__ __forceinline__ void st_store(uint64_t* p, uint64_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The sum of the words before word b of a chain (decoupled look-back), by the 64 lanes of one
+// wave: 64 words at a time, up to the nearest prefix.
+__device__ __forceinline__ uint64_t look_back(const uint64_t* status, uint32_t b, uint64_t epoch, uint32_t* err) {
+  const int lane = threadIdx.x & 63;
+  uint64_t excl = 0;
+  uint32_t spins = 0;
+  for (int64_t t = (int64_t)b - 1; t >= 0;) {
+    const bool in = t >= lane;
+    const uint64_t v = in ? st_load(status + t - lane) : 0;
+    const uint64_t unready = __ballot(in && !((v >> 48) == epoch && (v & (kStAgg | kStPre))));
+    const uint64_t pre = __ballot(!in || (v & kStPre));
+    const int stop = pre ? __ffsll((long long)pre) - 1 : 63;  // the last lane that counts
+    if (unready & (~0ull >> (63 - stop))) {
+      if (++spins > kSpinLimit) {
+        if (lane == 0) atomicOr(err, kErrSpin);
+        break;
+      }
+      continue;
+    }
+    uint64_t add = lane <= stop ? v & kStValMask : 0;
+    for (int o = 32; o > 0; o >>= 1) add += __shfl_xor(add, o, 64);
+    excl += add;
+    if (pre) break;
+    t -= 64;
+  }
+  return excl;
+}
+
 // One stable LSD pass over a segment-aligned tile. kSweep = false: the destination of each
 // (tile, digit) comes from the scanned per-tile histograms (hist_off). kSweep = true: tiles are
 // claimed in order through tile_ctr, each publishes its digit counts and looks back over the
 // earlier tiles of its segment for their prefix (decoupled look-back), and the digit's base
 // within the segment comes from the upfront histogram (base).
-template <typename K, typename W, bool kSweep>
+template <typename K, typename W, bool kSweep, int kItems = kSortItems>
 __global__ void __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(4)))
 k_sort_scatter(const K* __restrict__ keys_in, const W* __restrict__ w_in, K* __restrict__ keys_out,
                W* __restrict__ w_out, uint64_t T, uint32_t shift, Tiling tl,
@@ -777,7 +805,8 @@ k_sort_scatter(const K* __restrict__ keys_in, const W* __restrict__ w_in, K* __r
                const uint64_t* __restrict__ seg_off, uint64_t* __restrict__ status, uint32_t* __restrict__ tile_ctr,
                uint64_t epoch, uint32_t* err) {
   constexpr int kWaves = kSortBlock / 64;
-  constexpr int kRounds = kSortItems;                 // rounds per wave
+  constexpr int kRounds = kItems;                     // rounds per wave
+  constexpr int kTile = kSortBlock * kItems;          // elements a tile may hold
   constexpr int kWaveSpan = 64 * kRounds;             // tile elements per wave
   constexpr int kWords = sizeof(K) > 8 ? 2 : 1;
   // Four blocks per CU: under 40 KB of LDS and 128 VGPRs per thread. The digit of a sorted
@@ -785,8 +814,8 @@ k_sort_scatter(const K* __restrict__ keys_in, const W* __restrict__ w_in, K* __r
   // weights; two-word keys keep it in LDS, since the digit may lie in either word.
   constexpr bool kDigLds = kWords > 1;
   static_assert(kSortBlock == kRadix && kRounds % 4 == 0, "one thread per digit; four digits a word");
-  __shared__ uint64_t stage[kSortTile];               // key words, then weights (as raw 64-bit)
-  __shared__ uint8_t sdig[kDigLds ? kSortTile : 1];   // digit of each sorted slot (two-word keys)
+  __shared__ uint64_t stage[kTile];               // key words, then weights (as raw 64-bit)
+  __shared__ uint8_t sdig[kDigLds ? kTile : 1];   // digit of each sorted slot (two-word keys)
   __shared__ uint32_t wrun[kWaves][kRadix];            // per-wave running digit counts, then slot bases
   __shared__ uint32_t wdummy[kWaves][64];              // target of the lanes that lead no digit
   __shared__ uint64_t gdst[kRadix];                    // destination of tile slot j of digit d: gdst[d] + j
@@ -899,18 +928,28 @@ k_sort_scatter(const K* __restrict__ keys_in, const W* __restrict__ w_in, K* __r
     st_store(my, ep | (b == first ? kStPre : kStAgg) | tile_cnt);
     uint64_t excl = 0;
     if (b != first) {
-      uint32_t t = b - 1;
-      uint32_t spins = 0;
-      while (true) {
-        const uint64_t v = st_load(status + (uint64_t)t * kRadix + d);
-        const bool ready = (v >> 48) == epoch && (v & (kStAgg | kStPre));
-        if (!ready) {
-          if (++spins > kSpinLimit) { atomicOr(err, kErrSpin); break; }
-          continue;
+      // kAhead words at a time, their loads in flight together
+      constexpr uint32_t kAhead = 4;
+      uint32_t t = b - 1, spins = 0;
+      for (bool done = false; !done;) {
+        uint64_t v[kAhead];
+#pragma unroll
+        for (uint32_t a = 0; a < kAhead; ++a)
+          v[a] = st_load(status + (uint64_t)max(t - min(t, a), first) * kRadix + d);
+#pragma unroll
+        for (uint32_t a = 0; a < kAhead; ++a) {
+          if (done) continue;
+          if (!((v[a] >> 48) == epoch && (v[a] & (kStAgg | kStPre)))) {
+            if (++spins > kSpinLimit) {
+              atomicOr(err, kErrSpin);
+              done = true;
+            }
+            break;
+          }
+          excl += v[a] & kStValMask;
+          done = (v[a] & kStPre) || t == first;
+          if (!done) --t;
         }
-        excl += v & kStValMask;
-        if ((v & kStPre) || t == first) break;
-        --t;
       }
       st_store(my, ep | kStPre | (excl + tile_cnt));
     }
@@ -943,7 +982,7 @@ k_sort_scatter(const K* __restrict__ keys_in, const W* __restrict__ w_in, K* __r
   for (int r = 0; r < kRounds; ++r) {
     if (pos[r] != 0xFFFFFFFFu) {
       const uint32_t dd = (uint32_t)(key[r] >> shift) & (kRadix - 1);
-      if (pos[r] < (uint32_t)kSortTile) {
+      if (pos[r] < (uint32_t)kTile) {
         stage[pos[r]] = (uint64_t)key[r];
         if constexpr (kDigLds) sdig[pos[r]] = (uint8_t)dd;
       } else {
@@ -972,7 +1011,7 @@ k_sort_scatter(const K* __restrict__ keys_in, const W* __restrict__ w_in, K* __r
       __syncthreads();
 #pragma unroll
       for (int r = 0; r < kRounds; ++r)
-        if (pos[r] < (uint32_t)kSortTile) stage[pos[r]] = (uint64_t)(key[r] >> (64 * word));
+        if (pos[r] < (uint32_t)kTile) stage[pos[r]] = (uint64_t)(key[r] >> (64 * word));
       __syncthreads();
     }
 #pragma unroll
@@ -996,7 +1035,7 @@ k_sort_scatter(const K* __restrict__ keys_in, const W* __restrict__ w_in, K* __r
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
-    if (pos[r] < (uint32_t)kSortTile) {
+    if (pos[r] < (uint32_t)kTile) {
       if constexpr (sizeof(W) == 8) stage[pos[r]] = __double_as_longlong(wv[r]);
       else stage[pos[r]] = (uint64_t)__float_as_uint(wv[r]);
     }
@@ -1223,33 +1262,20 @@ k_count_expand(const K* __restrict__ keys, const typename WTraits<WP>::W* __rest
       run += fv[k2];
     }
   }
-  if (threadIdx.x == 0) {
-    loff[n] = (uint32_t)tot;
+  if (threadIdx.x < 64) {
     const uint64_t ep = epoch << 48;
-    st_store(status + b, ep | (b == 0 ? kStPre : kStAgg) | tot);
-    uint64_t excl = 0;
-    if (b > 0) {
-      uint32_t t = b - 1;
-      uint32_t spins = 0;
-      while (true) {
-        const uint64_t v = st_load(status + t);
-        const bool ready = (v >> 48) == epoch && (v & (kStAgg | kStPre));
-        if (!ready) {
-          if (++spins > kSpinLimit) { atomicOr(err, kErrSpin); break; }
-          continue;
-        }
-        excl += v & kStValMask;
-        if ((v & kStPre) || t == 0) break;
-        --t;
-      }
-      st_store(status + b, ep | kStPre | (excl + tot));
+    if (threadIdx.x == 0) st_store(status + b, ep | (b == 0 ? kStPre : kStAgg) | tot);
+    const uint64_t excl = look_back(status, b, epoch, err);
+    if (threadIdx.x == 0) {
+      loff[n] = (uint32_t)tot;
+      if (b > 0) st_store(status + b, ep | kStPre | (excl + tot));
+      base_sh = excl;
+      // the segments this tile starts (with any empty ones before it), and after the last tile
+      // the trailing empty segments and the total
+      for (uint32_t q = seg + 1; q-- > 0 && tl.seg_blk[q] == b;) img_seg[q] = excl;
+      if (b + 1 == tl.n_blocks)
+        for (uint32_t q = tl.n_segs; q > seg && tl.seg_blk[q] == tl.n_blocks; --q) img_seg[q] = excl + tot;
     }
-    base_sh = excl;
-    // the segments this tile starts (with any empty ones before it), and after the last tile
-    // the trailing empty segments and the total
-    for (uint32_t q = seg + 1; q-- > 0 && tl.seg_blk[q] == b;) img_seg[q] = excl;
-    if (b + 1 == tl.n_blocks)
-      for (uint32_t q = tl.n_segs; q > seg && tl.seg_blk[q] == tl.n_blocks; --q) img_seg[q] = excl + tot;
   }
   if (pa.useB) {
     __syncthreads();  // the A table is no longer read
@@ -3036,7 +3062,7 @@ __global__ void __launch_bounds__(256) k_dense_finish(const uint64_t* __restrict
 
 // Digit histograms of the radix passes p_begin .. n_pass-1 at once, per segment:
 // ghist[(s*n_pass + p)*256 + d].
-template <typename K>
+template <typename K, int kItems>
 __global__ void __launch_bounds__(kSortBlock) k_sort_upsweep(const K* __restrict__ keys, Tiling tl, uint32_t n_pass,
                                                              uint32_t p_begin, uint32_t* __restrict__ ghist) {
   constexpr int kWaves = sizeof(K) <= 8 ? kSortBlock / 64 : 1;  // private copies per wave
@@ -3047,15 +3073,15 @@ __global__ void __launch_bounds__(kSortBlock) k_sort_upsweep(const K* __restrict
   __syncthreads();
   const uint32_t b = blockIdx.x;
   const uint64_t begin = tl.blk_begin[b], end = tl.blk_end[b];
-  const uint32_t n = (uint32_t)(end - begin);  // at most kSortTile
-  K kr[kSortItems];
+  const uint32_t n = (uint32_t)(end - begin);  // at most kSortBlock * kItems
+  K kr[kItems];
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {  // every load in flight before the first use
+  for (int r = 0; r < kItems; ++r) {  // every load in flight before the first use
     const uint32_t li = r * kSortBlock + threadIdx.x;
     kr[r] = keys[n ? begin + min(li, n - 1) : 0];
   }
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {  // no early exit: the loads above stay in flight together
+  for (int r = 0; r < kItems; ++r) {  // no early exit: the loads above stay in flight together
     if (r * kSortBlock + threadIdx.x < n)
       for (uint32_t p = p_begin; p < n_pass; ++p) atomicAdd(&h[wid][p][(uint32_t)(kr[r] >> (8 * p)) & 255u], 1u);
   }
@@ -3097,17 +3123,17 @@ __device__ __forceinline__ W run_sum_tile(const KeyAt& key_at, const WAt& w_at, 
   return a.value();
 }
 
-template <typename K, typename W, int kMode>
+template <typename K, typename W, int kMode, int kItems = kSortItems>
 __global__ void __launch_bounds__(kSortBlock)
 k_merge(const K* __restrict__ keys, const W* __restrict__ w, Tiling tl, const PassArgs* __restrict__ pas,
         const uint32_t* __restrict__ seg_entry, int fp64_acc, uint32_t* __restrict__ blk_cnt,
         uint64_t* __restrict__ blk_off, K* __restrict__ keys_out, W* __restrict__ w_out, uint64_t out_cap,
         uint64_t* __restrict__ status, uint32_t* __restrict__ tile_ctr, uint64_t epoch, uint32_t* err) {
   constexpr bool kLds = sizeof(K) <= 8;  // 16-byte keys are read from global memory
-  // A thread takes kSortItems consecutive elements, so a wave reads LDS with a stride of
-  // kSortItems elements: one pad element after every 16 spreads those reads over the banks.
+  // A thread takes kItems consecutive elements, so a wave reads LDS with a stride of
+  // kItems elements: one pad element after every 16 spreads those reads over the banks.
   auto pad = [](uint32_t i) -> uint32_t { return i + (i >> 4); };
-  constexpr int kPadded = kSortTile + kSortTile / 16 + 1;
+  constexpr int kTile = kSortBlock * kItems, kPadded = kTile + kTile / 16 + 1;
   __shared__ K sk[kLds ? kPadded : 1];
   __shared__ W sw[kPadded];
   __shared__ uint64_t scan_sh[kSortBlock / 64];
@@ -3140,17 +3166,17 @@ k_merge(const K* __restrict__ keys, const W* __restrict__ w, Tiling tl, const Pa
   // key(i) for i in [-1, n_tile): sk[0] holds the key before the tile (if inside the segment);
   // weights in sw. Coalesced loads, all in flight before the first LDS store.
   {
-    K kr[kLds ? kSortItems : 1];
-    W wr[kSortItems];
+    K kr[kLds ? kItems : 1];
+    W wr[kItems];
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
+    for (int r = 0; r < kItems; ++r) {
       const uint32_t li = r * kSortBlock + threadIdx.x;
       const uint64_t gi = n_tile ? begin + min(li, n_tile - 1) : 0;
       if constexpr (kLds) kr[r] = keys[gi];
       wr[r] = w[gi];
     }
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
+    for (int r = 0; r < kItems; ++r) {
       const uint32_t li = r * kSortBlock + threadIdx.x;
       if (li < n_tile) {
         if constexpr (kLds) sk[pad(1 + li)] = kr[r];
@@ -3167,12 +3193,12 @@ k_merge(const K* __restrict__ keys, const W* __restrict__ w, Tiling tl, const Pa
     else return keys[begin + i1 - 1];
   };
   auto w_at = [&](uint32_t i) -> W { return sw[pad(i)]; };
-  const uint32_t i0 = threadIdx.x * kSortItems;
+  const uint32_t i0 = threadIdx.x * kItems;
   uint32_t keep = 0;
   uint32_t keep_mask = 0;
-  W sums[kSortItems];
+  W sums[kItems];
 #pragma unroll
-  for (int k = 0; k < kSortItems; ++k) {
+  for (int k = 0; k < kItems; ++k) {
     sums[k] = 0;
     const uint32_t li = i0 + k;
     if (li >= n_tile) continue;
@@ -3199,29 +3225,16 @@ k_merge(const K* __restrict__ keys, const W* __restrict__ w, Tiling tl, const Pa
     if (threadIdx.x == 0) blk_cnt[b] = (uint32_t)tot;
   } else {
     if constexpr (kMode == 2) {
-      if (threadIdx.x == 0) {
+      if (threadIdx.x < 64) {
         const uint64_t ep = epoch << 48;
-        st_store(status + b, ep | (b == 0 ? kStPre : kStAgg) | tot);
-        uint64_t excl = 0;
-        if (b > 0) {
-          uint32_t t = b - 1;
-          uint32_t spins = 0;
-          while (true) {
-            const uint64_t v = st_load(status + t);
-            const bool ready = (v >> 48) == epoch && (v & (kStAgg | kStPre));
-            if (!ready) {
-              if (++spins > kSpinLimit) { atomicOr(err, kErrSpin); break; }
-              continue;
-            }
-            excl += v & kStValMask;
-            if ((v & kStPre) || t == 0) break;
-            --t;
-          }
-          st_store(status + b, ep | kStPre | (excl + tot));
+        if (threadIdx.x == 0) st_store(status + b, ep | (b == 0 ? kStPre : kStAgg) | tot);
+        const uint64_t excl = look_back(status, b, epoch, err);
+        if (threadIdx.x == 0) {
+          if (b > 0) st_store(status + b, ep | kStPre | (excl + tot));
+          base_sh = excl;
+          blk_off[b] = excl;
+          if (b + 1 == n_tiles) blk_off[n_tiles] = excl + tot;
         }
-        base_sh = excl;
-        blk_off[b] = excl;
-        if (b + 1 == n_tiles) blk_off[n_tiles] = excl + tot;
       }
       __syncthreads();
     }
@@ -3230,14 +3243,14 @@ k_merge(const K* __restrict__ keys, const W* __restrict__ w, Tiling tl, const Pa
       // The kept runs leave through the tile's LDS arrays (every read of them came before the
       // scan's barriers): staged at their rank in the tile, then stored by consecutive threads,
       // so that a wave's stores fill whole lines instead of touching one element every
-      // kSortItems slots per lane.
-      K kk[kSortItems];
+      // kItems slots per lane.
+      K kk[kItems];
 #pragma unroll
-      for (int k = 0; k < kSortItems; ++k) kk[k] = key_at(1 + i0 + k);
+      for (int k = 0; k < kItems; ++k) kk[k] = key_at(1 + i0 + k);
       __syncthreads();
       uint32_t q = (uint32_t)pre;
 #pragma unroll
-      for (int k = 0; k < kSortItems; ++k)
+      for (int k = 0; k < kItems; ++k)
         if (keep_mask & (1u << k)) {
           sk[pad(q)] = kk[k];
           sw[pad(q)] = sums[k];
@@ -3256,7 +3269,7 @@ k_merge(const K* __restrict__ keys, const W* __restrict__ w, Tiling tl, const Pa
     } else {
       uint64_t o = ob + pre;
 #pragma unroll
-      for (int k = 0; k < kSortItems; ++k) {
+      for (int k = 0; k < kItems; ++k) {
         if (!(keep_mask & (1u << k))) continue;
         if (o < out_cap) {
           keys_out[o] = key_at(1 + i0 + k);
@@ -3868,8 +3881,15 @@ hipError_t launch_sort_pass(int KC, int WP, const void* keys_in, const void* w_i
   return hipGetLastError();
 }
 
+// Launches f(kItems) for the items per thread of a sort tile.
+template <typename F>
+static void with_items(uint32_t tile, const F& f) {
+  if (tile == (uint32_t)kSmallSortTile) f(std::integral_constant<int, kSmallSortTile / kSortBlock>());
+  else f(std::integral_constant<int, kSortItems>());
+}
+
 hipError_t launch_sort_sweep(int KC, int WP, void* const keys[2], void* const w[2], uint64_t T, uint32_t key_bits,
-                             uint32_t p_begin, bool upsweep, const Tiling& tl, const uint64_t* seg_off,
+                             uint32_t p_begin, bool upsweep, const Tiling& tl, uint32_t tile, const uint64_t* seg_off,
                              uint32_t* ghist, uint64_t* status, uint32_t* tile_ctr, uint64_t* epoch, uint32_t* err,
                              int* cur, hipStream_t s, Prof* prof, void* last_k, void* last_w) {
   *cur = 0;
@@ -3880,7 +3900,9 @@ hipError_t launch_sort_sweep(int KC, int WP, void* const keys[2], void* const w[
     hipEvent_t ev = nullptr;
     if (upsweep) {
       ev = prof_begin(prof, s, kKSortHist);
-      k_sort_upsweep<K><<<tl.n_blocks, kSortBlock, 0, s>>>((const K*)keys[0], tl, n_pass, p_begin, ghist);
+      with_items(tile, [&](auto items) {
+        k_sort_upsweep<K, items.value><<<tl.n_blocks, kSortBlock, 0, s>>>((const K*)keys[0], tl, n_pass, p_begin, ghist);
+      });
       prof_end(prof, s, ev, kKSortHist, kb * (double)T);
     }
     // the digit passes run back to back: one pair of events times them all (fewer event
@@ -3891,16 +3913,16 @@ hipError_t launch_sort_sweep(int KC, int WP, void* const keys[2], void* const w[
       const int c = *cur;
       void* const ko = p + 1 == n_pass && last_k ? last_k : keys[c ^ 1];
       void* const wo = p + 1 == n_pass && last_k ? last_w : w[c ^ 1];
-      if (WP == 64)
-        k_sort_scatter<K, double, true><<<tl.n_blocks, kSortBlock, 0, s>>>(
-            (const K*)keys[c], (const double*)w[c], (K*)ko, (double*)wo, T, 8u * p, tl, nullptr,
-            ghist + (uint64_t)p * kRadix, n_pass * kRadix, seg_off, status, tile_ctr + (uint64_t)p * kXcds, *epoch,
-            err);
-      else
-        k_sort_scatter<K, float, true><<<tl.n_blocks, kSortBlock, 0, s>>>(
-            (const K*)keys[c], (const float*)w[c], (K*)ko, (float*)wo, T, 8u * p, tl, nullptr,
-            ghist + (uint64_t)p * kRadix, n_pass * kRadix, seg_off, status, tile_ctr + (uint64_t)p * kXcds, *epoch,
-            err);
+      with_items(tile, [&](auto items) {
+        auto run = [&](auto weight) {
+          using W = decltype(weight);
+          k_sort_scatter<K, W, true, items.value><<<tl.n_blocks, kSortBlock, 0, s>>>(
+              (const K*)keys[c], (const W*)w[c], (K*)ko, (W*)wo, T, 8u * p, tl, nullptr, ghist + (uint64_t)p * kRadix,
+              n_pass * kRadix, seg_off, status, tile_ctr + (uint64_t)p * kXcds, *epoch, err);
+        };
+        if (WP == 64) run(double{});
+        else run(float{});
+      });
       *cur ^= 1;
     }
     if (n_pass > p_begin)
@@ -3992,8 +4014,8 @@ hipError_t launch_fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s) {
 }
 
 hipError_t launch_merge(int KC, int WP, int fp64_acc, const void* keys_in, const void* w_in, uint64_t T,
-                        const Tiling& tl, const PassArgs* pas, const uint32_t* seg_entry, void* keys_out, void* w_out,
-                        uint64_t out_cap, uint64_t* seg_off_out, uint32_t* blk_cnt, uint64_t* blk_off, uint64_t* tmp,
+                        const Tiling& tl, uint32_t tile, const PassArgs* pas, const uint32_t* seg_entry,
+                        void* keys_out, void* w_out, uint64_t out_cap, uint64_t* seg_off_out, uint32_t* blk_cnt, uint64_t* blk_off, uint64_t* tmp,
                         uint64_t* status, uint32_t* tile_ctr, uint64_t epoch, uint32_t* err, const MergeFin* fin,
                         hipStream_t s, Prof* prof) {
   if (tl.n_blocks == 0 && fin) {
@@ -4012,14 +4034,16 @@ hipError_t launch_merge(int KC, int WP, int fp64_acc, const void* keys_in, const
     if (status) {  // single sweep
       if (!fin) k_fill_u32<<<1, 64, 0, s>>>(tile_ctr, 1, 0u);  // with fin: zeroed by the caller
       hipEvent_t ev = prof_begin(prof, s, kKMergeWrite);
-      if (WP == 64)
-        k_merge<K, double, 2><<<tl.n_blocks, kSortBlock, 0, s>>>(
-            (const K*)keys_in, (const double*)w_in, tl, pas, seg_entry, fp64_acc, nullptr, blk_off, (K*)keys_out,
-            (double*)w_out, out_cap, status, tile_ctr, epoch, err);
-      else
-        k_merge<K, float, 2><<<tl.n_blocks, kSortBlock, 0, s>>>(
-            (const K*)keys_in, (const float*)w_in, tl, pas, seg_entry, fp64_acc, nullptr, blk_off, (K*)keys_out,
-            (float*)w_out, out_cap, status, tile_ctr, epoch, err);
+      with_items(tile, [&](auto items) {
+        auto run = [&](auto weight) {
+          using W = decltype(weight);
+          k_merge<K, W, 2, items.value><<<tl.n_blocks, kSortBlock, 0, s>>>(
+              (const K*)keys_in, (const W*)w_in, tl, pas, seg_entry, fp64_acc, nullptr, blk_off, (K*)keys_out,
+              (W*)w_out, out_cap, status, tile_ctr, epoch, err);
+        };
+        if (WP == 64) run(double{});
+        else run(float{});
+      });
       // the written terms are added by the caller once their count is back on the host
       prof_end(prof, s, ev, kKMergeWrite, (kb + wb) * (double)T);
     } else {

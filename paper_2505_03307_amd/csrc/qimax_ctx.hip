@@ -423,6 +423,11 @@ struct qimax_ctx {
   bool classic_passes = false;  // multi-launch global sort passes in every round (tests)
   bool gather = true;        // rounds of large fan-out merge before they expand (see k_gather_plan)
   bool merge_free = true;    // passes whose images all differ leave them unsorted (see KeySpan)
+  // Rounds of at most so many images (or a bound of them) sort and merge in tiles of 1024: with a
+  // few tiles on the chip a launch takes as long as one block takes over its tile (4096: 13 us,
+  // 1024: 9 us), and past this the look-back over four times the tiles costs more.
+  // Random circuits at n = 10, ten such rounds of 33: 3.99 -> 3.81 ms; with 2^23: 4.58.
+  uint64_t small_sort_max = 1u << 17;
   bool small_groups = true;  // consecutive small passes in one launch (k_small_passes)
   int dense_mode = 0;         // dense accumulation: 0 off, 1 wherever it applies, 2 a tuner candidate
   DevBuf dense_acc;           // its fixed-point slots
@@ -1381,6 +1386,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   }
   QCHK(ensure(c, c->img_seg, (S + 1) * 8));
   Tiling tl_exp{}, tl{};
+  uint32_t sort_tile = kSortTile;       // elements of a sort / merge tile
   TileJob2 img_jobs[2];
   GatherPlan gp{};
   std::vector<uint64_t> g_units[2], g_images;
@@ -1411,9 +1417,10 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   }
   if (bound_path || gather) {
     if (!gather) T_img = (uint64_t)f_round * T_in;  // capacity: an upper bound of the image count
+    if (sweep && T_img <= c->small_sort_max) sort_tile = kSmallSortTile;
     const uint32_t caps[2] = {(uint32_t)((T_img + kExpandTile - 1) / kExpandTile + S),
-                              (uint32_t)((T_img + kSortTile - 1) / kSortTile + S)};
-    const uint64_t tiles[2] = {(uint64_t)kExpandTile, (uint64_t)kSortTile};
+                              (uint32_t)((T_img + sort_tile - 1) / sort_tile + S)};
+    const uint64_t tiles[2] = {(uint64_t)kExpandTile, (uint64_t)sort_tile};
     Tiling* tls[2] = {&tl_exp, &tl};
     TileJob2* jobs = img_jobs;
     for (int i = 0; i < 2; ++i) {
@@ -1650,7 +1657,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
         cur ^= 1;
       }
     } else {
-      HIPCHK(c, launch_sort_sweep(c->KC, c->WP, kk, ww, T_img, key_bits, n_pass - m_top, !hist_in_expand && m_top > 0, tl,
+      HIPCHK(c, launch_sort_sweep(c->KC, c->WP, kk, ww, T_img, key_bits, n_pass - m_top, !hist_in_expand && m_top > 0, tl, sort_tile,
                                   (const uint64_t*)c->img_seg.p, (uint32_t*)c->ghist.p, (uint64_t*)c->sstatus.p, ctr,
                                   &c->epoch, (uint32_t*)c->err.p, &cur, c->stream, &c->prof,
                                   sorted_out ? c->pk[slot].p : nullptr, sorted_out ? c->pw[slot].p : nullptr), "sort");
@@ -1707,7 +1714,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
         c->mepoch += 1;
         mstatus = (uint64_t*)c->mstatus.p;
       }
-      HIPCHK(c, launch_merge(c->KC, c->WP, c->fp64_acc, c->ik[cur].p, c->iw[cur].p, T_img, tl, pas, sent,
+      HIPCHK(c, launch_merge(c->KC, c->WP, c->fp64_acc, c->ik[cur].p, c->iw[cur].p, T_img, tl, sort_tile, pas, sent,
                              c->pk[slot].p, c->pw[slot].p, T_img, (uint64_t*)c->pseg[slot].p, (uint32_t*)c->blk_cnt.p,
                              (uint64_t*)c->blk_off.p, (uint64_t*)c->scan_tmp.p, mstatus, ctr + kCtrMerge, c->mepoch,
                              (uint32_t*)c->err.p, sweep ? &fin : nullptr, c->stream, &c->prof), "merge");
@@ -1738,7 +1745,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
       HIPCHK(c, launch_fill_u64((uint64_t*)c->sstatus.p, c->sstatus.bytes / 8, 0ull, c->stream), "clear status");
       c->epoch = 0;
     }
-    HIPCHK(c, launch_sort_sweep(c->KC, c->WP, kk2, ww2, T_img, key_bits, 0, true, tl, (const uint64_t*)c->img_seg.p,
+    HIPCHK(c, launch_sort_sweep(c->KC, c->WP, kk2, ww2, T_img, key_bits, 0, true, tl, sort_tile, (const uint64_t*)c->img_seg.p,
                                 (uint32_t*)c->ghist.p, (uint64_t*)c->sstatus.p, ctr, &c->epoch, (uint32_t*)c->err.p,
                                 &cur2, c->stream, &c->prof), "sort");
     cur = pre_chunk ^ cur2;
@@ -3077,6 +3084,8 @@ qimax_status qimax_create(uint32_t n, const qimax_opts* opts, qimax_ctx** out) {
     if (env && env[0])
       c->chunk_tile = std::min<uint32_t>(std::max<uint32_t>((uint32_t)std::strtoul(env, nullptr, 10), kExpandTile),
                                          (uint32_t)kChunkCap);
+    env = std::getenv("QIMAX_SORT_TILE");  // 1024: small sort tiles in every round; 4096: in none
+    if (env && env[0]) c->small_sort_max = std::atoi(env) == kSmallSortTile ? ~0ull : 0;
     env = std::getenv("QIMAX_GATHER");  // 0: rounds of large fan-out expand every image
     c->gather = !(env && env[0] == '0');
     env = std::getenv("QIMAX_MERGE_FREE");  // 0: every pass sorted and merged

@@ -153,6 +153,7 @@ constexpr int kXcds = 8;  // accelerator complex dies of the chip; each has its 
 constexpr int kSortBlock = 256;            // threads per sort / merge block
 constexpr int kSortItems = 16;             // items per thread
 constexpr int kSortTile = kSortBlock * kSortItems;  // elements per tile (4096)
+constexpr int kSmallSortTile = kSortBlock * 4;  // ... where there are few of them (see small_sort_max)
 constexpr int kRadixBits = 8;
 constexpr uint32_t kSmallMaxSegs = 8192;  // segments of a small round (one block each)
 constexpr int kChunkCap = 4096;  // elements a chunk-local sort holds in LDS
@@ -292,7 +293,7 @@ hipError_t launch_sort_pass(int KC, int WP, const void* keys_in, const void* w_i
 // segments by their top digits only); upsweep: compute ghist for those passes first (else
 // it is current).
 hipError_t launch_sort_sweep(int KC, int WP, void* const keys[2], void* const w[2], uint64_t T, uint32_t key_bits,
-                             uint32_t p_begin, bool upsweep, const Tiling& tl, const uint64_t* seg_off,
+                             uint32_t p_begin, bool upsweep, const Tiling& tl, uint32_t tile, const uint64_t* seg_off,
                              uint32_t* ghist, uint64_t* status, uint32_t* tile_ctr, uint64_t* epoch, uint32_t* err,
                              int* cur, hipStream_t s, Prof* prof = nullptr, void* last_k = nullptr,
                              void* last_w = nullptr);
@@ -314,8 +315,8 @@ struct MergeFin {
   uint64_t seq;
 };
 hipError_t launch_merge(int KC, int WP, int fp64_acc, const void* keys_in, const void* w_in, uint64_t T,
-                        const Tiling& tl, const PassArgs* pas, const uint32_t* seg_entry, void* keys_out, void* w_out,
-                        uint64_t out_cap, uint64_t* seg_off_out, uint32_t* blk_cnt, uint64_t* blk_off, uint64_t* tmp,
+                        const Tiling& tl, uint32_t tile, const PassArgs* pas, const uint32_t* seg_entry,
+                        void* keys_out, void* w_out, uint64_t out_cap, uint64_t* seg_off_out, uint32_t* blk_cnt, uint64_t* blk_off, uint64_t* tmp,
                         uint64_t* status, uint32_t* tile_ctr, uint64_t epoch, uint32_t* err, const MergeFin* fin,
                         hipStream_t s, Prof* prof = nullptr);
 
