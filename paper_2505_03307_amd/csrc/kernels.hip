@@ -2370,7 +2370,7 @@ __global__ void __launch_bounds__(256) k_small_gather(const K* __restrict__ kslo
 // digit being an exact factor of +-1 taken apart) and every threshold are the general path's.
 // Measured, per step: the n = 16 two-layer ansatz in FP32 (1.7e8 images, 7.3e7 kept) 7.7 -> 3.3 ms,
 // expansion, sorts and merge of the second layer 6.9 -> 3.1; ten layers at n = 6 (6e6 images a
-// layer for 24570 terms) 6.0 -> 2.2 ms, the merge of long runs 3.5 ms of it before; n = 13 0.77 ->
+// layer for 24570 terms) 6.0 -> 1.5 ms, the merge of long runs 3.5 ms of it before; n = 13 0.77 ->
 // 0.57 ms. The plan takes 13 to 27 us (one block per generator).
 constexpr int kPlanBlock = 1024;
 template <typename K>
@@ -2646,8 +2646,14 @@ __device__ __forceinline__ K key_mul(K a, K b, uint32_t& neg) {
 // unit's image and the open digits' images. Outputs above the threshold are compacted in the
 // wave (ballots) and the tile's place found by look-back.
 // Bound: arithmetic and LDS reads of the matrix entries (one parent: the stores).
-template <typename K, int WP, int SW, typename Acc>
-__global__ void __launch_bounds__(gather_tile(SW == 3)) k_gather(GatherPlan gp, const uint64_t* __restrict__ goff,
+// Groups of many parents leave few units (n = 6, saturated: 132 waves of units for 1024 SIMDs,
+// 729 parents each at 420 cycles): there a team of eight waves forms the products and three of them
+// add, an output digit each (kTeam). That layer 0.128 -> 0.044 ms, of which 0.015 to 0.02 find the
+// units' groups and place the outputs; entries of four operators read at a time instead of one,
+// the n = 10 two-layer ansatz 0.042 -> 0.030 ms, n = 16 0.60 -> 0.54.
+constexpr uint32_t kTeamBlock = 512, kTeamChunk = 32;
+template <typename K, int WP, int SW, typename Acc, bool kTeam>
+__global__ void __launch_bounds__(kTeam ? kTeamBlock : gather_tile(SW == 3)) k_gather(GatherPlan gp, const uint64_t* __restrict__ goff,
                                                         const uint32_t* __restrict__ seg_tile,
                                                         const uint64_t* __restrict__ seg_in, uint32_t S, uint32_t n_tiles,
                                                         const PassArgs* __restrict__ pas,
@@ -2661,14 +2667,17 @@ __global__ void __launch_bounds__(gather_tile(SW == 3)) k_gather(GatherPlan gp, 
   using W = typename WTraits<WP>::W;
   constexpr int kTabN = table_entries<K>(), kTabS = table_sign_bytes<K>();
   constexpr uint32_t kTile = gather_tile(SW == 3);
-  constexpr int kOut = SW == 3 ? 27 : 3, kWaves = (int)kTile / 64;
+  constexpr uint32_t kBlock = kTeam ? kTeamBlock : kTile;
+  constexpr int kOut = SW == 3 ? 27 : 3, kWaves = (int)kBlock / 64;
+  static_assert(!kTeam || (SW == 1 && kTile == 64), "a team's waves share one wave of units");
   constexpr int kDescWords = (int)(sizeof(BlockDesc) / 8);
   __shared__ __align__(16) K tk[kTabN];
   __shared__ __align__(4) uint8_t tn[kTabS];
-  __shared__ uint64_t gsh[kMaxE1 * kDescWords];
+  __shared__ uint64_t gsh[kMaxE1 * kDescWords + 4];  // (then four ones)
   __shared__ uint64_t scan_sh[kWaves];
   __shared__ uint64_t base_sh;
   __shared__ uint32_t tile_sh, seg_sh, g_sh[2];
+  __shared__ W prod[kTeam ? 2 : 1][kTeam ? kTeamChunk : 1][3][kTeam ? 64 : 1];
   if (threadIdx.x == 0) {
     const uint32_t b = atomicAdd(ctr, 1u);  // launched with exactly n_tiles blocks
     uint32_t lo = 0, hi = S;                // last segment whose first tile is at most b: it has tiles
@@ -2688,7 +2697,8 @@ __global__ void __launch_bounds__(gather_tile(SW == 3)) k_gather(GatherPlan gp, 
   const uint64_t u0 = (uint64_t)(b - seg_tile[seg]) * kTile;
   const uint32_t n_u = (uint32_t)min<uint64_t>(kTile, U - u0);
   goff += a0;
-  for (uint32_t i = threadIdx.x; i < pa.nE1 * (uint32_t)kDescWords; i += kTile) gsh[i] = ((const uint64_t*)pa.G1)[i];
+  for (uint32_t i = threadIdx.x; i < pa.nE1 * (uint32_t)kDescWords; i += kBlock) gsh[i] = ((const uint64_t*)pa.G1)[i];
+  if (threadIdx.x < 4) ((W*)(gsh + kMaxE1 * kDescWords))[threadIdx.x] = (W)1;
   if (pa.useB) stage_table(pa.tB, tk, tn);
   // groups of the tile's first and last unit (by two waves where there are two)
   for (uint32_t k = threadIdx.x >> 6; k < 2; k += kWaves) {
@@ -2697,8 +2707,9 @@ __global__ void __launch_bounds__(gather_tile(SW == 3)) k_gather(GatherPlan gp, 
   }
   __syncthreads();
   const BlockDesc* const G = (const BlockDesc*)gsh;
-  const bool live = threadIdx.x < n_u;
-  const uint64_t u = u0 + min(threadIdx.x, n_u - 1);
+  const uint32_t ui = kTeam ? threadIdx.x & 63u : threadIdx.x;  // the thread's unit
+  const bool live = ui < n_u;
+  const uint64_t u = u0 + min(ui, n_u - 1);
   const uint32_t g = (uint32_t)(upper_bound_u64(goff, g_sh[0], (uint64_t)g_sh[1] + 1, u) - 1);
   const uint32_t p0 = gp.gstart[a0 + g], p1 = g + 1 < ng ? gp.gstart[a0 + g + 1] : n;
   const K* const pk = (const K*)gp.keys + a0;
@@ -2747,15 +2758,21 @@ __global__ void __launch_bounds__(gather_tile(SW == 3)) k_gather(GatherPlan gp, 
   Acc acc[kOut];
   // the matrix rows of the unit's first kPre operators and their digits' places, in registers (the
   // row's place in LDS in 8-byte or 4-byte entries): the loop over the parents then reads one
-  // entry per operator and nothing else; further operators are looked up as they come
+  // entry per operator and nothing else (ones where a lane's unit has fewer operators than
+  // another's); further operators are looked up as they come
   constexpr int kPre = SW == 1 ? 8 : 4;
   constexpr uint32_t kStride = (uint32_t)(sizeof(BlockDesc) / sizeof(W));
-  const W* const ent = (const W*)gsh + (WP == 64 ? offsetof(BlockDesc, r) / 8 : offsetof(BlockDesc, rf) / 4);
+  constexpr uint32_t kEnt = (uint32_t)(WP == 64 ? offsetof(BlockDesc, r) / 8 : offsetof(BlockDesc, rf) / 4);
+  constexpr uint32_t kOnes = (uint32_t)kMaxE1 * kStride - kEnt;  // (entries from ent on)
+  const W* const ent = (const W*)gsh + kEnt;
   uint32_t row[kPre], rpos[kPre];
   uint64_t rest = prefix;
+  uint32_t n_pre = 0;  // of the lane with most
 #pragma unroll
   for (int q = 0; q < kPre; ++q) {
-    row[q] = rpos[q] = ~0u;
+    row[q] = kOnes;
+    rpos[q] = 0;
+    n_pre += __ballot(rest != 0) != 0;
     if (rest) {
       const uint32_t e = (uint32_t)__ffsll((long long)rest) - 1;
       rest &= rest - 1;
@@ -2769,8 +2786,40 @@ __global__ void __launch_bounds__(gather_tile(SW == 3)) k_gather(GatherPlan gp, 
     const uint32_t e = open[m] == ~0u ? 0u : open[m];
     opos[m] = open[m] == ~0u ? 0u : G[e].pos;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) orow[m][i] = e * kStride + 4 * G[e].odig[oc[m]][i];
+    for (int i = 0; i < 3; ++i) orow[m][i] = open[m] == ~0u ? kOnes : e * kStride + 4 * G[e].odig[oc[m]][i];
   }
+  // kU parents' products with the unit's operators, and the open operators' entries
+  auto products = [&](const auto& kj, auto& v, auto count) {
+#pragma clang fp contract(off)
+    constexpr int kU = decltype(count)::value;
+    // four operators at a time, their reads in flight together (ones where there are fewer)
+#pragma unroll
+    for (int q4 = 0; q4 < kPre; q4 += 4) {
+      if ((uint32_t)q4 >= n_pre) break;
+      W x[4][kU];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int t = 0; t < kU; ++t) x[q][t] = ent[row[q4 + q] + get_d(kj[t], rpos[q4 + q])];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int t = 0; t < kU; ++t) v[t] *= x[q][t];
+    }
+    for (uint64_t m = rest; m; m &= m - 1) {
+      const uint32_t e = (uint32_t)__ffsll((long long)m) - 1, pos = G[e].pos, at = e * kStride + 4 * get_d(key, pos);
+#pragma unroll
+      for (int t = 0; t < kU; ++t) v[t] *= ent[at + get_d(kj[t], pos)];
+    }
+  };
+  auto entries = [&](K kj, W (&f)[SW][3]) {
+#pragma unroll
+    for (int m = 0; m < SW; ++m) {
+      const uint32_t in = get_d(kj, opos[m]);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) f[m][i] = ent[orow[m][i] + in];
+    }
+  };
   // kU parents at a time: their loads and products are independent, only the sums are in order
   auto parents = [&](uint32_t j, auto count) {
 #pragma clang fp contract(off)
@@ -2782,26 +2831,11 @@ __global__ void __launch_bounds__(gather_tile(SW == 3)) k_gather(GatherPlan gp, 
       kj[t] = pk[j + t];
       v[t] = pw[j + t];
     }
-#pragma unroll
-    for (int q = 0; q < kPre; ++q) {
-      if (row[q] == ~0u) break;
-#pragma unroll
-      for (int t = 0; t < kU; ++t) v[t] *= ent[row[q] + get_d(kj[t], rpos[q])];
-    }
-    for (uint64_t m = rest; m; m &= m - 1) {
-      const uint32_t e = (uint32_t)__ffsll((long long)m) - 1, pos = G[e].pos, at = e * kStride + 4 * get_d(key, pos);
-#pragma unroll
-      for (int t = 0; t < kU; ++t) v[t] *= ent[at + get_d(kj[t], pos)];
-    }
+    products(kj, v, count);
 #pragma unroll
     for (int t = 0; t < kU; ++t) {
       W f[SW][3];
-#pragma unroll
-      for (int m = 0; m < SW; ++m) {
-        const uint32_t in = get_d(kj[t], opos[m]);
-#pragma unroll
-        for (int i = 0; i < 3; ++i) f[m][i] = open[m] == ~0u ? (W)1 : ent[orow[m][i] + in];
-      }
+      entries(kj[t], f);
       if constexpr (SW == 1) {
 #pragma unroll
         for (int i = 0; i < 3; ++i)
@@ -2821,10 +2855,81 @@ __global__ void __launch_bounds__(gather_tile(SW == 3)) k_gather(GatherPlan gp, 
       }
     }
   };
-  constexpr uint32_t kBatch = SW == 1 ? 8 : 2;
-  uint32_t j = p0;
-  for (; p1 - j >= kBatch; j += kBatch) parents(j, std::integral_constant<int, (int)kBatch>{});
-  for (; j < p1; ++j) parents(j, std::integral_constant<int, 1>{});
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  if constexpr (!kTeam) {
+    constexpr uint32_t kBatch = SW == 1 ? 8 : 2;
+    uint32_t j = p0;
+    for (; p1 - j >= kBatch; j += kBatch) parents(j, std::integral_constant<int, (int)kBatch>{});
+    for (; j < p1; ++j) parents(j, std::integral_constant<int, 1>{});
+  } else {
+    // kTeamChunk parents at a time: every wave forms the products of its share of them for the
+    // 64 units, in LDS; the first three waves then add them in order, an output each, while the
+    // next chunk's are formed and the one after's loaded
+    constexpr int kShare = (int)kTeamChunk / kWaves;
+    const uint32_t len = p1 - p0;
+    uint32_t most = len;
+    for (int o = 32; o > 0; o >>= 1) most = max(most, (uint32_t)__shfl_xor(most, o, 64));
+    const uint32_t chunks = (most + kTeamChunk - 1) / kTeamChunk;
+    struct Share {
+      K k[kShare];
+      W v[kShare];
+    };
+    auto load = [&](uint32_t c, Share& x) {
+#pragma unroll
+      for (int t = 0; t < kShare; ++t) {
+        const uint32_t q = p0 + min(c * kTeamChunk + (uint32_t)(wid * kShare + t), len - 1);
+        x.k[t] = pk[q];
+        x.v[t] = pw[q];
+      }
+    };
+    auto form = [&](uint32_t c, Share& x) {
+#pragma clang fp contract(off)
+      products(x.k, x.v, std::integral_constant<int, kShare>{});
+#pragma unroll
+      for (int t = 0; t < kShare; ++t) {
+        W f[SW][3];
+        entries(x.k[t], f);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) prod[c & 1][wid * kShare + t][i][lane] = x.v[t] * f[0][i];
+      }
+    };
+    // chunk c formed, the one before added; the loads of chunk c + 2 stay in flight past the
+    // barrier, which orders LDS alone
+    auto step = [&](uint32_t c, Share& x) {
+      if (c < chunks) {
+        form(c, x);
+        load(c + 2, x);  // (past the parents: the last again)
+      }
+      if (c > 0 && c <= chunks && wid < 3) {
+        const uint32_t q0 = (c - 1) * kTeamChunk, nq = len > q0 ? min(len - q0, kTeamChunk) : 0u;
+        auto add = [&](auto all) {  // sixteen reads in flight at a time
+          for (uint32_t t0 = 0; t0 < kTeamChunk; t0 += 16) {
+            W y[16];
+#pragma unroll
+            for (uint32_t t = 0; t < 16; ++t) y[t] = prod[(c - 1) & 1][t0 + t][wid][lane];
+#pragma unroll
+            for (uint32_t t = 0; t < 16; ++t) {
+              Acc next = acc[0];
+              next.add(y[t]);
+              acc[0] = all.value || t0 + t < nq ? next : acc[0];
+            }
+          }
+        };
+        if (__all(nq == kTeamChunk)) add(std::true_type{});
+        else add(std::false_type{});
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
+    Share even, odd;
+    load(0, even);
+    load(1, odd);
+    for (uint32_t c = 0; c <= chunks; c += 2) {
+      step(c, even);
+      step(c + 1, odd);
+    }
+  }
   // kept outputs
   uint32_t keep = 0;
   W sum[kOut];
@@ -2832,11 +2937,11 @@ __global__ void __launch_bounds__(gather_tile(SW == 3)) k_gather(GatherPlan gp, 
   for (int o = 0; o < kOut; ++o) {
     sum[o] = acc[o].value();
     bool in;
-    if constexpr (SW == 1) in = (uint32_t)o < os[0];
+    if constexpr (kTeam) in = o == 0 && wid < 3 && (uint32_t)wid < os[0];  // wave i: the i-th open output
+    else if constexpr (SW == 1) in = (uint32_t)o < os[0];
     else in = (uint32_t)(o / 9) < os[0] && (uint32_t)(o / 3 % 3) < os[1] && (uint32_t)(o % 3) < os[2];
     if (live && in && fabs((double)sum[o]) > pa.thr) keep |= 1u << o;
   }
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   uint32_t wave_cnt = 0;
 #pragma unroll
   for (int o = 0; o < kOut; ++o) wave_cnt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64((keep >> o) & 1u));
@@ -2848,26 +2953,13 @@ __global__ void __launch_bounds__(gather_tile(SW == 3)) k_gather(GatherPlan gp, 
     if (w < wid) wave_at += scan_sh[w];
     tot += scan_sh[w];
   }
+  uint64_t excl = 0;
+  if (threadIdx.x < 64) {
+    if (threadIdx.x == 0) st_store(status + b, epoch << 48 | (b == 0 ? kStPre : kStAgg) | tot);
+    excl = look_back(status, b, epoch, err);
+  }
   if (threadIdx.x == 0) {
-    const uint64_t ep = epoch << 48;
-    st_store(status + b, ep | (b == 0 ? kStPre : kStAgg) | tot);
-    uint64_t excl = 0;
-    if (b > 0) {
-      uint32_t t = b - 1;
-      uint32_t spins = 0;
-      while (true) {
-        const uint64_t v = st_load(status + t);
-        const bool ready = (v >> 48) == epoch && (v & (kStAgg | kStPre));
-        if (!ready) {
-          if (++spins > kSpinLimit) { atomicOr(err, kErrSpin); break; }
-          continue;
-        }
-        excl += v & kStValMask;
-        if ((v & kStPre) || t == 0) break;
-        --t;
-      }
-      st_store(status + b, ep | kStPre | (excl + tot));
-    }
+    if (b > 0) st_store(status + b, epoch << 48 | kStPre | (excl + tot));
     base_sh = excl;
     // the segments this tile starts (with any before it that have no tiles), and after the last
     // tile the trailing ones and the total
@@ -2913,6 +3005,14 @@ __global__ void __launch_bounds__(gather_tile(SW == 3)) k_gather(GatherPlan gp, 
     at += (uint32_t)__popcll(bal);
   };
   auto times = [&](K k, K v, uint32_t& sg) -> K { return pa.useB ? key_mul(k, v, sg) : (K)(k | v); };
+  if constexpr (kTeam) {
+    if (wid < 3) {
+      uint32_t s1 = bneg ^ ((ineg[0] >> wid) & 1u);
+      const K k1 = times(key, wid == 0 ? ik[0][0] : wid == 1 ? ik[0][1] : ik[0][2], s1);
+      emit(0, k1, s1);
+    }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     uint32_t s1 = bneg ^ ((ineg[0] >> i) & 1u);
@@ -3816,19 +3916,22 @@ hipError_t launch_gather(int KC, int WP, int fp64_acc, int variant, const Gather
     return hipGetLastError();
   }
   hipEvent_t ev = prof_begin(prof, s, kKGather);
-#define QIMAX_GATHER(WPV, SWV, ACC)                                                                             \
-  k_gather<K, WPV, SWV, ACC><<<n_tiles, gather_tile(SWV == 3), 0, s>>>(gp, gp.goff[variant], gp.tiles[variant], seg_in, S, n_tiles, \
-                                                             pas, seg_entry, status, ctr, epoch, img_seg, (K*)keys_out,   \
-                                                             (typename WTraits<WPV>::W*)w_out, out_cap, err)
+#define QIMAX_GATHER(WPV, SWV, ACC, TEAM)                                                                          \
+  k_gather<K, WPV, SWV, ACC, TEAM><<<n_tiles, TEAM ? kTeamBlock : gather_tile(SWV == 3), 0, s>>>(                      \
+      gp, gp.goff[SWV == 3], gp.tiles[SWV == 3], seg_in, S, n_tiles, pas, seg_entry, status, ctr, epoch, img_seg,      \
+      (K*)keys_out, (typename WTraits<WPV>::W*)w_out, out_cap, err)
+#define QIMAX_GATHER_V(WPV, ACC)                         \
+  do {                                                   \
+    if (variant == 1) QIMAX_GATHER(WPV, 3, ACC, false);  \
+    else if (variant == 2) QIMAX_GATHER(WPV, 1, ACC, true); \
+    else QIMAX_GATHER(WPV, 1, ACC, false);               \
+  } while (0)
   QIMAX_DISPATCH_K(KC, {
-    if (WP == 64) {
-      if (variant) QIMAX_GATHER(64, 3, PlainSum<double>); else QIMAX_GATHER(64, 1, PlainSum<double>);
-    } else if (fp64_acc) {
-      if (variant) QIMAX_GATHER(32, 3, F64Sum); else QIMAX_GATHER(32, 1, F64Sum);
-    } else {
-      if (variant) QIMAX_GATHER(32, 3, RunSum<float>); else QIMAX_GATHER(32, 1, RunSum<float>);
-    }
+    if (WP == 64) QIMAX_GATHER_V(64, PlainSum<double>);
+    else if (fp64_acc) QIMAX_GATHER_V(32, F64Sum);
+    else QIMAX_GATHER_V(32, RunSum<float>);
   });
+#undef QIMAX_GATHER_V
 #undef QIMAX_GATHER
   prof_end(prof, s, ev, kKGather, 0.0);  // the outputs' bytes are added by the caller once known
   return hipGetLastError();

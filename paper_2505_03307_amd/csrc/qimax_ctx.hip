@@ -428,6 +428,7 @@ struct qimax_ctx {
   // 1024: 9 us), and past this the look-back over four times the tiles costs more.
   // Random circuits at n = 10, ten such rounds of 33: 3.99 -> 3.81 ms; with 2^23: 4.58.
   uint64_t small_sort_max = 1u << 17;
+  uint64_t team_images = 16;  // images per output from which gathered rounds work by teams of waves
   bool small_groups = true;  // consecutive small passes in one launch (k_small_passes)
   int dense_mode = 0;         // dense accumulation: 0 off, 1 wherever it applies, 2 a tuner candidate
   DevBuf dense_acc;           // its fixed-point slots
@@ -1584,11 +1585,14 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   } else if (gather) {
     // three operators in a unit where that leaves two waves per CU and more: the n = 12 ansatz
     // (59 Ki such units) 0.12 ms against 0.23 with one, n = 10 (7 Ki) 0.10 against 0.07, the
-    // saturated n = 6 one (1 Ki) 0.42 against 0.13 per layer
-    const int variant = g_units[1][S] >= (1ull << 15) ? 1 : 0;
+    // saturated n = 6 one (1 Ki) 0.42 against 0.13 per layer. With few units of many parents the
+    // waves that are there are too few: by teams (that layer 0.13 -> 0.043 ms; at an image or two
+    // per output the seven more waves only set up: n = 10 0.030 -> 0.036 ms)
+    const int by = g_units[1][S] >= (1ull << 15) ? 1 : 0;
+    const int variant = by == 0 && g_images[S] / c->team_images >= so_cap[S] ? 2 : by;
     uint64_t n_tiles = 0;
     for (uint32_t s = 0; s < S; ++s)
-      n_tiles += (g_units[variant][s + 1] - g_units[variant][s] + gather_tile(variant) - 1) / gather_tile(variant);
+      n_tiles += (g_units[by][s + 1] - g_units[by][s] + gather_tile(variant) - 1) / gather_tile(variant);
     if (n_tiles > 0x7FFFFFFFull) return fail(c, QIMAX_ETOOLARGE, "gather: too many outputs");
     QCHK(status_words(n_tiles));
     c->mepoch += 1;
@@ -3086,6 +3090,8 @@ qimax_status qimax_create(uint32_t n, const qimax_opts* opts, qimax_ctx** out) {
                                          (uint32_t)kChunkCap);
     env = std::getenv("QIMAX_SORT_TILE");  // 1024: small sort tiles in every round; 4096: in none
     if (env && env[0]) c->small_sort_max = std::atoi(env) == kSmallSortTile ? ~0ull : 0;
+    env = std::getenv("QIMAX_GATHER_TEAM");  // 1: teams of waves in all of their small variant; 0: in none
+    if (env && env[0]) c->team_images = env[0] == '0' ? ~0ull : 1;
     env = std::getenv("QIMAX_GATHER");  // 0: rounds of large fan-out expand every image
     c->gather = !(env && env[0] == '0');
     env = std::getenv("QIMAX_MERGE_FREE");  // 0: every pass sorted and merged

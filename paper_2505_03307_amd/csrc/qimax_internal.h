@@ -446,7 +446,7 @@ struct GatherPlan {
   uint32_t* tiles[2];  // S + 1: first tile (of gather_tile units) of every segment
 };
 // units of a tile, one thread each: variant 0 in blocks of one wave (few units: on more CUs)
-constexpr uint32_t gather_tile(int variant) { return variant ? 256u : 64u; }
+constexpr uint32_t gather_tile(int variant) { return variant == 1 ? 256u : 64u; }  // (2: as 0, by teams of waves)
 uint32_t gather_cap(int KC);
 // result: the scanned totals, four arrays of S + 1 words, then the error word and seq.
 hipError_t launch_gather_plan(int KC, int WP, const void* keys, const void* w, const uint64_t* seg_in, uint32_t S,

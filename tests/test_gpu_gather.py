@@ -174,3 +174,16 @@ def test_first_layer_of_single_strings(monkeypatch, n, weight):
     g = [_both(monkeypatch, make, QIMAX_SMALL_GROUPS=v) for v in "01"]
     for x in (g[0][1], g[1][0], g[1][1]):
         _same(g[0][0], x)
+
+
+@pytest.mark.parametrize("precision,merge", [(64, 0), (32, 0), (32, 1)])
+@pytest.mark.parametrize("n,layers", [(1, 3), (2, 5), (3, 6), (4, 5), (6, 4), (9, 2), (18, 1)])
+def test_teams_of_waves(monkeypatch, n, layers, precision, merge):
+    """Parents a chunk of the team's, fewer and more; units of one group and of several in a wave."""
+    c = W.c3_hea(n, n, layers, 0.0) if n < 16 else W.random_circuit(1, n, 3 * n)
+    got = []
+    for v in "01":
+        monkeypatch.setenv("QIMAX_GATHER_TEAM", v)
+        with Simulator(n, precision=precision, fp32_merge=merge) as s:
+            got.append(s.run(c).generators())
+    _same(*got)
