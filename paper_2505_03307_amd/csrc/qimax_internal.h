@@ -65,8 +65,8 @@ constexpr int kMaxE1 = 64;  // one-qubit operators of a pass
 // multiplicative, so the image of a whole key is the product of its parts' images (they
 // commute) with the product's phase.
 // Keys of 4 and 8 bytes: byte k of a key holds the digits of four qubits; tab_key[k*256 + b] is
-// the image key of that 4-qubit Pauli string under the chain and tab_neg[k*256 + b] its sign
-// bit (bit 0) and number of Y digits mod 4 (bits 1-2).
+// the image key of that 4-qubit Pauli string under the chain and tab_neg[k*256 + b] its number
+// of Y digits, and two more where its sign is negative, mod 4.
 // 16-byte keys: a group is four key bits (two qubits); tab_key[g*16 + v] is the image of the
 // string v of group g as its x plane (low 64 bits) and z plane (high), bit k of a plane being
 // the qubit at key bits 2k, 2k+1; tab_neg holds one 32-bit word per group, bits 2v, 2v+1 of it
