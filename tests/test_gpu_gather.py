@@ -177,7 +177,7 @@ def test_first_layer_of_single_strings(monkeypatch, n, weight):
 
 
 @pytest.mark.parametrize("precision,merge", [(64, 0), (32, 0), (32, 1)])
-@pytest.mark.parametrize("n,layers", [(1, 3), (2, 5), (3, 6), (4, 5), (6, 4), (9, 2), (18, 1)])
+@pytest.mark.parametrize("n,layers", [(1, 3), (2, 5), (3, 6), (4, 5), (6, 4), (9, 2), (18, 1), (36, 1)])
 def test_teams_of_waves(monkeypatch, n, layers, precision, merge):
     """Parents a chunk of the team's, fewer and more; units of one group and of several in a wave."""
     c = W.c3_hea(n, n, layers, 0.0) if n < 16 else W.random_circuit(1, n, 3 * n)
