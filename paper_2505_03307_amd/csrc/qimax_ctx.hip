@@ -1315,7 +1315,13 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
     c->st.alg_bytes += alg * (double)(c->kb + c->wb);
     c->st.rounds += 1;
     c->st.images += so_img[S];
-    c->st.sort_elems += plain ? 0 : (gather ? so_out[S] : so_img[S]) * n_pass;
+    uint64_t as_they_come = 0;  // images of a small round's unsorted passes
+    if (small)
+      for (uint32_t s = 0; s < S; ++s) {
+        const RoundEntry& en = entries[seg_entry[s]];
+        if (!en.drop && en.pass && en.pass->unsorted) as_they_come += so_img[s + 1] - so_img[s];
+      }
+    c->st.sort_elems += plain ? 0 : ((gather ? so_out[S] : so_img[S]) - as_they_come) * n_pass;
     return QIMAX_OK;
   };
   Tiling tl_in{};

@@ -120,3 +120,24 @@ def test_calls_after_a_replay(monkeypatch):
             g.close()
             return r
     _same(_with(monkeypatch, "0", make), _with(monkeypatch, "1", make))
+
+
+@pytest.mark.parametrize("precision", [64, 32])
+@pytest.mark.parametrize("spins", ["0", "64"])
+@pytest.mark.parametrize("sizes", [[(12, 14), (9, 12), (16, 6)], [(30, 12), (21, 5), (18, 13)], [(40, 11), (64, 13), (33, 4)]])
+def test_small_rounds(monkeypatch, sizes, spins, precision):
+    """Segments that fit a chunk leave it as they come beside others that are sorted, at once and
+    deferred: the terms of sorting every pass."""
+    cs = [W.c2_clifford_rz(seed=70 + i, n=n, depth=40 + 25 * i, n_rz=k) for i, (n, k) in enumerate(sizes)]
+    monkeypatch.setenv("QIMAX_DEFER_SPINS", spins)
+    monkeypatch.setenv("QIMAX_SMALL_GROUPS", "0")
+
+    def make():
+        with Batch(precision=precision, max_n=max(c.n for c in cs)) as b:
+            ids = [b.submit(c) for c in cs]
+            while b.step():
+                pass
+            return [x for i in ids for x in b.fetch(i)]
+    got = [_with(monkeypatch, v, make) for v in "01"]
+    for x, y in zip(*got):
+        assert np.array_equal(x, y)
