@@ -3734,7 +3734,9 @@ struct BatchCirc {
   std::vector<Pass> passes;
   std::vector<double> thr;
   size_t next = 0;
-  int state = 0;  // 0 queued, 1 active, 2 draining (result taken; terms leave next round), 3 done
+  // 0 queued, 1 active, 5 run to its end (result still on the device), 2 draining (result handed
+  // over; terms leave next round), 4 draining and fetched, 3 done
+  int state = 0;
   uint64_t updates = 0;
   std::vector<uint64_t> res_off;
   // the result, terms in memory that is first written by the threads that copy it there
@@ -3756,6 +3758,7 @@ struct qimax_batch {
   std::vector<uint64_t> so{0};  // host segment offsets of the term array
   bool seg_ready = false;       // the context's device offsets are these
   uint64_t rounds = 0;
+  uint64_t results = 0, fail_result = 0;  // results taken so far, and the one to fail (tests)
 };
 
 namespace {
@@ -3860,7 +3863,8 @@ qimax_status admit(qimax_batch* b) {
 }
 
 // Copy a finished circuit's generators (segments [s0, s0+n) of the committed array) to the host.
-qimax_status take_result(qimax_batch* b, BatchCirc& bc, size_t s0) {
+// Where that fails the circuit is as before, and the call can be made again.
+qimax_status take_result(qimax_batch* b, BatchCirc& bc, size_t s0) try {
   qimax_ctx* c = b->c;
   // a round returns once its offsets are in, while its compaction may still write the
   // terms: wait for the stream before copying them (the copies below are not ordered after
@@ -3872,9 +3876,9 @@ qimax_status take_result(qimax_batch* b, BatchCirc& bc, size_t s0) {
   const size_t T = e - a;
   const uint32_t n_words = bc.n <= 32 ? 1u : 2u;
   bc.res_terms = T;
-  bc.res_w.reset(new (std::nothrow) double[std::max<size_t>(T, 1)]);
-  bc.res_key.reset(new (std::nothrow) uint64_t[std::max<size_t>(T, 1) * n_words]);
-  if (!bc.res_w || !bc.res_key) return fail(c, QIMAX_ENOMEM, "no host memory for a circuit's result");
+  bc.res_w.reset(new double[std::max<size_t>(T, 1)]);
+  bc.res_key.reset(new uint64_t[std::max<size_t>(T, 1) * n_words]);
+  if (++b->results == b->fail_result) throw std::bad_alloc();
   bool done = false;
   QCHK(read_terms(c, a, T, n_words == 1 ? kReadWords1 : kReadWords2, bc.n, bc.res_key.get(), nullptr, bc.res_w.get(),
                   &done));
@@ -3891,17 +3895,52 @@ qimax_status take_result(qimax_batch* b, BatchCirc& bc, size_t s0) {
     for (size_t i = 0; i < T; ++i) bc.res_w[i] = w32[i];
   }
   return QIMAX_OK;
+} catch (const std::bad_alloc&) {
+  return fail(b->c, QIMAX_ENOMEM, "no host memory for a circuit's result");
+}
+
+// Hands over the results of the circuits that have run to their end. One that fails, and those
+// after it, stay so, their terms in the array: the next step tries again before anything else.
+qimax_status hand_over(qimax_batch* b) {
+  size_t s0 = 0;
+  bool any = false, active = false;
+  for (uint64_t id : b->order) {
+    BatchCirc& bc = b->circs.at(id);
+    if (bc.state == 5) {
+      QCHK(take_result(b, bc, s0));
+      bc.state = 2;
+      b->done.push_back(bc.id);
+      any = true;
+    }
+    active |= bc.state == 1;
+    s0 += bc.n;
+  }
+  if (!any || active) return QIMAX_OK;
+  for (uint64_t id : b->order) {  // every circuit left has handed over its result: empty the array
+    BatchCirc& bc = b->circs.at(id);
+    if (bc.state == 4) b->circs.erase(id);
+    else bc.state = 3;
+  }
+  b->order.clear();
+  b->so.assign(1, 0);
+  b->seg_ready = false;
+  b->c->T = 0;
+  return QIMAX_OK;
 }
 
 size_t active_count(const qimax_batch* b) {
   size_t k = 0;
-  for (uint64_t id : b->order)
-    if (b->circs.at(id).state == 1) ++k;
+  for (uint64_t id : b->order) {
+    const int state = b->circs.at(id).state;
+    if (state == 1 || state == 5) ++k;
+  }
   return k + b->queue.size();
 }
 
 // After a round (or a group of passes) over the array: its output, in pass slot 0 with segment
 // offsets so_out, becomes the array, circuit e having run adv[e] passes with upd[e] term updates.
+// Every circuit's place is brought up to date before the first result is handed over (which can
+// fail for want of memory).
 qimax_status batch_advance(qimax_batch* b, const std::vector<uint64_t>& so_out, const std::vector<uint64_t>& upd,
                            const std::vector<size_t>& adv, size_t* n_active) {
   qimax_ctx* c = b->c;
@@ -3910,7 +3949,7 @@ qimax_status batch_advance(qimax_batch* b, const std::vector<uint64_t>& so_out, 
   std::swap(c->seg, c->pseg[0]);
   b->so = so_out;
   c->T = so_out.back();
-  // finished circuits hand over their result; dropped ones leave the segment list
+  // dropped circuits leave the segment list
   std::vector<uint64_t> keep_order, erase;
   std::vector<uint64_t> keep_so{0};
   size_t s0 = 0;
@@ -3921,11 +3960,7 @@ qimax_status batch_advance(qimax_batch* b, const std::vector<uint64_t>& so_out, 
     if (bc.state == 1) {
       for (size_t k = 0; k < adv[e]; ++k, ++bc.next)
         if (!bc.passes[bc.next].E.empty()) c->st.passes += 1;
-      if (bc.next == bc.passes.size()) {
-        QCHK(take_result(b, bc, s0));
-        bc.state = 2;
-        b->done.push_back(bc.id);
-      }
+      if (bc.next == bc.passes.size()) bc.state = 5;
     } else {  // dropped this round: no terms left in the array
       leaves = true;
       if (bc.state == 4) erase.push_back(bc.id);
@@ -3938,19 +3973,12 @@ qimax_status batch_advance(qimax_batch* b, const std::vector<uint64_t>& so_out, 
     s0 += bc.n;
   }
   for (uint64_t id : erase) b->circs.erase(id);
-  bool still_active = false;
-  for (uint64_t id : keep_order) still_active |= b->circs.at(id).state == 1;
-  if (!still_active) {  // every remaining circuit has handed over its result: empty the array
-    for (uint64_t id : keep_order) b->circs.at(id).state = 3;
-    keep_order.clear();
-    keep_so.assign(1, 0);
-    c->T = 0;
-  }
   // the dropped circuits hold no terms any more, so the kept segments stay contiguous (and their
   // offsets on the device are those of the round unless a segment went)
   b->seg_ready = keep_so.size() == b->so.size() && c->T > 0;
   b->order.swap(keep_order);
   b->so.swap(keep_so);
+  QCHK(hand_over(b));
   if (n_active) *n_active = active_count(b);
   return QIMAX_OK;
 }
@@ -4078,6 +4106,8 @@ qimax_status qimax_batch_create(const qimax_opts* opts, uint32_t max_n, qimax_ba
   }
   b->c = c;
   b->max_n = cls;
+  const char* env = std::getenv("QIMAX_FAIL_RESULT");  // k: the k-th result finds no host memory (tests)
+  if (env && env[0]) b->fail_result = std::strtoull(env, nullptr, 10);
   c->T = 0;
   c->h_seg.assign(1, 0);
   *out = b;
@@ -4114,6 +4144,7 @@ qimax_status qimax_batch_step(qimax_batch* b, size_t* n_active) {
   qimax_ctx* c = b->c;
   BusyTimer bt(c);
   if (c->broken) return bfail(b, QIMAX_ESTATE, "batch unusable after an earlier device error");
+  QCHK(hand_over(b));  // (results that an earlier step could not hand over)
   QCHK(admit(b));
   // one entry per circuit in the array: its next pass, or a drop of a finished circuit
   std::vector<RoundEntry> entries;
@@ -4163,6 +4194,7 @@ qimax_status qimax_batch_run(qimax_batch* b) {
     bool ran = false;
     if (!b->c->broken) {
       BusyTimer bt(b->c);
+      QCHK(hand_over(b));
       QCHK(admit(b));
       if (!b->order.empty()) QCHK(batch_group(b, &act, &ran));
     }
@@ -4186,7 +4218,7 @@ qimax_status qimax_batch_fetch(qimax_batch* b, uint64_t id, uint64_t* gen_off, u
   auto it = b->circs.find(id);
   if (it == b->circs.end()) return bfail(b, QIMAX_EINVAL, "unknown circuit id");
   BatchCirc& bc = it->second;
-  if (bc.state < 2) return bfail(b, QIMAX_ESTATE, "circuit not finished");
+  if (bc.state < 2 || bc.state == 5) return bfail(b, QIMAX_ESTATE, "circuit not finished");
   *T = bc.res_terms;
   if (cap < bc.res_terms) return QIMAX_OK;
   if (!gen_off || (*T && (!keys || !w))) return bfail(b, QIMAX_EINVAL, "output buffers are NULL");
@@ -4208,9 +4240,7 @@ qimax_status qimax_batch_fetch(qimax_batch* b, uint64_t id, uint64_t* gen_off, u
 qimax_status qimax_batch_info(const qimax_batch* b, qimax_batch_info_t* out) {
   if (!b || !out) return QIMAX_EINVAL;
   out->queued = b->queue.size();
-  out->active = 0;
-  for (uint64_t id : b->order)
-    if (b->circs.at(id).state == 1) ++out->active;
+  out->active = active_count(b) - b->queue.size();
   out->finished = b->done.size();
   out->rounds = b->rounds;
   out->terms = b->so.back();
