@@ -443,6 +443,7 @@ struct qimax_ctx {
   size_t pinned_words = 0;
 
   size_t alloc_bytes = 0, peak_bytes = 0;
+  uint64_t growths = 0, fail_from = 0, fail_count = 0;  // device allocations so far, and those to fail (tests)
   std::string last_error;
   bool broken = false;
   qimax_stats st{};
@@ -509,6 +510,14 @@ void dev_free(qimax_ctx* c, DevBuf& b) {
   b.bytes = 0;
 }
 
+// Device memory for a context's buffer.
+hipError_t dev_malloc(qimax_ctx* c, void** p, size_t bytes) {
+  *p = nullptr;
+  c->growths += 1;
+  if (c->growths >= c->fail_from && c->growths - c->fail_from < c->fail_count) return hipErrorOutOfMemory;
+  return hipMalloc(p, bytes);
+}
+
 // Gives back the memory the context can do without (see qimax_ctx::chain_parts); false if it
 // holds none or a call is using it.
 void drop_sv(qimax_ctx* c) {
@@ -557,7 +566,7 @@ qimax_status ensure(qimax_ctx* c, DevBuf& b, size_t bytes, bool headroom = true)
     dev_free(c, b);
   }
   void* p = nullptr;
-  hipError_t e = hipMalloc(&p, want);
+  hipError_t e = dev_malloc(c, &p, want);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     if (drop_optional(c)) return ensure(c, b, bytes, headroom);
@@ -584,7 +593,7 @@ qimax_status ensure_keep(qimax_ctx* c, DevBuf& b, size_t bytes, size_t keep) {
       return fail(c, QIMAX_ENOMEM, "memory cap exceeded (requested " + std::to_string(bytes) + " bytes)");
     }
   }
-  hipError_t e = hipMalloc(&nb.p, want);
+  hipError_t e = dev_malloc(c, &nb.p, want);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     if (drop_optional(c)) return ensure_keep(c, b, bytes, keep);
@@ -618,7 +627,7 @@ qimax_status ensure_sv(qimax_ctx* c, size_t bytes) {
   }
   for (;;) {
     if (!c->cap || c->alloc_bytes + bytes <= c->cap) {
-      if (hipMalloc(&c->sv_mem, bytes) == hipSuccess) break;
+      if (dev_malloc(c, &c->sv_mem, bytes) == hipSuccess) break;
       (void)hipGetLastError();
       c->sv_mem = nullptr;
     }
@@ -630,6 +639,13 @@ qimax_status ensure_sv(qimax_ctx* c, size_t bytes) {
   return QIMAX_OK;
 }
 
+// A failed call's status, after what the call has queued: those launches read the staging areas and
+// descriptors, which the next call (or another way of doing the same) writes again.
+qimax_status settled(qimax_ctx* c, qimax_status s) {
+  if (s != QIMAX_OK && !c->rec && !c->broken) (void)hipStreamSynchronize(c->stream);
+  return s;
+}
+
 // Runs a call's work, and once more without the memory it can do without where that left too
 // little (a failing call leaves the state as it was).
 template <typename F>
@@ -638,7 +654,7 @@ qimax_status with_optional(qimax_ctx* c, const F& body) {
   const std::vector<uint64_t> upd0 = c->gen_updates;
   const int64_t base0 = c->group_base;
   c->opt_busy = true;
-  qimax_status s = body();
+  qimax_status s = settled(c, body());
   c->opt_busy = false;
   bool dropped = false;
   if (s == QIMAX_ENOMEM && !c->lean)
@@ -648,7 +664,7 @@ qimax_status with_optional(qimax_ctx* c, const F& body) {
     c->st = st0;
     c->gen_updates = upd0;
     c->group_base = base0;
-    s = body();
+    s = settled(c, body());
   }
   return s;
 }
@@ -2003,7 +2019,20 @@ qimax_status launch_group(qimax_ctx* c, const std::vector<RoundEntry>& en, const
   RoundDesc rd;
   QCHK(build_round_desc(c, en, seg_first, rd, seg_len));
   const uint64_t T_in = so_in[S];
+  // every buffer before the first launch: where one cannot be had nothing is queued
   QCHK(ensure(c, c->tile_ctr, 256 * 4));
+  const size_t eb = c->kb, wbt = c->wb;
+  const uint64_t n_work = (uint64_t)S * kChunkCap;
+  for (int i = 0; i < 2; ++i) {
+    QCHK(ensure(c, c->ik[i], n_work * eb));
+    QCHK(ensure(c, c->iw[i], n_work * wbt));
+  }
+  QCHK(ensure(c, c->pk[slot], n_work * eb));
+  QCHK(ensure(c, c->pw[slot], n_work * wbt));  // (also the images' weights during the passes)
+  QCHK(ensure(c, c->pseg[slot], (S + 1) * 8));
+  const size_t cnt_words = (k * S * 3 + 1) / 2;
+  QCHK(ensure(c, c->grp_cnt, cnt_words * 8));
+  QCHK(ensure_zres(c, cnt_words + 2));
   {
     // the round's first launch clears the error word and counters and pulls the descriptors
     // (the input tiling it also builds is not used by the group)
@@ -2022,18 +2051,6 @@ qimax_status launch_group(qimax_ctx* c, const std::vector<RoundEntry>& en, const
                                  (uint32_t*)c->ghist.p, 0, s_in, S, job, T_in, c->stream), "round start");
   }
   HIPCHK(c, launch_build_tables(c->KC, rd.tables, c->stream, &c->prof), "chain tables");
-  const size_t eb = c->kb, wbt = c->wb;
-  const uint64_t n_work = (uint64_t)S * kChunkCap;
-  for (int i = 0; i < 2; ++i) {
-    QCHK(ensure(c, c->ik[i], n_work * eb));
-    QCHK(ensure(c, c->iw[i], n_work * wbt));
-  }
-  QCHK(ensure(c, c->pk[slot], n_work * eb));
-  QCHK(ensure(c, c->pw[slot], n_work * wbt));  // (also the images' weights during the passes)
-  QCHK(ensure(c, c->pseg[slot], (S + 1) * 8));
-  const size_t cnt_words = (k * S * 3 + 1) / 2;
-  QCHK(ensure(c, c->grp_cnt, cnt_words * 8));
-  QCHK(ensure_zres(c, cnt_words + 2));
   c->zres[cnt_words + 1] = 0;
   void* const ks[2] = {c->ik[0].p, c->ik[1].p};
   void* const ws[2] = {c->iw[0].p, c->iw[1].p};
@@ -3108,6 +3125,12 @@ qimax_status qimax_create(uint32_t n, const qimax_opts* opts, qimax_ctx** out) {
     c->classic_passes = env && env[0] == '1';
     env = std::getenv("QIMAX_WIDE_OFFSETS");  // 1: the count's and expansion's paths for huge rounds
     c->wide_offsets = env && env[0] == '1';
+    env = std::getenv("QIMAX_FAIL_ALLOC");  // k or k:m: m device allocations from the k-th on fail (tests)
+    if (env && env[0]) {
+      c->fail_from = std::strtoull(env, nullptr, 10);
+      const char* m = std::strchr(env, ':');
+      c->fail_count = m ? std::strtoull(m + 1, nullptr, 10) : 1;
+    }
     env = std::getenv("QIMAX_AUTOTUNE");  // 0: always the heuristic's sort variant
     c->autotune = !(env && env[0] == '0');
   }
@@ -4050,8 +4073,8 @@ qimax_status batch_group(qimax_batch* b, size_t* n_active, bool* ran) {
   QCHK(batch_offsets(b));
   const uint32_t S = (uint32_t)first.size();
   c->opt_busy = true;  // (a round gives up memory for room; a group does not)
-  const qimax_status st = launch_group(c, en, first, &len, k, c->keys.p, c->w.p, (const uint64_t*)c->seg.p, b->so, 0,
-                                       nullptr);
+  const qimax_status st = settled(c, launch_group(c, en, first, &len, k, c->keys.p, c->w.p,
+                                                  (const uint64_t*)c->seg.p, b->so, 0, nullptr));
   c->opt_busy = false;
   if (st == QIMAX_ENOMEM) return QIMAX_OK;
   QCHK(st);
