@@ -394,13 +394,14 @@ struct qimax_ctx {
   DevBuf cnt, off, scan_tmp, hist, hist_off, blk_begin, blk_end, blk_seg, seg_blk, blk_cnt, blk_off, img_seg;
   DevBuf desc, desc2, err;
   DevBuf ptab;  // chain tables of a whole call, compiled in one launch
-  // Memory a context can do without: the scratch of long chains' joins (chain_parts) and the
-  // tables of 16-byte keys (wtab for a round's, ptab for a call's). Where it leaves too little
-  // for the rest, it is given back and the call runs again without it (lean from then on).
-  DevBuf chain_parts, wtab;
+  DevBuf chain_parts, wtab;  // scratch of long chains' joins; a round's tables of 16-byte keys
+  // A call that runs out of memory runs once more in its leanest form (see with_retry): lean while
+  // it does, and for the next lean_left calls where memory has been short before. busy: a call is
+  // using the scratch buffers.
+  bool busy = false, lean = false;
+  uint32_t lean_left = 0, lean_next = 0;
   void* sv_mem = nullptr;  // the statevector readout's memory (no part of a recorded step)
   size_t sv_bytes = 0;
-  bool opt_busy = false, lean = false;
   DevBuf akeys, asign;  // input terms after their pass's A chain, and the signs (count -> expand)
   DevBuf chunk_off, chunk_cnt, chunk_start;  // chunk-local merge: offset, kept terms, deferred runs per chunk
   DevBuf gat;      // gathered rounds: parents by group, groups, totals (see GatherPlan)
@@ -518,8 +519,26 @@ hipError_t dev_malloc(qimax_ctx* c, void** p, size_t bytes) {
   return hipMalloc(p, bytes);
 }
 
-// Gives back the memory the context can do without (see qimax_ctx::chain_parts); false if it
-// holds none or a call is using it.
+// Every device buffer but the state (the terms with their offsets, the error word) and the grouping
+// pass's: between calls they hold nothing.
+std::vector<DevBuf*> scratch(qimax_ctx* c) {
+  return {&c->pk[0], &c->pk[1], &c->pw[0], &c->pw[1], &c->pseg[0], &c->pseg[1], &c->ik[0], &c->ik[1], &c->iw[0],
+          &c->iw[1], &c->cnt, &c->off, &c->scan_tmp, &c->hist, &c->hist_off, &c->blk_begin, &c->blk_end, &c->blk_seg,
+          &c->seg_blk, &c->blk_cnt, &c->blk_off, &c->img_seg, &c->desc, &c->desc2, &c->ghist, &c->sbase, &c->sstatus,
+          &c->tile_ctr, &c->mstatus, &c->dtile[0], &c->dtile[1], &c->dtile[2], &c->ptab, &c->chain_parts, &c->wtab,
+          &c->akeys, &c->asign, &c->img_cnt, &c->dense_acc, &c->chunk_cnt, &c->chunk_start, &c->chunk_off,
+          &c->grp_cnt, &c->gat};
+}
+
+bool drop_scratch(qimax_ctx* c) {
+  bool any = false;
+  for (DevBuf* b : scratch(c)) any |= b->p != nullptr;
+  if (!any) return false;
+  (void)hipStreamSynchronize(c->stream);
+  for (DevBuf* b : scratch(c)) dev_free(c, *b);
+  return true;
+}
+
 void drop_sv(qimax_ctx* c) {
   if (!c->sv_mem) return;
   (void)hipFree(c->sv_mem);
@@ -528,20 +547,16 @@ void drop_sv(qimax_ctx* c) {
   c->sv_bytes = 0;
 }
 
-bool drop_optional(qimax_ctx* c) {
-  if (c->sv_mem && !c->rec) {  // (no propagation uses it)
+// Gives back memory that an allocation is short of: the statevector readout's (no propagation uses
+// it), or, between calls, the scratch buffers. False if there is none.
+bool give_back(qimax_ctx* c) {
+  if (c->rec) return false;
+  if (c->sv_mem) {
     (void)hipStreamSynchronize(c->stream);
     drop_sv(c);
     return true;
   }
-  DevBuf* const opt[] = {&c->chain_parts, &c->wtab, c->kb > 8 ? &c->ptab : nullptr};
-  bool any = false;
-  for (DevBuf* b : opt) any |= b && b->p;
-  if (!any || c->opt_busy || c->rec) return false;
-  (void)hipStreamSynchronize(c->stream);
-  for (DevBuf* b : opt)
-    if (b) dev_free(c, *b);
-  return true;
+  return !c->busy && drop_scratch(c);
 }
 
 // Grow-only device buffer with the context's memory cap.
@@ -550,14 +565,14 @@ qimax_status ensure(qimax_ctx* c, DevBuf& b, size_t bytes, bool headroom = true)
   if (c->rec) return fail(c, QIMAX_ESTATE, "a device buffer must grow while recording: run the step once first");
   c->buf_gen += 1;
   size_t want = bytes == 0 ? 256 : bytes;
-  if (headroom) want = want + want / 4;
+  if (headroom && !c->lean) want = want + want / 4;
   want = (want + 255) & ~(size_t)255;
   const size_t after = c->alloc_bytes - b.bytes + want;
   if (c->cap && after > c->cap) {
     if (bytes > 0 && c->alloc_bytes - b.bytes + bytes <= c->cap)
       want = (bytes + 255) & ~(size_t)255;
     if (c->alloc_bytes - b.bytes + want > c->cap) {
-      if (drop_optional(c)) return ensure(c, b, bytes, headroom);
+      if (give_back(c)) return ensure(c, b, bytes, headroom);
       return fail(c, QIMAX_ENOMEM, "memory cap exceeded (requested " + std::to_string(bytes) + " bytes)");
     }
   }
@@ -569,7 +584,7 @@ qimax_status ensure(qimax_ctx* c, DevBuf& b, size_t bytes, bool headroom = true)
   hipError_t e = dev_malloc(c, &p, want);
   if (e != hipSuccess) {
     (void)hipGetLastError();
-    if (drop_optional(c)) return ensure(c, b, bytes, headroom);
+    if (give_back(c)) return ensure(c, b, bytes, headroom);
     return fail(c, QIMAX_ENOMEM, "hipMalloc of " + std::to_string(want) + " bytes failed");
   }
   b.p = p;
@@ -589,14 +604,14 @@ qimax_status ensure_keep(qimax_ctx* c, DevBuf& b, size_t bytes, size_t keep) {
   if (c->cap && c->alloc_bytes + want > c->cap) {
     want = align256(bytes);
     if (c->alloc_bytes + want > c->cap) {
-      if (drop_optional(c)) return ensure_keep(c, b, bytes, keep);
+      if (give_back(c)) return ensure_keep(c, b, bytes, keep);
       return fail(c, QIMAX_ENOMEM, "memory cap exceeded (requested " + std::to_string(bytes) + " bytes)");
     }
   }
   hipError_t e = dev_malloc(c, &nb.p, want);
   if (e != hipSuccess) {
     (void)hipGetLastError();
-    if (drop_optional(c)) return ensure_keep(c, b, bytes, keep);
+    if (give_back(c)) return ensure_keep(c, b, bytes, keep);
     return fail(c, QIMAX_ENOMEM, "hipMalloc of " + std::to_string(want) + " bytes failed");
   }
   nb.bytes = want;
@@ -631,7 +646,7 @@ qimax_status ensure_sv(qimax_ctx* c, size_t bytes) {
       (void)hipGetLastError();
       c->sv_mem = nullptr;
     }
-    if (!drop_optional(c)) return fail(c, QIMAX_ENOMEM, "expect: no device memory for the statevector");
+    if (!give_back(c)) return fail(c, QIMAX_ENOMEM, "expect: no device memory for the statevector");
   }
   c->sv_bytes = bytes;
   c->alloc_bytes += bytes;
@@ -646,26 +661,34 @@ qimax_status settled(qimax_ctx* c, qimax_status s) {
   return s;
 }
 
-// Runs a call's work, and once more without the memory it can do without where that left too
-// little (a failing call leaves the state as it was).
+// Runs a call's work. Where it runs out of memory it runs once more (a failing call leaves the
+// state as it was) with every scratch buffer given back, and lean: buffers of just the size that a
+// round needs; no groups of small passes, gathered rounds or small sort tiles, whose buffers the other
+// ways do without; long chains in one run, and those of 16-byte keys without tables. The next call
+// tries the full form again; where that is short of memory too, the calls after it start lean, one,
+// three, then up to kLeanCalls of them at a time. A refused call leaves nothing behind.
+constexpr uint32_t kLeanCalls = 15;
 template <typename F>
-qimax_status with_optional(qimax_ctx* c, const F& body) {
+qimax_status with_retry(qimax_ctx* c, const F& body) {
   const qimax_stats st0 = c->st;
   const std::vector<uint64_t> upd0 = c->gen_updates;
   const int64_t base0 = c->group_base;
-  c->opt_busy = true;
+  const bool was_lean = c->lean = c->lean_left > 0;
+  if (c->lean_left && !c->tune_frozen) c->lean_left -= 1;  // (a recording's runs are all of one form)
+  c->busy = true;
   qimax_status s = settled(c, body());
-  c->opt_busy = false;
-  bool dropped = false;
-  if (s == QIMAX_ENOMEM && !c->lean)
-    while (drop_optional(c)) dropped = true;
-  if (dropped) {
+  if (s == QIMAX_OK && !was_lean) c->lean_next = 0;
+  if (s == QIMAX_ENOMEM && !c->rec && (drop_scratch(c) || !was_lean)) {
     c->lean = true;
     c->st = st0;
     c->gen_updates = upd0;
     c->group_base = base0;
     s = settled(c, body());
+    c->lean_left = s == QIMAX_OK ? c->lean_next : 0;
+    c->lean_next = s == QIMAX_OK ? std::min(kLeanCalls, 2 * c->lean_next + 1) : 0;
+    if (s == QIMAX_ENOMEM) drop_scratch(c);
   }
+  c->busy = c->lean = false;
   return s;
 }
 
@@ -1131,7 +1154,7 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
   std::vector<Exp1Desc> e1;
   std::vector<Exp2Desc> e2;
   std::vector<BlockDesc> g1;  // one per e1 entry, while every operator has one
-  bool blocks = c->gather;
+  bool blocks = c->gather && !c->lean;
   for (const RoundEntry& en : entries)
     if (en.pass && !en.drop) blocks = blocks && en.pass->fanout_bound >= 1.0;
   double f_max = 0.0;
@@ -1300,7 +1323,8 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   const uint64_t in_tile = fused ? (uint64_t)fuse_tile() : (uint64_t)kSortTile;
   // Gathered round: a large fan-out whose operators fall apart into full blocks, every segment's
   // terms few enough to be grouped by one block (see k_gather_plan).
-  bool gather = sweep && !c->host_tiling && !bound_path && rd.blocks && T_in > 0 && c->dense_mode != 1 && S <= kSmallMaxSegs;
+  bool gather = sweep && !c->host_tiling && !bound_path && rd.blocks && T_in > 0 && c->dense_mode != 1 &&
+                S <= kSmallMaxSegs;
   for (uint32_t s = 0; s < S && gather; ++s) gather = so_in[s + 1] - so_in[s] <= gather_cap(c->KC);
   // every pass of the round leaves its images unsorted: they are the round's output
   bool plain = fused && !c->dense_mode;
@@ -1440,7 +1464,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   }
   if (bound_path || gather) {
     if (!gather) T_img = (uint64_t)f_round * T_in;  // capacity: an upper bound of the image count
-    if (sweep && T_img <= c->small_sort_max) sort_tile = kSmallSortTile;
+    if (sweep && T_img <= c->small_sort_max && !c->lean) sort_tile = kSmallSortTile;
     const uint32_t caps[2] = {(uint32_t)((T_img + kExpandTile - 1) / kExpandTile + S),
                               (uint32_t)((T_img + sort_tile - 1) / sort_tile + S)};
     const uint64_t tiles[2] = {(uint64_t)kExpandTile, (uint64_t)sort_tile};
@@ -1983,7 +2007,13 @@ qimax_status prebuild_tables(qimax_ctx* c, std::vector<Pass>& passes) {
 // block holds (so do its images). 0: run the pass as a round.
 constexpr size_t kMaxGroupPasses = 64;
 bool small_group_ok(const qimax_ctx* c) {
-  return c->small_groups && c->small_rounds && !c->classic_sort && !c->host_tiling && c->n <= kSmallMaxSegs;
+  return c->small_groups && c->small_rounds && !c->classic_sort && !c->host_tiling && c->n <= kSmallMaxSegs && !c->lean;
+}
+
+// Whether a memory cap leaves room to spare for a group's slots, kChunkCap terms a segment (n = 64 in
+// FP64: 19 MB), where a round of the same passes is sized by its images.
+bool group_has_room(const qimax_ctx* c, size_t segs) {
+  return !c->cap || segs * kChunkCap * (c->kb + c->wb) * 3 <= c->cap / 16;
 }
 
 // The passes from i0 on (at most kMaxGroupPasses) that keep segments of the given lengths within
@@ -2176,8 +2206,9 @@ qimax_status apply_ops_once(qimax_ctx* c, std::vector<HostOp>& ops) {
     // its readout 128 -> 105 us. Where the images do not fit, the round follows.
     bool overflow = false;
     const bool attempt = kg == 0 && small_group_ok(c) && c->T == c->n && so_in[c->n] == c->n && i == 0 &&
-                         passes[i].fanout_bound > (double)kBoundPathMaxFanout;
+                         passes[i].fanout_bound > (double)kBoundPathMaxFanout && group_has_room(c, c->n);
     if (attempt) kg = 1;
+    else if (kg && (kg == 1 || c->KC > 1) && !group_has_room(c, c->n)) kg = 0;
     std::vector<std::vector<uint64_t>> gi, gg, go;
     if (kg) {  // small passes, one or consecutive: one launch
       qimax_status s = run_small_group(c, passes, i, kg, k_in, w_in, s_in, so_in, slot, gi, gg, go,
@@ -2233,7 +2264,7 @@ qimax_status apply_ops(qimax_ctx* c, std::vector<HostOp>& ops) {
   if (c->broken) return fail(c, QIMAX_ESTATE, "context unusable after an earlier device error");
   BusyTimer bt(c);
   for (auto& op : ops) op.run = op.group;
-  return with_optional(c, [&] { return apply_ops_once(c, ops); });
+  return with_retry(c, [&] { return apply_ops_once(c, ops); });
 }
 
 qimax_status flush_once(qimax_ctx* c) {
@@ -2264,7 +2295,7 @@ qimax_status flush_once(qimax_ctx* c) {
 
 qimax_status flush_pending(qimax_ctx* c) {
   if (c->pending.empty()) return QIMAX_OK;
-  return with_optional(c, [&] { return flush_once(c); });
+  return with_retry(c, [&] { return flush_once(c); });
 }
 
 qimax_status check_op_input(qimax_ctx* c, const qimax_op& in, int64_t group, HostOp& op) {
@@ -3721,12 +3752,8 @@ const char* qimax_last_error(const qimax_ctx* c) {
 void qimax_destroy(qimax_ctx* c) {
   if (!c) return;
   if (c->stream) (void)hipStreamSynchronize(c->stream);
-  DevBuf* bufs[] = {&c->keys, &c->w, &c->seg, &c->pk[0], &c->pk[1], &c->pw[0], &c->pw[1], &c->pseg[0],
-                    &c->pseg[1], &c->ik[0], &c->ik[1], &c->iw[0], &c->iw[1], &c->cnt, &c->off, &c->scan_tmp,
-                    &c->hist, &c->hist_off, &c->blk_begin, &c->blk_end, &c->blk_seg, &c->seg_blk, &c->blk_cnt,
-                    &c->blk_off, &c->img_seg, &c->desc, &c->desc2, &c->err, &c->gr_in, &c->gr_out, &c->ghist, &c->sbase, &c->sstatus, &c->tile_ctr, &c->mstatus, &c->dtile[0], &c->dtile[1], &c->dtile[2], &c->ptab, &c->chain_parts, &c->wtab, &c->akeys, &c->asign, &c->img_cnt, &c->dense_acc, &c->chunk_cnt, &c->chunk_start, &c->grp_cnt, &c->gat,
-                    &c->chunk_off};
-  for (DevBuf* b : bufs) dev_free(c, *b);
+  for (DevBuf* b : scratch(c)) dev_free(c, *b);
+  for (DevBuf* b : {&c->keys, &c->w, &c->seg, &c->err, &c->gr_in, &c->gr_out}) dev_free(c, *b);
   drop_sv(c);
   if (c->pinned) (void)hipHostFree(c->pinned);
   for (int i = 0; i < 2; ++i)
@@ -4032,8 +4059,8 @@ constexpr size_t kGroupSegs = 256, kGroupTables = 32u << 20;
 qimax_status batch_group(qimax_batch* b, size_t* n_active, bool* ran) {
   qimax_ctx* c = b->c;
   *ran = false;
-  const size_t segs = b->so.size() - 1, slots = segs * kChunkCap * (size_t)(c->kb + c->wb) * 3;
-  if (!small_group_ok(c) || c->T == 0 || segs > kGroupSegs || (c->cap && slots > c->cap / 16)) return QIMAX_OK;
+  const size_t segs = b->so.size() - 1;
+  if (!small_group_ok(c) || c->lean_left || c->T == 0 || segs > kGroupSegs || !group_has_room(c, segs)) return QIMAX_OK;
   const size_t most = kGroupTables / (2 * table_bytes(c) * std::max<size_t>(b->order.size(), 1));
   // passes each circuit can run: all it has left, or as many as are small; the least of the latter
   // is the group's length, so that the circuits keep step as they do in rounds
@@ -4072,10 +4099,10 @@ qimax_status batch_group(qimax_batch* b, size_t* n_active, bool* ran) {
   }
   QCHK(batch_offsets(b));
   const uint32_t S = (uint32_t)first.size();
-  c->opt_busy = true;  // (a round gives up memory for room; a group does not)
+  c->busy = true;  // (a round runs again in another form for want of memory; a group does not)
   const qimax_status st = settled(c, launch_group(c, en, first, &len, k, c->keys.p, c->w.p,
                                                   (const uint64_t*)c->seg.p, b->so, 0, nullptr));
-  c->opt_busy = false;
+  c->busy = false;
   if (st == QIMAX_ENOMEM) return QIMAX_OK;
   QCHK(st);
   const uint32_t* h = (const uint32_t*)c->zres;
@@ -4202,7 +4229,7 @@ qimax_status qimax_batch_step(qimax_batch* b, size_t* n_active) {
   }
   QCHK(batch_offsets(b));
   std::vector<uint64_t> so_out, so_img, upd;
-  QCHK(with_optional(c, [&] {
+  QCHK(with_retry(c, [&] {
     return run_round(c, entries, seg_entry, c->keys.p, c->w.p, (const uint64_t*)c->seg.p, b->so, 0, so_out, so_img,
                      &upd);
   }));
