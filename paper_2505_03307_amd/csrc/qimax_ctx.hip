@@ -281,10 +281,18 @@ bool is_conjugation(const std::vector<double>& R, int dim) {
 // Measured on the n = 32 Clifford+Rz circuit (40 rotations, 64 key bits: every axis independent):
 // 10.7 -> 5.2 ms per step, the sort and merge of 18 of its 19 large passes gone (chunk sort 3.2 ->
 // 0.96 ms, scatter 2.8 -> 0.87, compaction 0.95 -> 0.25); the bookkeeping is about 15 ns per operator.
+//
+// A sorted pass also drops the terms of weight zero, which an unsorted one would hold and expand
+// further: products of small entries vanish below the type's range, in FP32 already three of the 6e-17
+// that a rotation by pi / 2 has for a cosine (24 such rotations: 2^24 terms for 301). So a pass is
+// left unsorted only where no weight can have vanished, by a lower bound of all of them: an
+// operator multiplies it by its smallest entry, and where terms are summed, what is left of sums
+// of multiples of the smallest weight's last bit is no smaller than that bit.
 struct KeySpan {
   bool known = true;  // false: an operator was no linear map, or V is the whole space
   bool empty = true;
   uint32_t bits = 0, rank = 0;
+  double low = 0.0;  // log2 of the lower bound of the weights that are not zero
   unsigned __int128 col[128];
   unsigned __int128 row[128];  // row[b]: the basis vector with highest bit b (0: none)
 
@@ -292,6 +300,7 @@ struct KeySpan {
     known = empty = true;
     bits = 2 * n;
     rank = 0;
+    low = 0.0;
     for (uint32_t b = 0; b < bits; ++b) {
       col[b] = (unsigned __int128)1 << b;
       row[b] = 0;
@@ -337,9 +346,16 @@ struct KeySpan {
   bool expand(const HostOp& op) {
     if (!known) return false;
     uint32_t seen = 0;
+    double least = HUGE_VAL;
     for (int in = 0; in < op.dim; ++in)
-      for (int out = 0; out < op.dim; ++out)
-        if (op.R[out * op.dim + in] != 0.0) seen |= 1u << (in ^ out);
+      for (int out = 0; out < op.dim; ++out) {
+        const double v = op.R[out * op.dim + in];
+        if (v == 0.0) continue;
+        seen |= 1u << (in ^ out);
+        least = std::fabs(v) < least ? std::fabs(v) : least;
+        if (!std::isfinite(v)) low = -HUGE_VAL;
+      }
+    low += std::log2(least);  // (an operator of zeros leaves no terms)
     uint32_t local = 1;  // the span of the differences taken so far (bit set of local indices)
     bool full = true;
     for (int d = 1; d < op.dim; ++d) {
@@ -2153,19 +2169,26 @@ qimax_status run_small_group(qimax_ctx* c, std::vector<Pass>& passes, size_t i0,
   return QIMAX_OK;
 }
 
-// Marks the passes of one circuit whose output may stay unsorted (see Pass::unsorted); thr:
-// each pass's prune threshold (a pass that prunes is sorted), or null where only the last
-// prunes. The last pass is always sorted. span moves past the passes.
+// Marks the passes of one circuit whose output may stay unsorted (see Pass::unsorted, KeySpan);
+// thr: each pass's prune threshold (a pass that prunes is sorted), or null where only the last
+// prunes (by the context's). The last pass is always sorted. span moves past the passes.
 void mark_unsorted(qimax_ctx* c, std::vector<Pass>& passes, const std::vector<double>* thr, KeySpan& span) {
-  std::vector<char> distinct(passes.size());
+  // the smallest normal numbers' exponents, less one for the products' rounding; digits of a weight
+  const double least = c->WP == 64 ? -1021.0 : -125.0, digits = c->WP == 64 ? 53.0 : 24.0;
+  std::vector<char> distinct(passes.size()), whole(passes.size());
   for (size_t i = 0; i < passes.size(); ++i) {
     for (const HostOp* op : passes[i].A) span.permute(*op);
     distinct[i] = !passes[i].E.empty();
     for (const HostOp* op : passes[i].E) distinct[i] &= span.expand(*op);
     for (const HostOp* op : passes[i].B) span.permute(*op);
+    whole[i] = span.low >= least;  // no image's weight has vanished
+    if (!passes[i].E.empty() && !distinct[i]) span.low -= digits;
+    if (c->dense_mode) span.low = std::min(span.low, -57.0);  // (sums in units of 2^-56)
+    const double t = thr ? (*thr)[i] : i + 1 == passes.size() ? c->eps : 0.0;
+    if (t > 0.0) span.low = std::max(span.low, std::log2(t));
   }
   for (size_t i = 0; i + 1 < passes.size(); ++i)
-    passes[i].unsorted = c->merge_free && distinct[i] && distinct[i + 1] && !(thr && (*thr)[i] > 0.0);
+    passes[i].unsorted = c->merge_free && distinct[i] && distinct[i + 1] && whole[i] && !(thr && (*thr)[i] > 0.0);
 }
 
 qimax_status apply_ops_once(qimax_ctx* c, std::vector<HostOp>& ops) {
