@@ -2601,7 +2601,9 @@ __global__ void __launch_bounds__(kPlanBlock) k_gather_plan(
     }
   }
   __syncthreads();
-  // outputs and units of every group, and their scans
+  // outputs and units of every group, and their scans (a pass's fan-out is below 2^31 and a segment
+  // has at most 2^14 parents: a segment's totals stay below 2^45, those of 2^13 segments below 2^58)
+  static_assert(kCap <= 1 << 14 && kSmallMaxSegs <= 1u << 13, "totals in 64 bits");
   uint64_t outs = 0, units[2] = {0, 0}, images = 0;
   for (uint32_t g0 = 0; g0 < ng; g0 += kPlanBlock) {
     const uint32_t g = g0 + threadIdx.x;

@@ -378,7 +378,9 @@ constexpr uint32_t kDenseMaxN = 12;           // dense accumulation: at most 4^1
 constexpr double kDenseMaxBytes = 4.0e9;      // and at most this many bytes of slots in all
 constexpr double kDenseRatio = 8.0;           // tuned only where slots <= 8 x images
 constexpr int kMaxE2 = 8;
-constexpr double kMaxFanout = 2147483647.0;
+constexpr double kMaxFanout = 2147483647.0;  // of a pass: image numbers inside a term, and their products, in 32 bits
+// images (gathered: outputs) of a round: its smallest tiles of them are numbered in 31 bits
+constexpr uint64_t kMaxImages = (uint64_t)kSmallSortTile * 0x7FFF0000ull;
 
 }  // namespace
 
@@ -1451,6 +1453,19 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   Tiling tl_exp{}, tl{};
   uint32_t sort_tile = kSortTile;       // elements of a sort / merge tile
   TileJob2 img_jobs[2];
+  // the images' buffers, before anything that grows with them (tilings): a round too large ends here
+  uint64_t n_work = 1;
+  auto image_buffers = [&]() -> qimax_status {
+    if (T_img > kMaxImages)
+      return fail(c, QIMAX_ETOOLARGE, "propagation round: " + std::to_string(T_img) + " images");
+    // the capacity, or for a small round S chunks of kChunkCap
+    n_work = std::max<uint64_t>(small ? std::max<uint64_t>(T_img, (uint64_t)S * kChunkCap) : T_img, 1);
+    for (int i = 0; i < 2; ++i) {
+      QCHK(ensure(c, c->ik[i], n_work * c->kb));
+      QCHK(ensure(c, c->iw[i], n_work * c->wb));
+    }
+    return QIMAX_OK;
+  };
   GatherPlan gp{};
   std::vector<uint64_t> g_units[2], g_images;
   std::vector<uint64_t> so_cap;  // gathered: the segments' outputs before the prune
@@ -1480,6 +1495,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   }
   if (bound_path || gather) {
     if (!gather) T_img = (uint64_t)f_round * T_in;  // capacity: an upper bound of the image count
+    QCHK(image_buffers());
     if (sweep && T_img <= c->small_sort_max && !c->lean) sort_tile = kSmallSortTile;
     const uint32_t caps[2] = {(uint32_t)((T_img + kExpandTile - 1) / kExpandTile + S),
                               (uint32_t)((T_img + sort_tile - 1) / sort_tile + S)};
@@ -1507,6 +1523,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
     if (e) return fail(c, (e & kErrFanout) ? QIMAX_ETOOLARGE : QIMAX_EDEVICE, "count pass:" + err_text(e));
     so_img.assign(c->pinned, c->pinned + S + 1);
     T_img = so_img[S];
+    QCHK(image_buffers());
     // ---- image tilings (expand tiles, sort/merge tiles) in one upload
     HostTiling t_exp, t_sort;
     make_tiling(so_img, kExpandTile, t_exp);
@@ -1600,12 +1617,6 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   const bool hist_in_expand = sweep && !dense && !classic_passes && !gather && m_top <= kExpandHistPasses;
   // ---- expand into images
   const size_t eb = c->kb, wbt = c->wb;
-  // image buffers: the capacity, or for a small round S chunks of kChunkCap
-  const uint64_t n_work = std::max<uint64_t>(small ? std::max<uint64_t>(T_img, (uint64_t)S * kChunkCap) : T_img, 1);
-  QCHK(ensure(c, c->ik[0], n_work * eb));
-  QCHK(ensure(c, c->iw[0], n_work * wbt));
-  QCHK(ensure(c, c->ik[1], n_work * eb));
-  QCHK(ensure(c, c->iw[1], n_work * wbt));
   Tiling tc_small{};
   if (small) {
     const size_t o1 = 0, o2 = align256((size_t)S * 8), o3 = o2 + align256((size_t)S * 8);
