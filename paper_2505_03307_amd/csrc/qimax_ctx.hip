@@ -488,7 +488,8 @@ struct qimax_ctx {
   // synchronisations and replayed later as one graph
   struct qimax_graph* rec = nullptr;
   bool rec_capturing = false;
-  uint64_t buf_gen = 0;  // counts every (re)allocation or release of the context's memory
+  uint64_t buf_gen = 0;  // counts every (re)allocation or release of memory that a recording refers to
+  uint64_t stage_gen = 0;  // and of the staging areas (a recording reads copies of its own)
 };
 
 namespace {
@@ -869,7 +870,7 @@ size_t put_tiling(const HostTiling& t, uint8_t* host, uint8_t* dev, size_t off, 
 qimax_status ensure_stage(qimax_ctx* c, int i, size_t bytes) {
   if (bytes <= c->stage_bytes[i] && c->stage[i]) return QIMAX_OK;
   if (c->rec) return fail(c, QIMAX_ESTATE, "a staging buffer must grow while recording: run the step once first");
-  c->buf_gen += 1;
+  c->stage_gen += 1;
   if (c->stage[i]) {
     HIPCHK(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
     (void)hipHostFree(c->stage[i]);
@@ -3329,13 +3330,13 @@ qimax_status qimax_graph_record(qimax_ctx* c, const uint8_t* gate, const uint32_
     return flush_pending(c);
   };
   for (int runs = 0, quiet = 0; quiet < 3 && runs < 9; ++runs) {
-    const uint64_t gen = c->buf_gen;
+    const uint64_t gen = c->buf_gen + c->stage_gen;
     const qimax_status s0 = run_step();
     if (s0 != QIMAX_OK) {
       c->tune_frozen = false;
       return s0;
     }
-    quiet = c->buf_gen == gen ? quiet + 1 : 0;
+    quiet = c->buf_gen + c->stage_gen == gen ? quiet + 1 : 0;
   }
   HIPCHK(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
   qimax_graph* g = new qimax_graph;
