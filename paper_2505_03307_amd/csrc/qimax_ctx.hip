@@ -484,6 +484,7 @@ struct qimax_ctx {
   void* read_dev = nullptr;
   size_t read_bytes = 0;
   hipEvent_t read_ev[16] = {};
+  uint64_t fail_reads = 0;  // readouts that find no staging (tests)
   // step recording (qimax_graph_record): the work of a step is captured between the host's
   // synchronisations and replayed later as one graph
   struct qimax_graph* rec = nullptr;
@@ -2776,9 +2777,19 @@ void copy_large(void* dst, const void* src, size_t bytes) {
   });
 }
 
-// Staging of `slots` slots of `bytes` each; false (nothing held) if it cannot be had.
+// Staging of `slots` slots of `bytes` each; false if it, or an event for every slot, cannot be had.
 bool ensure_read_stage(qimax_ctx* c, int slots, size_t bytes) {
   const size_t want = (size_t)slots * bytes;
+  if (c->fail_reads) {
+    c->fail_reads -= 1;
+    return false;
+  }
+  for (hipEvent_t& ev : c->read_ev)
+    if (!ev && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      ev = nullptr;
+      return false;
+    }
   if (c->read_stage && c->read_bytes >= want) return true;
   if (c->read_stage) (void)hipHostFree(c->read_stage);  // (no readout is in flight)
   c->read_stage = nullptr;
@@ -2791,12 +2802,6 @@ bool ensure_read_stage(qimax_ctx* c, int slots, size_t bytes) {
     return false;
   }
   c->read_bytes = want;
-  for (int i = 0; i < kReadSlots; ++i)
-    if (!c->read_ev[i] && hipEventCreateWithFlags(&c->read_ev[i], hipEventDisableTiming) != hipSuccess) {
-      (void)hipGetLastError();
-      c->read_ev[i] = nullptr;
-      return false;
-    }
   return true;
 }
 
@@ -3191,6 +3196,8 @@ qimax_status qimax_create(uint32_t n, const qimax_opts* opts, qimax_ctx** out) {
     c->classic_passes = env && env[0] == '1';
     env = std::getenv("QIMAX_WIDE_OFFSETS");  // 1: the count's and expansion's paths for huge rounds
     c->wide_offsets = env && env[0] == '1';
+    env = std::getenv("QIMAX_FAIL_READS");  // k: the first k readouts find no pinned staging (tests)
+    if (env && env[0]) c->fail_reads = std::strtoull(env, nullptr, 10);
     env = std::getenv("QIMAX_FAIL_ALLOC");  // k or k:m: m device allocations from the k-th on fail (tests)
     if (env && env[0]) {
       c->fail_from = std::strtoull(env, nullptr, 10);
@@ -3559,7 +3566,19 @@ qimax_status qimax_get_generators_xz(qimax_ctx* c, uint64_t* gen_off, uint64_t* 
   if (c->T == 0) return QIMAX_OK;
   bool done = false;
   QCHK(read_terms(c, 0, c->T, kReadXz, c->n, x, z, w, &done));
-  return done ? QIMAX_OK : fail(c, QIMAX_ENOMEM, "get_generators_xz: no pinned host memory for the readout");
+  if (done) return QIMAX_OK;
+  HostGens g;
+  QCHK(fetch(c, g));
+  std::copy(g.w.begin(), g.w.end(), w);
+  for (uint64_t i = 0; i < c->T; ++i) {
+    x[i] = z[i] = 0;
+    for (uint32_t q = 0; q < c->n; ++q) {
+      const uint32_t d = (uint32_t)(g.key[i] >> (2 * (c->n - 1 - q))) & 3u;
+      x[i] |= (uint64_t)(d == 1u || d == 2u) << q;
+      z[i] |= (uint64_t)(d >= 2u) << q;
+    }
+  }
+  return QIMAX_OK;
 }
 
 namespace {
