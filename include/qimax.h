@@ -155,7 +155,10 @@ qimax_status qimax_num_terms(qimax_ctx* ctx, uint64_t* T);
  * gen_off[0..n] (n+1 words, generator j owns terms gen_off[j] .. gen_off[j+1]-1),
  * keys (T*W words, W = 1 for n <= 32, 2 for n <= 64) and weights as FP64. Terms come out ascending by
  * key within each generator. Two-call size query: with cap < T only *T is written
- * (gen_off, keys and w may then be NULL) and QIMAX_OK is returned. */
+ * (gen_off, keys and w may then be NULL) and QIMAX_OK is returned.
+ * Terms pass through pinned host memory, at most 33 MB while a call runs (mem_cap_bytes does
+ * not count it). The contexts and batches of a process share what is kept of it for later
+ * readouts, 72 MB at most; it is freed with the last of them. */
 qimax_status qimax_get_generators(qimax_ctx* ctx, uint64_t* gen_off, uint64_t* keys, double* w,
                                   size_t cap, size_t* T);
 

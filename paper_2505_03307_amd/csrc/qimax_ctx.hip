@@ -14,6 +14,7 @@
 #include <deque>
 #include <map>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <random>
 #include <string>
@@ -479,12 +480,8 @@ struct qimax_ctx {
   uint64_t* zres_dev = nullptr;
   size_t zres_words = 0;
   uint64_t zseq = 0;  // sequence word of the last results asked for
-  // pinned, device-mapped slots of the readout (see read_terms), and an event per slot
-  void* read_stage = nullptr;
-  void* read_dev = nullptr;
-  size_t read_bytes = 0;
-  hipEvent_t read_ev[16] = {};
   uint64_t fail_reads = 0;  // readouts that find no staging (tests)
+  bool counted = false;     // among the process's contexts (see ReadStage)
   // step recording (qimax_graph_record): the work of a step is captured between the host's
   // synchronisations and replayed later as one graph
   struct qimax_graph* rec = nullptr;
@@ -2777,32 +2774,103 @@ void copy_large(void* dst, const void* src, size_t bytes) {
   });
 }
 
-// Staging of `slots` slots of `bytes` each; false if it, or an event for every slot, cannot be had.
-bool ensure_read_stage(qimax_ctx* c, int slots, size_t bytes) {
-  const size_t want = (size_t)slots * bytes;
+// Staging of a readout: pinned, device-mapped memory and an event per slot. A readout takes one and
+// gives it back; those that wait for the next readout are shared by all contexts of the process,
+// up to kReadIdleBytes (two of the largest: a serving loop reads on two threads), and are freed
+// with the last context. (One per context held 32 MB for every warm context that had ever been read.)
+struct ReadStage {
+  int device = 0;
+  void* host = nullptr;
+  void* dev = nullptr;
+  size_t bytes = 0;
+  hipEvent_t ev[kReadSlots] = {};
+};
+constexpr size_t kReadIdleBytes = 72u << 20;
+constexpr int kReadIdle = 8;
+std::mutex g_read_mutex;             // guards the two below
+ReadStage* g_read_idle[kReadIdle];   // null: free places
+size_t g_contexts = 0;
+
+void free_stage(ReadStage* s) {
+  if (!s) return;
+  if (s->host) (void)hipHostFree(s->host);
+  for (hipEvent_t e : s->ev)
+    if (e) (void)hipEventDestroy(e);
+  delete s;
+}
+
+// A stage of at least `bytes` on the device; null if it, or an event for every slot, cannot be had.
+ReadStage* take_stage(qimax_ctx* c, size_t bytes) {
   if (c->fail_reads) {
     c->fail_reads -= 1;
-    return false;
+    return nullptr;
   }
-  for (hipEvent_t& ev : c->read_ev)
-    if (!ev && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
-      (void)hipGetLastError();
-      ev = nullptr;
-      return false;
+  ReadStage* out = nullptr;
+  {
+    // the smallest that is large enough, else a larger one takes the largest's place
+    std::lock_guard<std::mutex> lock(g_read_mutex);
+    int best = -1;
+    for (int i = 0; i < kReadIdle; ++i) {
+      const ReadStage* s = g_read_idle[i];
+      if (!s || s->device != c->device) continue;
+      if (best < 0) {
+        best = i;
+        continue;
+      }
+      const bool fits = s->bytes >= bytes, fit = g_read_idle[best]->bytes >= bytes;
+      if (fits != fit ? fits : fits ? s->bytes < g_read_idle[best]->bytes : s->bytes > g_read_idle[best]->bytes) best = i;
     }
-  if (c->read_stage && c->read_bytes >= want) return true;
-  if (c->read_stage) (void)hipHostFree(c->read_stage);  // (no readout is in flight)
-  c->read_stage = nullptr;
-  c->read_bytes = 0;
-  if (hipHostMalloc(&c->read_stage, want, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
-      hipHostGetDevicePointer(&c->read_dev, c->read_stage, 0) != hipSuccess) {
-    (void)hipGetLastError();
-    if (c->read_stage) (void)hipHostFree(c->read_stage);
-    c->read_stage = nullptr;
-    return false;
+    if (best >= 0) {
+      out = g_read_idle[best];
+      g_read_idle[best] = nullptr;
+    }
   }
-  c->read_bytes = want;
-  return true;
+  if (out && out->bytes >= bytes) return out;
+  free_stage(out);
+  out = new (std::nothrow) ReadStage;
+  if (!out) return nullptr;
+  out->device = c->device;
+  bool ok = true;
+  for (hipEvent_t& ev : out->ev) ok = ok && hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess;
+  ok = ok && hipHostMalloc(&out->host, bytes, hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
+       hipHostGetDevicePointer(&out->dev, out->host, 0) == hipSuccess;
+  if (!ok) {
+    (void)hipGetLastError();
+    free_stage(out);
+    return nullptr;
+  }
+  out->bytes = bytes;
+  return out;
+}
+
+// Nothing on the device writes the stage any more.
+void give_stage(ReadStage* s) {
+  {
+    std::lock_guard<std::mutex> lock(g_read_mutex);
+    size_t held = s->bytes;
+    int place = -1;
+    for (int i = 0; i < kReadIdle; ++i) {
+      if (g_read_idle[i]) held += g_read_idle[i]->bytes;
+      else place = i;
+    }
+    if (place >= 0 && held <= kReadIdleBytes && g_contexts) {
+      g_read_idle[place] = s;
+      return;
+    }
+  }
+  free_stage(s);
+}
+
+void count_context(qimax_ctx* c, bool open) {
+  ReadStage* rest[kReadIdle] = {};
+  {
+    std::lock_guard<std::mutex> lock(g_read_mutex);
+    if (open == c->counted) return;
+    c->counted = open;
+    g_contexts += open ? 1 : (size_t)-1;
+    if (!g_contexts) std::swap(rest, g_read_idle);
+  }
+  for (ReadStage* s : rest) free_stage(s);
 }
 
 // Terms [a, a + T) of the committed term arrays to host memory: n_words uint64 words per key in
@@ -2825,19 +2893,20 @@ qimax_status read_terms(qimax_ctx* c, uint64_t a, uint64_t T, ReadForm form, uin
   const uint64_t n_chunks = (T + m - 1) / m;
   const int slots = (int)std::min<uint64_t>(kReadSlots, n_chunks);
   const size_t slot_bytes = align256((size_t)std::min(m, T) * per + 256);
-  if (!ensure_read_stage(c, slots, slot_bytes)) return QIMAX_OK;
+  ReadStage* const stage = take_stage(c, (size_t)slots * slot_bytes);
+  if (!stage) return QIMAX_OK;
   const uint8_t* kb = (const uint8_t*)c->keys.p + a * c->kb;
   const uint8_t* wb = (const uint8_t*)c->w.p + a * c->wb;
   auto w_at = [&](uint64_t k) { return ((size_t)k * per_k + 15) / 16 * 16; };  // the weights' place in a slot
   auto launch = [&](uint64_t i) -> hipError_t {
     const uint64_t o = i * m, k = std::min(m, T - o);
     const size_t at = (size_t)(i % slots) * slot_bytes;
-    uint8_t* d = (uint8_t*)c->read_dev + at;
+    uint8_t* d = (uint8_t*)stage->dev + at;
     return launch_read(c->KC, c->WP, form == kReadXz, kb + o * c->kb, wb + o * c->wb, k, n, d, d + w_at(k), c->stream);
   };
   auto copy = [&](uint64_t i) {
     const uint64_t o = i * m, k = std::min(m, T - o);
-    const uint8_t* h = (const uint8_t*)c->read_stage + (size_t)(i % slots) * slot_bytes;
+    const uint8_t* h = (const uint8_t*)stage->host + (size_t)(i % slots) * slot_bytes;
     const uint64_t nw = form == kReadWords2 ? 2 : 1;
     if (form == kReadXz) {
       std::memcpy(words + o, h, k * 8);
@@ -2868,7 +2937,7 @@ qimax_status read_terms(qimax_ctx* c, uint64_t a, uint64_t T, ReadForm form, uin
   uint64_t launched = 0;
   auto launch_next = [&] {
     e = launch(launched);
-    if (e == hipSuccess) e = hipEventRecord(c->read_ev[launched % slots], c->stream);
+    if (e == hipSuccess) e = hipEventRecord(stage->ev[launched % slots], c->stream);
     ++launched;
   };
   while (launched < (uint64_t)slots && e == hipSuccess) launch_next();  // before any thread is made
@@ -2899,7 +2968,7 @@ qimax_status read_terms(qimax_ctx* c, uint64_t a, uint64_t T, ReadForm form, uin
       }
       launch_next();
     }
-    if (e == hipSuccess) e = hipEventSynchronize(c->read_ev[i % slots]);
+    if (e == hipSuccess) e = hipEventSynchronize(stage->ev[i % slots]);
     if (e != hipSuccess) break;
     ready.store(i + 1, std::memory_order_release);
     if (pool.empty()) {
@@ -2911,8 +2980,10 @@ qimax_status read_terms(qimax_ctx* c, uint64_t a, uint64_t T, ReadForm form, uin
   for (auto& t : pool) t.join();
   if (e != hipSuccess) {
     (void)hipStreamSynchronize(c->stream);  // nothing writes the slots any more
+    free_stage(stage);
     return hip_fail(c, e, "readout");
   }
+  give_stage(stage);
   *done = true;
   return QIMAX_OK;
 }
@@ -3245,6 +3316,7 @@ qimax_status qimax_create(uint32_t n, const qimax_opts* opts, qimax_ctx** out) {
   c->T = n;
   c->span.init(n);
   c->st.terms = n;
+  count_context(c, true);
   *out = c;
   return QIMAX_OK;
 }
@@ -3813,13 +3885,11 @@ void qimax_destroy(qimax_ctx* c) {
   for (int i = 0; i < 2; ++i)
     if (c->stage[i]) (void)hipHostFree(c->stage[i]);
   if (c->zres) (void)hipHostFree(c->zres);
-  if (c->read_stage) (void)hipHostFree(c->read_stage);
-  for (hipEvent_t e : c->read_ev)
-    if (e) (void)hipEventDestroy(e);
   prof_destroy(&c->prof);
   for (hipEvent_t e : c->tune_ev)
     if (e) (void)hipEventDestroy(e);
   if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
+  count_context(c, false);
   delete c;
 }
 
