@@ -3079,6 +3079,7 @@ struct CliffordReducer {
 constexpr uint32_t kSvMaxN = 30;     // device statevector readout: at most 2^30 amplitudes
 constexpr double kSvMaxWork = 4e13;  // sum over generators of terms x 2^n
 constexpr size_t kSvRows = 16384;    // strings of a launch
+constexpr size_t kSvSums = 1u << 20;   // bytes of sums
 constexpr size_t kSvKeep = 64u << 20;  // a statevector's memory up to this size is kept for the next call
 
 // Every generator a single term of weight +-1 (the state is a stabilizer state)?
@@ -3116,37 +3117,47 @@ qimax_status expect_device(qimax_ctx* c, const std::vector<std::vector<int>>& Ps
   if (n > kSvMaxN) return fail(c, QIMAX_ETOOLARGE, "expect: a state with non-Clifford generators and n > 30");
   const uint64_t D = 1ull << n, T = c->T;
   if ((double)T * (double)D > kSvMaxWork) return fail(c, QIMAX_ETOOLARGE, "expect: too many terms for the projection");
-  // device memory: v, the parts of G v (as many as the largest generator takes, at most v again
-  // or 32 bytes per term), the sums
+  // device memory: v and the parts of G v (as many as the largest generator takes, at most v again
+  // or 32 bytes per term), then the sums
   const size_t sv_bytes = (size_t)D * 16, limit = std::max(sv_bytes, (size_t)T * 32);
   uint32_t parts = 1;
   for (uint32_t j = 0; j < n; ++j) parts = std::max(parts, sv_parts(c->h_seg[j + 1] - c->h_seg[j], D, limit));
-  size_t k = zall ? 11 : std::min<size_t>(Ps.size(), kSvRows);  // rows of sums
-  if (c->cap) k = std::min(k, std::max<size_t>(11, std::min(sv_bytes, (size_t)T * 32) / 24));
-  QCHK(ensure_sv(c, sv_bytes * (1 + (size_t)parts) + k * 3 * 8 + 256));
+  const size_t sums = c->cap ? std::max<size_t>(33 * 8, std::min(sv_bytes, (size_t)T * 32)) : kSvSums;
+  const size_t k = zall ? 1 : std::min({Ps.size(), kSvRows, sums / 24});  // strings of a launch
+  const uint32_t blocks = sv_reduce_blocks(n, (uint32_t)k, zall, sums), per = zall ? 1 + n : 3;
+  const size_t words = k * blocks * per;
+  QCHK(ensure_sv(c, sv_bytes * (1 + (size_t)parts) + words * 8 + 256));
   uint8_t* m = (uint8_t*)c->sv_mem;
-  void* v = m;
-  void* part = m + sv_bytes;
   double* acc = (double*)(m + sv_bytes * (1 + (size_t)parts));
-  std::vector<double> h(std::max<size_t>(33, 3 * k));
-  hipError_t e = launch_sv_random(v, D, 0x5eed5eedull + n, c->stream);
+  std::vector<double> h(words);
+  uint32_t vs = 0;  // v's slot
+  hipError_t e = launch_sv_random(m, D, 0x5eed5eedull + n, c->stream);
   for (uint32_t j = 0; j < n && e == hipSuccess; ++j) {
     const uint64_t a = c->h_seg[j], b = c->h_seg[j + 1];
     e = launch_sv_project(c->KC, c->WP, (const uint8_t*)c->keys.p + a * c->kb, (const uint8_t*)c->w.p + a * c->wb, b - a,
-                          n, v, part, sv_parts(b - a, D, limit), c->stream);
+                          n, m, &vs, sv_parts(b - a, D, limit), c->stream);
   }
-  auto read = [&](size_t words) -> hipError_t {
-    hipError_t r = hipMemcpyAsync(h.data(), acc, words * 8, hipMemcpyDeviceToHost, c->stream);
-    return r == hipSuccess ? hipStreamSynchronize(c->stream) : r;
+  const void* const v = m + vs * sv_bytes;
+  // the sums of `rows` rows: every block's added, in order, to the first's
+  auto read = [&](size_t rows) -> hipError_t {
+    hipError_t r = hipMemcpyAsync(h.data(), acc, rows * blocks * per * 8, hipMemcpyDeviceToHost, c->stream);
+    if (r == hipSuccess) r = hipStreamSynchronize(c->stream);
+    for (size_t i = 0; i < rows && r == hipSuccess; ++i)
+      for (uint32_t t = 0; t < per; ++t) {
+        double sum = 0.0;
+        for (uint32_t q = 0; q < blocks; ++q) sum += h[(i * blocks + q) * per + t];
+        h[i * blocks * per + t] = sum;
+      }
+    return r;
   };
   qimax_status st = QIMAX_OK;
   if (e == hipSuccess && zall) {
-    e = launch_sv_reduce(v, n, nullptr, 0, acc, c->stream);
-    if (e == hipSuccess) e = read(1 + n);
+    e = launch_sv_reduce(v, n, nullptr, 0, blocks, acc, c->stream);
+    if (e == hipSuccess) e = read(1);
     if (e == hipSuccess && !(h[0] > 1e-280)) st = fail(c, QIMAX_EDEVICE, "expect: projection vanished");
     for (uint32_t q = 0; q < n && e == hipSuccess && st == QIMAX_OK; ++q) out[q] = h[1 + q] / h[0];
   }
-  // the strings in one launch (kSvRows at a time), read from mapped staging
+  // the strings, k at a time, read from mapped staging
   for (size_t i0 = 0; i0 < Ps.size() && e == hipSuccess && st == QIMAX_OK && !zall; i0 += k) {
     const size_t rows = std::min(k, Ps.size() - i0);
     st = ensure_stage(c, 0, rows * sizeof(SvString));
@@ -3165,11 +3176,12 @@ qimax_status expect_device(qimax_ctx* c, const std::vector<std::vector<int>>& Ps
       static const double ph[4][2] = {{1, 0}, {0, 1}, {-1, 0}, {0, -1}};
       str[i] = SvString{x, z, ph[ny & 3][0], ph[ny & 3][1]};
     }
-    e = launch_sv_reduce(v, n, (const SvString*)c->stage_dev[0], (uint32_t)rows, acc, c->stream);
-    if (e == hipSuccess) e = read(3 * rows);
+    e = launch_sv_reduce(v, n, (const SvString*)c->stage_dev[0], (uint32_t)rows, blocks, acc, c->stream);
+    if (e == hipSuccess) e = read(rows);
     for (size_t i = 0; i < rows && e == hipSuccess && st == QIMAX_OK; ++i) {
-      if (!(h[3 * i] > 1e-280)) st = fail(c, QIMAX_EDEVICE, "expect: projection vanished");
-      else out[i0 + i] = h[3 * i + 1] / h[3 * i];
+      const double* q = &h[i * blocks * per];
+      if (!(q[0] > 1e-280)) st = fail(c, QIMAX_EDEVICE, "expect: projection vanished");
+      else out[i0 + i] = q[1] / q[0];
     }
   }
   (void)hipStreamSynchronize(c->stream);

@@ -504,18 +504,22 @@ hipError_t launch_compare(int KC, int WPa, int WPb, const void* ka, const void* 
                           hipStream_t s);
 // Statevector readout: 2^n complex amplitudes (double2), n <= 30.
 hipError_t launch_sv_random(void* v, uint64_t D, uint64_t seed, hipStream_t s);
-// v <- (v + G v) / 2 for the generator given by T terms, G v summed in Y parts (part: Y * 2^n
-// amplitudes; sv_parts: the Y for T terms that takes at most `limit` bytes, at least 1).
+// v <- (v + G v) / 2 for the generator given by T terms, G v summed in Y parts. mem: 1 + Y slots of
+// 2^n amplitudes at least, v in slot *vs (0 or 1; updated). sv_parts: the Y for T terms that takes at
+// most `limit` bytes, at least 1.
 uint32_t sv_parts(uint64_t T, uint64_t D, size_t limit);
-hipError_t launch_sv_project(int KC, int WP, const void* keys, const void* w, uint64_t T, uint32_t n, void* v,
-                             void* part, uint32_t Y, hipStream_t s);
-// <v|v> and <v|c P|v> of k strings (in memory the device can read): acc[3i] = <v|v>, acc[3i + 1]
-// + i acc[3i + 2] = <v|c_i P_i|v>. str = null: acc[0] = <v|v> and acc[1 + q] = sum_i |v_i|^2
-// (1 - 2 bit_q(i)) for every qubit q < n (33 words).
+hipError_t launch_sv_project(int KC, int WP, const void* keys, const void* w, uint64_t T, uint32_t n, void* mem,
+                             uint32_t* vs, uint32_t Y, hipStream_t s);
+// <v|v> and <v|c P|v> of k strings (in memory the device can read) in `blocks` parts each, to be added:
+// part b of string i at acc[3 (i blocks + b)]: of <v|v>, of Re <v|c_i P_i|v> and of Im. str = null: part
+// b at acc[(1 + n) b]: of <v|v> and, per qubit q, of sum_i |v_i|^2 (1 - 2 bit_q(i)).
+// sv_reduce_blocks: the parts for so many rows whose sums take at most `limit` bytes, at least 1.
 struct SvString {
   uint64_t x, z;  // masks over the basis-index bits
   double re, im;  // c
 };
-hipError_t launch_sv_reduce(const void* v, uint32_t n, const SvString* str, uint32_t k, double* acc, hipStream_t s);
+uint32_t sv_reduce_blocks(uint32_t n, uint32_t rows, bool zall, size_t limit);
+hipError_t launch_sv_reduce(const void* v, uint32_t n, const SvString* str, uint32_t k, uint32_t blocks, double* acc,
+                            hipStream_t s);
 
 }  // namespace qimax

@@ -118,7 +118,7 @@ __global__ void k_sv_random(double2* __restrict__ v, uint64_t D, uint64_t seed) 
 }
 
 // A generator's terms [T y/Y, T (y+1)/Y) applied to v by the blocks (., y) of a grid of
-// ceil(D / kSvTile) x Y: part[y D + k] = sum over those terms t of c_t (-1)^{popcount(src & z_t)}
+// ceil(D / kSvTile) x Y: part y at k = sum over those terms t of c_t (-1)^{popcount(src & z_t)}
 // v[src], src = k ^ x_t. Small states have few amplitudes (n = 10: one tile), so the terms are
 // split too, over the blocks and over the kSvGroups groups of a block, whose sums meet in LDS: a
 // launch of D threads alone left 252 of 256 CUs idle. A wave holds 64 terms, one per lane, and
@@ -133,15 +133,25 @@ constexpr int kSvThreads = 256, kSvItems = 4, kSvTile = kSvThreads * kSvItems, k
 // generators of fewer take blocks of one group: 5 to 7 us for them against 10 to 11, where four
 // groups save 11 to 23 us of 28 to 64 on generators of 20 to 80 thousand terms
 constexpr uint64_t kSvManyTerms = 1u << 14;
+constexpr uint64_t kSvFewTerms = 16;
+
+// v and the parts lie in slots of D amplitudes: v in slot vs (0 or 1), part y in the y-th of the
+// others. With one part the projection is finished here, (v + g) / 2 written to the part's slot, which
+// is v's from then on: one launch a generator where it took two (one string of states of three
+// terms a generator: n = 11 125 -> 81 us, n = 14 157 -> 96, n = 18 224 -> 136; a thread per amplitude and two
+// launches took 122, 147 and 213).
+__device__ __forceinline__ uint64_t sv_slot(uint32_t y, uint32_t vs) { return y + (y >= vs ? 1u : 0u); }
 
 constexpr uint32_t kSvLdsQubits = 11;
 template <typename K, typename W, bool kLds, int kGroups>
 __global__ void __launch_bounds__(kSvThreads * kGroups)
-k_sv_apply(const K* __restrict__ keys, const W* __restrict__ w, uint64_t T, uint32_t n, const double2* __restrict__ v,
-           uint64_t D, double2* __restrict__ part) {
+k_sv_apply(const K* __restrict__ keys, const W* __restrict__ w, uint64_t T, uint32_t n, double2* mem, uint32_t vs,
+           uint64_t D) {
   extern __shared__ __align__(16) uint8_t lds[];
   __shared__ double2 sums[kGroups > 1 ? kGroups / 2 : 1][kSvTile];
   double2* const sv = (double2*)lds;
+  const double2* __restrict__ const v = mem + vs * D;
+  double2* __restrict__ const part = mem + sv_slot(blockIdx.y, vs) * D;
   if constexpr (kLds) {
     for (uint32_t i = threadIdx.x; i < (uint32_t)D; i += kSvThreads * kGroups) sv[i] = v[i];
     __syncthreads();
@@ -225,7 +235,13 @@ k_sv_apply(const K* __restrict__ keys, const W* __restrict__ w, uint64_t T, uint
 #pragma unroll
     for (int i = 0; i < kSvItems; ++i) {
       const uint64_t k = k0 + (uint64_t)i * kSvThreads;
-      if (k < D) part[blockIdx.y * D + k] = make_double2(re[i], im[i]);
+      if (k >= D) continue;
+      if (gridDim.y == 1) {
+        const double2 a = kLds ? sv[k] : v[k];
+        part[k] = make_double2(0.5 * (a.x + re[i]), 0.5 * (a.y + im[i]));
+      } else {
+        part[k] = make_double2(re[i], im[i]);
+      }
     }
   }
 }
@@ -233,18 +249,19 @@ k_sv_apply(const K* __restrict__ keys, const W* __restrict__ w, uint64_t T, uint
 // v = (v + g) / 2, the projection (I + G) / 2 applied given g = G v in Y parts: sixteen threads
 // per amplitude each add every sixteenth part, then their sums in a fixed order.
 constexpr int kSvSumLanes = 16, kSvSumAmps = 256 / kSvSumLanes;
-__global__ void __launch_bounds__(256) k_sv_half_sum(double2* __restrict__ v, const double2* __restrict__ part,
-                                                    uint64_t D, uint32_t Y) {
+__global__ void __launch_bounds__(256) k_sv_half_sum(double2* mem, uint32_t vs, uint64_t D, uint32_t Y) {
   __shared__ double2 sh[kSvSumLanes][kSvSumAmps];
   const uint32_t ka = threadIdx.x % kSvSumAmps, l = threadIdx.x / kSvSumAmps;
   const uint64_t k = (uint64_t)blockIdx.x * kSvSumAmps + ka;
+  double2* __restrict__ const v = mem + vs * D;
+  auto part = [&](uint32_t y) -> const double2* { return mem + sv_slot(y, vs) * D; };
   double re = 0.0, im = 0.0;
   if (k < D) {
     uint32_t y = l;
     for (; y + 3 * kSvSumLanes < Y; y += 4 * kSvSumLanes) {  // four loads in flight
       double2 p[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) p[i] = part[(uint64_t)(y + i * kSvSumLanes) * D + k];
+      for (int i = 0; i < 4; ++i) p[i] = part(y + i * kSvSumLanes)[k];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         re += p[i].x;
@@ -252,7 +269,7 @@ __global__ void __launch_bounds__(256) k_sv_half_sum(double2* __restrict__ v, co
       }
     }
     for (; y < Y; y += kSvSumLanes) {
-      const double2 p = part[(uint64_t)y * D + k];
+      const double2 p = part(y)[k];
       re += p.x;
       im += p.y;
     }
@@ -269,18 +286,10 @@ __global__ void __launch_bounds__(256) k_sv_half_sum(double2* __restrict__ v, co
   }
 }
 
-// v = (v + g) / 2 with g in one part.
-__global__ void k_sv_half_sum1(double2* __restrict__ v, const double2* __restrict__ g, uint64_t D) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= D) return;
-  const double2 a = v[i], b = g[i];
-  v[i] = make_double2(0.5 * (a.x + b.x), 0.5 * (a.y + b.y));
-}
-
-// String y (of gridDim.y): acc[3y] += sum |v|^2, acc[3y + 1] += Re sum conj(v) (P v),
-// acc[3y + 2] += Im of it; or with zall set (one row) acc[0] and acc[1 + q] += sum |v_i|^2
-// (1 - 2 bit_q(i)) for every qubit q (<Z_q>, unnormalised). One block per row stores its sums,
-// several add theirs (acc is then cleared before).
+// Block b of string y: sums over its amplitudes, sum |v|^2, Re sum conj(v) (P v) and Im of it; or with
+// zall set (one row) sum |v|^2 and sum |v_i|^2 (1 - 2 bit_q(i)) for every qubit q (<Z_q>,
+// unnormalised). acc[(y B + b) A ..] with B blocks a row and A sums a block: the host adds the
+// blocks' in order.
 constexpr uint32_t kSvMaxQubits = 32;  // statevectors hold at most 2^kSvMaxQubits amplitudes
 constexpr int kSvBlock = 256;
 __global__ void __launch_bounds__(kSvBlock) k_sv_reduce(const double2* __restrict__ v, uint64_t D, uint32_t n,
@@ -337,8 +346,7 @@ __global__ void __launch_bounds__(kSvBlock) k_sv_reduce(const double2* __restric
   if (threadIdx.x < nacc) {
     double s = 0.0;
     for (int w = 0; w < kSvBlock / 64; ++w) s += sh[w][threadIdx.x];
-    double* const o = acc + (uint64_t)blockIdx.y * 3 + threadIdx.x;
-    if (gridDim.x == 1) *o = s; else atomicAdd(o, s);
+    acc[((uint64_t)blockIdx.y * gridDim.x + blockIdx.x) * nacc + threadIdx.x] = s;
   }
 }
 
@@ -409,15 +417,16 @@ uint32_t sv_parts(uint64_t T, uint64_t D, size_t limit) {
   return (uint32_t)std::max<uint64_t>(y, 1);
 }
 
-hipError_t launch_sv_project(int KC, int WP, const void* keys, const void* w, uint64_t T, uint32_t n, void* v,
-                             void* part, uint32_t Y, hipStream_t s) {
+hipError_t launch_sv_project(int KC, int WP, const void* keys, const void* w, uint64_t T, uint32_t n, void* mem,
+                             uint32_t* vs, uint32_t Y, hipStream_t s) {
   const uint64_t D = 1ull << n;
-  if (n < 1 || n > 30 || KC > 1 || Y < 1 || Y > 65535) return hipErrorInvalidValue;
+  if (n < 1 || n > 30 || KC > 1 || Y < 1 || Y > 65535 || *vs > 1) return hipErrorInvalidValue;
   const dim3 grid((uint32_t)((D + kSvTile - 1) / kSvTile), Y);
-  const bool lds = n <= kSvLdsQubits;
+  // (a few terms a thread are read from L2 sooner than the state is staged)
+  const bool lds = n <= kSvLdsQubits && T > kSvFewTerms;
   const size_t bytes = lds ? (size_t)D * 16 : 0;
 #define QIMAX_SVA_G(K, W, L, G) \
-  k_sv_apply<K, W, L, G><<<grid, kSvThreads * G, bytes, s>>>((const K*)keys, (const W*)w, T, n, (const double2*)v, D, (double2*)part)
+  k_sv_apply<K, W, L, G><<<grid, kSvThreads * G, bytes, s>>>((const K*)keys, (const W*)w, T, n, (double2*)mem, *vs, D)
 #define QIMAX_SVA(K, W, L) do { if (T >= kSvManyTerms) QIMAX_SVA_G(K, W, L, kSvGroups); else QIMAX_SVA_G(K, W, L, 1); } while (0)
 #define QIMAX_SVA_L(K, W) do { if (lds) QIMAX_SVA(K, W, true); else QIMAX_SVA(K, W, false); } while (0)
   if (KC == 0) {
@@ -429,25 +438,28 @@ hipError_t launch_sv_project(int KC, int WP, const void* keys, const void* w, ui
 #undef QIMAX_SVA
 #undef QIMAX_SVA_G
   if (Y == 1)
-    k_sv_half_sum1<<<blocks_for(D, 256), 256, 0, s>>>((double2*)v, (const double2*)part, D);
+    *vs ^= 1u;
   else
-    k_sv_half_sum<<<blocks_for(D, kSvSumAmps), 256, 0, s>>>((double2*)v, (const double2*)part, D, Y);
+    k_sv_half_sum<<<blocks_for(D, kSvSumAmps), 256, 0, s>>>((double2*)mem, *vs, D, Y);
   return hipGetLastError();
 }
 
-hipError_t launch_sv_reduce(const void* v, uint32_t n, const SvString* str, uint32_t k, double* acc, hipStream_t s) {
-  const uint64_t D = 1ull << n;
-  if (k > 65535) return hipErrorInvalidValue;
+uint32_t sv_reduce_blocks(uint32_t n, uint32_t rows, bool zall, size_t limit) {
+  // eight amplitudes a thread (every <Z_q> at n = 14: one block 45 us, eight 10), and blocks enough for
+  // the chip over all rows
+  const uint64_t D = 1ull << n, per = 8ull * (zall ? 1 + n : 3) * std::max(rows, 1u);
+  return (uint32_t)std::max<uint64_t>(
+      std::min<uint64_t>({(D + kSvBlock * 8 - 1) / (kSvBlock * 8), std::max(4096u / std::max(rows, 1u), 1u), 1024,
+                          limit / per}), 1);
+}
+
+hipError_t launch_sv_reduce(const void* v, uint32_t n, const SvString* str, uint32_t k, uint32_t blocks, double* acc,
+                            hipStream_t s) {
+  if (k > 65535 || n > kSvMaxQubits || blocks < 1) return hipErrorInvalidValue;
   const bool zall = str == nullptr;
   const uint32_t rows = zall ? 1 : k;
   if (rows == 0) return hipSuccess;
-  // one block per row up to 2^14 amplitudes: 64 per thread, and no sums to combine
-  const uint32_t grid = D <= (1ull << 14) ? 1u : (uint32_t)std::min<uint64_t>(blocks_for(D, kSvBlock * 16), 1024);
-  if (grid > 1) {
-    const hipError_t e = launch_fill_u64((uint64_t*)acc, zall ? 1 + kSvMaxQubits : 3 * (uint64_t)rows, 0ull, s);
-    if (e != hipSuccess) return e;
-  }
-  k_sv_reduce<<<dim3(grid, rows), kSvBlock, 0, s>>>((const double2*)v, D, n, str, zall ? 1 : 0, acc);
+  k_sv_reduce<<<dim3(blocks, rows), kSvBlock, 0, s>>>((const double2*)v, 1ull << n, n, str, zall ? 1 : 0, acc);
   return hipGetLastError();
 }
 
