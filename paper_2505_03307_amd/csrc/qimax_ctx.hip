@@ -130,6 +130,9 @@ struct Pass {
   // input) or a later one sorts them. A pass before one that merges is sorted, because sums are
   // taken in the order of the pass's input.
   bool unsorted = false;
+  // The rest of a layer of more operators than a pass takes, whose first part gave few images a term:
+  // the round expands them, without a gather plan first (see apply_ops_once).
+  bool few_images = false;
   // Term updates of the pass's Clifford operator groups (each group counted once, whichever
   // of A and B holds its operators): ng_in groups precede the expanding group in circuit
   // order and see the pass's input terms, ng_out follow it and see the merged output.
@@ -1173,7 +1176,7 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
   std::vector<BlockDesc> g1;  // one per e1 entry, while every operator has one
   bool blocks = c->gather && !c->lean;
   for (const RoundEntry& en : entries)
-    if (en.pass && !en.drop) blocks = blocks && en.pass->fanout_bound >= 1.0;
+    if (en.pass && !en.drop) blocks = blocks && en.pass->fanout_bound >= 1.0 && !en.pass->few_images;
   double f_max = 0.0;
   for (const RoundEntry& en : entries)
     if (en.pass && !en.drop) f_max = std::max(f_max, en.pass->fanout_bound);
@@ -2231,7 +2234,12 @@ qimax_status apply_ops_once(qimax_ctx* c, std::vector<HostOp>& ops) {
   std::vector<uint64_t> so_in = c->h_seg, so_out, so_img, upd;
   std::vector<uint32_t> seg_entry(c->n, 0);
   int slot = 0;
+  uint64_t last_in = 0, last_img = 0;  // of the pass before
   for (size_t i = 0; i < passes.size(); ++i) {
+    // Terms of a wire or two under a rotation of every wire have three or nine images each and nothing
+    // to merge before them; only a plan or a count can tell, and the plan costs more (a layer at
+    // n = 64, four passes: 403 us with plans, 361 without). The layer's earlier pass tells for the rest.
+    passes[i].few_images = i && passes[i].egroup == passes[i - 1].egroup && last_img <= 4 * last_in;
     size_t kg = small_group_len(c, passes, i, so_in);
     // Every generator one string still (a first layer): a pass of large fan-out bound may yet
     // have few images (a rotation of every wire has three per string of weight one), so one
@@ -2259,6 +2267,8 @@ qimax_status apply_ops_once(qimax_ctx* c, std::vector<HostOp>& ops) {
       k_in = c->pk[slot].p;
       w_in = c->pw[slot].p;
       s_in = (const uint64_t*)c->pseg[slot].p;
+      last_in = gi.back()[c->n];
+      last_img = gg.back()[c->n];
       so_in = go.back();
       slot ^= 1;
       i += kg - 1;
@@ -2278,6 +2288,8 @@ qimax_status apply_ops_once(qimax_ctx* c, std::vector<HostOp>& ops) {
     k_in = c->pk[slot].p;
     w_in = c->pw[slot].p;
     s_in = (const uint64_t*)c->pseg[slot].p;
+    last_in = so_in[c->n];
+    last_img = so_img[c->n];
     so_in = so_out;
     slot ^= 1;
   }
