@@ -683,10 +683,11 @@ qimax_status settled(qimax_ctx* c, qimax_status s) {
 
 // Runs a call's work. Where it runs out of memory it runs once more (a failing call leaves the
 // state as it was) with every scratch buffer given back, and lean: buffers of just the size that a
-// round needs; no groups of small passes, gathered rounds or small sort tiles, whose buffers the other
-// ways do without; long chains in one run, and those of 16-byte keys without tables. The next call
-// tries the full form again; where that is short of memory too, the calls after it start lean, one,
-// three, then up to kLeanCalls of them at a time. A refused call leaves nothing behind.
+// round needs; no groups of small passes, gathered rounds, small sort tiles or sort variants under
+// trial, whose buffers the other ways do without; long chains in one run, and those of 16-byte
+// keys without tables. The next call tries the full form again; where that is short of memory too,
+// the calls after it start lean, one, three, then up to kLeanCalls of them at a time. A refused call
+// leaves nothing behind.
 constexpr uint32_t kLeanCalls = 15;
 template <typename F>
 qimax_status with_retry(qimax_ctx* c, const F& body) {
@@ -1595,7 +1596,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
       whole = gather && c->local_sort_m < 0 && seg_max <= (uint64_t)kChunkCap;
       if (whole) mm = 0;
       m_top = c->local_sort_m >= 0 ? std::min<uint32_t>((uint32_t)c->local_sort_m, n_pass) : mm;
-      if (c->autotune && c->local_sort_m < 0 && !whole && (m_top < n_pass || dense_ok)) {
+      if (c->autotune && c->local_sort_m < 0 && !whole && !c->lean && (m_top < n_pass || dense_ok)) {
         // size class: key class << 8 | FP64 weights << 6 | log2 of the image capacity (| 2^20 with dense)
         tune_key = ((uint32_t)c->KC << 8) + (c->WP == 64 ? 64u : 0u) + (uint32_t)std::min(63, ilog2_u64(T_img)) +
                    (dense_ok ? (1u << 20) : 0u) + (gather ? (1u << 21) : 0u);

@@ -17,28 +17,39 @@ def _circuit(n, k, theta, seed=1):
     return W.Circuit(c.n, c.gate, c.q0, c.q1, t, c.layer_end, c.eps, c.name)
 
 
-def _run(monkeypatch, value, c, precision):
+PATHS = {"groups": {}, "small rounds": {"QIMAX_SMALL_GROUPS": "0"}, "rounds": {"QIMAX_SMALL_ROUNDS": "0"}}
+
+
+def _run(monkeypatch, value, c, precision, path="groups"):
     monkeypatch.setenv("QIMAX_MERGE_FREE", value)
+    for k, v in PATHS[path].items():
+        monkeypatch.setenv(k, v)
     with Simulator(c.n, precision=precision) as s:
         s.run(c)
         return s.generators(), s.stats()
 
 
+@pytest.mark.parametrize("path", sorted(PATHS))
 @pytest.mark.parametrize("n", [16, 32, 48])
 @pytest.mark.parametrize("k,theta,precision", [(16, np.pi / 2, 32), (16, np.pi, 32), (12, 1e-12, 32), (12, 2e-38, 32),
                                                (16, 1e-25, 64), (12, 1e-300, 64)])
-def test_products_that_vanish(monkeypatch, n, k, theta, precision):
+def test_products_that_vanish(monkeypatch, n, k, theta, precision, path):
     c = _circuit(n, k, theta)
-    (g0, s0), (g1, s1) = (_run(monkeypatch, v, c, precision) for v in "01")
+    (g0, s0), (g1, s1) = (_run(monkeypatch, v, c, precision, path) for v in "01")
     for x, y in zip(g0, g1):
         assert np.array_equal(x, y)
     for key in ("images", "term_updates", "terms", "rounds"):
         assert s0[key] == s1[key], key
 
 
-@pytest.mark.parametrize("max_n", [16, 48])
-def test_batch(monkeypatch, max_n):
-    cs = [_circuit(max_n - i, 10 + i, np.pi / 2, i) for i in range(4)]
+@pytest.mark.parametrize("spins", ["0", "64"])
+@pytest.mark.parametrize("path", sorted(PATHS))
+@pytest.mark.parametrize("max_n", [16, 32, 48])
+def test_batch(monkeypatch, max_n, path, spins):
+    monkeypatch.setenv("QIMAX_DEFER_SPINS", spins)
+    for k, v in PATHS[path].items():
+        monkeypatch.setenv(k, v)
+    cs = [_circuit(max_n - i, 10 + i, np.pi / 2, i) for i in range(4)] + [W.c2_clifford_rz(7, max_n, 60, 12)]
     got = []
     for v in "01":
         monkeypatch.setenv("QIMAX_MERGE_FREE", v)
@@ -49,6 +60,22 @@ def test_batch(monkeypatch, max_n):
     assert got[0][0] == got[1][0]
     for x, y in zip(got[0][1], got[1][1]):
         assert np.array_equal(x, y)
+
+
+def test_a_recorded_step(monkeypatch):
+    """A recording of rounds that are run again, replayed."""
+    monkeypatch.setenv("QIMAX_SMALL_ROUNDS", "0")
+    c = _circuit(20, 12, np.pi / 2)
+    with Simulator(20, precision=32) as s:
+        s.run(c).flush()
+        want = s.generators()
+        with s.record_step(c) as g:
+            for _ in range(3):
+                s.reset()
+                g.launch()
+                s.sync()
+                for x, y in zip(s.generators(), want):
+                    assert np.array_equal(x, y)
 
 
 def test_ordinary_angles_stay_unsorted(monkeypatch):
