@@ -92,13 +92,13 @@ struct Ptm {
 // One operator on the host: PTM R[out][in] (dim 4 or 16), its wires and its operator
 // group (the index of the U_k / V_k run it belongs to).
 struct HostOp {
-  int arity = 1;
-  int q0 = 0, q1 = 0;
-  int dim = 4;
-  int64_t group = 0;  // operator group (U_k / V_k run); ids increase in circuit order
-  int64_t run = 0;    // its number within the call
+  uint8_t arity = 1;
+  uint8_t q0 = 0, q1 = 0;
+  uint8_t dim = 4;
   bool perm = false;
   bool conj = false;  // a signed permutation that is a conjugation by a unitary (multiplicative)
+  int32_t run = 0;    // operator group (U_k / V_k run) by its number within the call
+  int64_t group = 0;  // and within the context; ids increase in circuit order
   uint64_t mask = 0;  // wires touched
   Ptm R;              // dim*dim
 };
@@ -2309,7 +2309,7 @@ qimax_status apply_ops_once(qimax_ctx* c, std::vector<HostOp>& ops) {
 qimax_status apply_ops(qimax_ctx* c, std::vector<HostOp>& ops) {
   if (c->broken) return fail(c, QIMAX_ESTATE, "context unusable after an earlier device error");
   BusyTimer bt(c);
-  for (auto& op : ops) op.run = op.group;
+  for (auto& op : ops) op.run = (int32_t)op.group;
   return with_retry(c, [&] { return apply_ops_once(c, ops); });
 }
 
@@ -2483,34 +2483,28 @@ qimax_status group_circuit(qimax_ctx* c, uint32_t n, const uint8_t* gate, const 
   size_t nu = 0, nv = 0;
   // one-qubit chains: per U run, per wire in increasing order. A chain of Clifford gates is a
   // signed permutation, known here by its code; the others are composed on the device, and where
-  // there are none nothing is launched.
+  // there are none nothing is launched. Two passes over a run's gates, one for its chains' codes and
+  // lengths and one that writes those of the device's chains to their places in the staging.
   struct ChainRef { int run; int wire; int code; uint32_t at; };  // code < 0: the device's chain `at`
-  std::vector<uint8_t> c_gate;
-  std::vector<double> c_theta;
   std::vector<uint32_t> chain_off{0};
   std::vector<ChainRef> chains;
-  std::vector<std::vector<uint32_t>> per_wire(n);
+  std::vector<uint32_t> len(n, 0);
+  std::vector<int> code(n, kIdentityCode4);
   for (size_t r = 0; r < runs.size(); ++r) {
     if (runs[r].two) { ++nv; continue; }
     ++nu;
-    for (auto& v : per_wire) v.clear();
-    for (size_t i = runs[r].a; i < runs[r].b; ++i) per_wire[q0[i]].push_back((uint32_t)i);
+    for (size_t i = runs[r].a; i < runs[r].b; ++i) {
+      const uint32_t q = q0[i];
+      const int g = gate[i] < 9 ? kCliffordCode[gate[i]] : -1;
+      len[q] += 1;
+      if (code[q] >= 0) code[q] = g < 0 ? -1 : compose_code4(g, code[q]);
+    }
     for (uint32_t j = 0; j < n; ++j) {
-      if (per_wire[j].empty()) continue;
-      int code = kIdentityCode4;
-      for (uint32_t gi : per_wire[j]) {
-        const int g = gate[gi] < 9 ? kCliffordCode[gate[gi]] : -1;
-        code = g < 0 ? -1 : compose_code4(g, code);
-        if (code < 0) break;
-      }
-      if (code < 0) {
-        for (uint32_t gi : per_wire[j]) {
-          c_gate.push_back(gate[gi]);
-          c_theta.push_back(theta ? theta[gi] : 0.0);
-        }
-        chain_off.push_back((uint32_t)c_gate.size());
-      }
-      chains.push_back({(int)r, (int)j, code, (uint32_t)chain_off.size() - 2});
+      if (!len[j]) continue;
+      if (code[j] < 0) chain_off.push_back(chain_off.back() + len[j]);
+      chains.push_back({(int)r, (int)j, code[j], (uint32_t)chain_off.size() - 2});
+      len[j] = 0;
+      code[j] = kIdentityCode4;
     }
   }
   const size_t n_dev = chain_off.size() - 1;
@@ -2521,15 +2515,30 @@ qimax_status group_circuit(qimax_ctx* c, uint32_t n, const uint8_t* gate, const 
     // each with a flag that the host polls. (No launch still reads or writes the staging areas
     // here: a round's first launch reads them, and every round's results have been waited for;
     // a recording's launches have memory of their own.)
-    const size_t k = c_gate.size();
+    const size_t k = chain_off.back();
     const size_t oT = 0, oO = align256(k * 8), oG = oO + align256(chain_off.size() * 4);
     const size_t up = oG + align256(k), oF = align256(n_dev * 128), down = oF + n_dev * 8;
     QCHK(ensure_stage(c, 0, up));
     QCHK(ensure_stage(c, 1, down));
     uint8_t* hs = (uint8_t*)c->stage[0];
-    std::memcpy(hs + oT, c_theta.data(), k * 8);
     std::memcpy(hs + oO, chain_off.data(), chain_off.size() * 4);
-    std::memcpy(hs + oG, c_gate.data(), k);
+    size_t next = 0;  // chain
+    std::vector<uint32_t> at(n);  // next place of each wire's chain of the run
+    for (size_t r = 0; r < runs.size() && next < chains.size(); ++r) {
+      bool any = false;
+      std::fill(at.begin(), at.end(), ~0u);
+      for (; next < chains.size() && chains[next].run == (int)r; ++next)
+        if (chains[next].code < 0) {
+          at[chains[next].wire] = chain_off[chains[next].at];
+          any = true;
+        }
+      for (size_t i = runs[r].a; any && i < runs[r].b; ++i) {
+        uint32_t& to = at[q0[i]];
+        if (to == ~0u) continue;
+        ((double*)(hs + oT))[to] = theta ? theta[i] : 0.0;
+        (hs + oG)[to++] = gate[i];
+      }
+    }
     void* res = c->stage[1];
     void* res_dev = c->stage_dev[1];
     if (c->rec) {
@@ -2746,8 +2755,8 @@ qimax_status fetch(qimax_ctx* c, HostGens& g) {
 // faults included. A kernel brings 50 GB/s across the link whatever the chunk; the copy engine
 // brings 57 in one piece, but 34 in slots of 2 MB, for what a copy costs to start. Keys and weights
 // of four bytes cross as such.) Measured: 44.5 M terms, 711 MB, 68 ms with copies into pageable
-// memory, 16 ms here; the n = 16 ansatz in FP32, 583 MB for 1165, 111 and 19 ms. Readouts below
-// 4 MB take no further thread (177216 terms 0.37 -> 0.19 ms).
+// memory, 15 to 16 ms here; the n = 16 ansatz in FP32, 583 MB for 1165, 111 and 17 to 19 ms. Readouts
+// below 4 MB take no further thread (177216 terms 0.37 -> 0.20 ms).
 constexpr size_t kReadSlotBytes = 2u << 20;
 constexpr int kReadSlots = 16;
 constexpr uint32_t kReadThreads = 8;
