@@ -62,7 +62,8 @@ typedef struct {
   double prune_eps;     /* at the end of each apply call, drop terms with |w| <= prune_eps;
                            internal passes drop exact zeros only (Sec. III-B)                 */
   size_t mem_cap_bytes; /* 0 = limited by the device only; otherwise a cap on the bytes the
-                           context may hold on the device                                     */
+                           context may hold on the device. A call that runs out of memory is
+                           run once more in its leanest form before it is refused             */
   void* hip_stream;     /* hipStream_t to run on, or NULL for the context's own stream        */
   int validate;         /* 1 (default): every PTM must be unital, trace-preserving and
                            orthogonal within 1e-12; 0 admits any real matrix                  */
@@ -243,7 +244,8 @@ qimax_status qimax_get_stats(const qimax_ctx* ctx, qimax_stats* out);
 
 /* The autotuner's state (multi-circuit execution, Sec. VI: tile and bucket choices made per
  * size class of rounds). A size class is the key size, the weight precision, floor(log2) of
- * the round's image capacity and whether dense accumulation applies. The candidates are the
+ * the round's image capacity, whether dense accumulation applies and whether the round merges
+ * before it expands (the last is not told: two entries may be alike but for it). The candidates are the
  * same sort with: 0 the heuristic number of top-digit passes, 1 one pass more, 2 sort tiles
  * claimed in one global order instead of per XCD, 3 and 4 as 0 and 1 with multi-launch
  * global passes (histogram, scan, scatter) instead of single-sweep ones, 5 dense

@@ -2069,7 +2069,7 @@ __global__ void __launch_bounds__(256) k_chunk_compact(const K* __restrict__ key
 // {0,1,2}] receives segment s's input terms, images and kept terms in pass p. With seg_first /
 // seg_len set, segment s runs the seg_len[s] passes from pas[seg_first[s]] on (circuits of a batch;
 // at most n_grp) and counts nothing in the others; with none, its terms go.
-// 16-byte keys: half the terms, so that keys, images and counters fit a block's LDS (108 KB).
+// 16-byte keys: half the terms, so that keys, images and counters fit a block's LDS (112 KB).
 constexpr int kGroupBlock = 512;
 template <typename K>
 constexpr int group_cap() { return sizeof(K) > 8 ? kChunkCap / 2 : kChunkCap; }
