@@ -1288,6 +1288,14 @@ qimax_status build_round_desc(qimax_ctx* c, const std::vector<RoundEntry>& entri
   return QIMAX_OK;
 }
 
+// A pass's output buffers, for `terms` terms. They become the context's terms, which a reset writes
+// from the start again: n of them always fit.
+qimax_status output_buffers(qimax_ctx* c, int slot, uint64_t terms) {
+  terms = std::max<uint64_t>(terms, c->n);
+  QCHK(ensure(c, c->pk[slot], terms * c->kb));
+  return ensure(c, c->pw[slot], terms * c->wb);
+}
+
 // Runs one round: every segment s of the input (k_in, w_in; device offsets seg_in, host
 // offsets so_in) is processed with the pass of entries[seg_entry[s]], in one set of
 // launches for all segments. The merged result goes to pass slot `slot`; so_out / so_img
@@ -1430,8 +1438,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   uint64_t T_img = 0;
   if (plain) {
     const uint64_t cap = (uint64_t)f_round * T_in;
-    QCHK(ensure(c, c->pk[slot], std::max<uint64_t>(cap, 1) * c->kb));
-    QCHK(ensure(c, c->pw[slot], std::max<uint64_t>(cap, 1) * c->wb));
+    QCHK(output_buffers(c, slot, cap));
     QCHK(ensure(c, c->pseg[slot], (S + 1) * 8));
     QCHK(ensure_zres(c, 2 * (size_t)S + 4));
     QCHK(status_words(tl_in.n_blocks));
@@ -1693,8 +1700,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
   // gathered and sorted by global passes only: the last pass writes the round's output
   const bool sorted_out = gather && !dense && m_top == n_pass && T_img > 0;
   if (sorted_out) {
-    QCHK(ensure(c, c->pk[slot], T_img * eb));
-    QCHK(ensure(c, c->pw[slot], T_img * wbt));
+    QCHK(output_buffers(c, slot, T_img));
   }
   if (small) {
     pre_chunk = 0;
@@ -1745,8 +1751,7 @@ qimax_status run_round(qimax_ctx* c, const std::vector<RoundEntry>& entries, con
     if (m_top < n_pass) pre_chunk = cur;  // the chunk-local sort runs with the merge
   }
   // ---- segmented reduce + prune + compaction into the pass output slot
-  QCHK(ensure(c, c->pk[slot], std::max<uint64_t>(T_img, 1) * eb));
-  QCHK(ensure(c, c->pw[slot], std::max<uint64_t>(T_img, 1) * wbt));
+  QCHK(output_buffers(c, slot, T_img));
   QCHK(ensure(c, c->pseg[slot], (S + 1) * 8));
   QCHK(ensure(c, c->blk_cnt, (size_t)(tl.n_blocks + 1) * 4));
   QCHK(ensure(c, c->blk_off, (size_t)(tl.n_blocks + 1) * 8));
